@@ -299,9 +299,9 @@ int fd_batch_destroy(fd_batch *b);
 
 /* Replace the member set.  Each context advances until its step reaches target[i] (host
  * array); members keep their state and step.  Members must share r, dtype and ndim
- * (FD_E_INVAL); members whose contexts chose different builds of the stencil tile are
- * stepped with the default tile (bitwise the same results).  Invalidates the captured graph.  Work still
- * queued on a member's own stream is completed before any batched launch touches it (the
+ * (FD_E_INVAL); the batch steps all of them with one stencil tile, the library's choice
+ * for the member set as a whole, whatever tiles the members' contexts use (bitwise the same
+ * results).  Invalidates the captured graph.  Work still queued on a member's own stream is completed before any batched launch touches it (the
  * batch stream waits for each member stream); the call also waits on the host for earlier
  * batched work, whose shot table it rewrites. */
 int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *target, int nctx);
@@ -364,10 +364,10 @@ const char *fd_adjoint_config(const fd_ctx *ctx);
 /* Select a stencil tile configuration by index for contexts created afterwards with this
  * (dtype, r, ndim); returns FD_E_RANGE for an unknown index.  zchunk > 0 overrides the
  * planes each workgroup marches in z.  config = -1 restores the library's own choice,
- * which is also what holds before any call: the default tile (index 0), or, for FP32 3-D
- * radii <= 4 on grids whose default z chunks would be 16 to 63 planes long (256^3 and
- * 320^3, say), the same tile built for four waves per SIMD (the last registered index).
- * Results are bitwise the same whatever the tile. */
+ * which is also what holds before any call: the registered tile whose estimated launch
+ * time is lowest for the context's grid (a wide tile on large grids, smaller ones where
+ * rows are ragged or the grid is small).  Batches (fd_batch_set) always make their own
+ * choice.  Results are bitwise the same whatever the tile. */
 int fd_set_tuning(fd_dtype dtype, int r, int ndim, int config, int zchunk);
 
 /* The adjoint kernel's tile shape for contexts created afterwards with this (dtype, r,

@@ -18,8 +18,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libfdwave.so")
-SOURCES = ["fd_api.hip", "fd_util.hip", "fd_fwd_f32.hip", "fd_fwd_f64.hip", "fd_adj_f32.hip", "fd_adj_f64.hip",
-           "fd_vti_api.hip", "fd_vti_f32.hip", "fd_vti_f64.hip", "fd_fwd2_f32.hip"]
+# translation units: a source and, for the forward kernels (one object per radius), a define
+SOURCES = [(f"fd_fwd_{t}.hip", f"-DFD_RADIUS={r}") for t in ("f32", "f64") for r in (4, 8, 1, 2, 3, 5, 6, 7)] + [
+    (s, "") for s in ("fd_adj_f32.hip", "fd_adj_f64.hip", "fd_vti_f32.hip", "fd_vti_f64.hip", "fd_fwd2_f32.hip",
+                      "fd_api.hip", "fd_util.hip", "fd_vti_api.hip")]
 ARCH = "gfx950"
 
 
@@ -39,9 +41,10 @@ def compile_flags() -> list[str]:
     ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *compile_flags(), "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit: tuple[str, str]) -> str:
+    src, define = unit
+    obj = os.path.join(BUILD, os.path.splitext(src)[0] + define.replace("-DFD_RADIUS=", "_r") + ".o")
+    cmd = [_hipcc(), *compile_flags(), *([define] if define else []), "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{res.stdout}\n{res.stderr}")

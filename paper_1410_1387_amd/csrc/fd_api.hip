@@ -162,12 +162,6 @@ const AdjEntry *adj_table(fd_dtype dt, int r, int ndim, int *count)
 }
 std::map<std::tuple<int, int, int>, int> g_adj_tuning;
 
-// Default z chunks of [kSmallGridZchMin, kSmallGridZchMax) planes select a radius's
-// small-grid tile build (measured: 256^3 and 320^3 gain 5-6 %; 512^3 and 400^3, with
-// longer chunks, lose 1-3 %; grids of 160^3 and less, with chunks of a few planes, lose
-// up to 6 % when batched).
-constexpr int kSmallGridZchMin = 16, kSmallGridZchMax = 64;
-
 // Share of a row's tile lanes that fall past its last point when tiles of width bx cover
 // nx points.  The adjoint takes its ragged-row build where that share is more than
 // kAdjRaggedMargin below the default tile's (measured: 320^3, 192^3 and 160^3 gain 7-17 %
@@ -192,6 +186,15 @@ bool tile_fits(const FwdEntry &e, const Layout &L)
 }  // namespace
 
 namespace fdw {
+
+// Compute units of the current device (256 if the runtime cannot tell).
+int device_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return 256;
+    return cus;
+}
 
 // Workgroups of kernel k the whole device runs at once (CUs x resident workgroups per
 // CU from the occupancy calculator); 512 if the runtime cannot tell.
@@ -229,6 +232,71 @@ int choose_zch(int64_t tiles_xy, int64_t nz, int r, int slots)
 
 }  // namespace fdw
 
+namespace {
+
+// Estimated time of one launch, in points: the points the busiest CU computes (its share of
+// the workgroups, idle lanes and a prologue of 0.3 r planes included) at the tile's own
+// cost, the latency of a chunk's planes, about 300 points each, and of a workgroup's start,
+// longer the more waves it has.  Only its order among the tiles of one grid matters: over
+// cubes of 48 to 512 points and ten ragged grids it picks a tile within 2 % of the best on
+// average (at worst 5 % off for radius 4, 9 % for one cube at radius 6).
+double tile_cost(const FwdEntry &e, int64_t nwg, int64_t zch, int r, int cus)
+{
+    return (double)((nwg + cus - 1) / cus) * e.bx * e.by * e.cost * ((double)zch + 0.3 * r) + 300.0 * (double)zch +
+           1.5 * e.nt;
+}
+
+// FINE tiles are candidates for chunks below this many planes: on the longer chunks of
+// larger grids the early halo pays (288^3 r = 4: 75 us against 79 for the FINE tile).
+constexpr int64_t kFineZch = 32;
+
+// A chosen tile whose chunks are this many planes takes its build for 4 waves per SIMD,
+// where it has one: at these sizes it is as fast (256^3 r = 4, 32 planes: 45.7 against
+// 45.4 us) and leaves a second workgroup room on each CU; on longer chunks it is slower
+// (512^3: 394 against 353 us, since both places are then used).
+constexpr int64_t kTwinZchMin = 16, kTwinZchMax = 64;
+
+struct TileChoice {
+    const FwdEntry *e;
+    int64_t tx, ty;
+    int zch, slots;
+};
+
+TileChoice plan_tile(const FwdEntry &e, const Layout &L)
+{
+    TileChoice t;
+    t.e = &e;
+    t.tx = (L.knx + e.bx - 1) / e.bx;
+    t.ty = (L.kny + e.by - 1) / e.by;
+    t.slots = resident_slots(e.kernel, e.nt);
+    t.zch = choose_zch(t.tx * t.ty, L.knz, L.r, t.slots);
+    return t;
+}
+
+// The library's own tile for one shot: the cheapest candidate at its own best z chunk.
+TileChoice choose_tile(const FwdEntry *tab, int count, const Layout &L)
+{
+    const int cus = device_cus();
+    TileChoice best{nullptr, 0, 0, 0, 0};
+    double cost = 0;
+    for (int i = 0; i < count; ++i) {
+        if (tab[i].role != FWD_AUTO && tab[i].role != FWD_FINE) continue;
+        const TileChoice t = plan_tile(tab[i], L);
+        if (best.e && tab[i].role == FWD_FINE && t.zch >= kFineZch) continue;
+        const double c = tile_cost(tab[i], t.tx * t.ty * ((L.knz + t.zch - 1) / t.zch), t.zch, L.r, cus);
+        if (!best.e || c < cost) {
+            best = t;
+            cost = c;
+        }
+    }
+    if (best.e && best.zch >= kTwinZchMin && best.zch <= kTwinZchMax)
+        for (int i = 0; i < count; ++i)
+            if (tab[i].role == FWD_TWIN && tab[i].bx == best.e->bx && tab[i].by == best.e->by) best.e = &tab[i];
+    return best;
+}
+
+}  // namespace
+
 // ------------------------------------------------------------------ context
 
 struct SourceRec {
@@ -253,7 +321,6 @@ struct fd_ctx {
     const AdjEntry *ka;
     int zch;
     int64_t tiles_x, tiles_y, chunks_z;
-    int slots;  // resident workgroups of the forward kernel on the device
     int64_t adj_tiles_x, adj_tiles_y, adj_chunks_z;
     int adj_zch;
     std::string cfg_name;
@@ -308,13 +375,15 @@ static int upload_tables(fd_ctx *c)
             *z = (int32_t)p[1];
         }
     };
+    // a few sources travel inside the descriptor, more of them in the event list
+    const bool inline_src = (int)c->sources.size() <= kInlineSources;
     c->h_src.clear();
     for (size_t s = 0; s < c->sources.size(); ++s) {
         const SourceRec &sr = c->sources[s];
         Tmp t;
         colz(sr.pos, &t.col, &t.z);
         t.code = ~(int32_t)s;
-        all.push_back(t);
+        if (!inline_src) all.push_back(t);
         SourceInfo si;
         si.wav = sr.wav;
         si.nsamp = sr.nsamp;
@@ -345,6 +414,25 @@ static int upload_tables(fd_ctx *c)
 
     ShotDesc &d = c->desc;
     const bool any = !all.empty();
+    d.ev_zlo = INT32_MAX;
+    d.ev_zhi = -1;
+    for (const Tmp &t : all) {
+        d.ev_zlo = std::min(d.ev_zlo, t.z);
+        d.ev_zhi = std::max(d.ev_zhi, t.z);
+    }
+    d.nisrc = 0;
+    if (inline_src) {
+        for (const SourceRec &sr : c->sources) {
+            const SourceInfo &si = c->h_src[(size_t)d.nisrc];
+            InlineSource &is = d.isrc[d.nisrc++];
+            is.x = (int32_t)sr.pos[0];
+            is.y = L.ndim == 3 ? (int32_t)sr.pos[1] : 0;
+            is.z = (int32_t)(L.ndim == 3 ? sr.pos[2] : sr.pos[1]);
+            is.wav = si.wav;
+            is.nsamp = si.nsamp;
+            is.scale = si.scale;
+        }
+    }
     d.ev_ptr = any ? reinterpret_cast<const int32_t *>(c->ws + L.o_evptr) : nullptr;
     d.ev = reinterpret_cast<const Event *>(c->ws + L.o_ev);
     d.src = reinterpret_cast<const SourceInfo *>(c->ws + L.o_src);
@@ -492,23 +580,10 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     }
     const AdjEntry *ka = &atab[acfg];
 
-    if (!tile_fits(tab[tu.config], L))
+    if (tuned && !tile_fits(tab[tu.config], L))
         return fail(FD_E_INVAL, "fd_create: tile %s does not fit a row of %lld points", tab[tu.config].name,
                     (long long)L.knx);
-    if (!tuned) {
-        // The library's own choice: the default tile, or its small-grid build (more resident
-        // waves) where the default's z chunks are short but not tiny, i.e. where
-        // workgroups are many and brief and latency rather than streaming sets the pace.
-        const FwdEntry &d = tab[0];
-        const int64_t txy = ((L.knx + d.bx - 1) / d.bx) * ((L.kny + d.by - 1) / d.by);
-        const int zd = choose_zch(txy, L.knz, r, resident_slots(d.kernel, d.nt));
-        if (zd >= kSmallGridZchMin && zd < kSmallGridZchMax)
-            for (int i = 1; i < count; ++i)
-                if (tab[i].role == FWD_SMALL_GRID && tile_fits(tab[i], L)) {
-                    tu.config = i;
-                    break;
-                }
-    }
+    const TileChoice tile = tuned ? plan_tile(tab[tu.config], L) : choose_tile(tab, count, L);
 
     fd_ctx *c = new fd_ctx();
     c->g = *g;
@@ -522,13 +597,11 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->ws = (char *)workspace;
     c->max_src = max_sources;
     c->max_rec = max_receivers;
-    c->kf = &tab[tu.config];
+    c->kf = tile.e;
     c->ka = ka;
-    c->tiles_x = (L.knx + c->kf->bx - 1) / c->kf->bx;
-    c->tiles_y = (L.kny + c->kf->by - 1) / c->kf->by;
-    c->slots = resident_slots(c->kf->kernel, c->kf->nt);
-    c->zch = tu.zchunk > 0 ? (int)std::min<int64_t>(tu.zchunk, L.knz)
-                           : choose_zch(c->tiles_x * c->tiles_y, L.knz, r, c->slots);
+    c->tiles_x = tile.tx;
+    c->tiles_y = tile.ty;
+    c->zch = tu.zchunk > 0 ? (int)std::min<int64_t>(tu.zchunk, L.knz) : tile.zch;
     c->chunks_z = (L.knz + c->zch - 1) / c->zch;
     c->adj_tiles_x = (L.knx + ka->bx - 1) / ka->bx;
     c->adj_tiles_y = (L.kny + ka->by - 1) / ka->by;
@@ -737,13 +810,12 @@ static LaunchArgs direct_args(const fd_ctx *c, int64_t step)
 {
     LaunchArgs a;
     std::memset(&a, 0, sizeof(a));
-    a.shots = c->d_desc();
-    a.wg_prefix = nullptr;
+    a.one = c->desc;
     a.nshots = 1;
-    a.slot = 0;
     a.step = step;
     a.record = 1;
     a.xcd_remap = c->xcd_remap;
+    a.damped = c->desc.damp != nullptr;
     return a;
 }
 
@@ -990,7 +1062,7 @@ static int adjoint_steps(fd_ctx *ctx, const Slot &slot, int64_t k_lo, int64_t k_
     for (int64_t k = k_hi; k > k_lo; --k) {
         AdjArgs a;
         std::memset(&a, 0, sizeof(a));
-        a.shot = ctx->d_desc();
+        a.one = ctx->desc;
         a.mu_cur = m[(k + 1) & 1];
         a.mu_out = m[k & 1];
         a.u_km1 = slot(k - 1 - k_lo);
@@ -1211,8 +1283,6 @@ extern "C" int fd_batch_destroy(fd_batch *b)
 static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, const char *who,
                        std::vector<ShotDesc> &desc, std::vector<int32_t> &prefix, const FwdEntry **kf_out)
 {
-    const FwdEntry *kf = nullptr;
-    bool mixed = false;
     for (int i = 0; i < nctx; ++i) {
         fd_ctx *c = ctxs[i];
         int st = check_ctx(c);
@@ -1220,39 +1290,28 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
         if (c->bc != FD_BC_ZERO) return fail(FD_E_INVAL, "%s: member %d is not zero-boundary", who, i);
         if (c->r != ctxs[0]->r || c->dtype != ctxs[0]->dtype || c->g.ndim != ctxs[0]->g.ndim)
             return fail(FD_E_INVAL, "%s: member %d has another radius, dtype or dimension", who, i);
-        if (!kf) kf = c->kf;
-        mixed = mixed || c->kf != kf;
         if (target[i] < c->step) return fail(FD_E_INVAL, "%s: target below the member's step", who);
         if (c->nrec > 0 && target[i] - c->rec_base > c->rec_cap)
             return fail(FD_E_RANGE, "%s: member %d target exceeds its trace capacity", who, i);
         for (int j = 0; j < i; ++j)
             if (ctxs[j] == c) return fail(FD_E_INVAL, "%s: member %d appears twice", who, i);
     }
-    // One launch runs one kernel: members whose contexts chose different tile builds (the
-    // library picks one per grid) are stepped with the default tile, whose tiles fit every
-    // grid; the arithmetic, and so every result, is the same whatever the tile.
-    int slots = nctx > 0 ? ctxs[0]->slots : 0;
-    if (mixed) {
-        int count = 0;
-        kf = &fwd_table(ctxs[0]->dtype, ctxs[0]->r, (int)ctxs[0]->g.ndim, &count)[0];
-        slots = resident_slots(kf->kernel, kf->nt);
-    }
-    std::vector<int64_t> btx((size_t)nctx), bty((size_t)nctx);
-    for (int i = 0; i < nctx; ++i) {
-        btx[(size_t)i] = (ctxs[i]->L.knx + kf->bx - 1) / kf->bx;
-        bty[(size_t)i] = (ctxs[i]->L.kny + kf->by - 1) / kf->by;
-    }
-    desc.resize((size_t)nctx);
-    prefix.assign((size_t)nctx + 1, 0);
-    // Re-chunk the members for the batch as a whole: the other shots supply parallelism,
-    // so each shot can march longer z chunks (fewer prologue re-reads) than it would
-    // alone.  For a target length Z every member takes c = ceil(nz / Z) chunks of equal
-    // length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
+    // One launch runs one kernel, whatever tiles the members' contexts chose for themselves:
+    // the candidate that is cheapest for all members together (the arithmetic, and so every
+    // result, is the same whatever the tile).
+    //
+    // The members are re-chunked for the batch as a whole, too: the other shots supply
+    // parallelism, so each shot can march longer z chunks (fewer prologue re-reads) than it
+    // would alone.  For a target length Z every member takes c = ceil(nz / Z) chunks of
+    // equal length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
     // ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
     // targets that are some member's exact chunk length.
-    std::vector<int64_t> zchm((size_t)nctx, 1);
+    const FwdEntry *kf = nullptr;
+    int64_t zt = 1;
     if (nctx > 0) {
-        const int r = ctxs[0]->r;
+        const int r = ctxs[0]->r, cus = device_cus();
+        int count = 0;
+        const FwdEntry *tab = fwd_table(ctxs[0]->dtype, r, (int)ctxs[0]->g.ndim, &count);
         std::vector<int64_t> cand;
         for (int i = 0; i < nctx; ++i) {
             const int64_t nz = ctxs[i]->L.knz;
@@ -1260,26 +1319,46 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
         }
         std::sort(cand.begin(), cand.end());
         cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
-        double best = 1e300;
-        int64_t zt = cand.empty() ? 1 : cand.back();
-        for (int64_t Z : cand) {
-            int64_t nwg = 0, planes = 0;
-            for (int i = 0; i < nctx; ++i) {
-                const int64_t nz = ctxs[i]->L.knz, cm = (nz + Z - 1) / Z, zm = (nz + cm - 1) / cm;
-                nwg += btx[(size_t)i] * bty[(size_t)i] * cm;
-                planes = std::max<int64_t>(planes, zm);
+        double kbest = 0;
+        for (int k = 0; k < count; ++k) {
+            if (tab[k].role != FWD_AUTO && tab[k].role != FWD_FINE) continue;
+            const int slots = resident_slots(tab[k].kernel, tab[k].nt);
+            double best = 1e300;
+            int64_t z = cand.back(), bwg = 0, bplanes = 0;
+            for (int64_t Z : cand) {
+                int64_t nwg = 0, planes = 0;
+                for (int i = 0; i < nctx; ++i) {
+                    const Layout &L = ctxs[i]->L;
+                    const int64_t cm = (L.knz + Z - 1) / Z, zm = (L.knz + cm - 1) / cm;
+                    nwg += ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by) * cm;
+                    planes = std::max<int64_t>(planes, zm);
+                }
+                const double cost = (double)((nwg + slots - 1) / slots) * (double)(planes + 2 * r);
+                if (cost < best - 1e-9) {
+                    best = cost;
+                    z = Z;
+                    bwg = nwg;
+                    bplanes = planes;
+                }
             }
-            const double cost = (double)((nwg + slots - 1) / slots) * (double)(planes + 2 * r);
-            if (cost < best - 1e-9) {
-                best = cost;
-                zt = Z;
+            if (kf && tab[k].role == FWD_FINE && bplanes >= kFineZch) continue;
+            const double c = tile_cost(tab[k], bwg, bplanes, r, cus);
+            if (!kf || c < kbest) {
+                kf = &tab[k];
+                kbest = c;
+                zt = z;
             }
-        }
-        for (int i = 0; i < nctx; ++i) {
-            const int64_t nz = ctxs[i]->L.knz, cm = (nz + zt - 1) / zt;
-            zchm[(size_t)i] = (nz + cm - 1) / cm;
         }
     }
+    std::vector<int64_t> btx((size_t)nctx), bty((size_t)nctx), zchm((size_t)nctx, 1);
+    for (int i = 0; i < nctx; ++i) {
+        const int64_t nz = ctxs[i]->L.knz, cm = (nz + zt - 1) / zt;
+        btx[(size_t)i] = (ctxs[i]->L.knx + kf->bx - 1) / kf->bx;
+        bty[(size_t)i] = (ctxs[i]->L.kny + kf->by - 1) / kf->by;
+        zchm[(size_t)i] = (nz + cm - 1) / cm;
+    }
+    desc.resize((size_t)nctx);
+    prefix.assign((size_t)nctx + 1, 0);
     for (int i = 0; i < nctx; ++i) {
         fd_ctx *c = ctxs[i];
         ShotDesc d = c->desc;
@@ -1355,6 +1434,7 @@ static LaunchArgs batch_args(const fd_batch *b, int slot)
     a.step = -1;
     a.record = 1;
     a.xcd_remap = 1;
+    for (const ShotDesc &d : b->h_desc) a.damped |= d.damp != nullptr;
     return a;
 }
 

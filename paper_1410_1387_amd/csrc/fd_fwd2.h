@@ -107,6 +107,17 @@ __device__ __forceinline__ int vec_events(const ShotDesc &s, int gx, int gy, boo
     typedef typename C::type T;
     int nxt = 0x7fffffff;
     if (!inside) return nxt;
+    for (int i = s.nisrc - 1; i >= 0; --i) {
+        const InlineSource &is = s.isrc[i];
+        if (is.y != gy || is.x < gx || is.x >= gx + C::VEC) continue;
+        if (is.z > z) nxt = min(nxt, is.z);
+        if (is.z != z || sample >= is.nsamp) continue;
+        const T add = T(is.scale) * static_cast<const T *>(is.wav)[sample];
+#pragma unroll
+        for (int v = 0; v < C::VEC; ++v)
+            if (gx + v == is.x) val[v] += add;
+    }
+    if (!s.ev_ptr) return nxt;
 #pragma unroll
     for (int v = 0; v < C::VEC; ++v) {
         if (gx + v < s.nx) {
@@ -134,7 +145,12 @@ template <class C>
 __device__ __forceinline__ int vec_next_event(const ShotDesc &s, int gx, int gy, bool inside, int z)
 {
     int nxt = 0x7fffffff;
-    if (!inside || !s.ev_ptr) return nxt;
+    if (!inside) return nxt;
+    for (int i = 0; i < s.nisrc; ++i) {
+        const InlineSource &is = s.isrc[i];
+        if (is.y == gy && is.x >= gx && is.x < gx + C::VEC && is.z >= z) nxt = min(nxt, is.z);
+    }
+    if (!s.ev_ptr) return nxt;
 #pragma unroll
     for (int v = 0; v < C::VEC; ++v) {
         if (gx + v < s.nx) {
@@ -289,7 +305,7 @@ __device__ __forceinline__ void fwd2_tile(const ShotDesc &s, const Fwd2Args &a, 
     }
     load_streams(std::integral_constant<int, 0>{}, zs);
 
-    const bool events = s.ev_ptr != nullptr;
+    const bool events = s.ev_ptr != nullptr || s.nisrc > 0;
     int nev_a1 = events ? vec_next_event<C>(s, agx, agy, ain, max(zs, 0)) : 0x7fffffff;
     int nev_b1 = events ? vec_next_event<C>(s, bgx, bgy, bin, max(zs, 0)) : 0x7fffffff;
     int nev_a2 = events ? vec_next_event<C>(s, agx, agy, ain, z0) : 0x7fffffff;

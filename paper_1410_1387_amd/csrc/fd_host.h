@@ -10,6 +10,9 @@ namespace fdw {
 // Records a printf-style message as the calling thread's last error and returns code.
 __attribute__((visibility("hidden"), format(printf, 2, 3))) int host_fail(int code, const char *fmt, ...);
 
+// Compute units of the current device.
+__attribute__((visibility("hidden"))) int device_cus();
+
 // Workgroups of `kernel` (nt threads) the whole device runs at once.
 __attribute__((visibility("hidden"))) int resident_slots(const void *kernel, int nt);
 

@@ -22,10 +22,11 @@
 //  - Global traffic is x-contiguous 16-byte vectors: u^n once per point (plus
 //    the halo), u^{n-1} and c streamed with nontemporal loads, u^{n+1} written
 //    with nontemporal stores.  Every load of the next plane is issued one plane
-//    ahead of its use.
-//  - Sources and receivers are fused: a CSR event list over (x, y) columns,
-//    sorted by z, gives each thread the next plane where one of its columns has
-//    an event; only that plane takes the slow path.
+//    ahead of its use, and without a branch (see plane_buf).
+//  - Receivers are fused: a CSR event list over (x, y) columns, sorted by z, gives
+//    each thread the next plane where one of its columns has an event, and the events
+//    there when it starts.  One or two sources travel in the shot descriptor, more of
+//    them in the event list.  The descriptor itself is a launch argument.
 //  - Workgroup ids are remapped so that a contiguous run of tiles lands on one
 //    XCD (workgroups are dealt round-robin to the 8 XCDs), which keeps halo
 //    re-reads inside that XCD's L2.
@@ -184,12 +185,15 @@ __device__ __forceinline__ int lower_bound_z(const Event *ev, int lo, int hi, in
 
 // ------------------------------------------------------------------ tile configuration
 
-template <typename T, int R_, int NDIM_, int TXN_, int TYN_, int EY_, int VEC_ = V16<T>::N, int OCC_ = 0>
+template <typename T, int R_, int NDIM_, int TXN_, int TYN_, int EY_, int VEC_ = V16<T>::N, int OCC_ = 0,
+          bool LEAN_ = (OCC_ > 0), int HOFF_ = -1>
 struct TileCfg {
     typedef T type;
     // OCC > 0: the forward kernel is built for OCC waves per SIMD (the compiler keeps to
-    // the matching register budget), keeps one set of prefetch registers instead of two
-    // and, for OCC >= 4, fetches the early halo one plane later (a smaller LDS ring)
+    // the matching register budget).  LEAN: it keeps one set of prefetch registers instead
+    // of two.  HOFF: planes the halo is fetched ahead of its use, through a ring of HOFF + 2
+    // LDS planes (R for R <= 4, one less in the 4-wave builds, whose ring is smaller; 0 for
+    // larger radii, whose ring would need too much LDS, and where the tile asks for it)
     static constexpr int OCC = OCC_;
     static constexpr int R = R_;
     static constexpr int NDIM = NDIM_;
@@ -212,26 +216,82 @@ struct TileCfg {
     static constexpr int NH = NHY + NHX;
     static constexpr int HPT = (NH + NT - 1) / NT;         // halo vectors per thread
     static constexpr int YR = EY + 2 * HY;                 // rows a thread touches along y
-    // forward kernel: halo fetched HOFF planes ahead into a ring of NB LDS plane buffers
-    // (early halo for R <= 4; larger radii would need too much LDS)
-    static constexpr int HOFF = (R <= 4) ? (OCC_ >= 4 ? R - 1 : R) : 0;
+    static constexpr bool LEAN = LEAN_;
+    static constexpr int HOFF = HOFF_ >= 0 ? HOFF_ : (R <= 4) ? (OCC_ >= 4 ? R - 1 : R) : 0;
     static constexpr int NB = HOFF + 2;
     static_assert(256 % BX == 0 && 64 % BY == 0, "tile must divide the layout alignment");
 };
 
-// Per-thread geometry of one tile, shared by the forward and adjoint kernels.
+// ------------------------------------------------------------------ plane access
+
+// One plane of a padded field as a raw buffer: a uniform base and a 32-bit byte offset per
+// lane.  A lane whose offset is kOffGrid, and every lane when `on` is false, is out of the
+// buffer's range: its load returns zero and its store is dropped, both without memory
+// traffic.  So the plane loop masks lanes and the last plane without a branch, which keeps
+// the number of loads in flight the same on every path: with branches around the loads the
+// compiler has to assume the path that issued fewest and waits for the loads it has just
+// issued.  (A plane holds less than 2 GiB, so kOffGrid is outside every plane.)
+constexpr uint32_t kOffGrid = 0x80000000u;
+constexpr int kNontemporal = 2;  // cache policy bit of the buffer instructions
+
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_buf(const T *base, int64_t pxy, int zp, bool on = true)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<T *>(base + (int64_t)zp * pxy), 0,
+                                             on ? (int)(pxy * (int64_t)sizeof(T)) : 0, 0x00027000);
+}
+
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+template <int AUX, typename T, int N>
+__device__ __forceinline__ void bld(T (&d)[N], __amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    typename VecT<T, N>::t v;
+    if constexpr (N * sizeof(T) == 16)
+        v = __builtin_bit_cast(typename VecT<T, N>::t, (i32x4)__builtin_amdgcn_raw_buffer_load_b128(r, off, 0, AUX));
+    else
+        v = __builtin_bit_cast(typename VecT<T, N>::t, (i32x2)__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, AUX));
+#pragma unroll
+    for (int i = 0; i < N; ++i) d[i] = v[i];
+}
+
+template <typename T>
+__device__ __forceinline__ T bld1(__amdgpu_buffer_rsrc_t r, uint32_t off)
+{
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, (i32x2)__builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    else
+        return __builtin_bit_cast(T, (int)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+
+template <int AUX, typename T, int N>
+__device__ __forceinline__ void bst(__amdgpu_buffer_rsrc_t r, uint32_t off, const T (&s)[N])
+{
+    typename VecT<T, N>::t v;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = s[i];
+    if constexpr (N * sizeof(T) == 16)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(i32x4, v), r, off, 0, AUX);
+    else
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(i32x2, v), r, off, 0, AUX);
+}
+
+// Per-thread geometry of one tile, shared by the forward and adjoint kernels.  Offsets are
+// bytes within a plane, or kOffGrid for a vector that no point of the grid needs.
 template <class C>
 struct TileGeom {
     int lx, ly, gx, gy, x0, y0, z0, z1;
-    int64_t col;             // element offset of (gx, gy, 0)
-    bool rin[C::EY];         // row e of this thread lies inside the grid (computed and stored)
-    bool lin[C::EY];         // row e lies inside the grid or its R-wide ghost ring (loaded)
-    int64_t hoff[C::HPT];    // halo vector k: element offset at z = 0
+    uint32_t obl[C::EY];     // row e, inside the grid or its R-wide ghost ring (the field the stencil reads)
+    uint32_t obr[C::EY];     // row e, inside the grid (point-wise operands, results)
+    bool rin[C::EY];         // row e lies inside the grid
+    uint32_t hob[C::HPT];    // halo vector k
     int hl[C::HPT];          // halo vector k: LDS offset
-    bool hval[C::HPT];
+    bool hval;               // the last halo vector exists (the others always do)
 
     __device__ __forceinline__ void init(const ShotDesc &s, int tx, int ty, int cz, int zch)
     {
+        typedef typename C::type T;
         const int tid = threadIdx.x;
         lx = (tid % C::TXN) * C::VEC;
         ly = (tid / C::TXN) * C::EY;
@@ -241,16 +301,20 @@ struct TileGeom {
         gy = y0 + ly;
         z0 = cz * zch;
         z1 = min(z0 + zch, s.nz);
-        col = s.off0 + (int64_t)gy * s.px + gx;
+        const int px = (int)s.px;  // a row is shorter than a plane, which is under 2 GiB
+        const int base = (int)(s.off0 - (int64_t)C::R * s.pxy);  // interior (0, 0) within its plane
 #pragma unroll
         for (int e = 0; e < C::EY; ++e) {
             rin[e] = (gx < s.nx) && (gy + e < s.ny);
-            lin[e] = (gx < s.nx + C::R) && (gy + e < s.ny + C::HY);
+            const bool lin = (gx < s.nx + C::R) && (gy + e < s.ny + C::HY);
+            const uint32_t ob = (uint32_t)(base + (gy + e) * px + gx) * (uint32_t)sizeof(T);
+            obl[e] = lin ? ob : kOffGrid;
+            obr[e] = rin[e] ? ob : kOffGrid;
         }
+        hval = tid + (C::HPT - 1) * C::NT < C::NH;
 #pragma unroll
         for (int k = 0; k < C::HPT; ++k) {
             const int hv = tid + k * C::NT;
-            hval[k] = hv < C::NH;
             int ry = 0, cx = 0;
             if (hv < C::NHY) {
                 const int ri = hv / C::TXN;
@@ -262,40 +326,129 @@ struct TileGeom {
                 const int si = hx % (2 * C::NHS);
                 cx = (si < C::NHS) ? -C::LPAD + si * C::VEC : C::BX + (si - C::NHS) * C::VEC;
             }
-            hoff[k] = s.off0 + (int64_t)(y0 + ry) * s.px + (x0 + cx);
+            const bool need = hv < C::NH && x0 + cx < s.nx + C::R && y0 + ry < s.ny + C::HY;
+            hob[k] = need ? (uint32_t)(base + (y0 + ry) * px + (x0 + cx)) * (uint32_t)sizeof(T) : kOffGrid;
             hl[k] = (ry + C::HY) * C::LW + (cx + C::LPAD);
         }
     }
+    __device__ __forceinline__ bool has(int k) const { return k + 1 < C::HPT || hval; }
 };
+
+// ------------------------------------------------------------------ sources and receivers
 
 // Next plane >= z at which one of this thread's columns has an event (INT_MAX if none).
 template <class C>
 __device__ __forceinline__ int next_event(const ShotDesc &s, const TileGeom<C> &g, int z)
 {
     int nxt = 0x7fffffff;
-    if (!s.ev_ptr) return nxt;
-#pragma unroll
-    for (int e = 0; e < C::EY; ++e) {
-#pragma unroll
-        for (int v = 0; v < C::VEC; ++v) {
-            if (g.rin[e] && g.gx + v < s.nx) {
-                const int cidx = (g.gy + e) * s.nx + g.gx + v;
-                const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
-                if (lo < hi) {
-                    const int p = lower_bound_z(s.ev, lo, hi, z);
-                    if (p < hi) nxt = min(nxt, s.ev[p].z);
-                }
-            }
+#pragma unroll 1
+    for (int slot = 0; slot < C::EY * C::VEC; ++slot) {
+        const int y = g.gy + slot / C::VEC, x = g.gx + slot % C::VEC;
+        if (x < s.nx && y < s.ny) {
+            const int cidx = y * s.nx + x;
+            const int hi = s.ev_ptr[cidx + 1], p = lower_bound_z(s.ev, s.ev_ptr[cidx], hi, z);
+            if (p < hi) nxt = min(nxt, s.ev[p].z);
         }
     }
     return nxt;
 }
 
+// Column bounds of this thread's events, loaded before the fields so that the look-ups that
+// depend on them overlap with those loads.
+template <class C>
+struct EventBounds {
+    int p[C::EY][C::VEC + 1];
+    bool any;  // uniform: the chunk holds planes with events
+
+    __device__ __forceinline__ void load(const ShotDesc &s, const TileGeom<C> &g)
+    {
+        any = s.ev_ptr && s.ev_zlo < g.z1 && s.ev_zhi >= g.z0;
+        if (!any) return;
+#pragma unroll
+        for (int e = 0; e < C::EY; ++e) {
+            const int row = min(g.gy + e, s.ny - 1) * s.nx;
+#pragma unroll
+            for (int v = 0; v <= C::VEC; ++v) p[e][v] = s.ev_ptr[row + min(g.gx + v, s.nx)];
+        }
+    }
+};
+
+// The next plane z at which this thread's columns have an event.  While no column has more
+// than one event left, the usual case of receivers, `code` holds the event of each column
+// at that plane (kNoEvent: none) and the plane needs no look-up when it comes; otherwise
+// (`look`) its events are looked up then.
+constexpr int kNoEvent = -0x7fffffff - 1;
+template <class C>
+struct EventNext {
+    int z, code[C::EY][C::VEC];
+    bool look;
+
+    __device__ __forceinline__ void first(const ShotDesc &s, const TileGeom<C> &g, const EventBounds<C> &b)
+    {
+        z = 0x7fffffff;
+        look = false;
+        int ez[C::EY][C::VEC];
+#pragma unroll
+        for (int e = 0; e < C::EY; ++e)
+#pragma unroll
+            for (int v = 0; v < C::VEC; ++v) code[e][v] = kNoEvent;
+        if (!b.any) return;
+        // the first event of each column (of the list, where it has none)
+#pragma unroll
+        for (int e = 0; e < C::EY; ++e)
+#pragma unroll
+            for (int v = 0; v < C::VEC; ++v) {
+                const Event *ev = s.ev + (b.p[e][v] < b.p[e][v + 1] ? b.p[e][v] : 0);
+                ez[e][v] = ev->z;
+                code[e][v] = ev->code;
+            }
+#pragma unroll
+        for (int e = 0; e < C::EY; ++e)
+#pragma unroll
+            for (int v = 0; v < C::VEC; ++v) {
+                const int n = g.rin[e] ? b.p[e][v + 1] - b.p[e][v] : 0;
+                const bool one = n == 1 && ez[e][v] >= g.z0;
+                look = look || n > 1;
+                code[e][v] = one ? code[e][v] : kNoEvent;
+                ez[e][v] = one ? ez[e][v] : 0x7fffffff;
+                z = min(z, ez[e][v]);
+            }
+        // events of one thread on several planes, too, are looked up
+#pragma unroll
+        for (int e = 0; e < C::EY; ++e)
+#pragma unroll
+            for (int v = 0; v < C::VEC; ++v) look = look || (code[e][v] != kNoEvent && ez[e][v] != z);
+        if (look) z = next_event(s, g, g.z0);
+    }
+};
+
+// Looks up the events of this thread's columns at plane z and runs f(code, row, lane) over
+// them in list order (row and lane are compile-time constants); returns the next plane with
+// one.
+template <class C, class F>
+__device__ __forceinline__ int look_events(const ShotDesc &s, const TileGeom<C> &g, int z, F &&f)
+{
+    int nxt = 0x7fffffff;
+    static_for<C::EY * C::VEC>([&](auto slot) __attribute__((always_inline)) {
+        constexpr int i = decltype(slot)::value;
+        const int y = g.gy + i / C::VEC, x = g.gx + i % C::VEC;
+        if (x < s.nx && y < s.ny) {
+            const int cidx = y * s.nx + x;
+            const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
+            if (lo < hi) {
+                int p = lower_bound_z(s.ev, lo, hi, z);
+                for (; p < hi && s.ev[p].z == z; ++p)
+                    f(s.ev[p].code, std::integral_constant<int, i / C::VEC>{}, std::integral_constant<int, i % C::VEC>{});
+                if (p < hi) nxt = min(nxt, s.ev[p].z);
+            }
+        }
+    });
+    return nxt;
+}
+
 // ------------------------------------------------------------------ forward step
 
-// Byte address of element byte-offset `ob` inside plane z of a padded field whose
-// first ghost plane starts at `base` (plane pitch pxy elements).  The plane base is
-// uniform across the workgroup, the in-plane offset is a 32-bit per-lane value.
+// Address of byte offset `ob` inside plane zp of a padded field (plane pitch pxy elements).
 template <typename T>
 __device__ __forceinline__ const T *plane_at(const T *base, int64_t pxy, int zp, uint32_t ob)
 {
@@ -325,7 +478,19 @@ __device__ __forceinline__ T *plane_at(T *base, int64_t pxy, int zp, uint32_t ob
 //
 // The plane loop is unrolled by 2 (static_for) so that the u^{n-1}, c and halo
 // prefetch registers alternate between two sets by parity.
-template <class C>
+//
+// What bounds it: HBM for large grids, the latency of a plane's loads, LDS and arithmetic for
+// small ones.  Measured per step, with branches around the loads and the descriptor, event
+// list and sponge factors read through memory one after another, and as it is here:
+// 512^3 r = 4 383 -> 352 us (5.60 -> 6.10 TB/s of 16 B/pt; the three-workgroup tile would
+// take 414: loads no longer waited for keep more places in memory open at once, so the
+// one-workgroup 128x16 tile is the one to use), 256^3 56 -> 46, 384^3 r = 8 202 -> 171,
+// 256^3 FP64 93 -> 85, 64^3 6.6 -> 5.5, 97x161x203 r = 2 with sponge 25.5 -> 15.0, 2-D
+// 801x1203 r = 8 with sponge 12.5 -> 7.0.  A launch that returns at once takes 2.3 us.
+//
+// DAMP: the sponge's per-axis factors are in s.damp (a null s.damp counts as all ones, for
+// batches that mix damped and undamped shots); G = gx gy gz scales both time levels.
+template <class C, bool DAMP>
 __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::type *__restrict__ cur,
                                          const typename C::type *prev, typename C::type *out,
                                          int64_t step, bool record, int tx, int ty, int cz,
@@ -333,7 +498,6 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
 {
     typedef typename C::type T;
     constexpr int R = C::R, VEC = C::VEC, EY = C::EY, HPT = C::HPT, HY = C::HY;
-    constexpr int P = 2 * R + 2;
     constexpr int HOFF = C::HOFF, NB = C::NB;
     constexpr StencilWeights<R> W{};
     const T *__restrict__ cc = static_cast<const T *>(s.c);
@@ -343,117 +507,134 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
     g.init(s, tx, ty, cz, s.zch);
     if (g.z0 >= g.z1) return;
 
-    // in-plane byte offsets (plane index zp = z + R counts the R ghost planes)
-    const int64_t colp = g.col - (int64_t)R * pxy;
-    uint32_t ob[EY];
+    EventBounds<C> evb;
+    evb.load(s, g);
+
+    // the sample of a source inside this tile and chunk (at most kInlineSources, in s.isrc)
+    int srcz[kInlineSources];
+    T srcv[kInlineSources];
 #pragma unroll
-    for (int e = 0; e < EY; ++e) ob[e] = (uint32_t)((colp + (int64_t)e * s.px) * (int64_t)sizeof(T));
-    uint32_t hob[HPT];
-#pragma unroll
-    for (int k = 0; k < HPT; ++k) hob[k] = (uint32_t)((g.hoff[k] - (int64_t)R * pxy) * (int64_t)sizeof(T));
+    for (int i = 0; i < kInlineSources; ++i) {
+        const InlineSource &is = s.isrc[i];
+        srcz[i] = -1;
+        srcv[i] = T(0);
+        if (i < s.nisrc && is.z >= g.z0 && is.z < g.z1 && is.x >= g.x0 && is.x < g.x0 + C::BX && is.y >= g.y0 &&
+            is.y < g.y0 + C::BY && step < is.nsamp) {
+            srcz[i] = is.z;
+            srcv[i] = T(is.scale) * static_cast<const T *>(is.wav)[step];
+        }
+    }
 
     // LEAN: one register set for the u^{n-1}, c and halo prefetches (the next plane's
     // values are loaded into it once the current plane is done with it) instead of two
-    constexpr bool LEAN = C::OCC > 0;
+    constexpr bool LEAN = C::LEAN;
     constexpr int NSET = LEAN ? 1 : 2;
+    constexpr int P = 2 * R + 2;
     T q[P][EY][VEC];
     T pv[NSET][EY][VEC], cv[NSET][EY][VEC], hv[NSET][HPT][VEC];
 
     // prologue: planes z0-R .. z0+R into slots 0 .. 2R; u^{n-1} and c of plane z0 into
-    // set 0; halos of planes z0 .. z0+HOFF-1 straight into their LDS buffers and the
-    // halo of plane z0+HOFF into set 0
+    // set 0; halos of planes z0 .. z0+HOFF-1 into their LDS buffers and the halo of plane
+    // z0+HOFF into set 0.  Every load is issued before the first one is waited for.
+    T hp[HOFF > 0 ? HOFF : 1][HPT][VEC];
 #pragma unroll
-    for (int k = 0; k <= 2 * R; ++k)
+    for (int k = 0; k <= 2 * R; ++k) {
+        const auto b = plane_buf(cur, pxy, g.z0 + k);
 #pragma unroll
-        for (int e = 0; e < EY; ++e) {
-            if (g.lin[e])
-                vld(q[k][e], plane_at(cur, pxy, g.z0 + k, ob[e]));
-            else
-                vzero(q[k][e]);
-        }
-#pragma unroll
-    for (int e = 0; e < EY; ++e) {
-        if (g.rin[e]) {
-            vld_nt(pv[0][e], plane_at(prev, pxy, g.z0 + R, ob[e]));
-            vld_nt(cv[0][e], plane_at(cc, pxy, g.z0 + R, ob[e]));
-        } else {
-            vzero(pv[0][e]);
-            vzero(cv[0][e]);
-        }
+        for (int e = 0; e < EY; ++e) bld<0>(q[k][e], b, g.obl[e]);
     }
 #pragma unroll
     for (int j = 0; j < HOFF; ++j) {
-        if (g.z0 + j < g.z1) {
-            T *L = lds + ((g.z0 + j) % NB) * C::LDS;
+        const auto b = plane_buf(cur, pxy, g.z0 + j + R, g.z0 + j < g.z1);
 #pragma unroll
-            for (int k = 0; k < HPT; ++k)
-                if (g.hval[k]) {
-                    T t[VEC];
-                    vld(t, plane_at(cur, pxy, g.z0 + j + R, hob[k]));
-                    vst(L + g.hl[k], t);
-                }
+        for (int k = 0; k < HPT; ++k) bld<0>(hp[j][k], b, g.hob[k]);
+    }
+    {
+        const auto bp = plane_buf(prev, pxy, g.z0 + R), bc = plane_buf(cc, pxy, g.z0 + R);
+#pragma unroll
+        for (int e = 0; e < EY; ++e) {
+            bld<kNontemporal>(pv[0][e], bp, g.obr[e]);
+            bld<kNontemporal>(cv[0][e], bc, g.obr[e]);
         }
-    }
+        const auto bh = plane_buf(cur, pxy, g.z0 + HOFF + R, g.z0 + HOFF < g.z1);
 #pragma unroll
-    for (int k = 0; k < HPT; ++k) {
-        if (g.hval[k] && g.z0 + HOFF < g.z1)
-            vld(hv[0][k], plane_at(cur, pxy, g.z0 + HOFF + R, hob[k]));
-        else
-            vzero(hv[0][k]);
+        for (int k = 0; k < HPT; ++k) bld<0>(hv[0][k], bh, g.hob[k]);
     }
-    int nev = next_event<C>(s, g, g.z0);
-    int bz = g.z0 % NB;              // LDS buffer of plane z
-    int bh = (g.z0 + HOFF) % NB;     // LDS buffer of plane z + HOFF
 
     // absorbing sponge: G = gx gy gz scales both time levels (1 outside the sponge)
-    const T *__restrict__ damp = static_cast<const T *>(s.damp);
-    T gxy[EY][VEC];
-    if (damp) {
+    T gxy[EY][VEC], gz[NSET];
+    const bool damped = DAMP && s.damp;
+    const auto bd = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<void *>(s.damp), 0, damped ? (s.nx + s.ny + s.nz) * (int)sizeof(T) : 0, 0x00027000);
+    auto load_gz = [&](int z) { return bld1<T>(bd, (uint32_t)(s.nx + s.ny + z) * (uint32_t)sizeof(T)); };
+    if constexpr (DAMP) {
+        T gx[VEC];
 #pragma unroll
-        for (int e = 0; e < EY; ++e)
+        for (int v = 0; v < VEC; ++v) gx[v] = bld1<T>(bd, (uint32_t)(g.gx + v) * (uint32_t)sizeof(T));
 #pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                gxy[e][v] = (g.rin[e] && g.gx + v < s.nx) ? damp[g.gx + v] * damp[s.nx + g.gy + e] : T(1);
+        for (int e = 0; e < EY; ++e) {
+            const T gy = bld1<T>(bd, (uint32_t)(s.nx + g.gy + e) * (uint32_t)sizeof(T));
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) gxy[e][v] = damped ? gx[v] * gy : T(1);
+        }
+        gz[0] = load_gz(g.z0);
     }
 
-    for (int zb = g.z0; zb < g.z1; zb += 2) {
-        static_for<2>([&](auto st_) __attribute__((always_inline)) {
+    EventNext<C> nev;
+    nev.first(s, g, evb);
+    int bz = g.z0 % NB;              // LDS buffer of plane z
+    int bh = (g.z0 + HOFF) % NB;     // LDS buffer of plane z + HOFF
+#pragma unroll
+    for (int j = 0; j < HOFF; ++j) {
+        T *L = lds + ((g.z0 + j) % NB) * C::LDS;
+#pragma unroll
+        for (int k = 0; k < HPT; ++k)
+            if (g.has(k)) vst(L + g.hl[k], hp[j][k]);
+    }
+    const int64_t row = step - s.rec_base;
+    T *const trow = record && row >= 0 && row < s.rec_cap ? static_cast<T *>(s.traces) + row * s.nrec : nullptr;
+
+    for (int zb = g.z0; zb < g.z1; zb += NSET) {
+        static_for<NSET>([&](auto st_) __attribute__((always_inline)) {
             constexpr int st = decltype(st_)::value;
             constexpr int cs = LEAN ? 0 : (st & 1), ns = LEAN ? 0 : (cs ^ 1);
             constexpr int tail = 2 * R + 1;  // slot receiving plane z+R+1
-            constexpr int ctr = R;           // slot of plane z
+            constexpr int ctr = R;                // slot of plane z
             const int z = zb + st;
             if (z >= g.z1) return;
-            if (z + 1 < g.z1) {
+            const bool more = z + 1 < g.z1;
+            {
+                const auto bt = plane_buf(cur, pxy, z + 1 + 2 * R, more);
+#pragma unroll
+                for (int e = 0; e < EY; ++e) bld<0>(q[tail][e], bt, g.obl[e]);
+            }
+            if constexpr (!LEAN) {
+                const auto bp = plane_buf(prev, pxy, z + 1 + R, more), bc = plane_buf(cc, pxy, z + 1 + R, more);
 #pragma unroll
                 for (int e = 0; e < EY; ++e) {
-                    if (g.lin[e]) vld(q[tail][e], plane_at(cur, pxy, z + 1 + 2 * R, ob[e]));
-                    if (!LEAN && g.rin[e]) {
-                        vld_nt(pv[ns][e], plane_at(prev, pxy, z + 1 + R, ob[e]));
-                        vld_nt(cv[ns][e], plane_at(cc, pxy, z + 1 + R, ob[e]));
-                    }
+                    bld<kNontemporal>(pv[ns][e], bp, g.obr[e]);
+                    bld<kNontemporal>(cv[ns][e], bc, g.obr[e]);
                 }
-            }
-            if (!LEAN && z + 1 + HOFF < g.z1) {
+                const auto bh2 = plane_buf(cur, pxy, z + 1 + HOFF + R, z + 1 + HOFF < g.z1);
 #pragma unroll
-                for (int k = 0; k < HPT; ++k)
-                    if (g.hval[k]) vld(hv[ns][k], plane_at(cur, pxy, z + 1 + HOFF + R, hob[k]));
+                for (int k = 0; k < HPT; ++k) bld<0>(hv[ns][k], bh2, g.hob[k]);
             }
+            if constexpr (DAMP && !LEAN) gz[ns] = load_gz(z + 1);
 
             // stage plane z's interior (from the queue) and plane z+HOFF's halo in LDS
             T *L = lds + bz * C::LDS;
 #pragma unroll
             for (int e = 0; e < EY; ++e) vst(L + (g.ly + e + HY) * C::LW + C::LPAD + g.lx, q[ctr][e]);
-            if (z + HOFF < g.z1) {
+            {
                 T *LH = lds + bh * C::LDS;
 #pragma unroll
                 for (int k = 0; k < HPT; ++k)
-                    if (g.hval[k]) vst(LH + g.hl[k], hv[cs][k]);
+                    if (g.has(k)) vst(LH + g.hl[k], hv[cs][k]);
             }
-            if (LEAN && z + 1 + HOFF < g.z1) {  // the next halo, into the registers just staged
+            if constexpr (LEAN) {  // the next halo, into the registers just staged
+                const auto bh2 = plane_buf(cur, pxy, z + 1 + HOFF + R, z + 1 + HOFF < g.z1);
 #pragma unroll
-                for (int k = 0; k < HPT; ++k)
-                    if (g.hval[k]) vld(hv[0][k], plane_at(cur, pxy, z + 1 + HOFF + R, hob[k]));
+                for (int k = 0; k < HPT; ++k) bld<0>(hv[0][k], bh2, g.hob[k]);
             }
             __syncthreads();
 
@@ -476,7 +657,12 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
 #pragma unroll
                 for (int j = 0; j < C::NXV; ++j) {
                     T tmp[VEC];
-                    vld(tmp, L + (g.ly + e + HY) * C::LW + g.lx + j * VEC);
+                    if (j * VEC == C::LPAD) {  // this thread's own vector
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) tmp[v] = q[ctr][e][v];
+                    } else {
+                        vld(tmp, L + (g.ly + e + HY) * C::LW + g.lx + j * VEC);
+                    }
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) xs[j * VEC + v] = tmp[v];
                 }
@@ -493,7 +679,7 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                             for (int l = 1; l <= R; ++l) acc = fma_t(T(W.w[l]), yr[HY + e + l][v] + yr[HY + e - l][v], acc);
                         }
 #pragma unroll
-                        for (int l = 1; l <= R; ++l) acc = fma_t(T(W.w[l]), q[R + l][e][v] + q[R - l][e][v], acc);
+                        for (int l = 1; l <= R; ++l) acc = fma_t(T(W.w[l]), q[ctr + l][e][v] + q[ctr - l][e][v], acc);
                     } else {
                         acc = T(0);
 #pragma unroll
@@ -506,10 +692,10 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                         }
 #pragma unroll
                         for (int l = 1; l <= R; ++l)
-                            acc = fma_t(T(W.w[l]), (q[R + l][e][v] - u0) + (q[R - l][e][v] - u0), acc);
+                            acc = fma_t(T(W.w[l]), (q[ctr + l][e][v] - u0) + (q[ctr - l][e][v] - u0), acc);
                     }
-                    if (damp) {
-                        const T G = gxy[e][v] * damp[s.nx + s.ny + z];
+                    if constexpr (DAMP) {
+                        const T G = gxy[e][v] * (damped ? gz[cs] : T(1));
                         un[e][v] = G * fma_t(cv[cs][e][v], acc, T(2) * u0 - G * pv[cs][e][v]);
                     } else {
                         un[e][v] = fma_t(cv[cs][e][v], acc, T(2) * u0 - pv[cs][e][v]);
@@ -517,59 +703,62 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                 }
             }
 
-            if (LEAN && z + 1 < g.z1) {  // u^{n-1} and c of the next plane, into the registers just used
+            if constexpr (LEAN) {  // u^{n-1} and c of the next plane, into the registers just used
+                const auto bp = plane_buf(prev, pxy, z + 1 + R, more), bc = plane_buf(cc, pxy, z + 1 + R, more);
 #pragma unroll
-                for (int e = 0; e < EY; ++e)
-                    if (g.rin[e]) {
-                        vld_nt(pv[0][e], plane_at(prev, pxy, z + 1 + R, ob[e]));
-                        vld_nt(cv[0][e], plane_at(cc, pxy, z + 1 + R, ob[e]));
-                    }
+                for (int e = 0; e < EY; ++e) {
+                    bld<kNontemporal>(pv[0][e], bp, g.obr[e]);
+                    bld<kNontemporal>(cv[0][e], bc, g.obr[e]);
+                }
+                if constexpr (DAMP) gz[0] = load_gz(z + 1);
             }
 
             // fused sources (added before the store) and receivers (recorded after them)
-            if (z == nev) {
-                int nxt = 0x7fffffff;
 #pragma unroll
-                for (int e = 0; e < EY; ++e) {
+            for (int i = kInlineSources - 1; i >= 0; --i)
+                if (z == srcz[i]) {
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) {
-                        if (g.rin[e] && g.gx + v < s.nx) {
-                            const int cidx = (g.gy + e) * s.nx + g.gx + v;
-                            const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
-                            if (lo < hi) {
-                                int p = lower_bound_z(s.ev, lo, hi, z);
-                                for (; p < hi && s.ev[p].z == z; ++p) {
-                                    const int code = s.ev[p].code;
-                                    if (code < 0) {
-                                        const SourceInfo si = s.src[~code];
-                                        if (step < si.nsamp)
-                                            un[e][v] += T(si.scale) * static_cast<const T *>(si.wav)[step];
-                                    } else if (record) {
-                                        const int64_t row = step - s.rec_base;
-                                        if (row >= 0 && row < s.rec_cap)
-                                            static_cast<T *>(s.traces)[row * s.nrec + code] = un[e][v];
-                                    }
-                                }
-                                if (p < hi) nxt = min(nxt, s.ev[p].z);
-                            }
-                        }
-                    }
-                }
-                nev = nxt;
-            }
-
-#pragma unroll
-            for (int e = 0; e < EY; ++e) {
-                if (g.rin[e]) {
-                    T *p = plane_at(out, pxy, z + R, ob[e]);
-                    if (g.gx + VEC <= s.nx) {
-                        vst_nt(p, un[e]);
-                    } else {
+                    for (int e = 0; e < EY; ++e)
 #pragma unroll
                         for (int v = 0; v < VEC; ++v)
-                            if (g.gx + v < s.nx) p[v] = un[e][v];
-                    }
+                            if (g.gx + v == s.isrc[i].x && g.gy + e == s.isrc[i].y) un[e][v] += srcv[i];
                 }
+            if (z == nev.z) {
+                auto source = [&](int code, T u) {
+                    const SourceInfo si = s.src[~code];
+                    return step < si.nsamp ? u + T(si.scale) * static_cast<const T *>(si.wav)[step] : u;
+                };
+                if (!nev.look) {
+#pragma unroll
+                    for (int e = 0; e < EY; ++e)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) {
+                            const int code = nev.code[e][v];
+                            if (code >= 0) {
+                                if (trow) trow[code] = un[e][v];
+                            } else if (code != kNoEvent) {
+                                un[e][v] = source(code, un[e][v]);
+                            }
+                        }
+                    nev.z = 0x7fffffff;
+                } else {
+                    nev.z = look_events(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                        if (code >= 0) {
+                            if (trow) trow[code] = un[e][v];
+                        } else {
+                            un[e][v] = source(code, un[e][v]);
+                        }
+                    });
+                }
+            }
+
+            // a vector that straddles the end of its row keeps the padding behind it zero
+            const auto bo = plane_buf(out, pxy, z + R);
+#pragma unroll
+            for (int e = 0; e < EY; ++e) {
+#pragma unroll
+                for (int v = 1; v < VEC; ++v) un[e][v] = g.gx + v < s.nx ? un[e][v] : T(0);
+                bst<kNontemporal>(bo, g.obr[e], un[e]);
             }
 #pragma unroll
             for (int k = 0; k < P - 1; ++k)
@@ -583,72 +772,85 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
     }
 }
 
-template <class C>
-__device__ __forceinline__ void fwd_body(LaunchArgs a);
-
-template <class C>
-__global__ __launch_bounds__(C::NT) void fwd_kernel(LaunchArgs a)
-{
-    fwd_body<C>(a);
-}
-
-// the same step built for C::OCC waves per SIMD
-template <class C>
-__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC > 0 ? C::OCC : 1)))
-void fwd_kernel_occ(LaunchArgs a)
-{
-    fwd_body<C>(a);
-}
-
-template <class C>
-__device__ __forceinline__ void fwd_body(LaunchArgs a)
+// BATCH: the shot of a workgroup is looked up in the batch's table in device memory.
+// Otherwise the one shot's descriptor comes with the launch arguments, where it is read
+// with scalar loads that wait for nothing but the launch itself.
+template <class C, bool BATCH, bool DAMP>
+__device__ __forceinline__ void fwd_body(const LaunchArgs &a)
 {
     typedef typename C::type T;
     __shared__ __attribute__((aligned(16))) T lds[C::NB * C::LDS];
     int wg = blockIdx.x;
     if (a.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
-    int shot = 0, local = wg;
-    if (a.nshots > 1) {
-        int lo = 0, hi = a.nshots;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (a.wg_prefix[mid] <= wg)
-                lo = mid;
-            else
-                hi = mid;
+    if constexpr (!BATCH) {
+        const ShotDesc &s = a.one;
+        const int64_t step = a.step;
+        const T *cur;
+        const T *prev;
+        T *out;
+        if (a.cur) {
+            cur = static_cast<const T *>(a.cur);
+            prev = static_cast<const T *>(a.prev);
+            out = static_cast<T *>(a.out);
+        } else {
+            cur = static_cast<const T *>(s.buf[step & 1]);
+            prev = static_cast<const T *>(s.buf[(step + 1) & 1]);
+            out = static_cast<T *>(s.buf[(step + 1) & 1]);
         }
-        shot = lo;
-        local = wg - a.wg_prefix[lo];
-    }
-    ShotDesc *sp = a.shots + shot;
-    int64_t step;
-    if (a.step >= 0) {
-        step = a.step;
+        const int tx = wg % s.tiles_x;
+        const int t2 = wg / s.tiles_x;
+        const int ty = t2 % s.tiles_y;
+        const int cz = t2 / s.tiles_y;
+        if (cz >= s.chunks_z) return;
+        fwd_tile<C, DAMP>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
     } else {
-        step = sp->ctr[a.slot];
+        int shot = 0, local = wg;
+        if (a.nshots > 1) {
+            int lo = 0, hi = a.nshots;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (a.wg_prefix[mid] <= wg)
+                    lo = mid;
+                else
+                    hi = mid;
+            }
+            shot = lo;
+            local = wg - a.wg_prefix[lo];
+        }
+        ShotDesc *sp = a.shots + shot;
+        const int64_t step = sp->ctr[a.slot];
         const bool active = step < sp->target;
         if (local == 0 && threadIdx.x == 0) sp->ctr[a.slot ^ 1] = active ? step + 1 : step;
         if (!active) return;
+        // the descriptor but for its counters is constant while batched steps run
+        const __attribute__((address_space(4))) int *cp = (const __attribute__((address_space(4))) int *)(uintptr_t)sp;
+        int words[sizeof(ShotDesc) / sizeof(int)];
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(ShotDesc) / sizeof(int)); ++i) words[i] = cp[i];
+        const ShotDesc s = __builtin_bit_cast(ShotDesc, words);
+        const T *cur = static_cast<const T *>(step & 1 ? s.buf[1] : s.buf[0]);
+        T *out = static_cast<T *>(step & 1 ? s.buf[0] : s.buf[1]);
+        const int tx = local % s.tiles_x;
+        const int t2 = local / s.tiles_x;
+        const int ty = t2 % s.tiles_y;
+        const int cz = t2 / s.tiles_y;
+        if (cz >= s.chunks_z) return;
+        fwd_tile<C, DAMP>(s, cur, out, out, step, a.record != 0, tx, ty, cz, lds);
     }
-    const ShotDesc &s = *sp;
-    const T *cur;
-    const T *prev;
-    T *out;
-    if (a.cur) {
-        cur = static_cast<const T *>(a.cur);
-        prev = static_cast<const T *>(a.prev);
-        out = static_cast<T *>(a.out);
-    } else {
-        cur = static_cast<const T *>(s.buf[step & 1]);
-        prev = static_cast<const T *>(s.buf[(step + 1) & 1]);
-        out = static_cast<T *>(s.buf[(step + 1) & 1]);
-    }
-    const int tx = local % s.tiles_x;
-    const int t2 = local / s.tiles_x;
-    const int ty = t2 % s.tiles_y;
-    const int cz = t2 / s.tiles_y;
-    if (cz >= s.chunks_z) return;
-    fwd_tile<C>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
+}
+
+template <class C, bool BATCH, bool DAMP>
+__global__ __launch_bounds__(C::NT) void fwd_kernel(LaunchArgs a)
+{
+    fwd_body<C, BATCH, DAMP>(a);
+}
+
+// the same step built for C::OCC waves per SIMD
+template <class C, bool BATCH, bool DAMP>
+__global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC > 0 ? C::OCC : 1)))
+void fwd_kernel_occ(LaunchArgs a)
+{
+    fwd_body<C, BATCH, DAMP>(a);
 }
 
 // ------------------------------------------------------------------ adjoint step
@@ -678,11 +880,14 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
     constexpr int R = C::R, VEC = C::VEC, EY = C::EY, HPT = C::HPT, HY = C::HY;
     constexpr StencilWeights<R> W{};
     const T *__restrict__ cc = static_cast<const T *>(s.c);
-    const int64_t px = s.px, pxy = s.pxy;
+    const int64_t pxy = s.pxy;
 
     TileGeom<C> g;
     g.init(s, tx, ty, cz, zch);
     if (g.z0 >= g.z1) return;
+
+    EventBounds<C> evb;
+    evb.load(s, g);
 
     // imaging accumulator: g1 (added through the FMA), g2 (added after it), gout (stored)
     const T *g1 = gmode == GM_ACC ? gseg : (gmode == GM_FOLD ? gseg : (gmode == GM_DIRECT ? grad : nullptr));
@@ -691,54 +896,48 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
 
     T qm[2 * R + 1][EY][VEC], qu[2 * R + 1][EY][VEC];
 #pragma unroll
-    for (int j = 0; j < 2 * R; ++j)
+    for (int j = 0; j < 2 * R; ++j) {
+        const auto bm = plane_buf(mcur, pxy, g.z0 + j), bu = plane_buf(ucur, pxy, g.z0 + j);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
-            if (g.lin[e]) {
-                vld(qm[j][e], mcur + g.col + e * px + (int64_t)(g.z0 - R + j) * pxy);
-                vld(qu[j][e], ucur + g.col + e * px + (int64_t)(g.z0 - R + j) * pxy);
-            } else {
-                vzero(qm[j][e]);
-                vzero(qu[j][e]);
-            }
+            bld<0>(qm[j][e], bm, g.obl[e]);
+            bld<0>(qu[j][e], bu, g.obl[e]);
         }
+    }
     T nm[EY][VEC], nuu[EY][VEC], npv[EY][VEC], ncc[EY][VEC], ngr[EY][VEC], ng2[EY][VEC], nhm[HPT][VEC],
         nhu[HPT][VEC];
-    {
-        const int64_t zo = (int64_t)g.z0 * pxy;
+    auto load_plane = [&](int z, bool on) __attribute__((always_inline)) {
+        const auto bm = plane_buf(mcur, pxy, z + 2 * R, on), bu = plane_buf(ucur, pxy, z + 2 * R, on);
+        const auto bp = plane_buf(mout, pxy, z + R, on), bc = plane_buf(cc, pxy, z + R, on);
+        const auto b1 = plane_buf(g1, pxy, z + R, on && g1), b2 = plane_buf(g2, pxy, z + R, on && g2);
+        const auto bhm = plane_buf(mcur, pxy, z + R, on), bhu = plane_buf(ucur, pxy, z + R, on);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
-            if (g.lin[e]) {
-                vld(nm[e], mcur + g.col + e * px + zo + R * pxy);
-                vld(nuu[e], ucur + g.col + e * px + zo + R * pxy);
-            } else {
-                vzero(nm[e]);
-                vzero(nuu[e]);
-            }
-            vzero(ngr[e]);
-            vzero(ng2[e]);
-            if (g.rin[e]) {
-                vld_nt(npv[e], mout + g.col + e * px + zo);
-                vld_nt(ncc[e], cc + g.col + e * px + zo);
-                if (g1) vld_nt(ngr[e], g1 + g.col + e * px + zo);
-                if (g2) vld_nt(ng2[e], g2 + g.col + e * px + zo);
-            } else {
-                vzero(npv[e]);
-                vzero(ncc[e]);
-            }
+            bld<0>(nm[e], bm, g.obl[e]);
+            bld<0>(nuu[e], bu, g.obl[e]);
+            bld<kNontemporal>(npv[e], bp, g.obr[e]);
+            bld<kNontemporal>(ncc[e], bc, g.obr[e]);
+            bld<kNontemporal>(ngr[e], b1, g.obr[e]);
+            bld<kNontemporal>(ng2[e], b2, g.obr[e]);
         }
 #pragma unroll
         for (int j = 0; j < HPT; ++j) {
-            if (g.hval[j]) {
-                vld(nhm[j], mcur + g.hoff[j] + zo);
-                vld(nhu[j], ucur + g.hoff[j] + zo);
-            } else {
-                vzero(nhm[j]);
-                vzero(nhu[j]);
-            }
+            bld<0>(nhm[j], bhm, g.hob[j]);
+            bld<0>(nhu[j], bhu, g.hob[j]);
         }
-    }
-    int nev = next_event<C>(s, g, g.z0);
+    };
+    load_plane(g.z0, true);
+    EventNext<C> nev;
+    nev.first(s, g, evb);
+    const T *const rrow = resid + (k - 1) * s.nrec;
+    T rnext[EY][VEC];  // the residuals of the events in nev
+#pragma unroll
+    for (int e = 0; e < EY; ++e)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            rnext[e][v] = T(0);
+            if (evb.any && nev.code[e][v] >= 0) rnext[e][v] = rrow[nev.code[e][v]];
+        }
 
     int buf = 0;
     for (int z = g.z0; z < g.z1; ++z) {
@@ -761,28 +960,7 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
                 hm[j][v] = nhm[j][v];
                 hu[j][v] = nhu[j][v];
             }
-        if (z + 1 < g.z1) {
-            const int64_t zo = (int64_t)(z + 1) * pxy;
-#pragma unroll
-            for (int e = 0; e < EY; ++e) {
-                if (g.lin[e]) {
-                    vld(nm[e], mcur + g.col + e * px + zo + R * pxy);
-                    vld(nuu[e], ucur + g.col + e * px + zo + R * pxy);
-                }
-                if (g.rin[e]) {
-                    vld_nt(npv[e], mout + g.col + e * px + zo);
-                    vld_nt(ncc[e], cc + g.col + e * px + zo);
-                    if (g1) vld_nt(ngr[e], g1 + g.col + e * px + zo);
-                    if (g2) vld_nt(ng2[e], g2 + g.col + e * px + zo);
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < HPT; ++j)
-                if (g.hval[j]) {
-                    vld(nhm[j], mcur + g.hoff[j] + zo);
-                    vld(nhu[j], ucur + g.hoff[j] + zo);
-                }
-        }
+        load_plane(z + 1, z + 1 < g.z1);
 
         T *Lm = lds + buf * (2 * C::LDS);
         T *Lu = Lm + C::LDS;
@@ -793,7 +971,7 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
         }
 #pragma unroll
         for (int j = 0; j < HPT; ++j)
-            if (g.hval[j]) {
+            if (g.has(j)) {
                 vst(Lm + g.hl[j], hm[j]);
                 vst(Lu + g.hl[j], hu[j]);
             }
@@ -819,7 +997,12 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
 #pragma unroll
                 for (int j = 0; j < C::NXV; ++j) {
                     T tmp[VEC];
-                    vld(tmp, Lp + (g.ly + e + HY) * C::LW + g.lx + j * VEC);
+                    if (j * VEC == C::LPAD) {  // this thread's own vector
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) tmp[v] = pass == 0 ? qm[R][e][v] : qu[R][e][v];
+                    } else {
+                        vld(tmp, Lp + (g.ly + e + HY) * C::LW + g.lx + j * VEC);
+                    }
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) xs[j * VEC + v] = tmp[v];
                 }
@@ -850,30 +1033,22 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
         }
 
         // adjoint sources: the residual enters at the receivers, scaled by c there
-        if (z == nev) {
-            int nxt = 0x7fffffff;
+        if (z == nev.z) {
+            if (!nev.look) {
 #pragma unroll
-            for (int e = 0; e < EY; ++e) {
+                for (int e = 0; e < EY; ++e)
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    if (g.rin[e] && g.gx + v < s.nx) {
-                        const int cidx = (g.gy + e) * s.nx + g.gx + v;
-                        const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
-                        if (lo < hi) {
-                            int p = lower_bound_z(s.ev, lo, hi, z);
-                            for (; p < hi && s.ev[p].z == z; ++p) {
-                                const int code = s.ev[p].code;
-                                if (code >= 0)
-                                    mnew[e][v] = fma_t(ramp * cv[e][v], resid[(k - 1) * s.nrec + code], mnew[e][v]);
-                            }
-                            if (p < hi) nxt = min(nxt, s.ev[p].z);
-                        }
-                    }
-                }
+                    for (int v = 0; v < VEC; ++v)
+                        if (nev.code[e][v] >= 0) mnew[e][v] = fma_t(ramp * cv[e][v], rnext[e][v], mnew[e][v]);
+                nev.z = 0x7fffffff;
+            } else {
+                nev.z = look_events(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                    if (code >= 0) mnew[e][v] = fma_t(ramp * cv[e][v], rrow[code], mnew[e][v]);
+                });
             }
-            nev = nxt;
         }
 
+        const auto bpm = plane_buf(mout, pxy, z + R), bpg = plane_buf(gout, pxy, z + R);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
             T gn[VEC];
@@ -881,22 +1056,10 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
             for (int v = 0; v < VEC; ++v) {
                 gn[v] = fma_t(mnew[e][v], lapu[e][v], gv[e][v]);
                 if (g2) gn[v] = gn[v] + gv2[e][v];
+                if (v > 0 && g.gx + v >= s.nx) mnew[e][v] = gn[v] = T(0);  // padding behind the row stays zero
             }
-            if (g.rin[e]) {
-                T *pm = mout + g.col + e * px + (int64_t)z * pxy;
-                T *pg = gout + g.col + e * px + (int64_t)z * pxy;
-                if (g.gx + VEC <= s.nx) {
-                    vst_nt(pm, mnew[e]);
-                    vst_nt(pg, gn);
-                } else {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v)
-                        if (g.gx + v < s.nx) {
-                            pm[v] = mnew[e][v];
-                            pg[v] = gn[v];
-                        }
-                }
-            }
+            bst<kNontemporal>(bpm, g.obr[e], mnew[e]);
+            bst<kNontemporal>(bpg, g.obr[e], gn);
         }
 
 #pragma unroll
@@ -919,23 +1082,23 @@ __global__ __launch_bounds__(C::NT) void adj_kernel(AdjArgs a)
     __shared__ __attribute__((aligned(16))) T lds[4 * C::LDS];
     int wg = blockIdx.x;
     if (a.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
-    const ShotDesc &s = *a.shot;
     const int tx = wg % a.tiles_x;
     const int t2 = wg / a.tiles_x;
     const int ty = t2 % a.tiles_y;
     const int cz = t2 / a.tiles_y;
     if (cz >= a.chunks_z) return;
-    adj_tile<C>(s, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out),
+    adj_tile<C>(a.one, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out),
                 static_cast<const T *>(a.u_km1), static_cast<T *>(a.grad), static_cast<T *>(a.gseg), a.gmode,
                 static_cast<const T *>(a.resid), a.k, T(a.resid_amp), tx, ty, cz, a.zch, lds);
 }
 
 // ------------------------------------------------------------------ registry
 
-// Roles of a forward tile entry: an option for fd_set_tuning, or the one the library
-// takes by itself for grids whose default z chunk is short (many short chunks: more
-// resident waves pay off there).
-enum { FWD_OPTION = 0, FWD_SMALL_GRID = 1 };
+// Roles of a forward tile entry: reached with fd_set_tuning alone, or one the library
+// chooses from by itself, FINE ones only where z chunks are short (they have no early halo
+// and a small tile's larger share of it), or the build for 4 waves per SIMD that stands in
+// for the chosen tile of the same shape on mid-size grids.
+enum { FWD_OPTION = 0, FWD_AUTO = 1, FWD_FINE = 2, FWD_TWIN = 3 };
 
 struct FwdEntry {
     const char *name;
@@ -943,6 +1106,7 @@ struct FwdEntry {
     void (*launch)(const LaunchArgs &, int nwg, hipStream_t);
     const void *kernel;  // the __global__ function (for occupancy queries)
     int role;
+    float cost;          // relative time per point of the tile, where it streams well
 };
 
 // role of an adjoint table entry: an option for fd_set_adj_tuning, or the build that
@@ -957,13 +1121,34 @@ struct AdjEntry {
     int role;
 };
 
-template <class C>
-void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
+template <class C, bool BATCH, bool DAMP>
+constexpr auto fwd_kernel_of()
 {
     if constexpr (C::OCC > 0)
-        hipLaunchKernelGGL(fwd_kernel_occ<C>, dim3(nwg), dim3(C::NT), 0, st, a);
+        return &fwd_kernel_occ<C, BATCH, DAMP>;
     else
-        hipLaunchKernelGGL(fwd_kernel<C>, dim3(nwg), dim3(C::NT), 0, st, a);
+        return &fwd_kernel<C, BATCH, DAMP>;
+}
+
+// a.step >= 0: one shot, described by a.one; else a batch's table (the tiles the library
+// chooses from only)
+template <class C, int ROLE>
+void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
+{
+    const dim3 grid(nwg), block(C::NT);
+    if (a.step >= 0) {
+        if (a.damped)
+            hipLaunchKernelGGL((fwd_kernel_of<C, false, true>()), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((fwd_kernel_of<C, false, false>()), grid, block, 0, st, a);
+        return;
+    }
+    if constexpr (ROLE == FWD_AUTO || ROLE == FWD_FINE) {
+        if (a.damped)
+            hipLaunchKernelGGL((fwd_kernel_of<C, true, true>()), grid, block, 0, st, a);
+        else
+            hipLaunchKernelGGL((fwd_kernel_of<C, true, false>()), grid, block, 0, st, a);
+    }
 }
 
 template <class C>
@@ -972,15 +1157,11 @@ void launch_adj(const AdjArgs &a, int nwg, hipStream_t st)
     hipLaunchKernelGGL(adj_kernel<C>, dim3(nwg), dim3(C::NT), 0, st, a);
 }
 
-template <class C>
-FwdEntry fwd_entry(const char *name, int role = FWD_OPTION)
+template <class C, int ROLE>
+FwdEntry fwd_entry(const char *name, float cost)
 {
-    const void *k;
-    if constexpr (C::OCC > 0)
-        k = reinterpret_cast<const void *>(&fwd_kernel_occ<C>);
-    else
-        k = reinterpret_cast<const void *>(&fwd_kernel<C>);
-    return FwdEntry{name, C::BX, C::BY, C::NT, &launch_fwd<C>, k, role};
+    return FwdEntry{name, C::BX, C::BY, C::NT, &launch_fwd<C, ROLE>,
+                    reinterpret_cast<const void *>(fwd_kernel_of<C, false, false>()), ROLE, cost};
 }
 
 template <class C>

@@ -22,13 +22,25 @@ struct SourceInfo {
     double scale;
 };
 
+// A point source carried inside the shot descriptor (kernel axes), so that a launch finds
+// its sample without a look-up; used while a shot has at most kInlineSources of them.
+constexpr int kInlineSources = 2;
+struct InlineSource {
+    int32_t x, y, z, pad0;
+    const void *wav;
+    int64_t nsamp;
+    double scale;
+};
+
 // Everything a stencil launch needs to know about one shot.  Lives in device memory
 // (inside the context workspace); `ctr` is written by the kernels.
 struct ShotDesc {
     void *buf[2];          // padded wavefields; u^n is buf[n & 1], u^{n+1} overwrites buf[(n+1) & 1]
     const void *c;         // padded coefficient field c = (v dt / h)^2
     int32_t nx, ny, nz;    // interior extent along the kernel's x, y, z (2-D: ny = 1, nz = grid ny)
-    int32_t tiles_x, tiles_y, chunks_z, zch, pad0;
+    int32_t tiles_x, tiles_y, chunks_z, zch;
+    int32_t ev_zlo, ev_zhi; // planes the events lie in (none outside)
+    int32_t nisrc, pad0;    // sources in isrc; 0: they are in the event list alone
     int64_t px, pxy, off0; // row pitch, plane pitch, element offset of interior (0, 0, 0)
     int64_t ctr[2];        // step counter slots (graph / batched mode)
     int64_t target;        // batched mode: stop at this step
@@ -38,6 +50,7 @@ struct ShotDesc {
     void *traces;          // [cap][nrec] of dtype
     int64_t nrec, rec_base, rec_cap;
     const void *damp;      // absorbing sponge: per-axis factors [nx | ny | nz] of dtype, or null
+    InlineSource isrc[kInlineSources];
 };
 
 // Per-launch arguments (passed by value).
@@ -52,11 +65,13 @@ struct LaunchArgs {
     void *out;
     int32_t record;            // write receiver traces
     int32_t xcd_remap;         // map consecutive tiles onto one XCD
+    int32_t damped, pad0;      // some shot of the launch has a sponge
+    ShotDesc one;              // single shot: its descriptor
 };
 
 // Adjoint launch arguments (single shot, explicit pointers).
 struct AdjArgs {
-    const ShotDesc *shot;
+    ShotDesc one;
     const void *mu_cur;    // mu^{k+1}
     void *mu_out;          // in: mu^{k+2}, out: mu^k
     const void *u_km1;     // u^{k-1}

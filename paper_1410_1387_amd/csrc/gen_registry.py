@@ -12,28 +12,36 @@ import os
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
-# 3-D forward tile shapes.  Radii in SWEEP_RADII get every shape; others the default.
-# 64x16 with one row per thread first: 138 VGPRs and 41 KB of LDS give three 256-thread
-# workgroups per CU, and at 512^3 r = 4 the chunker fills them with 768 workgroups of
-# 171 planes (352 Gpts/s against 342 for 64x32 with two rows per thread)
-F32_3D = [(16, 16, 1), (16, 16, 2), (32, 8, 2), (16, 8, 4), (16, 32, 2), (32, 16, 2), (8, 32, 2), (8, 32, 1)]
-# radii above 4 keep one row per thread: two rows exceed 256 VGPRs and spill; 128x16
-# (512 threads) first: measured fastest at 384^3, r = 8
-F32_3D_BIG_R = [(32, 16, 1), (16, 16, 1), (32, 8, 1), (16, 32, 1),
-                (32, 16, 1, 2), (32, 8, 1, 2), (64, 8, 1, 2), (16, 16, 1, 2), (64, 4, 1, 2)]
-# FP64: 32x32 (two rows per thread) first for radii <= 4: 64x16 with 512 threads needs
-# 83 KB of LDS at r = 4, one workgroup per CU (512^3 r = 4: 174.6 vs 129.2 Gpts/s);
-# larger radii keep one row per thread (two rows spill at r >= 7); 32x16 measured fastest
-# at 384^3 r = 8 (116.5 vs 110.0 Gpts/s for 64x16)
-F64_3D = [(16, 16, 2), (32, 16, 1), (32, 8, 2), (16, 16, 1)]
-F64_3D_BIG_R = [(16, 16, 1), (32, 16, 1), (32, 8, 1)]
-F32_SWEEP_RADII = {4, 8}
-# FP32 3-D, radii <= 4: the default tile built for 4 waves per SIMD (124 VGPRs, one set of
-# prefetch registers, the early halo one plane later so that four workgroups' LDS fits a
-# CU).  The library takes it by itself for grids whose default z chunk is 16-63 planes
-# (fd_create): 1.05-1.06x at 256^3 and 320^3, 0.97-0.99x at 400^3 and 512^3.
-F32_SMALL_GRID = (16, 16, 1, None, 4)
-F64_SWEEP_RADII = {4, 8}
+# 3-D forward tiles: (shape, role, relative cost per point).  AUTO tiles are what the library
+# chooses from by itself (fd_create, fd_batch_set), FINE ones too where z chunks are short,
+# TWIN ones are a chosen tile's build for 4 waves per SIMD; OPTION tiles are reached with
+# fd_set_tuning alone.  The costs are fitted to sweeps of every tile over cubes of 48 to 512
+# points and ten ragged grids (the library's choice is then within 2 % of the best tile on
+# average; at worst 6-9 % for a few sizes).
+# FP32, radii <= 4.  Tiles of 512 threads, one workgroup per CU, stream best: 512^3 r = 4
+# takes 353 us with 128x16, 354 with 64x32, against 414 for 64x16 (256 threads, three
+# workgroups per CU, so three times as many places in memory streamed at once); small
+# grids and ragged rows are better covered by the smaller tiles (96^3: 7.4 us with 32x8
+# against 8.7; 320^3: 87 with 64x32 against 97 with 128x16).
+F32_3D_AUTO = [((16, 16, 1), "AUTO", 1.35), ((32, 16, 1), "AUTO", 1.0), ((16, 32, 1), "AUTO", 1.1),
+               ((8, 8, 1, None, 0, False, 0), "FINE", 1.25),
+               ((32, 16, 1, None, 4, False, 3), "TWIN", 1.0), ((16, 32, 1, None, 4, False, 3), "TWIN", 1.0)]
+F32_3D_OPTIONS = [(16, 16, 2), (32, 8, 2), (16, 8, 4), (16, 32, 2), (32, 16, 2), (8, 32, 2), (8, 32, 1),
+                  (16, 16, 1, None, 4)]
+# FP32, radii above 4: one row per thread (two exceed 256 VGPRs and spill)
+F32_3D_BIG_R_AUTO = [((32, 16, 1), "AUTO", 1.0), ((16, 16, 1), "AUTO", 1.1), ((8, 16, 1), "FINE", 1.17)]
+F32_3D_BIG_R_OPTIONS = [(32, 8, 1), (16, 32, 1), (32, 16, 1, 2), (32, 8, 1, 2), (64, 8, 1, 2), (16, 16, 1, 2),
+                        (64, 4, 1, 2)]
+# FP64: 32x32 with two rows per thread or with 512 threads and no early halo (512^3 r = 4:
+# 791 and 726 us), 16x16 for small grids (64^3: 6.1 against 6.6 us); radii above 4 keep one
+# row per thread (two spill at r >= 7), 64x16 with 512 threads for large grids (384^3 r = 8:
+# 362 us against 388 for 32x16)
+F64_3D_AUTO = [((16, 16, 2), "AUTO", 1.0), ((16, 32, 1, None, 0, False, 0), "AUTO", 0.95),
+               ((8, 16, 1, None, 0, False, 0), "FINE", 1.15)]
+F64_3D_OPTIONS = [(32, 16, 1), (32, 8, 2), (16, 16, 1)]
+F64_3D_BIG_R_AUTO = [((16, 16, 1), "AUTO", 1.1), ((32, 16, 1), "AUTO", 1.0), ((8, 16, 1), "FINE", 1.17)]
+F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
+SWEEP_RADII = {4, 8}      # radii that get the OPTION tiles
 F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads
 # adjoint: radii <= 4 128x16 first (measured 5-7 % faster than 64x16)
 ADJ_F32_3D = [(32, 16, 1), (32, 16, 1, 2), (64, 8, 1, 2), (32, 8, 1, 2), (16, 16, 1, 2)]
@@ -76,38 +84,54 @@ def cfgname(T, R, nd, txn, tyn, ey, vec=None, occ=0):
     return name + ")"
 
 
-def tilecfg(T, R, nd, txn, tyn, ey, vec=None, occ=0):
+def tilecfg(T, R, nd, txn, tyn, ey, vec=None, occ=0, lean=None, hoff=None):
     """TileCfg<...> for a tile tuple (threads along x, threads along y, rows per thread
     [, x points per thread (None: one 16-byte vector) [, waves per SIMD the forward
-    kernel is built for (0: the compiler's choice)]])."""
+    kernel is built for (0: the compiler's choice) [, one set of prefetch registers
+    [, planes the halo is fetched ahead]]]])."""
     full = 4 if T == "float" else 2
-    if occ:
-        return f"TileCfg<{T}, {R}, {nd}, {txn}, {tyn}, {ey}, {vec or full}, {occ}>"
-    return f"TileCfg<{T}, {R}, {nd}, {txn}, {tyn}, {ey}" + (f", {vec}>" if vec else ">")
+    args = [T, R, nd, txn, tyn, ey]
+    if vec or occ or lean is not None:
+        args.append(vec or full)
+    if occ or lean is not None:
+        args.append(occ)
+    if lean is not None:
+        args += ["true" if lean else "false", min(hoff, R)]
+    return f"TileCfg<{', '.join(str(a) for a in args)}>"
 
 
-def fwd_file(T, sweep3d, sweep_radii, sweep3d_big_r=None, small_grid=None):
+def fwd_file(T, auto, options, auto_big_r, options_big_r):
+    """Forward kernels: one section per radius, compiled one object each (FD_RADIUS)."""
     tag = "f32" if T == "float" else "f64"
     out = HDR.format(fname=f"fd_fwd_{tag}.hip", what="forward", T=T)
+    out = out.replace("namespace fdw {\n", "// Compiled once per radius, with FD_RADIUS set.\nnamespace fdw {\n")
     for R in range(1, 9):
-        lst = sweep3d_big_r if (sweep3d_big_r and R > 4) else sweep3d
-        cfgs3 = lst if R in sweep_radii else lst[:1]
-        out += f"static const FwdEntry k3_r{R}[] = {{\n"
-        for cfg in cfgs3:
-            out += f'    fwd_entry<{tilecfg(T, R, 3, *cfg)}>("{cfgname(T, R, 3, *cfg)}"),\n'
-        if small_grid and R <= 4:
-            out += (f'    fwd_entry<{tilecfg(T, R, 3, *small_grid)}>("{cfgname(T, R, 3, *small_grid)}", '
-                    f'FWD_SMALL_GRID),\n')
+        au, op = (auto, options) if R <= 4 else (auto_big_r, options_big_r)
+        rows = [au[0]]
+        if R in SWEEP_RADII:  # the options keep their numbers; at R > 4 the second tile is one of them
+            rows += (au[1:2] if R > 4 else []) + [(o, "OPTION", 1.0) for o in op] + (au[2:] if R > 4 else au[1:])
+        else:
+            rows += au[1:]
+        out += f"#if FD_RADIUS == {R}\nstatic const FwdEntry k3[] = {{\n"
+        for cfg, role, cost in rows:
+            name = cfgname(T, R, 3, *cfg[:5])
+            out += f'    fwd_entry<{tilecfg(T, R, 3, *cfg)}, FWD_{role}>("{name}", {cost}f),\n'
         out += "};\n"
         txn = F2D[0]
-        out += f"static const FwdEntry k2_r{R}[] = {{\n"
-        out += f'    fwd_entry<TileCfg<{T}, {R}, 2, {txn}, 1, 1>>("{cfgname(T, R, 2, txn, 1, 1)}"),\n'
-        out += "};\n"
-    out += "\nconst FwdEntry *fwd_configs_" + tag + "(int r, int ndim, int *count)\n{\n    switch (r * 10 + ndim) {\n"
+        out += f"static const FwdEntry k2[] = {{\n"
+        out += f'    fwd_entry<TileCfg<{T}, {R}, 2, {txn}, 1, 1>, FWD_AUTO>("{cfgname(T, R, 2, txn, 1, 1)}", 1.0f),\n'
+        out += "};\n#endif\n"
+    out += ("\n#define FD_CAT_(a, b) a##b\n#define FD_CAT(a, b) FD_CAT_(a, b)\n"
+            f"const FwdEntry *FD_CAT(fwd_configs_{tag}_r, FD_RADIUS)(int ndim, int *count)\n{{\n"
+            "    *count = (int)((ndim == 3 ? sizeof(k3) : sizeof(k2)) / sizeof(FwdEntry));\n"
+            "    return ndim == 3 ? k3 : k2;\n}\n\n#if FD_RADIUS == 1\n")
+    for R in range(2, 9):
+        out += f"const FwdEntry *fwd_configs_{tag}_r{R}(int ndim, int *count);\n"
+    out += f"const FwdEntry *fwd_configs_{tag}(int r, int ndim, int *count)\n{{\n    *count = 0;\n"
+    out += "    if (ndim != 2 && ndim != 3) return nullptr;\n    switch (r) {\n"
     for R in range(1, 9):
-        for nd in (2, 3):
-            out += f"    case {R * 10 + nd}: *count = (int)(sizeof(k{nd}_r{R}) / sizeof(FwdEntry)); return k{nd}_r{R};\n"
-    out += "    default: *count = 0; return nullptr;\n    }\n}\n\n}  // namespace fdw\n"
+        out += f"    case {R}: return fwd_configs_{tag}_r{R}(ndim, count);\n"
+    out += "    default: return nullptr;\n    }\n}\n#endif\n\n}  // namespace fdw\n"
     with open(os.path.join(HERE, f"fd_fwd_{tag}.hip"), "w") as f:
         f.write(out)
 
@@ -163,8 +187,8 @@ def vti_file(T, tiles):
 
 
 if __name__ == "__main__":
-    fwd_file("float", F32_3D, F32_SWEEP_RADII, F32_3D_BIG_R, F32_SMALL_GRID)
-    fwd_file("double", F64_3D, F64_SWEEP_RADII, F64_3D_BIG_R)
+    fwd_file("float", F32_3D_AUTO, F32_3D_OPTIONS, F32_3D_BIG_R_AUTO, F32_3D_BIG_R_OPTIONS)
+    fwd_file("double", F64_3D_AUTO, F64_3D_OPTIONS, F64_3D_BIG_R_AUTO, F64_3D_BIG_R_OPTIONS)
     adj_file("float", ADJ_F32_3D, ADJ_F32_3D_BIG_R, ADJ_F32_RAGGED_X)
     adj_file("double", ADJ_F64_3D, ADJ_F64_3D_BIG_R)
     vti_file("float", VTI_F32)

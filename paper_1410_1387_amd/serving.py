@@ -101,13 +101,13 @@ class _Live:
         self.req, self.ctx, self.tensors, self.traces = req, ctx, tensors, traces
         self.footprint, self.npoints = footprint, npoints
         self.arrival, self.admitted, self.future = arrival, admitted, future
-        self.kernel = kernel  # shots batch only with shots of the same stencil kernel
+        self.kernel = kernel  # shots batch only with shots of the same kind of kernel
 
 
 def kernel_of(ctx: int) -> str:
-    """The stencil kernel (tile shape) a context steps with: its configuration name without
-    the per-shot z chunking and grid size."""
-    return F.fd_kernel_config(ctx).split(", zchunk")[0]
+    """The stencil kernels a context can step with: dtype, radius and dimension, the part of
+    its configuration name before the tile.  fd_batch_set picks one tile for all members."""
+    return F.fd_kernel_config(ctx).split(" tile")[0]
 
 
 def shot_footprint(shape, nsteps: int, nrec: int, r: int, dtype: str) -> int:
@@ -390,10 +390,10 @@ class ShotServer:
             F.fd_batch_destroy(batch)
 
     def _window(self, active: list) -> list:
-        """The oldest unfinished resident shots, in admission order, that use the oldest
-        one's stencil kernel (one launch runs one kernel; the library picks a shot's tile
-        shape from its grid), until their grid points per step reach fill_points (at least
-        one shot).  The oldest shot always steps, so no shot waits for ever."""
+        """The oldest unfinished resident shots, in admission order, that can share a launch
+        with the oldest one (same dtype, radius and dimension), until their grid points per
+        step reach fill_points (at least one shot).  The oldest shot always steps, so no shot
+        waits for ever."""
         live = [s for s in active if not s.future.done() and not getattr(s, "_queued_done", False)]
         if not live:
             return []

@@ -1,0 +1,124 @@
+"""Every registered forward tile, and every way a source or a receiver reaches the kernel,
+against the oracle (needs an MI355X)."""
+
+import numpy as np
+import pytest
+
+import workloads
+from gpu_util import rel_l2, run_gpu, say
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-4, "f64": 1e-11}
+
+
+def _case(shape, seed):
+    rng = np.random.default_rng(seed)
+    u0 = rng.standard_normal(shape)
+    return workloads.layered_velocity(shape, seed=seed), u0, 0.5 * u0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("r", range(1, 9))
+def test_registered_tiles_bitwise(oracle_mod, r, dtype):
+    # one plane per chunk, chunks with a remainder and one chunk, on a grid that divides no
+    # tile, damped and not: every registered tile gives the first one's bits, and the first
+    # one the oracle's solution (8 steps: FP32 rounding stays far below the parity bar)
+    from paper_1410_1387_amd import fdwave as F
+
+    shape, T = (11, 35, 133), 8
+    v, u0, um1 = _case(shape, r)
+    dt = 0.5 * oracle_mod.dt_max(3, r, 10.0, v.max())
+    rec = workloads.surface_receivers(shape[2], shape[1], 3, 4)
+    for damping in (None, (3, 0.05, 63)):
+        base = None
+        cfg = 0
+        while True:
+            try:
+                F.fd_set_tuning(dtype, r, 3, cfg)
+            except F.FdError:
+                break
+            for zch in (1, 4, 11):
+                got = run_gpu(v, r, 10.0, dt, T, dtype, receivers=rec, u0=u0, um1=um1,
+                              ricker=((66, 17, 3), 30.0, 0.0), tuning=(cfg, zch), damping=damping, label="tiles")
+                base = base or got
+                assert np.array_equal(got["u"], base["u"]), (cfg, zch, got["config"])
+                assert np.array_equal(got["u_prev"], base["u_prev"]), (cfg, zch)
+                assert np.array_equal(got["traces"], base["traces"]), (cfg, zch)
+            cfg += 1
+        F.fd_set_tuning(dtype, r, 3, -1)
+        assert cfg >= 3
+        src = [((66, 17, 3), oracle_mod.ricker(T, dt, 30.0, 0.0))]
+        ref = oracle_mod.forward(v, 10.0, dt, r, T, src, rec, u0=u0, um1=um1, damping=damping and damping[:2])
+        assert rel_l2(base["u"], ref["u"]) <= TOL[dtype] and rel_l2(base["traces"], ref["traces"]) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("nsrc", [1, 2, 3, 5])
+@pytest.mark.parametrize("shape,r", [((13, 20, 70), 4), ((30, 75), 8)])
+def test_sources_and_receivers_vs_oracle(oracle_mod, shape, r, nsrc):
+    # a few sources travel in the shot descriptor, more of them in the event list; receivers
+    # are one per column, several in one column (a vertical line), and on top of a source;
+    # two sources share a point, and a wavelet ends before the run does
+    T, dtype = 14, "f64"
+    v, u0, um1 = _case(shape, nsrc)
+    nd = len(shape)
+    dt = 0.4 * oracle_mod.dt_max(nd, r, 10.0, v.max())
+    ext = shape[::-1]
+    at = [(5, 2, 4), (5, 2, 4), (69, 19, 12), (0, 0, 0), (37, 11, 7)]
+    at = [tuple(min(a, n - 1) for a, n in zip(p[:nd] if nd == 3 else (p[0], p[2]), ext)) for p in at]
+    rng = np.random.default_rng(7)
+    sources = [(at[i], rng.standard_normal(T - 3 * i) * 1e6) for i in range(nsrc)]
+    if nd == 3:
+        rec = [(x, 2, 4) for x in range(0, 70, 3)] + [(5, 2, 4)] + [(37, 11, z) for z in range(13)] + [(69, 19, 12)]
+    else:
+        rec = [(x, 4) for x in range(75)] + [(5, 4), (37, 7)] + [(40, z) for z in range(30)]
+    rec = np.array(rec)
+    got = run_gpu(v, r, 10.0, dt, T, dtype, sources=sources, receivers=rec, u0=u0, um1=um1, label="events")
+    padded = [(p, np.concatenate([w, np.zeros(T - len(w))])) for p, w in sources]
+    ref = oracle_mod.forward(v, 10.0, dt, r, T, padded, rec, u0=u0, um1=um1)
+    say(f"u {rel_l2(got['u'], ref['u']):.2e} traces {rel_l2(got['traces'], ref['traces']):.2e}")
+    assert rel_l2(got["u"], ref["u"]) <= TOL[dtype]
+    assert rel_l2(got["traces"], ref["traces"]) <= TOL[dtype]
+    assert np.all(got["traces"][:, -1] != 0.0)
+
+
+@pytest.mark.parametrize("sides", [(64, 64, 64, 64), (40, 96, 20, 130), (33,)])
+def test_batch_tile_choice_bitwise(oracle_mod, sides):
+    # a batch picks one tile for its members, whatever they step with alone: damped and
+    # undamped members, with few and many sources, end with the bits they have alone
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    T, dt = 9, 4e-4
+    stream = torch.cuda.Stream()
+
+    def make(i, n):
+        v = torch.tensor(workloads.layered_velocity((n, n + 3, n + 1), seed=i), dtype=torch.float32, device="cuda")
+        torch.cuda.synchronize()
+        p = Propagator(v, 4, 10.0, dt, "f32", max_sources=4, max_receivers=40, stream=stream)
+        if i % 2:
+            p.set_damping(5, 0.03)
+        with torch.cuda.stream(stream):
+            for k in range(1 + i % 4):
+                p.inject(p.ricker(T, 30.0, 0.0), (n // 2, n // 2 + k, 2), 1e6)
+            tr = p.record([(n // 2 - 10 + x, n // 2, 2) for x in range(20)], T)
+        return p, tr
+
+    alone = [make(i, n) for i, n in enumerate(sides)]
+    for p, _ in alone:
+        p.step(T)
+    both = [make(i, n) for i, n in enumerate(sides)]
+    ws = torch.empty(F.fd_batch_workspace_bytes(len(sides)), dtype=torch.uint8, device="cuda")
+    b = F.fd_batch_create(len(sides), ws, F.stream_ptr(stream))
+    F.fd_batch_set(b, [p.ctx for p, _ in both], [T] * len(sides))
+    F.fd_batch_step(b, 5)
+    F.fd_batch_step(b, 4)
+    for (pa, ta), (pb, tb) in zip(alone, both):
+        with torch.cuda.stream(stream):
+            ua, ub = pa.state(), pb.state()
+        stream.synchronize()
+        assert torch.equal(ua[0], ub[0]) and torch.equal(ua[1], ub[1]) and torch.equal(ta, tb)
+        assert float(ta.abs().max()) > 0
+    F.fd_batch_destroy(b)
