@@ -372,10 +372,9 @@ int fd_set_tuning(fd_dtype dtype, int r, int ndim, int config, int zchunk);
 
 /* The adjoint kernel's tile shape for contexts created afterwards with this (dtype, r,
  * ndim): config indexes the registered adjoint tiles.  config = -1 restores the library's
- * own choice, which is also what holds before any call: the default tile (index 0, 128
- * points wide for FP32 radii <= 4), or, for FP32 3-D radii <= 4 on grids whose rows that
- * tile covers badly (x = 160, 192 or 320, say, where 17-38 % of its lanes would idle), a
- * 64-point-wide tile (the last registered index).  Process-wide, thread-safe; a tuning
+ * own choice, which is also what holds before any call: for FP32 3-D radii <= 4 a 128- or
+ * 64-point-wide tile, by how the grid's rows fill them, elsewhere the default (index 0) or,
+ * on the smallest grids, the next.  Process-wide, thread-safe; a tuning
  * knob like fd_set_tuning; the gradient is bitwise the same whatever the tile.  Errors:
  * FD_E_INVAL (no adjoint kernel for dtype/r/ndim), FD_E_RANGE (config outside [-1, count)). */
 int fd_set_adj_tuning(fd_dtype dtype, int r, int ndim, int config);

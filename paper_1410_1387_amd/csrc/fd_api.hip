@@ -163,10 +163,10 @@ const AdjEntry *adj_table(fd_dtype dt, int r, int ndim, int *count)
 std::map<std::tuple<int, int, int>, int> g_adj_tuning;
 
 // Share of a row's tile lanes that fall past its last point when tiles of width bx cover
-// nx points.  The adjoint takes its ragged-row build where that share is more than
-// kAdjRaggedMargin below the default tile's (measured: 320^3, 192^3 and 160^3 gain 7-17 %
-// with the 64-wide tile; 448^3 is even; 400^3, with 11 points of difference, loses 1 %;
-// grids whose rows are a multiple of 128 lose 4-5 %).
+// nx points.  The adjoint's widest tile is not a candidate where that share is more than
+// kAdjRaggedMargin above a narrower one's, nor on rows it covers alone with points to
+// spare; elsewhere it is the only one (320^3 r = 4: 180 us with 64x32 against 191 with
+// 128x16, 160^3 30 against 33, 96^3 10.7 against 10.9; 256^3 87 with 128x16 against 91).
 double row_waste(int64_t nx, int bx)
 {
     const int64_t cover = (nx + bx - 1) / bx * bx;
@@ -240,7 +240,8 @@ namespace {
 // longer the more waves it has.  Only its order among the tiles of one grid matters: over
 // cubes of 48 to 512 points and ten ragged grids it picks a tile within 2 % of the best on
 // average (at worst 5 % off for radius 4, 9 % for one cube at radius 6).
-double tile_cost(const FwdEntry &e, int64_t nwg, int64_t zch, int r, int cus)
+template <class Entry>
+double tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
 {
     return (double)((nwg + cus - 1) / cus) * e.bx * e.by * e.cost * ((double)zch + 0.3 * r) + 300.0 * (double)zch +
            1.5 * e.nt;
@@ -256,34 +257,37 @@ constexpr int64_t kFineZch = 32;
 // (512^3: 394 against 353 us, since both places are then used).
 constexpr int64_t kTwinZchMin = 16, kTwinZchMax = 64;
 
+template <class Entry>
 struct TileChoice {
-    const FwdEntry *e;
+    const Entry *e;
     int64_t tx, ty;
-    int zch, slots;
+    int zch;
+
+    int64_t nwg(const Layout &L) const { return tx * ty * ((L.knz + zch - 1) / zch); }
 };
 
-TileChoice plan_tile(const FwdEntry &e, const Layout &L)
+template <class Entry>
+TileChoice<Entry> plan_tile(const Entry &e, const Layout &L)
 {
-    TileChoice t;
+    TileChoice<Entry> t;
     t.e = &e;
     t.tx = (L.knx + e.bx - 1) / e.bx;
     t.ty = (L.kny + e.by - 1) / e.by;
-    t.slots = resident_slots(e.kernel, e.nt);
-    t.zch = choose_zch(t.tx * t.ty, L.knz, L.r, t.slots);
+    t.zch = choose_zch(t.tx * t.ty, L.knz, L.r, resident_slots(e.kernel, e.nt));
     return t;
 }
 
 // The library's own tile for one shot: the cheapest candidate at its own best z chunk.
-TileChoice choose_tile(const FwdEntry *tab, int count, const Layout &L)
+TileChoice<FwdEntry> choose_tile(const FwdEntry *tab, int count, const Layout &L)
 {
     const int cus = device_cus();
-    TileChoice best{nullptr, 0, 0, 0, 0};
+    TileChoice<FwdEntry> best{nullptr, 0, 0, 0};
     double cost = 0;
     for (int i = 0; i < count; ++i) {
         if (tab[i].role != FWD_AUTO && tab[i].role != FWD_FINE) continue;
-        const TileChoice t = plan_tile(tab[i], L);
+        const TileChoice<FwdEntry> t = plan_tile(tab[i], L);
         if (best.e && tab[i].role == FWD_FINE && t.zch >= kFineZch) continue;
-        const double c = tile_cost(tab[i], t.tx * t.ty * ((L.knz + t.zch - 1) / t.zch), t.zch, L.r, cus);
+        const double c = tile_cost(tab[i], t.nwg(L), t.zch, L.r, cus);
         if (!best.e || c < cost) {
             best = t;
             cost = c;
@@ -292,6 +296,31 @@ TileChoice choose_tile(const FwdEntry *tab, int count, const Layout &L)
     if (best.e && best.zch >= kTwinZchMin && best.zch <= kTwinZchMax)
         for (int i = 0; i < count; ++i)
             if (tab[i].role == FWD_TWIN && tab[i].bx == best.e->bx && tab[i].by == best.e->by) best.e = &tab[i];
+    return best;
+}
+
+// The same for the adjoint (the first entry is its widest tile, where it has several).
+TileChoice<AdjEntry> choose_adj_tile(const AdjEntry *tab, int count, const Layout &L)
+{
+    const int cus = device_cus();
+    int narrow = tab[0].bx;
+    for (int i = 1; i < count; ++i)
+        if (tab[i].role == ADJ_AUTO) narrow = std::min(narrow, tab[i].bx);
+    const bool wide = row_waste(L.knx, narrow) + kAdjRaggedMargin >= row_waste(L.knx, tab[0].bx) && L.knx >= tab[0].bx;
+    TileChoice<AdjEntry> best{nullptr, 0, 0, 0};
+    double cost = 0;
+    for (int i = 0; i < count; ++i) {
+        if (tab[i].role != ADJ_AUTO || (narrow < tab[0].bx && (tab[i].bx == tab[0].bx) != wide)) continue;
+        const TileChoice<AdjEntry> t = plan_tile(tab[i], L);
+        const double c = tile_cost(tab[i], t.nwg(L), t.zch, L.r, cus);
+        if (!best.e || c < cost) {
+            best = t;
+            cost = c;
+        }
+    }
+    if (best.zch == 1)
+        for (int i = 0; i < count; ++i)
+            if (tab[i].role == ADJ_ONE_PLANE) best = plan_tile(tab[i], L);
     return best;
 }
 
@@ -568,22 +597,11 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
         auto ia = g_adj_tuning.find(std::make_tuple((int)dtype, r, (int)g->ndim));
         if (ia != g_adj_tuning.end()) acfg = ia->second;
     }
-    if (acfg < 0) {
-        // The library's own adjoint tile: the default, or its ragged-row build (a narrower
-        // tile) where a grid row leaves clearly more of the default tile's lanes idle.
-        acfg = 0;
-        for (int i = 1; i < acount; ++i)
-            if (atab[i].role == ADJ_RAGGED_X) {
-                if (row_waste(L.knx, atab[i].bx) + kAdjRaggedMargin < row_waste(L.knx, atab[0].bx)) acfg = i;
-                break;
-            }
-    }
-    const AdjEntry *ka = &atab[acfg];
-
     if (tuned && !tile_fits(tab[tu.config], L))
         return fail(FD_E_INVAL, "fd_create: tile %s does not fit a row of %lld points", tab[tu.config].name,
                     (long long)L.knx);
-    const TileChoice tile = tuned ? plan_tile(tab[tu.config], L) : choose_tile(tab, count, L);
+    const TileChoice<FwdEntry> tile = tuned ? plan_tile(tab[tu.config], L) : choose_tile(tab, count, L);
+    const TileChoice<AdjEntry> adj = acfg >= 0 ? plan_tile(atab[acfg], L) : choose_adj_tile(atab, acount, L);
 
     fd_ctx *c = new fd_ctx();
     c->g = *g;
@@ -598,14 +616,14 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->max_src = max_sources;
     c->max_rec = max_receivers;
     c->kf = tile.e;
-    c->ka = ka;
+    c->ka = adj.e;
     c->tiles_x = tile.tx;
     c->tiles_y = tile.ty;
     c->zch = tu.zchunk > 0 ? (int)std::min<int64_t>(tu.zchunk, L.knz) : tile.zch;
     c->chunks_z = (L.knz + c->zch - 1) / c->zch;
-    c->adj_tiles_x = (L.knx + ka->bx - 1) / ka->bx;
-    c->adj_tiles_y = (L.kny + ka->by - 1) / ka->by;
-    c->adj_zch = choose_zch(c->adj_tiles_x * c->adj_tiles_y, L.knz, r, resident_slots(ka->kernel, ka->nt));
+    c->adj_tiles_x = adj.tx;
+    c->adj_tiles_y = adj.ty;
+    c->adj_zch = adj.zch;
     c->adj_chunks_z = (L.knz + c->adj_zch - 1) / c->adj_zch;
     c->nrec = 0;
     c->traces = nullptr;

@@ -289,10 +289,9 @@ struct TileGeom {
     int hl[C::HPT];          // halo vector k: LDS offset
     bool hval;               // the last halo vector exists (the others always do)
 
-    __device__ __forceinline__ void init(const ShotDesc &s, int tx, int ty, int cz, int zch)
+    __device__ __forceinline__ void init(const ShotDesc &s, int tx, int ty, int cz, int zch, int tid)
     {
         typedef typename C::type T;
-        const int tid = threadIdx.x;
         lx = (tid % C::TXN) * C::VEC;
         ly = (tid / C::TXN) * C::EY;
         x0 = tx * C::BX;
@@ -504,7 +503,7 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
     const int64_t pxy = s.pxy;
 
     TileGeom<C> g;
-    g.init(s, tx, ty, cz, s.zch);
+    g.init(s, tx, ty, cz, s.zch, threadIdx.x);
     if (g.z0 >= g.z1) return;
 
     EventBounds<C> evb;
@@ -859,8 +858,8 @@ void fwd_kernel_occ(LaunchArgs a)
 // imaging condition:
 //     mu^k = 2 mu^{k+1} - mu^{k+2} + c Lh mu^{k+1} + resid_amp c_j resid[k-1][j] e_j
 //     t    = mu^k * Lh u^{k-1}
-// Two register queues (mu^{k+1}, u^{k-1}) march in z together; both planes are
-// staged in LDS.  The imaging term t is summed in the working precision, blocked by
+// mu^{k+1} and u^{k-1} march in z together, each with its own threads (adj_half).  The
+// imaging term t is summed in the working precision, blocked by
 // checkpoint segment so that the rounding error grows with the segment length plus
 // the number of segments instead of with the number of steps:
 //     gmode 0: gseg += t         (inside a segment)
@@ -868,129 +867,160 @@ void fwd_kernel_occ(LaunchArgs a)
 //     gmode 2: g    += gseg + t  (last step of a segment)
 //     gmode 3: g    += t         (unblocked)
 enum { GM_ACC = 0, GM_FIRST = 1, GM_FOLD = 2, GM_DIRECT = 3 };
-template <class C>
-__device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::type *__restrict__ mcur,
-                                         typename C::type *mout, const typename C::type *__restrict__ ucur,
-                                         typename C::type *grad, typename C::type *gseg, int gmode,
-                                         const typename C::type *__restrict__ resid,
-                                         int64_t k, typename C::type ramp, int tx, int ty, int cz, int zch,
-                                         typename C::type *lds)
+
+// One half of the workgroup's threads (ROLE 0) advances mu over the tile and chunk, the
+// other half (ROLE 1) evaluates Lh u^{k-1} over the same tile and accumulates the image: thread t of
+// each half owns the same points.  Each half keeps one register queue and stages one field,
+// so a tile holds twice the waves that it would with both queues in every thread, each with
+// half the registers, loads and arithmetic of a plane.  ROLE 0 leaves mu^k of plane z in mx
+// and ROLE 1 adds plane z's image after the next plane's barrier, the only one of a plane:
+// the two buffers of mx alternate, and plane z's is rewritten two barriers later.
+//
+// What bounds it: HBM for large grids (28 B per point; 256^3 r = 4: 96 -> 87 us per step,
+// 5.4 TB/s), and before the split, for r = 8, the registers of two queues (more than 256,
+// so one wave per SIMD): 192^3 89 -> 56 us, 93x118x141 36 -> 20 us.
+template <class C, int ROLE>
+__device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::type *__restrict__ field,
+                                         typename C::type *mout, const typename C::type *g1,
+                                         const typename C::type *g2, typename C::type *gout,
+                                         const typename C::type *__restrict__ rrow, typename C::type ramp,
+                                         const TileGeom<C> &g, typename C::type *lds, typename C::type *mx)
 {
     typedef typename C::type T;
     constexpr int R = C::R, VEC = C::VEC, EY = C::EY, HPT = C::HPT, HY = C::HY;
+    constexpr int P = 2 * R + 2;
+    constexpr int HOFF = C::HOFF, NB = C::NB;
     constexpr StencilWeights<R> W{};
     const T *__restrict__ cc = static_cast<const T *>(s.c);
     const int64_t pxy = s.pxy;
 
-    TileGeom<C> g;
-    g.init(s, tx, ty, cz, zch);
-    if (g.z0 >= g.z1) return;
-
     EventBounds<C> evb;
-    evb.load(s, g);
+    if constexpr (ROLE == 0) evb.load(s, g);
 
-    // imaging accumulator: g1 (added through the FMA), g2 (added after it), gout (stored)
-    const T *g1 = gmode == GM_ACC ? gseg : (gmode == GM_FOLD ? gseg : (gmode == GM_DIRECT ? grad : nullptr));
-    const T *g2 = gmode == GM_FOLD ? grad : nullptr;
-    T *gout = (gmode == GM_ACC || gmode == GM_FIRST) ? gseg : grad;
-
-    T qm[2 * R + 1][EY][VEC], qu[2 * R + 1][EY][VEC];
+    // the queue and the halo work as in fwd_tile; pv and cv are ROLE 0's, g1 and g2 of a
+    // plane are loaded while it is computed and used one plane later
+    T q[P][EY][VEC], hv[2][HPT][VEC], hp[HOFF > 0 ? HOFF : 1][HPT][VEC];
+    T pv[2][EY][VEC], cv[2][EY][VEC];
 #pragma unroll
-    for (int j = 0; j < 2 * R; ++j) {
-        const auto bm = plane_buf(mcur, pxy, g.z0 + j), bu = plane_buf(ucur, pxy, g.z0 + j);
+    for (int k = 0; k <= 2 * R; ++k) {
+        const auto b = plane_buf(field, pxy, g.z0 + k);
+#pragma unroll
+        for (int e = 0; e < EY; ++e) bld<0>(q[k][e], b, g.obl[e]);
+    }
+#pragma unroll
+    for (int j = 0; j < HOFF; ++j) {
+        const auto b = plane_buf(field, pxy, g.z0 + j + R, g.z0 + j < g.z1);
+#pragma unroll
+        for (int k = 0; k < HPT; ++k) bld<0>(hp[j][k], b, g.hob[k]);
+    }
+    if constexpr (ROLE == 0) {
+        const auto bp = plane_buf(mout, pxy, g.z0 + R), bc = plane_buf(cc, pxy, g.z0 + R);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
-            bld<0>(qm[j][e], bm, g.obl[e]);
-            bld<0>(qu[j][e], bu, g.obl[e]);
+            bld<kNontemporal>(pv[0][e], bp, g.obr[e]);
+            bld<kNontemporal>(cv[0][e], bc, g.obr[e]);
         }
     }
-    T nm[EY][VEC], nuu[EY][VEC], npv[EY][VEC], ncc[EY][VEC], ngr[EY][VEC], ng2[EY][VEC], nhm[HPT][VEC],
-        nhu[HPT][VEC];
-    auto load_plane = [&](int z, bool on) __attribute__((always_inline)) {
-        const auto bm = plane_buf(mcur, pxy, z + 2 * R, on), bu = plane_buf(ucur, pxy, z + 2 * R, on);
-        const auto bp = plane_buf(mout, pxy, z + R, on), bc = plane_buf(cc, pxy, z + R, on);
-        const auto b1 = plane_buf(g1, pxy, z + R, on && g1), b2 = plane_buf(g2, pxy, z + R, on && g2);
-        const auto bhm = plane_buf(mcur, pxy, z + R, on), bhu = plane_buf(ucur, pxy, z + R, on);
+    {
+        const auto bh = plane_buf(field, pxy, g.z0 + HOFF + R, g.z0 + HOFF < g.z1);
 #pragma unroll
-        for (int e = 0; e < EY; ++e) {
-            bld<0>(nm[e], bm, g.obl[e]);
-            bld<0>(nuu[e], bu, g.obl[e]);
-            bld<kNontemporal>(npv[e], bp, g.obr[e]);
-            bld<kNontemporal>(ncc[e], bc, g.obr[e]);
-            bld<kNontemporal>(ngr[e], b1, g.obr[e]);
-            bld<kNontemporal>(ng2[e], b2, g.obr[e]);
-        }
-#pragma unroll
-        for (int j = 0; j < HPT; ++j) {
-            bld<0>(nhm[j], bhm, g.hob[j]);
-            bld<0>(nhu[j], bhu, g.hob[j]);
-        }
-    };
-    load_plane(g.z0, true);
+        for (int k = 0; k < HPT; ++k) bld<0>(hv[0][k], bh, g.hob[k]);
+    }
     EventNext<C> nev;
-    nev.first(s, g, evb);
-    const T *const rrow = resid + (k - 1) * s.nrec;
     T rnext[EY][VEC];  // the residuals of the events in nev
-#pragma unroll
-    for (int e = 0; e < EY; ++e)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            rnext[e][v] = T(0);
-            if (evb.any && nev.code[e][v] >= 0) rnext[e][v] = rrow[nev.code[e][v]];
-        }
-
-    int buf = 0;
-    for (int z = g.z0; z < g.z1; ++z) {
-        T pv[EY][VEC], cv[EY][VEC], gv[EY][VEC], gv2[EY][VEC], hm[HPT][VEC], hu[HPT][VEC];
+    if constexpr (ROLE == 0) {
+        nev.first(s, g, evb);
 #pragma unroll
         for (int e = 0; e < EY; ++e)
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                qm[2 * R][e][v] = nm[e][v];
-                qu[2 * R][e][v] = nuu[e][v];
-                pv[e][v] = npv[e][v];
-                cv[e][v] = ncc[e][v];
-                gv[e][v] = ngr[e][v];
-                gv2[e][v] = ng2[e][v];
+                rnext[e][v] = T(0);
+                if (evb.any && nev.code[e][v] >= 0) rnext[e][v] = rrow[nev.code[e][v]];
             }
+    }
+    int bz = g.z0 % NB, bh = (g.z0 + HOFF) % NB;
 #pragma unroll
-        for (int j = 0; j < HPT; ++j)
+    for (int j = 0; j < HOFF; ++j) {
+        T *L = lds + ((g.z0 + j) % NB) * C::LDS;
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                hm[j][v] = nhm[j][v];
-                hu[j][v] = nhu[j][v];
-            }
-        load_plane(z + 1, z + 1 < g.z1);
+        for (int k = 0; k < HPT; ++k)
+            if (g.has(k)) vst(L + g.hl[k], hp[j][k]);
+    }
 
-        T *Lm = lds + buf * (2 * C::LDS);
-        T *Lu = Lm + C::LDS;
+    // ROLE 1: Lh u, g1 and g2 of the plane before
+    T lap[EY][VEC], gv[2][EY][VEC], gv2[2][EY][VEC];
+    auto finish = [&](int z, const T (&a1)[EY][VEC], const T (&a2)[EY][VEC]) __attribute__((always_inline)) {
+        const auto bg = plane_buf(gout, pxy, z + R);
+        const T *M = mx + (z & 1) * (C::BX * C::BY);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
-            vst(Lm + (g.ly + e + HY) * C::LW + C::LPAD + g.lx, qm[R][e]);
-            vst(Lu + (g.ly + e + HY) * C::LW + C::LPAD + g.lx, qu[R][e]);
-        }
+            T m[VEC], gn[VEC];
+            vld(m, M + (g.ly + e) * C::BX + g.lx);
 #pragma unroll
-        for (int j = 0; j < HPT; ++j)
-            if (g.has(j)) {
-                vst(Lm + g.hl[j], hm[j]);
-                vst(Lu + g.hl[j], hu[j]);
+            for (int v = 0; v < VEC; ++v) {
+                gn[v] = fma_t(m[v], lap[e][v], a1[e][v]);
+                if (g2) gn[v] = gn[v] + a2[e][v];
+                if (v > 0 && g.gx + v >= s.nx) gn[v] = T(0);  // padding behind the row stays zero
             }
-        __syncthreads();
+            bst<kNontemporal>(bg, g.obr[e], gn);
+        }
+    };
 
-        T mnew[EY][VEC], lapu[EY][VEC];
+    for (int zb = g.z0; zb < g.z1; zb += 2) {
+        static_for<2>([&](auto st_) __attribute__((always_inline)) {
+            constexpr int cs = decltype(st_)::value, ns = cs ^ 1;
+            const int z = zb + cs;
+            if (z >= g.z1) return;
+            const bool more = z + 1 < g.z1;
+            {
+                const auto bt = plane_buf(field, pxy, z + 1 + 2 * R, more);
 #pragma unroll
-        for (int pass = 0; pass < 2; ++pass) {
-            const T *Lp = pass == 0 ? Lm : Lu;
+                for (int e = 0; e < EY; ++e) bld<0>(q[2 * R + 1][e], bt, g.obl[e]);
+            }
+            if constexpr (ROLE == 0) {
+                const auto bp = plane_buf(mout, pxy, z + 1 + R, more), bc = plane_buf(cc, pxy, z + 1 + R, more);
+#pragma unroll
+                for (int e = 0; e < EY; ++e) {
+                    bld<kNontemporal>(pv[ns][e], bp, g.obr[e]);
+                    bld<kNontemporal>(cv[ns][e], bc, g.obr[e]);
+                }
+            } else {
+                const auto b1 = plane_buf(g1, pxy, z + R, g1 != nullptr), b2 = plane_buf(g2, pxy, z + R, g2 != nullptr);
+#pragma unroll
+                for (int e = 0; e < EY; ++e) {
+                    bld<kNontemporal>(gv[cs][e], b1, g.obr[e]);
+                    bld<kNontemporal>(gv2[cs][e], b2, g.obr[e]);
+                }
+            }
+            {
+                const auto bh2 = plane_buf(field, pxy, z + 1 + HOFF + R, z + 1 + HOFF < g.z1);
+#pragma unroll
+                for (int k = 0; k < HPT; ++k) bld<0>(hv[ns][k], bh2, g.hob[k]);
+            }
+            T *L = lds + bz * C::LDS;
+#pragma unroll
+            for (int e = 0; e < EY; ++e) vst(L + (g.ly + e + HY) * C::LW + C::LPAD + g.lx, q[R][e]);
+            {
+                T *LH = lds + bh * C::LDS;
+#pragma unroll
+                for (int k = 0; k < HPT; ++k)
+                    if (g.has(k)) vst(LH + g.hl[k], hv[cs][k]);
+            }
+            __syncthreads();
+            if constexpr (ROLE == 1)
+                if (z > g.z0) finish(z - 1, gv[ns], gv2[ns]);
+
             T yr[C::YR][VEC];
 #pragma unroll
             for (int j = 0; j < C::YR; ++j) {
                 if (j >= HY && j < HY + EY) {
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v) yr[j][v] = pass == 0 ? qm[R][j - HY][v] : qu[R][j - HY][v];
+                    for (int v = 0; v < VEC; ++v) yr[j][v] = q[R][j - HY][v];
                 } else {
-                    vld(yr[j], Lp + (g.ly + j) * C::LW + C::LPAD + g.lx);
+                    vld(yr[j], L + (g.ly + j) * C::LW + C::LPAD + g.lx);
                 }
             }
+            T mnew[EY][VEC];
 #pragma unroll
             for (int e = 0; e < EY; ++e) {
                 T xs[C::NXV * VEC];
@@ -999,16 +1029,16 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
                     T tmp[VEC];
                     if (j * VEC == C::LPAD) {  // this thread's own vector
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) tmp[v] = pass == 0 ? qm[R][e][v] : qu[R][e][v];
+                        for (int v = 0; v < VEC; ++v) tmp[v] = q[R][e][v];
                     } else {
-                        vld(tmp, Lp + (g.ly + e + HY) * C::LW + g.lx + j * VEC);
+                        vld(tmp, L + (g.ly + e + HY) * C::LW + g.lx + j * VEC);
                     }
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) xs[j * VEC + v] = tmp[v];
                 }
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
-                    const T u0 = pass == 0 ? qm[R][e][v] : qu[R][e][v];
+                    const T u0 = q[R][e][v];
                     T acc = T(0);
 #pragma unroll
                     for (int l = 1; l <= R; ++l)
@@ -1019,67 +1049,66 @@ __device__ __forceinline__ void adj_tile(const ShotDesc &s, const typename C::ty
                             acc = fma_t(T(W.w[l]), (yr[HY + e + l][v] - u0) + (yr[HY + e - l][v] - u0), acc);
                     }
 #pragma unroll
-                    for (int l = 1; l <= R; ++l) {
-                        const T zp = pass == 0 ? qm[R + l][e][v] : qu[R + l][e][v];
-                        const T zm = pass == 0 ? qm[R - l][e][v] : qu[R - l][e][v];
-                        acc = fma_t(T(W.w[l]), (zp - u0) + (zm - u0), acc);
-                    }
-                    if (pass == 0)
-                        mnew[e][v] = fma_t(cv[e][v], acc, T(2) * u0 - pv[e][v]);
+                    for (int l = 1; l <= R; ++l)
+                        acc = fma_t(T(W.w[l]), (q[R + l][e][v] - u0) + (q[R - l][e][v] - u0), acc);
+                    if constexpr (ROLE == 0)
+                        mnew[e][v] = fma_t(cv[cs][e][v], acc, T(2) * u0 - pv[cs][e][v]);
                     else
-                        lapu[e][v] = acc;
+                        lap[e][v] = acc;
                 }
             }
-        }
 
-        // adjoint sources: the residual enters at the receivers, scaled by c there
-        if (z == nev.z) {
-            if (!nev.look) {
+            if constexpr (ROLE == 0) {
+                // adjoint sources: the residual enters at the receivers, scaled by c there
+                if (z == nev.z) {
+                    if (!nev.look) {
+#pragma unroll
+                        for (int e = 0; e < EY; ++e)
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v)
+                                if (nev.code[e][v] >= 0)
+                                    mnew[e][v] = fma_t(ramp * cv[cs][e][v], rnext[e][v], mnew[e][v]);
+                        nev.z = 0x7fffffff;
+                    } else {
+                        nev.z = look_events(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                            if (code >= 0) mnew[e][v] = fma_t(ramp * cv[cs][e][v], rrow[code], mnew[e][v]);
+                        });
+                    }
+                }
+                const auto bpm = plane_buf(mout, pxy, z + R);
+                T *M = mx + (z & 1) * (C::BX * C::BY);
+#pragma unroll
+                for (int e = 0; e < EY; ++e) {
+#pragma unroll
+                    for (int v = 1; v < VEC; ++v) mnew[e][v] = g.gx + v < s.nx ? mnew[e][v] : T(0);
+                    vst(M + (g.ly + e) * C::BX + g.lx, mnew[e]);
+                    bst<kNontemporal>(bpm, g.obr[e], mnew[e]);
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < P - 1; ++j)
 #pragma unroll
                 for (int e = 0; e < EY; ++e)
 #pragma unroll
-                    for (int v = 0; v < VEC; ++v)
-                        if (nev.code[e][v] >= 0) mnew[e][v] = fma_t(ramp * cv[e][v], rnext[e][v], mnew[e][v]);
-                nev.z = 0x7fffffff;
-            } else {
-                nev.z = look_events(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
-                    if (code >= 0) mnew[e][v] = fma_t(ramp * cv[e][v], rrow[code], mnew[e][v]);
-                });
-            }
-        }
-
-        const auto bpm = plane_buf(mout, pxy, z + R), bpg = plane_buf(gout, pxy, z + R);
-#pragma unroll
-        for (int e = 0; e < EY; ++e) {
-            T gn[VEC];
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                gn[v] = fma_t(mnew[e][v], lapu[e][v], gv[e][v]);
-                if (g2) gn[v] = gn[v] + gv2[e][v];
-                if (v > 0 && g.gx + v >= s.nx) mnew[e][v] = gn[v] = T(0);  // padding behind the row stays zero
-            }
-            bst<kNontemporal>(bpm, g.obr[e], mnew[e]);
-            bst<kNontemporal>(bpg, g.obr[e], gn);
-        }
-
-#pragma unroll
-        for (int j = 0; j < 2 * R; ++j)
-#pragma unroll
-            for (int e = 0; e < EY; ++e)
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    qm[j][e][v] = qm[j + 1][e][v];
-                    qu[j][e][v] = qu[j + 1][e][v];
-                }
-        buf ^= 1;
+                    for (int v = 0; v < VEC; ++v) q[j][e][v] = q[j + 1][e][v];
+            bz = (bz + 1 == NB) ? 0 : bz + 1;
+            bh = (bh + 1 == NB) ? 0 : bh + 1;
+        });
+    }
+    __syncthreads();
+    if constexpr (ROLE == 1) {
+        if ((g.z1 - 1 - g.z0) & 1)
+            finish(g.z1 - 1, gv[1], gv2[1]);
+        else
+            finish(g.z1 - 1, gv[0], gv2[0]);
     }
 }
 
 template <class C>
-__global__ __launch_bounds__(C::NT) void adj_kernel(AdjArgs a)
+__global__ __launch_bounds__(2 * C::NT) void adj_kernel(AdjArgs a)
 {
     typedef typename C::type T;
-    __shared__ __attribute__((aligned(16))) T lds[4 * C::LDS];
+    __shared__ __attribute__((aligned(16))) T lds[2 * C::NB * C::LDS + 2 * C::BX * C::BY];
     int wg = blockIdx.x;
     if (a.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
     const int tx = wg % a.tiles_x;
@@ -1087,9 +1116,25 @@ __global__ __launch_bounds__(C::NT) void adj_kernel(AdjArgs a)
     const int ty = t2 % a.tiles_y;
     const int cz = t2 / a.tiles_y;
     if (cz >= a.chunks_z) return;
-    adj_tile<C>(a.one, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out),
-                static_cast<const T *>(a.u_km1), static_cast<T *>(a.grad), static_cast<T *>(a.gseg), a.gmode,
-                static_cast<const T *>(a.resid), a.k, T(a.resid_amp), tx, ty, cz, a.zch, lds);
+    const bool image = __builtin_amdgcn_readfirstlane((int)threadIdx.x) >= C::NT;  // uniform over a wave
+
+    const ShotDesc &s = a.one;
+    TileGeom<C> g;
+    g.init(s, tx, ty, cz, a.zch, (int)threadIdx.x - (image ? C::NT : 0));
+    if (g.z0 >= g.z1) return;
+
+    // imaging accumulator: g1 (added through the FMA), g2 (added after it), gout (stored)
+    T *const grad = static_cast<T *>(a.grad), *const gseg = static_cast<T *>(a.gseg);
+    const T *g1 = a.gmode == GM_FIRST ? nullptr : a.gmode == GM_DIRECT ? grad : gseg;
+    const T *g2 = a.gmode == GM_FOLD ? grad : nullptr;
+    T *gout = (a.gmode == GM_ACC || a.gmode == GM_FIRST) ? gseg : grad;
+    T *const mx = lds + 2 * C::NB * C::LDS;
+    if (image)
+        adj_half<C, 1>(s, static_cast<const T *>(a.u_km1), nullptr, g1, g2, gout, nullptr, T(0), g,
+                       lds + C::NB * C::LDS, mx);
+    else
+        adj_half<C, 0>(s, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out), nullptr, nullptr, nullptr,
+                       static_cast<const T *>(a.resid) + (a.k - 1) * s.nrec, T(a.resid_amp), g, lds, mx);
 }
 
 // ------------------------------------------------------------------ registry
@@ -1109,9 +1154,9 @@ struct FwdEntry {
     float cost;          // relative time per point of the tile, where it streams well
 };
 
-// role of an adjoint table entry: an option for fd_set_adj_tuning, or the build that
-// fd_create takes by itself for grids whose rows the default tile fits badly
-enum { ADJ_OPTION = 0, ADJ_RAGGED_X = 1 };
+// Roles of an adjoint tile entry: reached with fd_set_adj_tuning alone, one the library
+// chooses from by itself, or the one it takes where a chunk is a single plane.
+enum { ADJ_OPTION = 0, ADJ_AUTO = 1, ADJ_ONE_PLANE = 2 };
 
 struct AdjEntry {
     const char *name;
@@ -1119,6 +1164,7 @@ struct AdjEntry {
     void (*launch)(const AdjArgs &, int nwg, hipStream_t);
     const void *kernel;
     int role;
+    float cost;  // as in FwdEntry
 };
 
 template <class C, bool BATCH, bool DAMP>
@@ -1154,7 +1200,7 @@ void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
 template <class C>
 void launch_adj(const AdjArgs &a, int nwg, hipStream_t st)
 {
-    hipLaunchKernelGGL(adj_kernel<C>, dim3(nwg), dim3(C::NT), 0, st, a);
+    hipLaunchKernelGGL(adj_kernel<C>, dim3(nwg), dim3(2 * C::NT), 0, st, a);
 }
 
 template <class C, int ROLE>
@@ -1165,9 +1211,10 @@ FwdEntry fwd_entry(const char *name, float cost)
 }
 
 template <class C>
-AdjEntry adj_entry(const char *name, int role = ADJ_OPTION)
+AdjEntry adj_entry(const char *name, int role, float cost)
 {
-    return AdjEntry{name, C::BX, C::BY, C::NT, &launch_adj<C>, reinterpret_cast<const void *>(&adj_kernel<C>), role};
+    return AdjEntry{name, C::BX, C::BY, 2 * C::NT, &launch_adj<C>, reinterpret_cast<const void *>(&adj_kernel<C>), role,
+                    cost};
 }
 
 // Implemented in the per-dtype translation units.

@@ -43,17 +43,21 @@ F64_3D_BIG_R_AUTO = [((16, 16, 1), "AUTO", 1.1), ((32, 16, 1), "AUTO", 1.0), ((8
 F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
 SWEEP_RADII = {4, 8}      # radii that get the OPTION tiles
 F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads
-# adjoint: radii <= 4 128x16 first (measured 5-7 % faster than 64x16)
-ADJ_F32_3D = [(32, 16, 1), (32, 16, 1, 2), (64, 8, 1, 2), (32, 8, 1, 2), (16, 16, 1, 2)]
-# FP32 3-D adjoint, radii <= 4: a 64-wide tile (256 threads) for grids whose rows leave many
-# of the default 128-wide tile's lanes idle; fd_create takes it by itself there (measured,
-# 205 launches each: 320^3 190.0 vs 203.3 us, 192^3 47.2 vs 53.6, 160^3 32.0 vs 38.5; where
-# 128 divides the row the default is faster: 256^3 92.8 vs 97.0, 512^3 700 vs 733)
-ADJ_F32_RAGGED_X = (16, 16, 1)
-ADJ_F32_3D_BIG_R = [(16, 16, 1), (32, 16, 1, 2)]  # radii > 4: two queues of 2r+2 planes
-ADJ_F64_3D = [(32, 16, 1)]        # radii <= 4: 64x16, 512 threads (256^3: 176.0 vs 189.8 us for 64x8)
-ADJ_F64_3D_BIG_R = [(32, 8, 1)]
-ADJ_SWEEP_RADII = {4, 8}
+# 3-D adjoint tiles: (shape, role, relative cost per point); half of a tile's threads own mu,
+# half u, so a workgroup has twice the threads of the shape.  FP32, radii <= 4: the library
+# takes the 128-wide tile or one of the 64-wide ones by how rows fill them, then the cheaper
+# (per step: 256^3 r = 4 87 us with 128x16, 94 with 64x16; 320^3 180 with 64x32, 191 with
+# 128x16; 64^3 5.2 with 64x16, 6.7 with 128x16).
+ADJ_F32_3D = [((32, 16, 1), "AUTO", 1.0), ((16, 32, 1), "AUTO", 1.0), ((16, 16, 1), "AUTO", 1.05)]
+ADJ_F32_3D_OPTIONS = [(8, 16, 1), (32, 8, 1), (8, 8, 1)]
+# radii above 4: 32x8 (192^3 r = 8: 56 us against 61 for 64x16), 64x16 where a chunk is one
+# plane (64^3: 6.6 us against 7.2)
+ADJ_F32_3D_BIG_R = [((8, 8, 1), "AUTO", 1.0), ((16, 16, 1), "ONE_PLANE", 1.0)]
+# FP64: radii <= 4 64x16, two rows per thread (192^3 r = 4: 74 us against 84 with one row and
+# 1024 threads, which spills); radii above 4 16x16 (160^3 r = 8: 63 us against 75 for 64x8)
+ADJ_F64_3D = [((32, 8, 2), "AUTO", 1.0)]
+ADJ_F64_3D_BIG_R = [((8, 16, 1), "AUTO", 1.0)]
+ADJ_OPTION_RADII = {4}
 # VTI kernel: (xy radius, z radius) pairs and tile shapes (threads along x, rows along y)
 VTI_RADII = [(2, 1), (2, 2), (4, 1), (4, 2), (4, 4), (8, 1), (8, 2), (8, 4), (8, 8),
              (12, 1), (12, 2), (12, 4), (12, 8)]
@@ -136,24 +140,22 @@ def fwd_file(T, auto, options, auto_big_r, options_big_r):
         f.write(out)
 
 
-def adj_file(T, d3, d3_big_r=None, ragged_x=None):
-    """Adjoint kernels: a list of 3-D tile shapes per radius (the first is the default),
-    the ragged-row build for radii <= 4 (if given), and one 2-D shape."""
+def adj_file(T, d3, d3_big_r, options=()):
+    """Adjoint kernels: the 3-D tiles of each radius and one 2-D shape.  No early halo: its
+    ring measured 2 % faster at 512^3 and slower everywhere below."""
     tag = "f32" if T == "float" else "f64"
     out = HDR.format(fname=f"fd_adj_{tag}.hip", what="adjoint", T=T)
     for R in range(1, 9):
-        lst = d3_big_r if (d3_big_r and R > 4) else d3
-        lst = lst if R in ADJ_SWEEP_RADII else lst[:1]
+        lst = d3 if R <= 4 else d3_big_r
+        lst = lst + [(o, "OPTION", 1.0) for o in options if R in ADJ_OPTION_RADII]
         out += f"static const AdjEntry a3_r{R}[] = {{\n"
-        for cfg in lst:
-            out += f'    adj_entry<{tilecfg(T, R, 3, *cfg)}>("{cfgname(T, R, 3, *cfg)}"),\n'
-        if ragged_x and R <= 4:
-            out += (f'    adj_entry<{tilecfg(T, R, 3, *ragged_x)}>("{cfgname(T, R, 3, *ragged_x)}", '
-                    f'ADJ_RAGGED_X),\n')
+        for cfg, role, cost in lst:
+            out += (f'    adj_entry<{tilecfg(T, R, 3, *cfg, None, 0, False, 0)}>("{cfgname(T, R, 3, *cfg)}", '
+                    f'ADJ_{role}, {cost}f),\n')
         out += "};\n"
         txn = F2D[0]
-        out += (f"static const AdjEntry a2_r{R}[] = {{adj_entry<TileCfg<{T}, {R}, 2, {txn}, 1, 1>>"
-                f'("{cfgname(T, R, 2, txn, 1, 1)}")}};\n')
+        out += (f"static const AdjEntry a2_r{R}[] = {{adj_entry<{tilecfg(T, R, 2, txn, 1, 1, None, 0, False, 0)}>"
+                f'("{cfgname(T, R, 2, txn, 1, 1)}", ADJ_AUTO, 1.0f)}};\n')
     out += "\nconst AdjEntry *adj_configs_" + tag + "(int r, int ndim, int *count)\n{\n    switch (r * 10 + ndim) {\n"
     for R in range(1, 9):
         for nd in (2, 3):
@@ -189,7 +191,7 @@ def vti_file(T, tiles):
 if __name__ == "__main__":
     fwd_file("float", F32_3D_AUTO, F32_3D_OPTIONS, F32_3D_BIG_R_AUTO, F32_3D_BIG_R_OPTIONS)
     fwd_file("double", F64_3D_AUTO, F64_3D_OPTIONS, F64_3D_BIG_R_AUTO, F64_3D_BIG_R_OPTIONS)
-    adj_file("float", ADJ_F32_3D, ADJ_F32_3D_BIG_R, ADJ_F32_RAGGED_X)
+    adj_file("float", ADJ_F32_3D, ADJ_F32_3D_BIG_R, ADJ_F32_3D_OPTIONS)
     adj_file("double", ADJ_F64_3D, ADJ_F64_3D_BIG_R)
     vti_file("float", VTI_F32)
     vti_file("double", VTI_F64)

@@ -122,3 +122,35 @@ def test_batch_tile_choice_bitwise(oracle_mod, sides):
         assert torch.equal(ua[0], ub[0]) and torch.equal(ua[1], ub[1]) and torch.equal(ta, tb)
         assert float(ta.abs().max()) > 0
     F.fd_batch_destroy(b)
+
+
+@pytest.mark.parametrize("dtype,tol", [("f64", 1e-9), ("f32", 1e-3)])
+@pytest.mark.parametrize("r", [1, 3, 4, 5, 8])
+def test_registered_adjoint_tiles(oracle_mod, r, dtype, tol):
+    # chunks of one, two and an odd number of planes, a grid that divides no tile, the image
+    # summed straight into g and by segments of one and several steps: every registered tile
+    # gives the first one's bits, and that the oracle's gradient (the adjoint's bars)
+    from paper_1410_1387_amd import fdwave as F
+    from test_gpu_adjoint import _gpu_gradient, _problem
+
+    v, pb, obs = _problem(oracle_mod, (23, 21, 133), r, 40, 7, dtype, seed=20 + r)
+    ref = oracle_mod.gradient(v, pb.h, pb.dt, r, pb.nsteps, [(pb.source, oracle_mod.ricker(40, pb.dt, pb.f0, pb.t0))],
+                              pb.receivers, obs)
+    for blocked, ckpt in ((False, 7), (True, 7), (True, 13)):
+        pb.blocked, pb.ckpt = blocked, ckpt
+        base, cfg = None, 0
+        try:
+            while True:
+                try:
+                    F.fd_set_adj_tuning(dtype, r, 3, cfg)
+                except F.FdError:
+                    break
+                say(f"adjoint tile {cfg} {dtype} r={r} blocked={blocked} segments of {ckpt}")
+                g = _gpu_gradient(v, pb, obs)[1]
+                base = g if base is None else base
+                assert np.array_equal(g, base), (cfg, blocked, ckpt)
+                cfg += 1
+        finally:
+            F.fd_set_adj_tuning(dtype, r, 3, -1)
+        assert rel_l2(_gpu_gradient(v, pb, obs)[1], base) == 0.0
+        assert rel_l2(base, ref["grad_v"]) <= tol
