@@ -458,7 +458,9 @@ int fd_vti_set_state(fd_vti_ctx *ctx, const void *p, const void *p_prev, const v
                      int64_t step);
 
 /* Kernel tile configuration in use, and the tuning override (config index, z chunk; 0 = auto)
- * for contexts created afterwards. */
+ * for contexts created afterwards.  (0, 0), which is also what holds before any call, is the
+ * library's own choice: the registered tile whose estimated launch time is lowest for the
+ * grid.  Results are bitwise the same whatever the tile. */
 const char *fd_vti_kernel_config(const fd_vti_ctx *ctx);
 int fd_vti_set_tuning(fd_dtype dtype, int rxy, int rz, int config, int zchunk);
 

@@ -234,19 +234,6 @@ int choose_zch(int64_t tiles_xy, int64_t nz, int r, int slots)
 
 namespace {
 
-// Estimated time of one launch, in points: the points the busiest CU computes (its share of
-// the workgroups, idle lanes and a prologue of 0.3 r planes included) at the tile's own
-// cost, the latency of a chunk's planes, about 300 points each, and of a workgroup's start,
-// longer the more waves it has.  Only its order among the tiles of one grid matters: over
-// cubes of 48 to 512 points and ten ragged grids it picks a tile within 2 % of the best on
-// average (at worst 5 % off for radius 4, 9 % for one cube at radius 6).
-template <class Entry>
-double tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
-{
-    return (double)((nwg + cus - 1) / cus) * e.bx * e.by * e.cost * ((double)zch + 0.3 * r) + 300.0 * (double)zch +
-           1.5 * e.nt;
-}
-
 // FINE tiles are candidates for chunks below this many planes: on the longer chunks of
 // larger grids the early halo pays (288^3 r = 4: 75 us against 79 for the FINE tile).
 constexpr int64_t kFineZch = 32;
@@ -258,36 +245,22 @@ constexpr int64_t kFineZch = 32;
 constexpr int64_t kTwinZchMin = 16, kTwinZchMax = 64;
 
 template <class Entry>
-struct TileChoice {
-    const Entry *e;
-    int64_t tx, ty;
-    int zch;
-
-    int64_t nwg(const Layout &L) const { return tx * ty * ((L.knz + zch - 1) / zch); }
-};
-
-template <class Entry>
 TileChoice<Entry> plan_tile(const Entry &e, const Layout &L)
 {
-    TileChoice<Entry> t;
-    t.e = &e;
-    t.tx = (L.knx + e.bx - 1) / e.bx;
-    t.ty = (L.kny + e.by - 1) / e.by;
-    t.zch = choose_zch(t.tx * t.ty, L.knz, L.r, resident_slots(e.kernel, e.nt));
-    return t;
+    return plan_tile(e, L.knx, L.kny, L.knz, L.r);
 }
 
 // The library's own tile for one shot: the cheapest candidate at its own best z chunk.
 TileChoice<FwdEntry> choose_tile(const FwdEntry *tab, int count, const Layout &L)
 {
     const int cus = device_cus();
-    TileChoice<FwdEntry> best{nullptr, 0, 0, 0};
+    TileChoice<FwdEntry> best{};
     double cost = 0;
     for (int i = 0; i < count; ++i) {
         if (tab[i].role != FWD_AUTO && tab[i].role != FWD_FINE) continue;
         const TileChoice<FwdEntry> t = plan_tile(tab[i], L);
         if (best.e && tab[i].role == FWD_FINE && t.zch >= kFineZch) continue;
-        const double c = tile_cost(tab[i], t.nwg(L), t.zch, L.r, cus);
+        const double c = tile_cost(tab[i], t.nwg, t.zch, L.r, cus);
         if (!best.e || c < cost) {
             best = t;
             cost = c;
@@ -307,12 +280,12 @@ TileChoice<AdjEntry> choose_adj_tile(const AdjEntry *tab, int count, const Layou
     for (int i = 1; i < count; ++i)
         if (tab[i].role == ADJ_AUTO) narrow = std::min(narrow, tab[i].bx);
     const bool wide = row_waste(L.knx, narrow) + kAdjRaggedMargin >= row_waste(L.knx, tab[0].bx) && L.knx >= tab[0].bx;
-    TileChoice<AdjEntry> best{nullptr, 0, 0, 0};
+    TileChoice<AdjEntry> best{};
     double cost = 0;
     for (int i = 0; i < count; ++i) {
         if (tab[i].role != ADJ_AUTO || (narrow < tab[0].bx && (tab[i].bx == tab[0].bx) != wide)) continue;
         const TileChoice<AdjEntry> t = plan_tile(tab[i], L);
-        const double c = tile_cost(tab[i], t.nwg(L), t.zch, L.r, cus);
+        const double c = tile_cost(tab[i], t.nwg, t.zch, L.r, cus);
         if (!best.e || c < cost) {
             best = t;
             cost = c;

@@ -19,4 +19,37 @@ __attribute__((visibility("hidden"))) int resident_slots(const void *kernel, int
 // Planes per z chunk for tiles_xy tiles over nz planes with a z halo of r planes.
 __attribute__((visibility("hidden"))) int choose_zch(int64_t tiles_xy, int64_t nz, int r, int slots);
 
+// Estimated time of one launch, in points: the points the busiest CU computes (its share of
+// the workgroups, idle lanes and a prologue of 0.3 r planes included) at the tile's own
+// cost, the latency of a chunk's planes, about 300 points each, and of a workgroup's start,
+// longer the more waves it has.  Only its order among the tiles of one grid matters: over
+// cubes of 48 to 512 points and ten ragged grids it picks a tile within 2 % of the best on
+// average (at worst 5 % off for radius 4, 9 % for one cube at radius 6).
+template <class Entry>
+double tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
+{
+    return (double)((nwg + cus - 1) / cus) * e.bx * e.by * e.cost * ((double)zch + 0.3 * r) + 300.0 * (double)zch +
+           1.5 * e.nt;
+}
+
+// A tile entry (bx x by points, nt threads, its kernel) laid out over one grid.
+template <class Entry>
+struct TileChoice {
+    const Entry *e = nullptr;
+    int64_t tx = 0, ty = 0, nwg = 0;
+    int zch = 0;
+};
+
+template <class Entry>
+TileChoice<Entry> plan_tile(const Entry &e, int64_t nx, int64_t ny, int64_t nz, int r)
+{
+    TileChoice<Entry> t;
+    t.e = &e;
+    t.tx = (nx + e.bx - 1) / e.bx;
+    t.ty = (ny + e.by - 1) / e.by;
+    t.zch = choose_zch(t.tx * t.ty, nz, r, resident_slots(e.kernel, e.nt));
+    t.nwg = t.tx * t.ty * ((nz + t.zch - 1) / t.zch);
+    return t;
+}
+
 }  // namespace fdw

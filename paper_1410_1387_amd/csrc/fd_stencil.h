@@ -207,6 +207,7 @@ struct TileCfg {
     static constexpr int LPAD = (R + VEC - 1) / VEC * VEC; // x halo rounded to vectors
     static constexpr int LW = BX + 2 * LPAD;               // LDS row length
     static constexpr int HY = (NDIM == 3) ? R : 0;         // y halo rows
+    static constexpr int GZ = R;                           // ghost planes
     static constexpr int LH = BY + 2 * HY;
     static constexpr int LDS = LW * LH;                    // elements per LDS plane
     static constexpr int NXV = 2 * LPAD / VEC + 1;         // vectors read per row for x neighbours
@@ -289,7 +290,8 @@ struct TileGeom {
     int hl[C::HPT];          // halo vector k: LDS offset
     bool hval;               // the last halo vector exists (the others always do)
 
-    __device__ __forceinline__ void init(const ShotDesc &s, int tx, int ty, int cz, int zch, int tid)
+    template <class Desc>
+    __device__ __forceinline__ void init(const Desc &s, int tx, int ty, int cz, int zch, int tid)
     {
         typedef typename C::type T;
         lx = (tid % C::TXN) * C::VEC;
@@ -301,7 +303,7 @@ struct TileGeom {
         z0 = cz * zch;
         z1 = min(z0 + zch, s.nz);
         const int px = (int)s.px;  // a row is shorter than a plane, which is under 2 GiB
-        const int base = (int)(s.off0 - (int64_t)C::R * s.pxy);  // interior (0, 0) within its plane
+        const int base = (int)(s.off0 - (int64_t)C::GZ * s.pxy);  // interior (0, 0) within its plane
 #pragma unroll
         for (int e = 0; e < C::EY; ++e) {
             rin[e] = (gx < s.nx) && (gy + e < s.ny);
@@ -336,8 +338,8 @@ struct TileGeom {
 // ------------------------------------------------------------------ sources and receivers
 
 // Next plane >= z at which one of this thread's columns has an event (INT_MAX if none).
-template <class C>
-__device__ __forceinline__ int next_event(const ShotDesc &s, const TileGeom<C> &g, int z)
+template <class C, class Desc>
+__device__ __forceinline__ int next_event(const Desc &s, const TileGeom<C> &g, int z)
 {
     int nxt = 0x7fffffff;
 #pragma unroll 1
@@ -359,7 +361,8 @@ struct EventBounds {
     int p[C::EY][C::VEC + 1];
     bool any;  // uniform: the chunk holds planes with events
 
-    __device__ __forceinline__ void load(const ShotDesc &s, const TileGeom<C> &g)
+    template <class Desc>
+    __device__ __forceinline__ void load(const Desc &s, const TileGeom<C> &g)
     {
         any = s.ev_ptr && s.ev_zlo < g.z1 && s.ev_zhi >= g.z0;
         if (!any) return;
@@ -382,7 +385,8 @@ struct EventNext {
     int z, code[C::EY][C::VEC];
     bool look;
 
-    __device__ __forceinline__ void first(const ShotDesc &s, const TileGeom<C> &g, const EventBounds<C> &b)
+    template <class Desc>
+    __device__ __forceinline__ void first(const Desc &s, const TileGeom<C> &g, const EventBounds<C> &b)
     {
         z = 0x7fffffff;
         look = false;
@@ -417,15 +421,15 @@ struct EventNext {
         for (int e = 0; e < C::EY; ++e)
 #pragma unroll
             for (int v = 0; v < C::VEC; ++v) look = look || (code[e][v] != kNoEvent && ez[e][v] != z);
-        if (look) z = next_event(s, g, g.z0);
+        if (look) z = next_event<C>(s, g, g.z0);
     }
 };
 
 // Looks up the events of this thread's columns at plane z and runs f(code, row, lane) over
 // them in list order (row and lane are compile-time constants); returns the next plane with
 // one.
-template <class C, class F>
-__device__ __forceinline__ int look_events(const ShotDesc &s, const TileGeom<C> &g, int z, F &&f)
+template <class C, class Desc, class F>
+__device__ __forceinline__ int look_events(const Desc &s, const TileGeom<C> &g, int z, F &&f)
 {
     int nxt = 0x7fffffff;
     static_for<C::EY * C::VEC>([&](auto slot) __attribute__((always_inline)) {
@@ -741,7 +745,7 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                         }
                     nev.z = 0x7fffffff;
                 } else {
-                    nev.z = look_events(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                    nev.z = look_events<C>(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
                         if (code >= 0) {
                             if (trow) trow[code] = un[e][v];
                         } else {
@@ -1070,7 +1074,7 @@ __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::ty
                                     mnew[e][v] = fma_t(ramp * cv[cs][e][v], rnext[e][v], mnew[e][v]);
                         nev.z = 0x7fffffff;
                     } else {
-                        nev.z = look_events(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                        nev.z = look_events<C>(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
                             if (code >= 0) mnew[e][v] = fma_t(ramp * cv[cs][e][v], rrow[code], mnew[e][v]);
                         });
                     }

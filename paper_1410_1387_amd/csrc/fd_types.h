@@ -96,6 +96,10 @@ struct VtiSource {
     int64_t nsamp;
     double scale_p, scale_q;
 };
+struct VtiInlineSource {  // as InlineSource
+    int32_t x, y, z, pad0;
+    VtiSource src;
+};
 
 // Everything one VTI launch reads (passed by value as the kernel argument).
 struct VtiDesc {
@@ -114,6 +118,8 @@ struct VtiDesc {
     void *traces_p;        // [cap][nrec] or null
     void *traces_q;
     int64_t nrec, rec_base, rec_cap;
+    int32_t ev_zlo, ev_zhi, nisrc, pad0;  // as in ShotDesc
+    VtiInlineSource isrc[kInlineSources];
 };
 
 }  // namespace fdw

@@ -27,7 +27,11 @@
 //    written with nontemporal stores over p^{n-1} and q^{n-1}.  Every load of the
 //    next plane is issued one plane ahead of its use.
 //  - The z weights of plane z are uniform across the workgroup (scalar loads).
-//  - Sources and receivers use the column-sorted event list of the acoustic kernel.
+//  - Loads without branches, sources and receivers as in the acoustic kernel.
+//
+// What bounds it: HBM for large grids (36 B per point in FP32: 512^3 R_xy = 12, R_z = 8
+// 862 -> 831 us per step, 5.81 TB/s, when the loads lost their branches and the tile
+// became 128x16), the latency of a plane for small ones (93x118x141 22.6 -> 18.5 us).
 #pragma once
 
 #include "fd_stencil.h"
@@ -39,6 +43,7 @@ struct VtiCfg {
     typedef T type;
     static constexpr int RXY = RXY_;
     static constexpr int RZ = RZ_;
+    static constexpr int R = RXY, HY = RXY, GZ = RZ, EY = 1;  // as TileGeom names them
     static constexpr int TXN = TXN_;                          // threads along x
     static constexpr int TYN = TYN_;                          // threads (= rows) along y
     static constexpr int VEC = V16<T>::N;
@@ -80,41 +85,29 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
     const T *__restrict__ wz = static_cast<const T *>(s.wz);
     const int64_t pxy = s.pxy;
 
-    const int tid = threadIdx.x;
-    const int lx = (tid % C::TXN) * VEC, ly = tid / C::TXN;
-    const int x0 = tx * C::BX, y0 = ty * C::BY;
-    const int gx = x0 + lx, gy = y0 + ly;
-    const int z0 = cz * s.zch;
-    const int z1 = min(z0 + s.zch, s.nz);
-    if (z0 >= z1) return;  // uniform over the workgroup
-    const bool rin = gx < s.nx && gy < s.ny;
+    TileGeom<C> g;
+    g.init(s, tx, ty, cz, s.zch, threadIdx.x);
+    if (g.z0 >= g.z1) return;  // uniform over the workgroup
+    const uint32_t ob = g.obr[0];
 
-    // byte offsets inside a plane; the plane index zp = z + RZ counts the ghost planes.
-    // Every tile point lies inside the aligned row/plane extents, whose padding is zero,
-    // so the loads of the thread's own column need no mask.
-    const int64_t colp = s.off0 + (int64_t)gy * s.px + gx - (int64_t)RZ * pxy;
-    const uint32_t ob = (uint32_t)(colp * (int64_t)sizeof(T));
-    uint32_t hob[HPT];
-    int hl[HPT];
-    bool hval[HPT];
+    EventBounds<C> evb;
+    evb.load(s, g);
+
+    // the samples of a source inside this tile and chunk (see fwd_tile)
+    int srcz[kInlineSources];
+    T srcp[kInlineSources], srcq[kInlineSources];
 #pragma unroll
-    for (int k = 0; k < HPT; ++k) {
-        const int hv = tid + k * C::NT;
-        hval[k] = hv < C::NH;
-        int ry = 0, cx = 0;
-        if (hv < C::NHY) {
-            const int ri = hv / C::TXN;
-            cx = (hv % C::TXN) * VEC;
-            ry = (ri < RXY) ? ri - RXY : C::BY + (ri - RXY);
-        } else if (hv < C::NH) {
-            const int hx = hv - C::NHY;
-            ry = hx / (2 * C::NHS);
-            const int si = hx % (2 * C::NHS);
-            cx = (si < C::NHS) ? -C::LPAD + si * VEC : C::BX + (si - C::NHS) * VEC;
+    for (int i = 0; i < kInlineSources; ++i) {
+        const VtiInlineSource &is = s.isrc[i];
+        srcz[i] = -1;
+        srcp[i] = srcq[i] = T(0);
+        if (i < s.nisrc && is.z >= g.z0 && is.z < g.z1 && is.x >= g.x0 && is.x < g.x0 + C::BX && is.y >= g.y0 &&
+            is.y < g.y0 + C::BY && step < is.src.nsamp) {
+            const T sv = static_cast<const T *>(is.src.wav)[step];
+            srcz[i] = is.z;
+            srcp[i] = T(is.src.scale_p) * sv;
+            srcq[i] = T(is.src.scale_q) * sv;
         }
-        const int64_t ho = s.off0 + (int64_t)(y0 + ry) * s.px + (x0 + cx) - (int64_t)RZ * pxy;
-        hob[k] = (uint32_t)(ho * (int64_t)sizeof(T));
-        hl[k] = (ry + RXY) * C::LW + (cx + C::LPAD);
     }
 
     T q[P][VEC];
@@ -123,67 +116,51 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
 
     // prologue: q planes z0-RZ .. z0+RZ into slots 0 .. 2RZ; everything of plane z0 into set 0
 #pragma unroll
-    for (int k = 0; k <= 2 * RZ; ++k) vld(q[k], plane_at(qcur, pxy, z0 + k, ob));
-    vld(pc[0], plane_at(pcur, pxy, z0 + RZ, ob));
-    vld_nt(pm[0], plane_at(pprev, pxy, z0 + RZ, ob));
-    vld_nt(qm[0], plane_at(qprev, pxy, z0 + RZ, ob));
-    vld_nt(a1[0], plane_at(fax, pxy, z0 + RZ, ob));
-    vld_nt(a2[0], plane_at(fan, pxy, z0 + RZ, ob));
-    vld_nt(a3[0], plane_at(faz, pxy, z0 + RZ, ob));
+    for (int k = 0; k <= 2 * RZ; ++k) bld<0>(q[k], plane_buf(qcur, pxy, g.z0 + k), ob);
+    auto load_plane = [&](auto set, int z, bool on) __attribute__((always_inline)) {
+        constexpr int i = decltype(set)::value;
+        const auto bp = plane_buf(pcur, pxy, z + RZ, on);
+        bld<0>(pc[i], bp, ob);
+        bld<kNontemporal>(pm[i], plane_buf(pprev, pxy, z + RZ, on), ob);
+        bld<kNontemporal>(qm[i], plane_buf(qprev, pxy, z + RZ, on), ob);
+        bld<kNontemporal>(a1[i], plane_buf(fax, pxy, z + RZ, on), ob);
+        bld<kNontemporal>(a2[i], plane_buf(fan, pxy, z + RZ, on), ob);
+        bld<kNontemporal>(a3[i], plane_buf(faz, pxy, z + RZ, on), ob);
 #pragma unroll
-    for (int k = 0; k < HPT; ++k) {
-        if (hval[k])
-            vld(hv[0][k], plane_at(pcur, pxy, z0 + RZ, hob[k]));
-        else
-            vzero(hv[0][k]);
-    }
-
-    // next plane >= z with an event in this thread's column (INT_MAX if none)
-    auto next_ev = [&](int z) {
-        int nxt = 0x7fffffff;
-        if (!s.ev_ptr || !rin) return nxt;
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            if (gx + v < s.nx) {
-                const int cidx = gy * s.nx + gx + v;
-                const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
-                if (lo < hi) {
-                    const int p = lower_bound_z(s.ev, lo, hi, z);
-                    if (p < hi) nxt = min(nxt, s.ev[p].z);
-                }
-            }
-        }
-        return nxt;
+        for (int k = 0; k < HPT; ++k) bld<0>(hv[i][k], bp, g.hob[k]);
     };
-    int nev = next_ev(z0);
+    load_plane(std::integral_constant<int, 0>{}, g.z0, true);
 
-    for (int zb = z0; zb < z1; zb += 2) {
+    EventNext<C> nev;
+    nev.first(s, g, evb);
+    const int64_t row = step - s.rec_base;
+    const bool rec = row >= 0 && row < s.rec_cap;
+    T *const trp = rec && s.traces_p ? static_cast<T *>(s.traces_p) + row * s.nrec : nullptr;
+    T *const trq = rec && s.traces_q ? static_cast<T *>(s.traces_q) + row * s.nrec : nullptr;
+
+    for (int zb = g.z0; zb < g.z1; zb += 2) {
         static_for<2>([&](auto st_) __attribute__((always_inline)) {
             constexpr int cs = decltype(st_)::value, ns = cs ^ 1;
             constexpr int tail = 2 * RZ + 1;
             const int z = zb + cs;
-            if (z >= z1) return;
-            if (z + 1 < z1) {
-                const int zn = z + 1 + RZ;
-                vld(q[tail], plane_at(qcur, pxy, zn + RZ, ob));
-                vld(pc[ns], plane_at(pcur, pxy, zn, ob));
-                vld_nt(pm[ns], plane_at(pprev, pxy, zn, ob));
-                vld_nt(qm[ns], plane_at(qprev, pxy, zn, ob));
-                vld_nt(a1[ns], plane_at(fax, pxy, zn, ob));
-                vld_nt(a2[ns], plane_at(fan, pxy, zn, ob));
-                vld_nt(a3[ns], plane_at(faz, pxy, zn, ob));
+            if (z >= g.z1) return;
+            const bool more = z + 1 < g.z1;
+            bld<0>(q[tail], plane_buf(qcur, pxy, z + 1 + 2 * RZ, more), ob);
+            load_plane(std::integral_constant<int, ns>{}, z + 1, more);
+
+            // this plane's z weights (uniform: scalar loads)
+            const T *__restrict__ wrow = wz + (int64_t)z * NWZ;
+            T wk[NWZ];
 #pragma unroll
-                for (int k = 0; k < HPT; ++k)
-                    if (hval[k]) vld(hv[ns][k], plane_at(pcur, pxy, zn, hob[k]));
-            }
+            for (int j = 0; j < NWZ; ++j) wk[j] = wrow[j];
 
             // stage plane z of p^n (interior from registers, halo) in LDS buffer cs;
             // buffer cs was last read two planes ago, before the previous barrier
             T *L = lds + cs * C::LDS;
-            vst(L + (ly + RXY) * C::LW + C::LPAD + lx, pc[cs]);
+            vst(L + (g.ly + RXY) * C::LW + C::LPAD + g.lx, pc[cs]);
 #pragma unroll
             for (int k = 0; k < HPT; ++k)
-                if (hval[k]) vst(L + hl[k], hv[cs][k]);
+                if (g.has(k)) vst(L + g.hl[k], hv[cs][k]);
             __syncthreads();
 
             // Sxy from LDS
@@ -193,7 +170,12 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
 #pragma unroll
                 for (int j = 0; j < C::NXV; ++j) {
                     T tmp[VEC];
-                    vld(tmp, L + (ly + RXY) * C::LW + lx + j * VEC);
+                    if (j * VEC == C::LPAD) {  // this thread's own vector
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) tmp[v] = pc[cs][v];
+                    } else {
+                        vld(tmp, L + (g.ly + RXY) * C::LW + g.lx + j * VEC);
+                    }
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) xs[j * VEC + v] = tmp[v];
                 }
@@ -208,27 +190,21 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
 #pragma unroll
                 for (int l = 1; l <= RXY; ++l) {
                     T up[VEC], dn[VEC];
-                    vld(up, L + (ly + RXY - l) * C::LW + C::LPAD + lx);
-                    vld(dn, L + (ly + RXY + l) * C::LW + C::LPAD + lx);
+                    vld(up, L + (g.ly + RXY - l) * C::LW + C::LPAD + g.lx);
+                    vld(dn, L + (g.ly + RXY + l) * C::LW + C::LPAD + g.lx);
 #pragma unroll
                     for (int v = 0; v < VEC; ++v) sxy[v] = fma_t(T(W.w[l]), up[v] + dn[v], sxy[v]);
                 }
             }
 
-            // Sz from the queue with this plane's weights (uniform: scalar loads)
+            // Sz from the queue
             T sz[VEC];
-            {
-                const T *__restrict__ wrow = wz + (int64_t)z * NWZ;
-                T wk[NWZ];
 #pragma unroll
-                for (int j = 0; j < NWZ; ++j) wk[j] = wrow[j];
+            for (int v = 0; v < VEC; ++v) {
+                T acc = wk[0] * q[0][v];
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    T acc = wk[0] * q[0][v];
-#pragma unroll
-                    for (int j = 1; j < NWZ; ++j) acc = fma_t(wk[j], q[j][v], acc);
-                    sz[v] = acc;
-                }
+                for (int j = 1; j < NWZ; ++j) acc = fma_t(wk[j], q[j][v], acc);
+                sz[v] = acc;
             }
 
             T pn[VEC], qn[VEC];
@@ -241,54 +217,47 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
             }
 
             // fused sources (before the store) and receivers (after them)
-            if (z == nev) {
-                int nxt = 0x7fffffff;
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    if (rin && gx + v < s.nx) {
-                        const int cidx = gy * s.nx + gx + v;
-                        const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
-                        if (lo < hi) {
-                            int p = lower_bound_z(s.ev, lo, hi, z);
-                            for (; p < hi && s.ev[p].z == z; ++p) {
-                                const int code = s.ev[p].code;
-                                if (code < 0) {
-                                    const VtiSource si = s.src[~code];
-                                    if (step < si.nsamp) {
-                                        const T sv = static_cast<const T *>(si.wav)[step];
-                                        pn[v] += T(si.scale_p) * sv;
-                                        qn[v] += T(si.scale_q) * sv;
-                                    }
-                                } else {
-                                    const int64_t row = step - s.rec_base;
-                                    if (row >= 0 && row < s.rec_cap) {
-                                        if (s.traces_p) static_cast<T *>(s.traces_p)[row * s.nrec + code] = pn[v];
-                                        if (s.traces_q) static_cast<T *>(s.traces_q)[row * s.nrec + code] = qn[v];
-                                    }
-                                }
-                            }
-                            if (p < hi) nxt = min(nxt, s.ev[p].z);
-                        }
-                    }
-                }
-                nev = nxt;
-            }
-
-            if (rin) {
-                T *pp = plane_at(pout, pxy, z + RZ, ob);
-                T *qp = plane_at(qout, pxy, z + RZ, ob);
-                if (gx + VEC <= s.nx) {
-                    vst_nt(pp, pn);
-                    vst_nt(qp, qn);
-                } else {
+            for (int i = kInlineSources - 1; i >= 0; --i)
+                if (z == srcz[i]) {
 #pragma unroll
                     for (int v = 0; v < VEC; ++v)
-                        if (gx + v < s.nx) {
-                            pp[v] = pn[v];
-                            qp[v] = qn[v];
+                        if (g.gx + v == s.isrc[i].x && g.gy == s.isrc[i].y) {
+                            pn[v] += srcp[i];
+                            qn[v] += srcq[i];
                         }
                 }
+            if (z == nev.z) {
+                auto event = [&](int code, T &p, T &qv) __attribute__((always_inline)) {
+                    if (code >= 0) {
+                        if (trp) trp[code] = p;
+                        if (trq) trq[code] = qv;
+                    } else if (code != kNoEvent) {
+                        const VtiSource si = s.src[~code];
+                        if (step < si.nsamp) {
+                            const T sv = static_cast<const T *>(si.wav)[step];
+                            p += T(si.scale_p) * sv;
+                            qv += T(si.scale_q) * sv;
+                        }
+                    }
+                };
+                if (!nev.look) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) event(nev.code[0][v], pn[v], qn[v]);
+                    nev.z = 0x7fffffff;
+                } else {
+                    nev.z = look_events<C>(s, g, z, [&](int code, auto, auto v) __attribute__((always_inline)) {
+                        event(code, pn[v], qn[v]);
+                    });
+                }
             }
+
+            // a vector that straddles the end of its row keeps the padding behind it zero
+#pragma unroll
+            for (int v = 1; v < VEC; ++v)
+                if (g.gx + v >= s.nx) pn[v] = qn[v] = T(0);
+            bst<kNontemporal>(plane_buf(pout, pxy, z + RZ), ob, pn);
+            bst<kNontemporal>(plane_buf(qout, pxy, z + RZ), ob, qn);
 #pragma unroll
             for (int k = 0; k < P - 1; ++k)
 #pragma unroll
@@ -312,11 +281,16 @@ __global__ __launch_bounds__(C::NT) void vti_kernel(VtiDesc s, int64_t step)
     vti_tile<C>(s, step, tx, ty, cz, lds);
 }
 
+// Roles: reached with fd_vti_set_tuning alone, or one the library chooses from by itself.
+enum { VTI_OPTION = 0, VTI_AUTO = 1 };
+
 struct VtiEntry {
     const char *name;
     int rxy, rz, bx, by, nt;
     void (*launch)(const VtiDesc &, int64_t step, int nwg, hipStream_t);
     const void *kernel;
+    int role;
+    float cost;  // as in FwdEntry
 };
 
 template <class C>
@@ -326,10 +300,10 @@ void launch_vti(const VtiDesc &d, int64_t step, int nwg, hipStream_t st)
 }
 
 template <class C>
-VtiEntry vti_entry(const char *name)
+VtiEntry vti_entry(const char *name, int role, float cost)
 {
     return VtiEntry{name, C::RXY, C::RZ, C::BX, C::BY, C::NT, &launch_vti<C>,
-                    reinterpret_cast<const void *>(&vti_kernel<C>)};
+                    reinterpret_cast<const void *>(&vti_kernel<C>), role, cost};
 }
 
 // Implemented in the per-dtype translation units.

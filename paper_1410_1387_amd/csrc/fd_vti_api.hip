@@ -253,10 +253,12 @@ static int upload_vti_tables(fd_vti_ctx *c)
         int32_t z, code;
     };
     std::vector<Tmp> all;
+    // a few sources travel inside the descriptor, more of them in the event list
+    const bool inline_src = (int)c->sources.size() <= kInlineSources;
     c->h_src.clear();
     for (size_t s = 0; s < c->sources.size(); ++s) {
         const VtiSourceRec &sr = c->sources[s];
-        all.push_back(Tmp{sr.pos[1] * L.nx + sr.pos[0], (int32_t)sr.pos[2], ~(int32_t)s});
+        if (!inline_src) all.push_back(Tmp{sr.pos[1] * L.nx + sr.pos[0], (int32_t)sr.pos[2], ~(int32_t)s});
         const double k = c->dt * c->dt / (c->h * c->h * c->dzc[(size_t)sr.pos[2]]);
         c->h_src.push_back(VtiSource{sr.wav, sr.nsamp, sr.amp_p * k, sr.amp_q * k});
     }
@@ -277,6 +279,22 @@ static int upload_vti_tables(fd_vti_ctx *c)
     for (int64_t i = 0; i < L.ncol; ++i) c->h_evptr[(size_t)i + 1] += c->h_evptr[(size_t)i];
     VtiDesc &d = c->desc;
     const bool any = !all.empty();
+    d.ev_zlo = INT32_MAX;
+    d.ev_zhi = -1;
+    for (const Tmp &t : all) {
+        d.ev_zlo = std::min(d.ev_zlo, t.z);
+        d.ev_zhi = std::max(d.ev_zhi, t.z);
+    }
+    d.nisrc = 0;
+    if (inline_src) {
+        for (const VtiSourceRec &sr : c->sources) {
+            VtiInlineSource &is = d.isrc[d.nisrc];
+            is.x = (int32_t)sr.pos[0];
+            is.y = (int32_t)sr.pos[1];
+            is.z = (int32_t)sr.pos[2];
+            is.src = c->h_src[(size_t)d.nisrc++];
+        }
+    }
     d.ev_ptr = any ? reinterpret_cast<const int32_t *>(c->ws + L.o_evptr) : nullptr;
     d.ev = reinterpret_cast<const Event *>(c->ws + L.o_ev);
     d.src = reinterpret_cast<const VtiSource *>(c->ws + L.o_src);
@@ -344,7 +362,7 @@ extern "C" int fd_vti_set_tuning(fd_dtype dtype, int rxy, int rz, int config, in
     if ((dtype != FD_F32 && dtype != FD_F64) || !radii_ok(rxy, rz))
         return fail(FD_E_INVAL, "fd_vti_set_tuning: bad dtype or radius pair");
     vti_table(dtype, rxy, rz, &count);
-    if (config < 0 || config >= count || zchunk < 0)
+    if (config < 0 || config >= count || zchunk < 0)  // (0, 0): the library's own choice
         return fail(FD_E_RANGE, "fd_vti_set_tuning: config %d of %d, zchunk %d", config, count, zchunk);
     std::lock_guard<std::mutex> lk(g_vtune_mu);
     g_vtuning[std::make_tuple((int)dtype, rxy, rz)] = Tuning{config, zchunk};
@@ -400,11 +418,25 @@ extern "C" int fd_vti_create(fd_vti_ctx **out, const fd_grid *g, int rxy, int rz
     c->ws = (char *)workspace;
     c->max_src = max_sources;
     c->max_rec = max_receivers;
-    c->kv = &tab[tu.config];
-    c->tiles_x = (L.nx + c->kv->bx - 1) / c->kv->bx;
-    c->tiles_y = (L.ny + c->kv->by - 1) / c->kv->by;
-    c->zch = tu.zchunk > 0 ? (int)std::min<int64_t>(tu.zchunk, L.nz)
-                           : choose_zch(c->tiles_x * c->tiles_y, L.nz, rz, resident_slots(c->kv->kernel, c->kv->nt));
+    TileChoice<VtiEntry> tile = plan_tile(tab[tu.config], L.nx, L.ny, L.nz, rz);
+    if (tu.config == 0 && tu.zchunk == 0) {
+        // the library's own choice: the candidate that is cheapest for this grid
+        const int cus = device_cus();
+        double best = 1e300;
+        for (int i = 0; i < count; ++i) {
+            if (tab[i].role != VTI_AUTO) continue;
+            const TileChoice<VtiEntry> t = plan_tile(tab[i], L.nx, L.ny, L.nz, rz);
+            const double cost = tile_cost(tab[i], t.nwg, t.zch, rz, cus);
+            if (cost < best) {
+                best = cost;
+                tile = t;
+            }
+        }
+    }
+    c->kv = tile.e;
+    c->tiles_x = tile.tx;
+    c->tiles_y = tile.ty;
+    c->zch = tu.zchunk > 0 ? (int)std::min<int64_t>(tu.zchunk, L.nz) : tile.zch;
     c->chunks_z = (L.nz + c->zch - 1) / c->zch;
     c->dzc.resize((size_t)L.nz);
     for (int64_t k = 0; k < L.nz; ++k) c->dzc[(size_t)k] = 0.5 * (z[(size_t)(k + rz + 1)] - z[(size_t)(k + rz - 1)]);

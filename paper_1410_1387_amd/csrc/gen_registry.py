@@ -61,8 +61,11 @@ ADJ_OPTION_RADII = {4}
 # VTI kernel: (xy radius, z radius) pairs and tile shapes (threads along x, rows along y)
 VTI_RADII = [(2, 1), (2, 2), (4, 1), (4, 2), (4, 4), (8, 1), (8, 2), (8, 4), (8, 8),
              (12, 1), (12, 2), (12, 4), (12, 8)]
-VTI_F32 = [(16, 16), (32, 8), (16, 8), (32, 16)]
-VTI_F64 = [(16, 16), (32, 8)]
+# candidates with their relative cost per point (512^3 R_xy = 12, R_z = 8: 831 us with
+# 128x16, 899 with 64x16; 96^3 11.6 with 32x8, 12.4 with 128x16), and options
+VTI_F32 = [((16, 16), "AUTO", 1.1), ((32, 16), "AUTO", 1.0), ((8, 8), "AUTO", 1.12)]
+VTI_F64 = [((16, 16), "AUTO", 1.2), ((32, 16), "AUTO", 1.0), ((8, 8), "AUTO", 1.2)]
+VTI_OPTIONS = [((32, 8), "OPTION", 1.0), ((16, 8), "OPTION", 1.0)]
 VTI_SWEEP = {(12, 8), (4, 4)}
 
 HDR = """// {fname} -- explicit instantiations of the {what} stencil kernels for {T}
@@ -173,11 +176,11 @@ def vti_file(T, tiles):
     out = HDR.format(fname=f"fd_vti_{tag}.hip", what="VTI", T=T).replace('#include "fd_stencil.h"',
                                                                          '#include "fd_vti.h"')
     for (rxy, rz) in VTI_RADII:
-        lst = tiles if (rxy, rz) in VTI_SWEEP else tiles[:1]
+        lst = tiles + (VTI_OPTIONS if (rxy, rz) in VTI_SWEEP else [])
         out += f"static const VtiEntry v_{rxy}_{rz}[] = {{\n"
-        for (txn, tyn) in lst:
+        for (txn, tyn), role, cost in lst:
             name = f"{tag} vti rxy{rxy} rz{rz} tile {txn * vec}x{tyn} ({txn * tyn} thr)"
-            out += f'    vti_entry<VtiCfg<{T}, {rxy}, {rz}, {txn}, {tyn}>>("{name}"),\n'
+            out += f'    vti_entry<VtiCfg<{T}, {rxy}, {rz}, {txn}, {tyn}>>("{name}", VTI_{role}, {cost}f),\n'
         out += "};\n"
     out += "\nconst VtiEntry *vti_configs_" + tag + "(int rxy, int rz, int *count)\n{\n    switch (rxy * 100 + rz) {\n"
     for (rxy, rz) in VTI_RADII:

@@ -154,3 +154,39 @@ def test_registered_adjoint_tiles(oracle_mod, r, dtype, tol):
             F.fd_set_adj_tuning(dtype, r, 3, -1)
         assert rel_l2(_gpu_gradient(v, pb, obs)[1], base) == 0.0
         assert rel_l2(base, ref["grad_v"]) <= tol
+
+
+@pytest.mark.parametrize("dtype,tol", [("f32", 1e-4), ("f64", 1e-11)])
+@pytest.mark.parametrize("rxy,rz,nsrc", [(12, 8, 1), (4, 4, 3), (8, 2, 2), (2, 1, 5)])
+def test_registered_vti_tiles(oracle_mod, rxy, rz, nsrc, dtype, tol):
+    # every registered tile and chunks of one, several and all planes give the bits of the
+    # library's own choice, and that the oracle's solution; few and many sources, two of
+    # them at one point, and receivers one per column, in a line and on the sources
+    from paper_1410_1387_amd import fdwave as F
+    from test_gpu_vti import _model, run_vti_gpu
+
+    shape, h, T = (11, 19, 70), 10.0, 8
+    vz, eps, delta = _model(shape, seed=rxy)
+    zc = workloads.stretched_z(shape[0], rz, h)
+    dt = 0.5 * oracle_mod.vti_dt_max(rxy, rz, h, oracle_mod.z_weights(zc, rz), vz, eps, delta)
+    rng = np.random.default_rng(rz)
+    at = [(5, 2, 4), (5, 2, 4), (69, 18, 10), (0, 0, 0), (37, 11, 7)]
+    src = [(at[i], rng.standard_normal(T) * 1e6, 1.0, 0.3 * i) for i in range(nsrc)]
+    rec = np.array([(x, 2, 4) for x in range(0, 70, 3)] + [(5, 2, 4)] + [(6, 3, z) for z in range(11)] + [(69, 18, 10)])
+    ref = oracle_mod.vti_forward(vz, eps, delta, h, dt, rxy, rz, T, zc=zc, sources=src, receivers=rec)
+    base = run_vti_gpu(vz, eps, delta, h, zc, dt, rxy, rz, T, dtype, sources=src, receivers=rec)
+    for f in ("p", "q", "traces_p", "traces_q"):
+        assert rel_l2(base[f], ref[f]) <= tol, f
+    cfg = 0
+    while True:
+        try:
+            F.fd_vti_set_tuning(dtype, rxy, rz, cfg, 1)
+        except F.FdError:
+            break
+        for zch in (1, 3, 11):
+            got = run_vti_gpu(vz, eps, delta, h, zc, dt, rxy, rz, T, dtype, sources=src, receivers=rec,
+                              tuning=(cfg, zch))
+            assert all(np.array_equal(got[f], base[f]) for f in base if isinstance(base[f], np.ndarray)), (cfg, zch)
+        cfg += 1
+    F.fd_vti_set_tuning(dtype, rxy, rz, 0, 0)
+    assert cfg >= 3
