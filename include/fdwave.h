@@ -170,6 +170,9 @@ int fd_ricker(void *out, int64_t nsamp, double dt, double f0, double t0, fd_dtyp
 
 /* Advance nsteps leapfrog steps (Sec. 1 time scheme), one stencil launch per step, with
  * the sources added and the receivers recorded inside the launch.  nsteps = 0 is a no-op.
+ * On 2-D grids of up to 64 MiB per field with the zero boundary, no tile set by
+ * fd_set_tuning and at most two sources a launch advances up to eight steps (through two
+ * more fields in the workspace); the results are bitwise those of single steps.
  * Errors: FD_E_RANGE if recording is on and the trace capacity would be exceeded (checked
  * before anything is enqueued), FD_E_STATE if poisoned. */
 int fd_step(fd_ctx *ctx, int64_t nsteps);

@@ -21,7 +21,7 @@ LIB = os.path.join(HERE, "libfdwave.so")
 # translation units: a source and, for the forward kernels (one object per radius), a define
 SOURCES = [(f"fd_fwd_{t}.hip", f"-DFD_RADIUS={r}") for t in ("f32", "f64") for r in (4, 8, 1, 2, 3, 5, 6, 7)] + [
     (s, "") for s in ("fd_adj_f32.hip", "fd_adj_f64.hip", "fd_vti_f32.hip", "fd_vti_f64.hip", "fd_fwd2_f32.hip",
-                      "fd_api.hip", "fd_util.hip", "fd_vti_api.hip")]
+                      "fd_multi2d_f32.hip", "fd_multi2d_f64.hip", "fd_api.hip", "fd_util.hip", "fd_vti_api.hip")]
 ARCH = "gfx950"
 
 

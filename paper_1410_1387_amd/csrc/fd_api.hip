@@ -17,6 +17,7 @@
 
 #include "../../include/fdwave.h"
 #include "fd_fwd2.h"
+#include "fd_multi2d.h"
 #include "fd_stencil.h"
 #include "fd_types.h"
 #include "fd_util.h"
@@ -74,9 +75,13 @@ struct Layout {
     int64_t pxy, off0, elems;
     size_t field_bytes;      // one padded field, rounded to 256 bytes
     // workspace offsets
-    size_t o_desc, o_partial, o_minmax, o_buf0, o_buf1, o_c, o_evptr, o_ev, o_src, o_damp, total;
+    size_t o_desc, o_partial, o_minmax, o_buf0, o_buf1, o_c, o_evptr, o_ev, o_src, o_damp, o_pair, total;
+    bool pair;  // two more fields for launches of several steps (2-D)
     int64_t ncol;
 };
+
+// 2-D grids of up to this many bytes per field step several times per launch.
+constexpr size_t kMulti2dFieldBytes = (size_t)64 << 20;
 
 bool make_layout(const fd_grid *g, int r, fd_dtype dt, int64_t max_src, int64_t max_rec, Layout *L)
 {
@@ -126,6 +131,9 @@ bool make_layout(const fd_grid *g, int r, fd_dtype dt, int64_t max_src, int64_t 
     o += align_up(std::max<int64_t>(1, max_src) * (int64_t)sizeof(SourceInfo), 256);
     L->o_damp = o;
     o += align_up((L->knx + L->kny + L->knz) * (int64_t)L->esize, 256);
+    L->pair = L->ndim == 2 && L->field_bytes <= kMulti2dFieldBytes;
+    L->o_pair = o;
+    if (L->pair) o += 2 * L->field_bytes;
     L->total = o;
     return true;
 }
@@ -297,6 +305,24 @@ TileChoice<AdjEntry> choose_adj_tile(const AdjEntry *tab, int count, const Layou
     return best;
 }
 
+// The several-steps kernel of a 2-D grid.  While one round of workgroups covers the grid the
+// time is the chain load, k steps, store, so many steps on small tiles win; beyond that it is
+// the work on the widened tiles, which wants large tiles and few steps (k r around 8), and
+// for r > 4 a tile of any size that fits LDS costs more than the launches it saves
+// (1203 x 800 points, r = 8, FP32: 7.4 us against 6.3 for a single step), so those stay with
+// the single-step kernel.  The tables hold both sides of each line.
+const Multi2dEntry *choose_multi2d(fd_dtype dt, const Layout &L)
+{
+    if (!L.pair) return nullptr;
+    int count = 0;
+    const Multi2dEntry *tab = dt == FD_F32 ? multi2d_configs_f32(L.r, &count) : multi2d_configs_f64(L.r, &count);
+    for (int i = 0; i < count; ++i) {
+        const int64_t tiles = ((L.knx + tab[i].tx - 1) / tab[i].tx) * ((L.knz + tab[i].tz - 1) / tab[i].tz);
+        if (!tab[i].per_cu || tiles <= (int64_t)tab[i].per_cu * device_cus()) return &tab[i];
+    }
+    return nullptr;
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------ context
@@ -340,6 +366,8 @@ struct fd_ctx {
     int64_t step;
     bool poisoned;
     int xcd_remap;
+    // several steps per launch (2-D)
+    const Multi2dEntry *km;
     // two-step forward (temporal blocking): two caller-provided padded fields
     void *aux[2];
     const Fwd2Entry *k2;
@@ -598,6 +626,7 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->adj_tiles_y = adj.ty;
     c->adj_zch = adj.zch;
     c->adj_chunks_z = (L.knz + c->adj_zch - 1) / c->adj_zch;
+    c->km = tuned ? nullptr : choose_multi2d(dtype, L);  // a caller's tile is used for every step
     c->nrec = 0;
     c->traces = nullptr;
     c->rec_cap = 0;
@@ -614,7 +643,7 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->adj_cfg_name = nm;
 
     // zero the workspace: both wavefields (u^0 = u^-1 = 0), c ghosts, tables
-    hipError_t e = hipMemsetAsync(workspace, 0, L.total, c->stream);
+    hipError_t e = hipMemsetAsync(workspace, 0, L.o_pair, c->stream);
     if (e == hipSuccess) {
         const double k = (dt / h) * (dt / h);
         e = launch_prep((int)dtype, geom_of(L), velocity, c->cfield(), k, (double *)(c->ws + L.o_partial),
@@ -859,6 +888,37 @@ extern "C" int fd_set_time_blocking(fd_ctx *ctx, void *aux, size_t aux_bytes, in
     return FD_OK;
 }
 
+// Steps n .. n+k-1 of a 2-D context in one launch: u^n and u^{n-1} from cur and prev; u^{n+k}
+// and u^{n+k-1} into out and out_prev, or, with `all`, every new level into consecutive
+// fields from there.  No output may be an input.
+static void launch_multi2d(fd_ctx *c, const void *cur, const void *prev, void *out, void *out_prev, void *all,
+                           int64_t step, int64_t k, int record)
+{
+    Multi2dArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.one = c->desc;
+    a.cur = cur;
+    a.prev = prev;
+    a.out = out;
+    a.out_prev = out_prev;
+    a.all = all;
+    a.field = (int64_t)c->L.field_bytes;
+    a.step = step;
+    a.k = (int32_t)k;
+    a.record = record;
+    a.tiles_x = (int32_t)((c->L.knx + c->km->tx - 1) / c->km->tx);
+    a.tiles_z = (int32_t)((c->L.knz + c->km->tz - 1) / c->km->tz);
+    a.xcd_remap = c->xcd_remap;
+    c->km->launch(a, c->stream);
+}
+
+// Whether this context's steps can share launches: its sources have to travel in the
+// descriptor.
+static bool multi2d_ok(const fd_ctx *c)
+{
+    return c->km && c->bc == FD_BC_ZERO && c->desc.nisrc == (int32_t)c->sources.size();
+}
+
 extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
 {
     int st = check_ctx(ctx);
@@ -881,6 +941,22 @@ extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
             launch_two_step(ctx, ctx->aux[1], ctx->aux[0], ctx->buf((int)((n + 3) & 1)), ctx->buf((int)(n & 1)), n + 2);
             HIP_TRY(ctx, hipGetLastError());
             ctx->step += 4;
+        }
+    }
+    if (multi2d_ok(ctx)) {
+        // pairs of launches, into the second pair of fields and back into the first, which
+        // then has its usual roles; the last pair shares out what is left
+        void *const pair[2] = {ctx->ws + ctx->L.o_pair, ctx->ws + ctx->L.o_pair + ctx->L.field_bytes};
+        while (nsteps - i >= 2) {
+            const int64_t n = ctx->step, two = std::min<int64_t>(nsteps - i, 2 * ctx->km->kmax);
+            const int64_t k1 = (two + 1) / 2, m = n + two;
+            launch_multi2d(ctx, ctx->buf((int)(n & 1)), ctx->buf((int)((n + 1) & 1)), pair[0], pair[1], nullptr, n, k1, 1);
+            HIP_TRY(ctx, hipGetLastError());
+            launch_multi2d(ctx, pair[0], pair[1], ctx->buf((int)(m & 1)), ctx->buf((int)((m + 1) & 1)), nullptr, n + k1,
+                           two - k1, 1);
+            HIP_TRY(ctx, hipGetLastError());
+            ctx->step = m;
+            i += two;
         }
     }
     for (; i < nsteps; ++i) {

@@ -1,0 +1,112 @@
+"""2-D grids, whose steps share launches, against single steps and the oracle (needs an
+MI355X)."""
+
+import numpy as np
+import pytest
+
+import workloads
+from gpu_util import rel_l2, say
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-4, "f64": 1e-11}
+T, START = 37, 5
+
+
+def _run(shape, r, dtype, dt, calls, sources, rec, v, u0, um1, damping):
+    """T steps from step START in calls of the given sizes, recorded from the second call on."""
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+
+    def dev(a):
+        return torch.tensor(np.asarray(a), dtype=tdt, device="cuda")
+
+    p = Propagator(dev(v), r, 10.0, dt, dtype, max_sources=max(1, len(sources)), max_receivers=len(rec))
+    if damping:
+        p.set_damping(*damping)
+    for pos, wav in sources:
+        p.inject(dev(wav), pos)
+    p.set_state(dev(u0), dev(um1), START)
+    p.step(calls[0])
+    traces = p.record(rec, T)
+    for n in calls[1:]:
+        p.step(n)
+    u, u_prev, step = p.state()
+    p.sync()
+    assert step == START + T
+    return u.cpu().numpy(), u_prev.cpu().numpy(), traces.cpu().numpy()
+
+
+def _inputs(oracle_mod, shape, r, nsrc, seed):
+    # sources that share a point, lie in corners, end early and (the third) end the sharing;
+    # receivers on every point of two lines, on a source and twice at one point
+    nz, nx = shape
+    rng = np.random.default_rng(seed)
+    v = workloads.layered_velocity(shape, seed=seed)
+    u0 = rng.standard_normal(shape)
+    dt = 0.4 * oracle_mod.dt_max(2, r, 10.0, v.max())
+    at = [(nx // 2, nz // 3), (nx // 2, nz // 3), (nx - 1, nz - 1)]
+    sources = [(at[i], 100.0 * rng.standard_normal(START + T - 11 * i)) for i in range(nsrc)]
+    rec = [(x, nz // 2) for x in range(nx)] + [(nx // 3, z) for z in range(nz)] + [at[0], (0, 0), (0, 0), at[2]]
+    return v, u0, 0.5 * u0, dt, sources, np.array(rec)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("r", range(1, 9))
+def test_shared_launches_bitwise(oracle_mod, r, dtype):
+    # one tile, several with remainders, and (as many tiles as choose the deep, the shallow
+    # and no shared launch) larger grids; whole calls and calls of every size
+    for shape, nsrc, damping in [((1, 1), 0, None), ((5, 3), 1, None), ((29, 133), 2, (6, 0.05)), ((75, 38), 2, None),
+                                 ((33, 66), 3, None), ((521, 545), 1, (9, 0.03)), ((550, 1601), 1, None),
+                                 ((1101, 1599), 2, None)]:
+        v, u0, um1, dt, sources, rec = _inputs(oracle_mod, shape, r, nsrc, r)
+        one = [1] * T
+        say(f"2-D shared launches shape={shape} r={r} dtype={dtype} sources={nsrc} damping={damping}")
+        want = _run(shape, r, dtype, dt, one, sources, rec, v, u0, um1, damping)
+        for calls in ([T], [1, T - 1], [2, 3, 5, 9, 1, 17]):
+            got = _run(shape, r, dtype, dt, calls, sources, rec, v, u0, um1, damping)
+            assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), (shape, calls)
+            n = T - calls[0]  # rows recorded by both
+            assert np.array_equal(got[2][:n], want[2][T - 1 - n:T - 1]), (shape, calls)
+        if shape[0] * shape[1] > 4000:
+            continue
+        late = [(p, np.concatenate([w[START:], np.zeros(START + T - len(w))])) for p, w in sources]
+        ref = oracle_mod.forward(v, 10.0, dt, r, T, late, rec, u0=u0, um1=um1, damping=damping)
+        assert rel_l2(want[0], ref["u"]) <= TOL[dtype] and rel_l2(want[2][:T - 1], ref["traces"][1:]) <= TOL[dtype]
+
+
+def test_shared_launches_under_capture(oracle_mod):
+    # a captured call of several steps replays what it did, from the state it is given
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+
+    v, u0, um1, dt, sources, rec = _inputs(oracle_mod, (90, 210), 4, 1, 3)
+    stream = torch.cuda.Stream()
+    vd = torch.tensor(v, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    p = Propagator(vd, 4, 10.0, dt, "f32", max_receivers=len(rec), stream=stream)
+    state = [torch.tensor(a, dtype=torch.float32, device="cuda") for a in (u0, um1)]
+    wav = torch.tensor(sources[0][1], dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        p.inject(wav, sources[0][0])
+        traces = p.record(rec, 2 * T)
+        p.set_state(state[0], state[1], 0)
+        p.step(20)
+        want, want_tr = p.state()[0].clone(), traces.clone()
+        p.sync()
+        p.set_state(state[0], state[1], 0)
+        p.sync()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            p.step(20)
+        for _ in range(3):
+            p.set_state(state[0], state[1], 20)
+            traces.zero_()
+            g.replay()
+            assert torch.equal(p.state()[0], want)
+            assert torch.equal(traces, want_tr)
