@@ -5,52 +5,52 @@
 
 namespace fdw {
 static const AdjEntry a3_r1[] = {
-    adj_entry<TileCfg<float, 1, 3, 32, 16, 1, 4, 0, false, 0>>("f32 r1 3d tile 128x16 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 1, 3, 16, 32, 1, 4, 0, false, 0>>("f32 r1 3d tile 64x32 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 1, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r1 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_AUTO, 1.05f),
+    adj_entry<TileCfg<float, 1, 3, 32, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r1 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 1, 3, 16, 32, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r1 3d tile 64x32 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 1, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r1 3d tile 64x16 (256 thr, 1 row/thr)", 1.05f),
 };
-static const AdjEntry a2_r1[] = {adj_entry<TileCfg<float, 1, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r1 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r1[] = {adj_entry<TileCfg<float, 1, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r1 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r2[] = {
-    adj_entry<TileCfg<float, 2, 3, 32, 16, 1, 4, 0, false, 0>>("f32 r2 3d tile 128x16 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 2, 3, 16, 32, 1, 4, 0, false, 0>>("f32 r2 3d tile 64x32 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 2, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r2 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_AUTO, 1.05f),
+    adj_entry<TileCfg<float, 2, 3, 32, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r2 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 2, 3, 16, 32, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r2 3d tile 64x32 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 2, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r2 3d tile 64x16 (256 thr, 1 row/thr)", 1.05f),
 };
-static const AdjEntry a2_r2[] = {adj_entry<TileCfg<float, 2, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r2 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r2[] = {adj_entry<TileCfg<float, 2, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r2 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r3[] = {
-    adj_entry<TileCfg<float, 3, 3, 32, 16, 1, 4, 0, false, 0>>("f32 r3 3d tile 128x16 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 3, 3, 16, 32, 1, 4, 0, false, 0>>("f32 r3 3d tile 64x32 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 3, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r3 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_AUTO, 1.05f),
+    adj_entry<TileCfg<float, 3, 3, 32, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r3 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 3, 3, 16, 32, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r3 3d tile 64x32 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 3, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r3 3d tile 64x16 (256 thr, 1 row/thr)", 1.05f),
 };
-static const AdjEntry a2_r3[] = {adj_entry<TileCfg<float, 3, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r3 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r3[] = {adj_entry<TileCfg<float, 3, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r3 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r4[] = {
-    adj_entry<TileCfg<float, 4, 3, 32, 16, 1, 4, 0, false, 0>>("f32 r4 3d tile 128x16 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 4, 3, 16, 32, 1, 4, 0, false, 0>>("f32 r4 3d tile 64x32 (512 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 4, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r4 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_AUTO, 1.05f),
-    adj_entry<TileCfg<float, 4, 3, 8, 16, 1, 4, 0, false, 0>>("f32 r4 3d tile 32x16 (128 thr, 1 row/thr)", ADJ_OPTION, 1.0f),
-    adj_entry<TileCfg<float, 4, 3, 32, 8, 1, 4, 0, false, 0>>("f32 r4 3d tile 128x8 (256 thr, 1 row/thr)", ADJ_OPTION, 1.0f),
-    adj_entry<TileCfg<float, 4, 3, 8, 8, 1, 4, 0, false, 0>>("f32 r4 3d tile 32x8 (64 thr, 1 row/thr)", ADJ_OPTION, 1.0f),
+    adj_entry<TileCfg<float, 4, 3, 32, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r4 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 4, 3, 16, 32, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r4 3d tile 64x32 (512 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 4, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r4 3d tile 64x16 (256 thr, 1 row/thr)", 1.05f),
+    adj_entry<TileCfg<float, 4, 3, 8, 16, 1, 4, 0, false, 0>, ADJ_OPTION>("f32 r4 3d tile 32x16 (128 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 4, 3, 32, 8, 1, 4, 0, false, 0>, ADJ_OPTION>("f32 r4 3d tile 128x8 (256 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 4, 3, 8, 8, 1, 4, 0, false, 0>, ADJ_OPTION>("f32 r4 3d tile 32x8 (64 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r4[] = {adj_entry<TileCfg<float, 4, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r4 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r4[] = {adj_entry<TileCfg<float, 4, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r4 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r5[] = {
-    adj_entry<TileCfg<float, 5, 3, 8, 8, 1, 4, 0, false, 0>>("f32 r5 3d tile 32x8 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 5, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r5 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_ONE_PLANE, 1.0f),
+    adj_entry<TileCfg<float, 5, 3, 8, 8, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r5 3d tile 32x8 (64 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 5, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_ONE_PLANE>("f32 r5 3d tile 64x16 (256 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r5[] = {adj_entry<TileCfg<float, 5, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r5 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r5[] = {adj_entry<TileCfg<float, 5, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r5 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r6[] = {
-    adj_entry<TileCfg<float, 6, 3, 8, 8, 1, 4, 0, false, 0>>("f32 r6 3d tile 32x8 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 6, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r6 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_ONE_PLANE, 1.0f),
+    adj_entry<TileCfg<float, 6, 3, 8, 8, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r6 3d tile 32x8 (64 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 6, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_ONE_PLANE>("f32 r6 3d tile 64x16 (256 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r6[] = {adj_entry<TileCfg<float, 6, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r6 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r6[] = {adj_entry<TileCfg<float, 6, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r6 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r7[] = {
-    adj_entry<TileCfg<float, 7, 3, 8, 8, 1, 4, 0, false, 0>>("f32 r7 3d tile 32x8 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 7, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r7 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_ONE_PLANE, 1.0f),
+    adj_entry<TileCfg<float, 7, 3, 8, 8, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r7 3d tile 32x8 (64 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 7, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_ONE_PLANE>("f32 r7 3d tile 64x16 (256 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r7[] = {adj_entry<TileCfg<float, 7, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r7 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r7[] = {adj_entry<TileCfg<float, 7, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r7 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r8[] = {
-    adj_entry<TileCfg<float, 8, 3, 8, 8, 1, 4, 0, false, 0>>("f32 r8 3d tile 32x8 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
-    adj_entry<TileCfg<float, 8, 3, 16, 16, 1, 4, 0, false, 0>>("f32 r8 3d tile 64x16 (256 thr, 1 row/thr)", ADJ_ONE_PLANE, 1.0f),
+    adj_entry<TileCfg<float, 8, 3, 8, 8, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r8 3d tile 32x8 (64 thr, 1 row/thr)", 1.0f),
+    adj_entry<TileCfg<float, 8, 3, 16, 16, 1, 4, 0, false, 0>, ADJ_ONE_PLANE>("f32 r8 3d tile 64x16 (256 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r8[] = {adj_entry<TileCfg<float, 8, 2, 64, 1, 1, 4, 0, false, 0>>("f32 r8 2d tile 256x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r8[] = {adj_entry<TileCfg<float, 8, 2, 64, 1, 1, 4, 0, false, 0>, ADJ_AUTO>("f32 r8 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f)};
 
 const AdjEntry *adj_configs_f32(int r, int ndim, int *count)
 {

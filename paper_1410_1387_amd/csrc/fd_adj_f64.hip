@@ -5,37 +5,37 @@
 
 namespace fdw {
 static const AdjEntry a3_r1[] = {
-    adj_entry<TileCfg<double, 1, 3, 32, 8, 2, 2, 0, false, 0>>("f64 r1 3d tile 64x16 (256 thr, 2 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 1, 3, 32, 8, 2, 2, 0, false, 0>, ADJ_AUTO>("f64 r1 3d tile 64x16 (256 thr, 2 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r1[] = {adj_entry<TileCfg<double, 1, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r1 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r1[] = {adj_entry<TileCfg<double, 1, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r1 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r2[] = {
-    adj_entry<TileCfg<double, 2, 3, 32, 8, 2, 2, 0, false, 0>>("f64 r2 3d tile 64x16 (256 thr, 2 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 2, 3, 32, 8, 2, 2, 0, false, 0>, ADJ_AUTO>("f64 r2 3d tile 64x16 (256 thr, 2 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r2[] = {adj_entry<TileCfg<double, 2, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r2 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r2[] = {adj_entry<TileCfg<double, 2, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r2 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r3[] = {
-    adj_entry<TileCfg<double, 3, 3, 32, 8, 2, 2, 0, false, 0>>("f64 r3 3d tile 64x16 (256 thr, 2 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 3, 3, 32, 8, 2, 2, 0, false, 0>, ADJ_AUTO>("f64 r3 3d tile 64x16 (256 thr, 2 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r3[] = {adj_entry<TileCfg<double, 3, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r3 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r3[] = {adj_entry<TileCfg<double, 3, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r3 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r4[] = {
-    adj_entry<TileCfg<double, 4, 3, 32, 8, 2, 2, 0, false, 0>>("f64 r4 3d tile 64x16 (256 thr, 2 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 4, 3, 32, 8, 2, 2, 0, false, 0>, ADJ_AUTO>("f64 r4 3d tile 64x16 (256 thr, 2 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r4[] = {adj_entry<TileCfg<double, 4, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r4 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r4[] = {adj_entry<TileCfg<double, 4, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r4 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r5[] = {
-    adj_entry<TileCfg<double, 5, 3, 8, 16, 1, 2, 0, false, 0>>("f64 r5 3d tile 16x16 (128 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 5, 3, 8, 16, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r5 3d tile 16x16 (128 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r5[] = {adj_entry<TileCfg<double, 5, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r5 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r5[] = {adj_entry<TileCfg<double, 5, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r5 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r6[] = {
-    adj_entry<TileCfg<double, 6, 3, 8, 16, 1, 2, 0, false, 0>>("f64 r6 3d tile 16x16 (128 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 6, 3, 8, 16, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r6 3d tile 16x16 (128 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r6[] = {adj_entry<TileCfg<double, 6, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r6 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r6[] = {adj_entry<TileCfg<double, 6, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r6 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r7[] = {
-    adj_entry<TileCfg<double, 7, 3, 8, 16, 1, 2, 0, false, 0>>("f64 r7 3d tile 16x16 (128 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 7, 3, 8, 16, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r7 3d tile 16x16 (128 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r7[] = {adj_entry<TileCfg<double, 7, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r7 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r7[] = {adj_entry<TileCfg<double, 7, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r7 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 static const AdjEntry a3_r8[] = {
-    adj_entry<TileCfg<double, 8, 3, 8, 16, 1, 2, 0, false, 0>>("f64 r8 3d tile 16x16 (128 thr, 1 row/thr)", ADJ_AUTO, 1.0f),
+    adj_entry<TileCfg<double, 8, 3, 8, 16, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r8 3d tile 16x16 (128 thr, 1 row/thr)", 1.0f),
 };
-static const AdjEntry a2_r8[] = {adj_entry<TileCfg<double, 8, 2, 64, 1, 1, 2, 0, false, 0>>("f64 r8 2d tile 128x1 (64 thr, 1 row/thr)", ADJ_AUTO, 1.0f)};
+static const AdjEntry a2_r8[] = {adj_entry<TileCfg<double, 8, 2, 64, 1, 1, 2, 0, false, 0>, ADJ_AUTO>("f64 r8 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f)};
 
 const AdjEntry *adj_configs_f64(int r, int ndim, int *count)
 {

@@ -32,6 +32,17 @@ double tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
            1.5 * e.nt;
 }
 
+// Whether `bytes` of fields that every step reads and writes stay in the 256 MB last-level
+// cache from one step to the next.  Then loads that a step makes once per point (u^{n-1},
+// c, ...) keep their lines; otherwise they are nontemporal, so that they do not push out the
+// lines of u^n that neighbouring tiles share.  Measured, nontemporal -> cached, us per step:
+// 96x118x141 FP32 r = 4 10.3 -> 9.1, 160^3 19.1 -> 16.2, 192^3 (85 MB) 25.3 -> 23.6, 256^3
+// (201 MB) 45.8 -> 44.2; past the line 480x303x130 (227 MB) 69.4 -> 70.5, 140x440x330 (244
+// MB) 60.0 -> 60.5, 288^3 (287 MB) 73.6 -> 76.1, 320^3 (393 MB) 87.6 -> 109; VTI 192^3 (198
+// MB) 62 -> 57.6, 160^3 FP64 (229 MB) 50.6 -> 50.9, 256^3 (470 MB) 103 -> 124.
+constexpr double kCacheBytes = 208.0 * (1 << 20);
+inline bool cache_keeps(double bytes) { return bytes <= kCacheBytes; }
+
 // A tile entry (bx x by points, nt threads, its kernel) laid out over one grid.
 template <class Entry>
 struct TileChoice {

@@ -235,6 +235,12 @@ struct TileCfg {
 constexpr uint32_t kOffGrid = 0x80000000u;
 constexpr int kNontemporal = 2;  // cache policy bit of the buffer instructions
 
+// Cache policy of the loads of fields that a step reads point by point (u^{n-1}, c, ...):
+// CACHED where a step's fields stay in the last-level cache until the next step reads them
+// again, nontemporal otherwise (the host decides, cache_keeps()).
+template <bool CACHED>
+constexpr int kPointLoads = CACHED ? 0 : kNontemporal;
+
 template <typename T>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_buf(const T *base, int64_t pxy, int zp, bool on = true)
 {
@@ -493,7 +499,7 @@ __device__ __forceinline__ T *plane_at(T *base, int64_t pxy, int zp, uint32_t ob
 //
 // DAMP: the sponge's per-axis factors are in s.damp (a null s.damp counts as all ones, for
 // batches that mix damped and undamped shots); G = gx gy gz scales both time levels.
-template <class C, bool DAMP>
+template <class C, bool DAMP, int LD>
 __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::type *__restrict__ cur,
                                          const typename C::type *prev, typename C::type *out,
                                          int64_t step, bool record, int tx, int ty, int cz,
@@ -556,8 +562,8 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
         const auto bp = plane_buf(prev, pxy, g.z0 + R), bc = plane_buf(cc, pxy, g.z0 + R);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
-            bld<kNontemporal>(pv[0][e], bp, g.obr[e]);
-            bld<kNontemporal>(cv[0][e], bc, g.obr[e]);
+            bld<LD>(pv[0][e], bp, g.obr[e]);
+            bld<LD>(cv[0][e], bc, g.obr[e]);
         }
         const auto bh = plane_buf(cur, pxy, g.z0 + HOFF + R, g.z0 + HOFF < g.z1);
 #pragma unroll
@@ -615,8 +621,8 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                 const auto bp = plane_buf(prev, pxy, z + 1 + R, more), bc = plane_buf(cc, pxy, z + 1 + R, more);
 #pragma unroll
                 for (int e = 0; e < EY; ++e) {
-                    bld<kNontemporal>(pv[ns][e], bp, g.obr[e]);
-                    bld<kNontemporal>(cv[ns][e], bc, g.obr[e]);
+                    bld<LD>(pv[ns][e], bp, g.obr[e]);
+                    bld<LD>(cv[ns][e], bc, g.obr[e]);
                 }
                 const auto bh2 = plane_buf(cur, pxy, z + 1 + HOFF + R, z + 1 + HOFF < g.z1);
 #pragma unroll
@@ -710,8 +716,8 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                 const auto bp = plane_buf(prev, pxy, z + 1 + R, more), bc = plane_buf(cc, pxy, z + 1 + R, more);
 #pragma unroll
                 for (int e = 0; e < EY; ++e) {
-                    bld<kNontemporal>(pv[0][e], bp, g.obr[e]);
-                    bld<kNontemporal>(cv[0][e], bc, g.obr[e]);
+                    bld<LD>(pv[0][e], bp, g.obr[e]);
+                    bld<LD>(cv[0][e], bc, g.obr[e]);
                 }
                 if constexpr (DAMP) gz[0] = load_gz(z + 1);
             }
@@ -778,7 +784,7 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
 // BATCH: the shot of a workgroup is looked up in the batch's table in device memory.
 // Otherwise the one shot's descriptor comes with the launch arguments, where it is read
 // with scalar loads that wait for nothing but the launch itself.
-template <class C, bool BATCH, bool DAMP>
+template <class C, bool BATCH, bool DAMP, int LD>
 __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
 {
     typedef typename C::type T;
@@ -805,7 +811,7 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         const int ty = t2 % s.tiles_y;
         const int cz = t2 / s.tiles_y;
         if (cz >= s.chunks_z) return;
-        fwd_tile<C, DAMP>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
+        fwd_tile<C, DAMP, LD>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
     } else {
         int shot = 0, local = wg;
         if (a.nshots > 1) {
@@ -838,22 +844,22 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         const int ty = t2 % s.tiles_y;
         const int cz = t2 / s.tiles_y;
         if (cz >= s.chunks_z) return;
-        fwd_tile<C, DAMP>(s, cur, out, out, step, a.record != 0, tx, ty, cz, lds);
+        fwd_tile<C, DAMP, LD>(s, cur, out, out, step, a.record != 0, tx, ty, cz, lds);
     }
 }
 
-template <class C, bool BATCH, bool DAMP>
+template <class C, bool BATCH, bool DAMP, int LD>
 __global__ __launch_bounds__(C::NT) void fwd_kernel(LaunchArgs a)
 {
-    fwd_body<C, BATCH, DAMP>(a);
+    fwd_body<C, BATCH, DAMP, LD>(a);
 }
 
 // the same step built for C::OCC waves per SIMD
-template <class C, bool BATCH, bool DAMP>
+template <class C, bool BATCH, bool DAMP, int LD>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC > 0 ? C::OCC : 1)))
 void fwd_kernel_occ(LaunchArgs a)
 {
-    fwd_body<C, BATCH, DAMP>(a);
+    fwd_body<C, BATCH, DAMP, LD>(a);
 }
 
 // ------------------------------------------------------------------ adjoint step
@@ -883,7 +889,7 @@ enum { GM_ACC = 0, GM_FIRST = 1, GM_FOLD = 2, GM_DIRECT = 3 };
 // What bounds it: HBM for large grids (28 B per point; 256^3 r = 4: 96 -> 87 us per step,
 // 5.4 TB/s), and before the split, for r = 8, the registers of two queues (more than 256,
 // so one wave per SIMD): 192^3 89 -> 56 us, 93x118x141 36 -> 20 us.
-template <class C, int ROLE>
+template <class C, int ROLE, int LD>
 __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::type *__restrict__ field,
                                          typename C::type *mout, const typename C::type *g1,
                                          const typename C::type *g2, typename C::type *gout,
@@ -921,8 +927,8 @@ __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::ty
         const auto bp = plane_buf(mout, pxy, g.z0 + R), bc = plane_buf(cc, pxy, g.z0 + R);
 #pragma unroll
         for (int e = 0; e < EY; ++e) {
-            bld<kNontemporal>(pv[0][e], bp, g.obr[e]);
-            bld<kNontemporal>(cv[0][e], bc, g.obr[e]);
+            bld<LD>(pv[0][e], bp, g.obr[e]);
+            bld<LD>(cv[0][e], bc, g.obr[e]);
         }
     }
     {
@@ -985,15 +991,15 @@ __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::ty
                 const auto bp = plane_buf(mout, pxy, z + 1 + R, more), bc = plane_buf(cc, pxy, z + 1 + R, more);
 #pragma unroll
                 for (int e = 0; e < EY; ++e) {
-                    bld<kNontemporal>(pv[ns][e], bp, g.obr[e]);
-                    bld<kNontemporal>(cv[ns][e], bc, g.obr[e]);
+                    bld<LD>(pv[ns][e], bp, g.obr[e]);
+                    bld<LD>(cv[ns][e], bc, g.obr[e]);
                 }
             } else {
                 const auto b1 = plane_buf(g1, pxy, z + R, g1 != nullptr), b2 = plane_buf(g2, pxy, z + R, g2 != nullptr);
 #pragma unroll
                 for (int e = 0; e < EY; ++e) {
-                    bld<kNontemporal>(gv[cs][e], b1, g.obr[e]);
-                    bld<kNontemporal>(gv2[cs][e], b2, g.obr[e]);
+                    bld<LD>(gv[cs][e], b1, g.obr[e]);
+                    bld<LD>(gv2[cs][e], b2, g.obr[e]);
                 }
             }
             {
@@ -1108,7 +1114,7 @@ __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::ty
     }
 }
 
-template <class C>
+template <class C, int LD>
 __global__ __launch_bounds__(2 * C::NT) void adj_kernel(AdjArgs a)
 {
     typedef typename C::type T;
@@ -1134,10 +1140,10 @@ __global__ __launch_bounds__(2 * C::NT) void adj_kernel(AdjArgs a)
     T *gout = (a.gmode == GM_ACC || a.gmode == GM_FIRST) ? gseg : grad;
     T *const mx = lds + 2 * C::NB * C::LDS;
     if (image)
-        adj_half<C, 1>(s, static_cast<const T *>(a.u_km1), nullptr, g1, g2, gout, nullptr, T(0), g,
+        adj_half<C, 1, LD>(s, static_cast<const T *>(a.u_km1), nullptr, g1, g2, gout, nullptr, T(0), g,
                        lds + C::NB * C::LDS, mx);
     else
-        adj_half<C, 0>(s, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out), nullptr, nullptr, nullptr,
+        adj_half<C, 0, LD>(s, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out), nullptr, nullptr, nullptr,
                        static_cast<const T *>(a.resid) + (a.k - 1) * s.nrec, T(a.resid_amp), g, lds, mx);
 }
 
@@ -1171,54 +1177,69 @@ struct AdjEntry {
     float cost;  // as in FwdEntry
 };
 
-template <class C, bool BATCH, bool DAMP>
+template <class C, bool BATCH, bool DAMP, int LD>
 constexpr auto fwd_kernel_of()
 {
     if constexpr (C::OCC > 0)
-        return &fwd_kernel_occ<C, BATCH, DAMP>;
+        return &fwd_kernel_occ<C, BATCH, DAMP, LD>;
     else
-        return &fwd_kernel<C, BATCH, DAMP>;
+        return &fwd_kernel<C, BATCH, DAMP, LD>;
 }
 
 // a.step >= 0: one shot, described by a.one; else a batch's table (the tiles the library
-// chooses from only)
-template <class C, int ROLE>
-void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
+// chooses from, which are the ones a batch can take; the others have no build for it, nor
+// one for fields that stay in the cache).
+template <class C, int ROLE, bool DAMP>
+void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
 {
     const dim3 grid(nwg), block(C::NT);
+    constexpr int KEEP = kPointLoads<ROLE != FWD_OPTION>, ONCE = kPointLoads<false>;
     if (a.step >= 0) {
-        if (a.damped)
-            hipLaunchKernelGGL((fwd_kernel_of<C, false, true>()), grid, block, 0, st, a);
+        if (a.cached)
+            hipLaunchKernelGGL((fwd_kernel_of<C, false, DAMP, KEEP>()), grid, block, 0, st, a);
         else
-            hipLaunchKernelGGL((fwd_kernel_of<C, false, false>()), grid, block, 0, st, a);
+            hipLaunchKernelGGL((fwd_kernel_of<C, false, DAMP, ONCE>()), grid, block, 0, st, a);
         return;
     }
     if constexpr (ROLE == FWD_AUTO || ROLE == FWD_FINE) {
-        if (a.damped)
-            hipLaunchKernelGGL((fwd_kernel_of<C, true, true>()), grid, block, 0, st, a);
+        if (a.cached)
+            hipLaunchKernelGGL((fwd_kernel_of<C, true, DAMP, KEEP>()), grid, block, 0, st, a);
         else
-            hipLaunchKernelGGL((fwd_kernel_of<C, true, false>()), grid, block, 0, st, a);
+            hipLaunchKernelGGL((fwd_kernel_of<C, true, DAMP, ONCE>()), grid, block, 0, st, a);
     }
 }
 
-template <class C>
+template <class C, int ROLE>
+void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
+{
+    if (a.damped)
+        launch_fwd_as<C, ROLE, true>(a, nwg, st);
+    else
+        launch_fwd_as<C, ROLE, false>(a, nwg, st);
+}
+
+template <class C, int ROLE>
 void launch_adj(const AdjArgs &a, int nwg, hipStream_t st)
 {
-    hipLaunchKernelGGL(adj_kernel<C>, dim3(nwg), dim3(2 * C::NT), 0, st, a);
+    constexpr int KEEP = kPointLoads<ROLE != ADJ_OPTION>, ONCE = kPointLoads<false>;
+    if (a.cached)
+        hipLaunchKernelGGL((adj_kernel<C, KEEP>), dim3(nwg), dim3(2 * C::NT), 0, st, a);
+    else
+        hipLaunchKernelGGL((adj_kernel<C, ONCE>), dim3(nwg), dim3(2 * C::NT), 0, st, a);
 }
 
 template <class C, int ROLE>
 FwdEntry fwd_entry(const char *name, float cost)
 {
     return FwdEntry{name, C::BX, C::BY, C::NT, &launch_fwd<C, ROLE>,
-                    reinterpret_cast<const void *>(fwd_kernel_of<C, false, false>()), ROLE, cost};
+                    reinterpret_cast<const void *>(fwd_kernel_of<C, false, false, kNontemporal>()), ROLE, cost};
 }
 
-template <class C>
-AdjEntry adj_entry(const char *name, int role, float cost)
+template <class C, int ROLE>
+AdjEntry adj_entry(const char *name, float cost)
 {
-    return AdjEntry{name, C::BX, C::BY, 2 * C::NT, &launch_adj<C>, reinterpret_cast<const void *>(&adj_kernel<C>), role,
-                    cost};
+    return AdjEntry{name, C::BX, C::BY, 2 * C::NT, &launch_adj<C, ROLE>,
+                    reinterpret_cast<const void *>(&adj_kernel<C, kNontemporal>), ROLE, cost};
 }
 
 // Implemented in the per-dtype translation units.

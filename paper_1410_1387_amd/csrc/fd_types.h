@@ -65,7 +65,8 @@ struct LaunchArgs {
     void *out;
     int32_t record;            // write receiver traces
     int32_t xcd_remap;         // map consecutive tiles onto one XCD
-    int32_t damped, pad0;      // some shot of the launch has a sponge
+    int32_t damped;            // some shot of the launch has a sponge
+    int32_t cached;            // the fields stay in the last-level cache from step to step
     ShotDesc one;              // single shot: its descriptor
 };
 
@@ -84,7 +85,8 @@ struct AdjArgs {
     double resid_amp;
     int32_t xcd_remap;
     int32_t zch;           // the adjoint kernel's own tiling (its tile differs from the forward one)
-    int32_t tiles_x, tiles_y, chunks_z, pad0;
+    int32_t tiles_x, tiles_y, chunks_z;
+    int32_t cached;        // as in LaunchArgs
 };
 
 // ------------------------------------------------------------------ VTI propagator
@@ -111,6 +113,7 @@ struct VtiDesc {
     const void *wz;        // [nz][2 RZ + 1] z weights times h^2
     int32_t nx, ny, nz;
     int32_t tiles_x, tiles_y, chunks_z, zch, xcd_remap;
+    int32_t cached;        // as in LaunchArgs
     int64_t px, pxy, off0;
     const int32_t *ev_ptr; // CSR over (x, y) columns, as for the acoustic kernel
     const Event *ev;

@@ -64,7 +64,7 @@ struct VtiCfg {
     static_assert(256 % BX == 0 && 64 % BY == 0, "tile must divide the layout alignment");
 };
 
-template <class C>
+template <class C, int LD>
 __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx, int ty, int cz,
                                          typename C::type *lds)
 {
@@ -121,11 +121,11 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
         constexpr int i = decltype(set)::value;
         const auto bp = plane_buf(pcur, pxy, z + RZ, on);
         bld<0>(pc[i], bp, ob);
-        bld<kNontemporal>(pm[i], plane_buf(pprev, pxy, z + RZ, on), ob);
-        bld<kNontemporal>(qm[i], plane_buf(qprev, pxy, z + RZ, on), ob);
-        bld<kNontemporal>(a1[i], plane_buf(fax, pxy, z + RZ, on), ob);
-        bld<kNontemporal>(a2[i], plane_buf(fan, pxy, z + RZ, on), ob);
-        bld<kNontemporal>(a3[i], plane_buf(faz, pxy, z + RZ, on), ob);
+        bld<LD>(pm[i], plane_buf(pprev, pxy, z + RZ, on), ob);
+        bld<LD>(qm[i], plane_buf(qprev, pxy, z + RZ, on), ob);
+        bld<LD>(a1[i], plane_buf(fax, pxy, z + RZ, on), ob);
+        bld<LD>(a2[i], plane_buf(fan, pxy, z + RZ, on), ob);
+        bld<LD>(a3[i], plane_buf(faz, pxy, z + RZ, on), ob);
 #pragma unroll
         for (int k = 0; k < HPT; ++k) bld<0>(hv[i][k], bp, g.hob[k]);
     };
@@ -266,7 +266,7 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
     }
 }
 
-template <class C>
+template <class C, int LD>
 __global__ __launch_bounds__(C::NT) void vti_kernel(VtiDesc s, int64_t step)
 {
     typedef typename C::type T;
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(C::NT) void vti_kernel(VtiDesc s, int64_t step)
     const int ty = t2 % s.tiles_y;
     const int cz = t2 / s.tiles_y;
     if (cz >= s.chunks_z) return;
-    vti_tile<C>(s, step, tx, ty, cz, lds);
+    vti_tile<C, LD>(s, step, tx, ty, cz, lds);
 }
 
 // Roles: reached with fd_vti_set_tuning alone, or one the library chooses from by itself.
@@ -293,17 +293,21 @@ struct VtiEntry {
     float cost;  // as in FwdEntry
 };
 
-template <class C>
+template <class C, int ROLE>
 void launch_vti(const VtiDesc &d, int64_t step, int nwg, hipStream_t st)
 {
-    hipLaunchKernelGGL(vti_kernel<C>, dim3(nwg), dim3(C::NT), 0, st, d, step);
+    constexpr int KEEP = kPointLoads<ROLE != VTI_OPTION>, ONCE = kPointLoads<false>;
+    if (d.cached)
+        hipLaunchKernelGGL((vti_kernel<C, KEEP>), dim3(nwg), dim3(C::NT), 0, st, d, step);
+    else
+        hipLaunchKernelGGL((vti_kernel<C, ONCE>), dim3(nwg), dim3(C::NT), 0, st, d, step);
 }
 
-template <class C>
-VtiEntry vti_entry(const char *name, int role, float cost)
+template <class C, int ROLE>
+VtiEntry vti_entry(const char *name, float cost)
 {
-    return VtiEntry{name, C::RXY, C::RZ, C::BX, C::BY, C::NT, &launch_vti<C>,
-                    reinterpret_cast<const void *>(&vti_kernel<C>), role, cost};
+    return VtiEntry{name, C::RXY, C::RZ, C::BX, C::BY, C::NT, &launch_vti<C, ROLE>,
+                    reinterpret_cast<const void *>(&vti_kernel<C, kNontemporal>), ROLE, cost};
 }
 
 // Implemented in the per-dtype translation units.

@@ -508,6 +508,7 @@ extern "C" int fd_vti_create(fd_vti_ctx **out, const fd_grid *g, int rxy, int rz
     d.chunks_z = (int32_t)c->chunks_z;
     d.zch = c->zch;
     d.xcd_remap = 1;
+    d.cached = cache_keeps(7.0 * (double)L.nx * (double)L.ny * (double)L.nz * (double)L.esize);
     d.px = L.px;
     d.pxy = L.pxy;
     d.off0 = L.off0;

@@ -153,12 +153,12 @@ def adj_file(T, d3, d3_big_r, options=()):
         lst = lst + [(o, "OPTION", 1.0) for o in options if R in ADJ_OPTION_RADII]
         out += f"static const AdjEntry a3_r{R}[] = {{\n"
         for cfg, role, cost in lst:
-            out += (f'    adj_entry<{tilecfg(T, R, 3, *cfg, None, 0, False, 0)}>("{cfgname(T, R, 3, *cfg)}", '
-                    f'ADJ_{role}, {cost}f),\n')
+            out += (f'    adj_entry<{tilecfg(T, R, 3, *cfg, None, 0, False, 0)}, ADJ_{role}>('
+                    f'"{cfgname(T, R, 3, *cfg)}", {cost}f),\n')
         out += "};\n"
         txn = F2D[0]
-        out += (f"static const AdjEntry a2_r{R}[] = {{adj_entry<{tilecfg(T, R, 2, txn, 1, 1, None, 0, False, 0)}>"
-                f'("{cfgname(T, R, 2, txn, 1, 1)}", ADJ_AUTO, 1.0f)}};\n')
+        out += (f"static const AdjEntry a2_r{R}[] = {{adj_entry<{tilecfg(T, R, 2, txn, 1, 1, None, 0, False, 0)}, ADJ_AUTO>"
+                f'("{cfgname(T, R, 2, txn, 1, 1)}", 1.0f)}};\n')
     out += "\nconst AdjEntry *adj_configs_" + tag + "(int r, int ndim, int *count)\n{\n    switch (r * 10 + ndim) {\n"
     for R in range(1, 9):
         for nd in (2, 3):
@@ -180,7 +180,7 @@ def vti_file(T, tiles):
         out += f"static const VtiEntry v_{rxy}_{rz}[] = {{\n"
         for (txn, tyn), role, cost in lst:
             name = f"{tag} vti rxy{rxy} rz{rz} tile {txn * vec}x{tyn} ({txn * tyn} thr)"
-            out += f'    vti_entry<VtiCfg<{T}, {rxy}, {rz}, {txn}, {tyn}>>("{name}", VTI_{role}, {cost}f),\n'
+            out += f'    vti_entry<VtiCfg<{T}, {rxy}, {rz}, {txn}, {tyn}>, VTI_{role}>("{name}", {cost}f),\n'
         out += "};\n"
     out += "\nconst VtiEntry *vti_configs_" + tag + "(int rxy, int rz, int *count)\n{\n    switch (rxy * 100 + rz) {\n"
     for (rxy, rz) in VTI_RADII:
