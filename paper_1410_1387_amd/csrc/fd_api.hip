@@ -252,6 +252,8 @@ constexpr int64_t kFineZch = 32;
 // (512^3: 394 against 353 us, since both places are then used).
 constexpr int64_t kTwinZchMin = 16, kTwinZchMax = 64;
 
+double interior_bytes(const Layout &L) { return (double)L.knx * (double)L.kny * (double)L.knz * (double)L.esize; }
+
 template <class Entry>
 TileChoice<Entry> plan_tile(const Entry &e, const Layout &L)
 {
@@ -266,9 +268,18 @@ TileChoice<FwdEntry> choose_tile(const FwdEntry *tab, int count, const Layout &L
     double cost = 0;
     for (int i = 0; i < count; ++i) {
         if (tab[i].role != FWD_AUTO && tab[i].role != FWD_FINE) continue;
-        const TileChoice<FwdEntry> t = plan_tile(tab[i], L);
+        TileChoice<FwdEntry> t = plan_tile(tab[i], L);
+        const bool cached = tab[i].cached_zch && cache_keeps(3.0 * interior_bytes(L));
+        if (cached) {
+            const int64_t z = fine_zch([&](int64_t Z) { return t.tx * t.ty * ((L.knz + Z - 1) / Z); }, L.knz,
+                                       tab[i].nt, tab[i].cached_zch, cus);
+            const int64_t chunks = (L.knz + z - 1) / z;
+            t.zch = (int)((L.knz + chunks - 1) / chunks);
+            t.nwg = t.tx * t.ty * ((L.knz + t.zch - 1) / t.zch);
+        }
         if (best.e && tab[i].role == FWD_FINE && t.zch >= kFineZch) continue;
-        const double c = tile_cost(tab[i], t.nwg, t.zch, L.r, cus);
+        const double c = cached ? cached_tile_cost(tab[i], t.nwg, t.zch, L.r, cus)
+                                : tile_cost(tab[i], t.nwg, t.zch, L.r, cus);
         if (!best.e || c < cost) {
             best = t;
             cost = c;
@@ -826,8 +837,6 @@ extern "C" int fd_ricker(void *out, int64_t nsamp, double dt, double f0, double 
 
 // ------------------------------------------------------------------ stepping
 
-static double interior_bytes(const Layout &L) { return (double)L.knx * (double)L.kny * (double)L.knz * (double)L.esize; }
-
 static LaunchArgs direct_args(const fd_ctx *c, int64_t step)
 {
     LaunchArgs a;
@@ -1383,11 +1392,14 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
     // would alone.  For a target length Z every member takes c = ceil(nz / Z) chunks of
     // equal length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
     // ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
-    // targets that are some member's exact chunk length.
+    // targets that are some member's exact chunk length.  A FINE tile's chunks in the
+    // last-level cache are short instead (fine_zch).
     const FwdEntry *kf = nullptr;
     int64_t zt = 1;
     if (nctx > 0) {
         const int r = ctxs[0]->r, cus = device_cus();
+        double interior = 0;
+        for (int i = 0; i < nctx; ++i) interior += interior_bytes(ctxs[i]->L);
         int count = 0;
         const FwdEntry *tab = fwd_table(ctxs[0]->dtype, r, (int)ctxs[0]->g.ndim, &count);
         std::vector<int64_t> cand;
@@ -1403,14 +1415,26 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
             const int slots = resident_slots(tab[k].kernel, tab[k].nt);
             double best = 1e300;
             int64_t z = cand.back(), bwg = 0, bplanes = 0;
-            for (int64_t Z : cand) {
-                int64_t nwg = 0, planes = 0;
+            auto lay = [&](int64_t Z, int64_t *planes) {
+                int64_t nwg = 0;
                 for (int i = 0; i < nctx; ++i) {
                     const Layout &L = ctxs[i]->L;
                     const int64_t cm = (L.knz + Z - 1) / Z, zm = (L.knz + cm - 1) / cm;
                     nwg += ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by) * cm;
-                    planes = std::max<int64_t>(planes, zm);
+                    *planes = std::max<int64_t>(*planes, zm);
                 }
+                return nwg;
+            };
+            const bool cached = tab[k].cached_zch && cache_keeps(3.0 * interior);
+            if (cached) {
+                int64_t any = 0;
+                z = fine_zch([&](int64_t Z) { return lay(Z, &any); }, cand.back(), tab[k].nt, tab[k].cached_zch, cus);
+                bwg = lay(z, &bplanes);
+            }
+            for (int64_t Z : cand) {
+                if (cached) break;
+                int64_t planes = 0;
+                const int64_t nwg = lay(Z, &planes);
                 const double cost = (double)((nwg + slots - 1) / slots) * (double)(planes + 2 * r);
                 if (cost < best - 1e-9) {
                     best = cost;
@@ -1420,7 +1444,8 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
                 }
             }
             if (kf && tab[k].role == FWD_FINE && bplanes >= kFineZch) continue;
-            const double c = tile_cost(tab[k], bwg, bplanes, r, cus);
+            const double c = cached ? cached_tile_cost(tab[k], bwg, bplanes, r, cus)
+                                    : tile_cost(tab[k], bwg, bplanes, r, cus);
             if (!kf || c < kbest) {
                 kf = &tab[k];
                 kbest = c;

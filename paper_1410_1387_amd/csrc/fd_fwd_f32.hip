@@ -10,7 +10,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 1, 3, 16, 16, 1>, FWD_AUTO>("f32 r1 3d tile 64x16 (256 thr, 1 row/thr)", 1.35f),
     fwd_entry<TileCfg<float, 1, 3, 32, 16, 1>, FWD_AUTO>("f32 r1 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
     fwd_entry<TileCfg<float, 1, 3, 16, 32, 1>, FWD_AUTO>("f32 r1 3d tile 64x32 (512 thr, 1 row/thr)", 1.1f),
-    fwd_entry<TileCfg<float, 1, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r1 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f),
+    fwd_entry<TileCfg<float, 1, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r1 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f, 0.9f, 2),
     fwd_entry<TileCfg<float, 1, 3, 32, 16, 1, 4, 4, false, 1>, FWD_TWIN>("f32 r1 3d tile 128x16 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
     fwd_entry<TileCfg<float, 1, 3, 16, 32, 1, 4, 4, false, 1>, FWD_TWIN>("f32 r1 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
@@ -23,7 +23,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 2, 3, 16, 16, 1>, FWD_AUTO>("f32 r2 3d tile 64x16 (256 thr, 1 row/thr)", 1.35f),
     fwd_entry<TileCfg<float, 2, 3, 32, 16, 1>, FWD_AUTO>("f32 r2 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
     fwd_entry<TileCfg<float, 2, 3, 16, 32, 1>, FWD_AUTO>("f32 r2 3d tile 64x32 (512 thr, 1 row/thr)", 1.1f),
-    fwd_entry<TileCfg<float, 2, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r2 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f),
+    fwd_entry<TileCfg<float, 2, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r2 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f, 0.9f, 2),
     fwd_entry<TileCfg<float, 2, 3, 32, 16, 1, 4, 4, false, 2>, FWD_TWIN>("f32 r2 3d tile 128x16 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
     fwd_entry<TileCfg<float, 2, 3, 16, 32, 1, 4, 4, false, 2>, FWD_TWIN>("f32 r2 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
@@ -36,7 +36,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 3, 3, 16, 16, 1>, FWD_AUTO>("f32 r3 3d tile 64x16 (256 thr, 1 row/thr)", 1.35f),
     fwd_entry<TileCfg<float, 3, 3, 32, 16, 1>, FWD_AUTO>("f32 r3 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
     fwd_entry<TileCfg<float, 3, 3, 16, 32, 1>, FWD_AUTO>("f32 r3 3d tile 64x32 (512 thr, 1 row/thr)", 1.1f),
-    fwd_entry<TileCfg<float, 3, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r3 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f),
+    fwd_entry<TileCfg<float, 3, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r3 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f, 0.9f, 2),
     fwd_entry<TileCfg<float, 3, 3, 32, 16, 1, 4, 4, false, 3>, FWD_TWIN>("f32 r3 3d tile 128x16 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
     fwd_entry<TileCfg<float, 3, 3, 16, 32, 1, 4, 4, false, 3>, FWD_TWIN>("f32 r3 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
@@ -57,7 +57,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 4, 3, 16, 16, 1, 4, 4>, FWD_OPTION>("f32 r4 3d tile 64x16 (256 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
     fwd_entry<TileCfg<float, 4, 3, 32, 16, 1>, FWD_AUTO>("f32 r4 3d tile 128x16 (512 thr, 1 row/thr)", 1.0f),
     fwd_entry<TileCfg<float, 4, 3, 16, 32, 1>, FWD_AUTO>("f32 r4 3d tile 64x32 (512 thr, 1 row/thr)", 1.1f),
-    fwd_entry<TileCfg<float, 4, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r4 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f),
+    fwd_entry<TileCfg<float, 4, 3, 8, 8, 1, 4, 0, false, 0>, FWD_FINE>("f32 r4 3d tile 32x8 (64 thr, 1 row/thr)", 1.25f, 1.25f, 4),
     fwd_entry<TileCfg<float, 4, 3, 32, 16, 1, 4, 4, false, 3>, FWD_TWIN>("f32 r4 3d tile 128x16 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
     fwd_entry<TileCfg<float, 4, 3, 16, 32, 1, 4, 4, false, 3>, FWD_TWIN>("f32 r4 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };

@@ -9,7 +9,7 @@ namespace fdw {
 static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 1, 3, 16, 16, 2>, FWD_AUTO>("f64 r1 3d tile 32x32 (256 thr, 2 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 1, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r1 3d tile 32x32 (512 thr, 1 row/thr)", 0.95f),
-    fwd_entry<TileCfg<double, 1, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r1 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f),
+    fwd_entry<TileCfg<double, 1, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r1 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
 };
 static const FwdEntry k2[] = {
     fwd_entry<TileCfg<double, 1, 2, 64, 1, 1>, FWD_AUTO>("f64 r1 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
@@ -19,7 +19,7 @@ static const FwdEntry k2[] = {
 static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 2, 3, 16, 16, 2>, FWD_AUTO>("f64 r2 3d tile 32x32 (256 thr, 2 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 2, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r2 3d tile 32x32 (512 thr, 1 row/thr)", 0.95f),
-    fwd_entry<TileCfg<double, 2, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r2 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f),
+    fwd_entry<TileCfg<double, 2, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r2 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
 };
 static const FwdEntry k2[] = {
     fwd_entry<TileCfg<double, 2, 2, 64, 1, 1>, FWD_AUTO>("f64 r2 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
@@ -29,7 +29,7 @@ static const FwdEntry k2[] = {
 static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 3, 3, 16, 16, 2>, FWD_AUTO>("f64 r3 3d tile 32x32 (256 thr, 2 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 3, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r3 3d tile 32x32 (512 thr, 1 row/thr)", 0.95f),
-    fwd_entry<TileCfg<double, 3, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r3 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f),
+    fwd_entry<TileCfg<double, 3, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r3 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
 };
 static const FwdEntry k2[] = {
     fwd_entry<TileCfg<double, 3, 2, 64, 1, 1>, FWD_AUTO>("f64 r3 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
@@ -42,7 +42,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 4, 3, 32, 8, 2>, FWD_OPTION>("f64 r4 3d tile 64x16 (256 thr, 2 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 4, 3, 16, 16, 1>, FWD_OPTION>("f64 r4 3d tile 32x16 (256 thr, 1 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 4, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r4 3d tile 32x32 (512 thr, 1 row/thr)", 0.95f),
-    fwd_entry<TileCfg<double, 4, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r4 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f),
+    fwd_entry<TileCfg<double, 4, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r4 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 1.0f, 4),
 };
 static const FwdEntry k2[] = {
     fwd_entry<TileCfg<double, 4, 2, 64, 1, 1>, FWD_AUTO>("f64 r4 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace fdw {
 
 // Records a printf-style message as the calling thread's last error and returns code.
@@ -32,6 +34,15 @@ double tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
            1.5 * e.nt;
 }
 
+// The same for a FINE tile on fields that stay in the last-level cache: its many workgroups
+// hide each other's latency.  With it the choice over 13 such grids is within 1 % of the best
+// tile and chunk on average for r <= 3 (6 % without), 2 % for r = 4 (7 %), 2-3 % in FP64 (7 %).
+template <class Entry>
+double cached_tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
+{
+    return (double)((nwg + cus - 1) / cus) * e.bx * e.by * e.cached_cost * ((double)zch + 0.3 * r) + 1.5 * e.nt;
+}
+
 // Whether `bytes` of fields that every step reads and writes stay in the 256 MB last-level
 // cache from one step to the next.  Then loads that a step makes once per point (u^{n-1},
 // c, ...) keep their lines; otherwise they are nontemporal, so that they do not push out the
@@ -42,6 +53,24 @@ double tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus)
 // MB) 62 -> 57.6, 160^3 FP64 (229 MB) 50.6 -> 50.9, 256^3 (470 MB) 103 -> 124.
 constexpr double kCacheBytes = 208.0 * (1 << 20);
 inline bool cache_keeps(double bytes) { return bytes <= kCacheBytes; }
+
+// Planes per chunk of a FINE tile on fields that stay in the last-level cache; count(Z) is
+// the number of workgroups with chunks of at most Z of nz planes.  Where there are plenty,
+// short chunks in many rounds are best: a chunk's first planes come from the L2 that the
+// chunk below has just filled, and the CUs stay balanced.  Otherwise one round, but of at
+// most eight waves per CU: more of them push each other's planes out.  Best measured length
+// against one round of all places, us per step: 201x119x333 r = 2 2 planes 22.1 (9: 25.1),
+// r = 4 4 planes 25.5 (12: 29.9); 160^3 r = 4 8 planes 15.2 (6: 15.8), 93x118x141 4 planes
+// 8.2 (3: 8.4); a batch of seven 78..152-cubes 6 planes 50.9 (23: 55).
+template <class Count>
+int fine_zch(const Count &count, int64_t nz, int nt, int short_zch, int cus)
+{
+    const int64_t waves = nt / 64;
+    if (count(std::min<int64_t>(4, nz)) * waves >= 20 * cus) return (int)std::min<int64_t>(short_zch, nz);
+    int64_t z = 1;
+    while (z < nz && count(z) * waves > 8 * cus) ++z;
+    return (int)z;
+}
 
 // A tile entry (bx x by points, nt threads, its kernel) laid out over one grid.
 template <class Entry>

@@ -1162,6 +1162,8 @@ struct FwdEntry {
     const void *kernel;  // the __global__ function (for occupancy queries)
     int role;
     float cost;          // relative time per point of the tile, where it streams well
+    float cached_cost;   // FINE tiles on grids that stay in the last-level cache: the same there
+    int cached_zch;      // and the planes per chunk to use (0: as elsewhere)
 };
 
 // Roles of an adjoint tile entry: reached with fd_set_adj_tuning alone, one the library
@@ -1229,10 +1231,11 @@ void launch_adj(const AdjArgs &a, int nwg, hipStream_t st)
 }
 
 template <class C, int ROLE>
-FwdEntry fwd_entry(const char *name, float cost)
+FwdEntry fwd_entry(const char *name, float cost, float cached_cost = 0, int cached_zch = 0)
 {
     return FwdEntry{name, C::BX, C::BY, C::NT, &launch_fwd<C, ROLE>,
-                    reinterpret_cast<const void *>(fwd_kernel_of<C, false, false, kNontemporal>()), ROLE, cost};
+                    reinterpret_cast<const void *>(fwd_kernel_of<C, false, false, kNontemporal>()), ROLE, cost, cached_cost,
+                    cached_zch};
 }
 
 template <class C, int ROLE>

@@ -41,6 +41,12 @@ F64_3D_AUTO = [((16, 16, 2), "AUTO", 1.0), ((16, 32, 1, None, 0, False, 0), "AUT
 F64_3D_OPTIONS = [(32, 16, 1), (32, 8, 2), (16, 16, 1)]
 F64_3D_BIG_R_AUTO = [((16, 16, 1), "AUTO", 1.1), ((32, 16, 1), "AUTO", 1.0), ((8, 16, 1), "FINE", 1.17)]
 F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
+# FINE tiles of grids that stay in the last-level cache: relative cost per point and planes per
+# chunk (224^3 r = 2 FP32: 29.1 us with chunks of 2 planes, 30.0 of 4, 33.9 with 128x16; 192^3
+# FP64 35.1 against 39.9).  At larger radii a short chunk's first planes cost too much (201x119x
+# 333 r = 8: 34.5 us with 4 planes, 31.7 with 128x16).
+FINE_CACHED = {"f32": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.25f", 4)},
+               "f64": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.0f", 4)}}
 SWEEP_RADII = {4, 8}      # radii that get the OPTION tiles
 F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads
 # 3-D adjoint tiles: (shape, role, relative cost per point); half of a tile's threads own mu,
@@ -122,7 +128,8 @@ def fwd_file(T, auto, options, auto_big_r, options_big_r):
         out += f"#if FD_RADIUS == {R}\nstatic const FwdEntry k3[] = {{\n"
         for cfg, role, cost in rows:
             name = cfgname(T, R, 3, *cfg[:5])
-            out += f'    fwd_entry<{tilecfg(T, R, 3, *cfg)}, FWD_{role}>("{name}", {cost}f),\n'
+            cached = "".join(f", {v}" for v in FINE_CACHED[tag].get(R, ())) if role == "FINE" else ""
+            out += f'    fwd_entry<{tilecfg(T, R, 3, *cfg)}, FWD_{role}>("{name}", {cost}f{cached}),\n'
         out += "};\n"
         txn = F2D[0]
         out += f"static const FwdEntry k2[] = {{\n"

@@ -53,6 +53,25 @@ def test_registered_tiles_bitwise(oracle_mod, r, dtype):
         assert rel_l2(base["u"], ref["u"]) <= TOL[dtype] and rel_l2(base["traces"], ref["traces"]) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 6])
+def test_own_choice_bitwise(oracle_mod, r, dtype):
+    # the library's own tile and chunk gives the bits of the first tile with one chunk: fewer
+    # planes than a short chunk has, many short chunks, one round, and (the last shape) fields
+    # past the last-level cache, whose loads have another cache policy
+    T = 5
+    for shape in [(1, 17, 40), (2, 300, 130), (3, 9, 1000), (61, 70, 300), (200, 33, 333), (150, 410, 310)]:
+        v, u0, um1 = _case(shape, r)
+        dt = 0.5 * oracle_mod.dt_max(3, r, 10.0, v.max())
+        rec = workloads.surface_receivers(shape[2], shape[1], shape[0] // 2, 16)
+        kw = dict(receivers=rec, u0=u0, um1=um1, ricker=((shape[2] // 2, 8, 0), 30.0, 0.0), label="own choice")
+        got = run_gpu(v, r, 10.0, dt, T, dtype, **kw)
+        base = run_gpu(v, r, 10.0, dt, T, dtype, tuning=(0, shape[0]), **kw)
+        say(got["config"])
+        for k in ("u", "u_prev", "traces"):
+            assert np.array_equal(got[k], base[k]), (shape, k, got["config"])
+
+
 @pytest.mark.parametrize("nsrc", [1, 2, 3, 5])
 @pytest.mark.parametrize("shape,r", [((13, 20, 70), 4), ((30, 75), 8)])
 def test_sources_and_receivers_vs_oracle(oracle_mod, shape, r, nsrc):
