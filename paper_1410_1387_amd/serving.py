@@ -212,6 +212,7 @@ class ShotServer:
     def stop(self):
         self._stop.set()
         if self._thread is not None:
+            self._inbox.put(None)  # wakes a loop that waits for requests (it would look 5 ms later)
             self._thread.join()
             self._thread = None
         if self._error is not None:
@@ -248,9 +249,11 @@ class ShotServer:
             pending = list(self._outstanding)
             while True:
                 try:
-                    pending.append(self._inbox.get_nowait()[2])
+                    item = self._inbox.get_nowait()
                 except queue.Empty:
                     break
+                if item is not None:
+                    pending.append(item[2])
             for fut in pending:
                 try:
                     fut.set_exception(e)
@@ -286,9 +289,11 @@ class ShotServer:
                         item = self._inbox.get(timeout=0.005) if block else self._inbox.get_nowait()
                     except queue.Empty:
                         break
+                    block = False
+                    if item is None:
+                        continue
                     pending.append(item)
                     self._outstanding.add(item[2])
-                    block = False
                 if not active and not pending and not inflight:
                     if self._stop.is_set():
                         break
