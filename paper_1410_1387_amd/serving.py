@@ -283,7 +283,7 @@ class ShotServer:
         try:
             while True:
                 # drain the inbox; block only when there is nothing else to do
-                block = not active and not pending
+                block = not active and not pending and not self._stop.is_set()
                 while True:
                     try:
                         item = self._inbox.get(timeout=0.005) if block else self._inbox.get_nowait()
