@@ -295,7 +295,8 @@ size_t fd_batch_workspace_bytes(int max_shots);
 /* A batch advances many same-(r, dtype, ndim) zero-boundary shots of different grid sizes
  * in one stencil launch per step: each workgroup looks up its (shot, tile) from a prefix
  * table, and each shot keeps its step counter in device memory, so a captured graph of
- * an even number of steps can be replayed while shots come and go.
+ * an even number of steps can be replayed while shots come and go.  Members whose fields
+ * fit the last-level cache together only in groups take one launch per step and group.
  *   workspace  device, fd_batch_workspace_bytes(max_shots), borrowed until destroy */
 int fd_batch_create(fd_batch **out, int max_shots, void *workspace, size_t ws_bytes, void *stream);
 int fd_batch_destroy(fd_batch *b);

@@ -1206,6 +1206,12 @@ extern "C" int fd_gradient_finish(fd_ctx *ctx, const void *grad_padded, const vo
 
 // ------------------------------------------------------------------ batched serving
 
+// Members that share launches: [m0, m1) of the batch.
+struct BatchGroup {
+    int m0, m1;
+    bool cached;  // their fields stay in the last-level cache
+};
+
 struct fd_batch {
     int max_shots;
     char *ws;
@@ -1215,9 +1221,8 @@ struct fd_batch {
     std::vector<fd_ctx *> members;
     std::vector<int64_t> target;
     std::vector<ShotDesc> h_desc;
-    double interior;  // bytes of one field of every member
+    std::vector<BatchGroup> groups;
     std::vector<int32_t> h_prefix;
-    int64_t nwg;
     int slot;
     const FwdEntry *kf;
     hipGraphExec_t exec;
@@ -1252,7 +1257,6 @@ extern "C" int fd_batch_create(fd_batch **out, int max_shots, void *workspace, s
     b->max_shots = max_shots;
     b->ws = (char *)workspace;
     b->stream = (hipStream_t)stream;
-    b->nwg = 0;
     b->slot = 0;
     b->kf = nullptr;
     b->has_exec = false;
@@ -1325,7 +1329,7 @@ extern "C" int fd_batch_create_noalloc(fd_batch **out, int max_shots, void *stre
     b->target.clear();
     b->h_desc.clear();
     b->h_prefix.clear();
-    b->nwg = 0;
+    b->groups.clear();
     b->slot = 0;
     b->kf = nullptr;
     b->has_exec = false;
@@ -1353,7 +1357,6 @@ extern "C" int fd_batch_destroy(fd_batch *b)
         std::lock_guard<std::mutex> lk(g_noalloc_mu);
         b->members.clear();
         b->target.clear();
-        b->nwg = 0;
         g_noalloc[b->device].in_use = false;
         return FD_OK;
     }
@@ -1364,11 +1367,53 @@ extern "C" int fd_batch_destroy(fd_batch *b)
     return FD_OK;
 }
 
+static double group_bytes(fd_ctx *const *ctxs, int m0, int m1)
+{
+    double bytes = 0;
+    for (int i = m0; i < m1; ++i) bytes += 3.0 * interior_bytes(ctxs[i]->L);
+    return bytes;
+}
+
+// Members whose fields fit the last-level cache are stepped in groups that fit it together,
+// each group all the steps of a call before the next one, so that a step finds the fields of
+// the step before in the cache; a run of such members is split evenly.  Members that do not
+// fit share their launches, which fill the chip without gaps.  Measured, one launch for all
+// -> groups, us per step: eleven cubes of 64..152 points (201 MB) 69 -> 62, sixteen of 100
+// 78 -> 72, twelve of 64..152 71.6 -> 65.2, 24 of 128 186 -> 165, four of 256 216 -> 188,
+// eight of 128 (201 MB, whole lines in every row) 55.5 -> 56.9.  A limit of 100 MB costs the
+// groups more in idle places (six cubes of 192: 189 against 126 us).
+constexpr double kGroupBytes = 165.0 * (1 << 20);
+
+static std::vector<BatchGroup> batch_groups(fd_ctx *const *ctxs, int nctx)
+{
+    auto fits = [&](int m) { return cache_keeps(group_bytes(ctxs, m, m + 1)); };
+    std::vector<BatchGroup> groups;
+    for (int m = 0, end = 0; m < nctx; m = end) {
+        while (end < nctx && fits(end) == fits(m)) ++end;  // a run of members of one kind
+        if (!fits(m)) {
+            groups.push_back(BatchGroup{m, end, false});
+            continue;
+        }
+        const double total = group_bytes(ctxs, m, end), parts = std::ceil(total / kGroupBytes);
+        int first = m;
+        for (int k = 1; first < end; ++k) {
+            BatchGroup g{first, first + 1, false};
+            while (g.m1 < end && group_bytes(ctxs, m, g.m1) + 0.5 * group_bytes(ctxs, g.m1, g.m1 + 1) < total * k / parts)
+                ++g.m1;
+            g.cached = cache_keeps(group_bytes(ctxs, g.m0, g.m1));
+            groups.push_back(g);
+            first = g.m1;
+        }
+    }
+    return groups;
+}
+
 // Validate a member set and build its shot table: descriptors with both step-counter
 // slots at the member's step, the member's target and the batch's z chunking, plus the
 // workgroup prefix.
 static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, const char *who,
-                       std::vector<ShotDesc> &desc, std::vector<int32_t> &prefix, const FwdEntry **kf_out)
+                       std::vector<ShotDesc> &desc, std::vector<int32_t> &prefix, std::vector<BatchGroup> &groups,
+                       const FwdEntry **kf_out)
 {
     for (int i = 0; i < nctx; ++i) {
         fd_ctx *c = ctxs[i];
@@ -1392,18 +1437,21 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
     // would alone.  For a target length Z every member takes c = ceil(nz / Z) chunks of
     // equal length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
     // ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
-    // targets that are some member's exact chunk length.  A FINE tile's chunks in the
+    // targets that are some member's exact chunk length.  The largest group of members decides
+    // for all.  A FINE tile's chunks in the
     // last-level cache are short instead (fine_zch).
     const FwdEntry *kf = nullptr;
     int64_t zt = 1;
+    groups = batch_groups(ctxs, nctx);
     if (nctx > 0) {
         const int r = ctxs[0]->r, cus = device_cus();
-        double interior = 0;
-        for (int i = 0; i < nctx; ++i) interior += interior_bytes(ctxs[i]->L);
+        BatchGroup top = groups[0];  // the largest group decides
+        for (const BatchGroup &g : groups)
+            if (group_bytes(ctxs, g.m0, g.m1) > group_bytes(ctxs, top.m0, top.m1)) top = g;
         int count = 0;
         const FwdEntry *tab = fwd_table(ctxs[0]->dtype, r, (int)ctxs[0]->g.ndim, &count);
         std::vector<int64_t> cand;
-        for (int i = 0; i < nctx; ++i) {
+        for (int i = top.m0; i < top.m1; ++i) {
             const int64_t nz = ctxs[i]->L.knz;
             for (int64_t c = 1; c <= std::max<int64_t>(1, nz); ++c) cand.push_back((nz + c - 1) / c);
         }
@@ -1417,7 +1465,7 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
             int64_t z = cand.back(), bwg = 0, bplanes = 0;
             auto lay = [&](int64_t Z, int64_t *planes) {
                 int64_t nwg = 0;
-                for (int i = 0; i < nctx; ++i) {
+                for (int i = top.m0; i < top.m1; ++i) {
                     const Layout &L = ctxs[i]->L;
                     const int64_t cm = (L.knz + Z - 1) / Z, zm = (L.knz + cm - 1) / cm;
                     nwg += ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by) * cm;
@@ -1425,7 +1473,7 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
                 }
                 return nwg;
             };
-            const bool cached = tab[k].cached_zch && cache_keeps(3.0 * interior);
+            const bool cached = tab[k].cached_zch && top.cached;
             if (cached) {
                 int64_t any = 0;
                 z = fine_zch([&](int64_t Z) { return lay(Z, &any); }, cand.back(), tab[k].nt, tab[k].cached_zch, cus);
@@ -1487,8 +1535,9 @@ extern "C" int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *tar
         return fail(FD_E_INVAL, "fd_batch_set: bad arguments");
     std::vector<ShotDesc> desc;
     std::vector<int32_t> prefix;
+    std::vector<BatchGroup> groups;
     const FwdEntry *kf = nullptr;
-    int st = batch_table(ctxs, target, nctx, "fd_batch_set", desc, prefix, &kf);
+    int st = batch_table(ctxs, target, nctx, "fd_batch_set", desc, prefix, groups, &kf);
     if (st) return st;
     if (b->noalloc)
         for (int i = 0; i < nctx; ++i)
@@ -1511,10 +1560,8 @@ extern "C" int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *tar
     b->members.assign(ctxs, ctxs + nctx);
     b->target.assign(target, target + nctx);
     b->h_desc.swap(desc);
-    b->interior = 0;
-    for (int i = 0; i < nctx; ++i) b->interior += interior_bytes(ctxs[i]->L);
+    b->groups.swap(groups);
     b->h_prefix.swap(prefix);
-    b->nwg = b->h_prefix[(size_t)nctx];
     b->kf = kf;
     b->slot = 0;
     if (nctx > 0) {
@@ -1528,20 +1575,27 @@ extern "C" int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *tar
     return FD_OK;
 }
 
-static LaunchArgs batch_args(const fd_batch *b, int slot)
+// The next n steps of every member, group by group.
+static void batch_launch(const fd_batch *b, int64_t n, hipStream_t st)
 {
     LaunchArgs a;
     std::memset(&a, 0, sizeof(a));
     a.shots = b->d_desc();
-    a.wg_prefix = b->members.size() > 1 ? b->d_prefix() : nullptr;
-    a.nshots = (int32_t)b->members.size();
-    a.slot = slot;
+    a.wg_prefix = b->d_prefix();
     a.step = -1;
     a.record = 1;
     a.xcd_remap = 1;
     for (const ShotDesc &d : b->h_desc) a.damped |= d.damp != nullptr;
-    a.cached = cache_keeps(3.0 * b->interior);
-    return a;
+    for (const BatchGroup &g : b->groups) {
+        a.shot0 = g.m0;
+        a.nshots = g.m1 - g.m0;
+        a.wg0 = b->h_prefix[(size_t)g.m0];
+        a.cached = g.cached;
+        for (int64_t i = 0; i < n; ++i) {
+            a.slot = (int32_t)((b->slot + i) & 1);
+            b->kf->launch(a, b->h_prefix[(size_t)g.m1] - a.wg0, st);
+        }
+    }
 }
 
 extern "C" int fd_batch_step(fd_batch *b, int64_t nsteps)
@@ -1551,7 +1605,7 @@ extern "C" int fd_batch_step(fd_batch *b, int64_t nsteps)
     int64_t done = 0;
     // align to slot 0 with a direct launch, then replay the captured even-length chunk
     while (done < nsteps && (b->slot != 0 || nsteps - done < 2)) {
-        b->kf->launch(batch_args(b, b->slot), (int)b->nwg, b->stream);
+        batch_launch(b, 1, b->stream);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(FD_E_DEVICE, "fd_batch_step: %s", hipGetErrorString(e));
         b->slot ^= 1;
@@ -1565,7 +1619,7 @@ extern "C" int fd_batch_step(fd_batch *b, int64_t nsteps)
             hipGraph_t graph;
             hipError_t e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
             if (e != hipSuccess) return fail(FD_E_DEVICE, "fd_batch_step: capture: %s", hipGetErrorString(e));
-            for (int64_t i = 0; i < chunk; ++i) b->kf->launch(batch_args(b, (int)(i & 1)), (int)b->nwg, b->cap_stream);
+            batch_launch(b, chunk, b->cap_stream);
             e = hipStreamEndCapture(b->cap_stream, &graph);
             if (e != hipSuccess) return fail(FD_E_DEVICE, "fd_batch_step: end capture: %s", hipGetErrorString(e));
             e = hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0);
@@ -1579,12 +1633,11 @@ extern "C" int fd_batch_step(fd_batch *b, int64_t nsteps)
         done += chunk;
     }
     // an odd tail
-    while (done < nsteps) {
-        b->kf->launch(batch_args(b, b->slot), (int)b->nwg, b->stream);
+    if (done < nsteps) {
+        batch_launch(b, nsteps - done, b->stream);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return fail(FD_E_DEVICE, "fd_batch_step: %s", hipGetErrorString(e));
-        b->slot ^= 1;
-        ++done;
+        b->slot ^= (int)((nsteps - done) & 1);
     }
     // Later work on a member's own stream (fd_sync, fd_get_state, fd_step, ...) is ordered
     // after these batched steps: each member stream waits for the batch stream's tail.

@@ -813,9 +813,10 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         if (cz >= s.chunks_z) return;
         fwd_tile<C, DAMP, LD>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
     } else {
-        int shot = 0, local = wg;
+        int shot = a.shot0, local = wg;
         if (a.nshots > 1) {
-            int lo = 0, hi = a.nshots;
+            wg += a.wg0;
+            int lo = a.shot0, hi = a.shot0 + a.nshots;
             while (hi - lo > 1) {
                 const int mid = (lo + hi) >> 1;
                 if (a.wg_prefix[mid] <= wg)

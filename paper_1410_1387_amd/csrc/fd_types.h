@@ -57,7 +57,8 @@ struct ShotDesc {
 struct LaunchArgs {
     ShotDesc *shots;           // device array of shot descriptors
     const int32_t *wg_prefix;  // device, nshots + 1 workgroup offsets (NULL when nshots == 1)
-    int32_t nshots;
+    int32_t nshots, shot0;     // shots of this launch: [shot0, shot0 + nshots)
+    int32_t wg0;               // and the workgroup offset of the first one
     int32_t slot;              // counter mode: this launch reads ctr[slot], writes ctr[slot ^ 1]
     int64_t step;              // >= 0: step index for the single shot; < 0: counter mode
     const void *cur;           // explicit-pointer mode (single shot): u^n, u^{n-1}, u^{n+1}
