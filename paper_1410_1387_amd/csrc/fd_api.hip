@@ -246,6 +246,11 @@ namespace {
 // larger grids the early halo pays (288^3 r = 4: 75 us against 79 for the FINE tile).
 constexpr int64_t kFineZch = 32;
 
+// Rows per chunk of 2-D grids past the last-level cache, at most: a longer chunk has the whole
+// chip in rows far apart (8192^2 FP32 r = 4 170 us against 224 with 64 rows, r = 8 183 against
+// 200 with 86; 6000^2 FP64 r = 8 194 against 217 with 93).
+constexpr int kLongZch2d = 10;
+
 // A chosen tile whose chunks are this many planes takes its build for 4 waves per SIMD,
 // where it has one: at these sizes it is as fast (256^3 r = 4, 32 planes: 45.7 against
 // 45.4 us) and leaves a second workgroup room on each CU; on longer chunks it is slower
@@ -276,6 +281,9 @@ TileChoice<FwdEntry> choose_tile(const FwdEntry *tab, int count, const Layout &L
             const int64_t chunks = (L.knz + z - 1) / z;
             t.zch = (int)((L.knz + chunks - 1) / chunks);
             t.nwg = t.tx * t.ty * ((L.knz + t.zch - 1) / t.zch);
+        } else if (L.ndim == 2 && t.zch > kLongZch2d) {
+            t.zch = kLongZch2d;
+            t.nwg = t.tx * ((L.knz + t.zch - 1) / t.zch);
         }
         if (best.e && tab[i].role == FWD_FINE && t.zch >= kFineZch) continue;
         const double c = cached ? cached_tile_cost(tab[i], t.nwg, t.zch, L.r, cus)

@@ -15,7 +15,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 1, 3, 16, 32, 1, 4, 4, false, 1>, FWD_TWIN>("f32 r1 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 1, 2, 64, 1, 1>, FWD_AUTO>("f32 r1 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 1, 2, 64, 1, 1>, FWD_AUTO>("f32 r1 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 2
@@ -28,7 +28,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 2, 3, 16, 32, 1, 4, 4, false, 2>, FWD_TWIN>("f32 r2 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 2, 2, 64, 1, 1>, FWD_AUTO>("f32 r2 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 2, 2, 64, 1, 1>, FWD_AUTO>("f32 r2 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 3
@@ -41,7 +41,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 3, 3, 16, 32, 1, 4, 4, false, 3>, FWD_TWIN>("f32 r3 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 3, 2, 64, 1, 1>, FWD_AUTO>("f32 r3 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 3, 2, 64, 1, 1>, FWD_AUTO>("f32 r3 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 4
@@ -62,7 +62,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 4, 3, 16, 32, 1, 4, 4, false, 3>, FWD_TWIN>("f32 r4 3d tile 64x32 (512 thr, 1 row/thr, built for 4 waves/SIMD)", 1.0f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 4, 2, 64, 1, 1>, FWD_AUTO>("f32 r4 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 4, 2, 64, 1, 1>, FWD_AUTO>("f32 r4 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 5
@@ -72,7 +72,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 5, 3, 8, 16, 1>, FWD_FINE>("f32 r5 3d tile 32x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 5, 2, 64, 1, 1>, FWD_AUTO>("f32 r5 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 5, 2, 64, 1, 1>, FWD_AUTO>("f32 r5 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 6
@@ -82,7 +82,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 6, 3, 8, 16, 1>, FWD_FINE>("f32 r6 3d tile 32x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 6, 2, 64, 1, 1>, FWD_AUTO>("f32 r6 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 6, 2, 64, 1, 1>, FWD_AUTO>("f32 r6 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 7
@@ -92,7 +92,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 7, 3, 8, 16, 1>, FWD_FINE>("f32 r7 3d tile 32x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 7, 2, 64, 1, 1>, FWD_AUTO>("f32 r7 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 7, 2, 64, 1, 1>, FWD_AUTO>("f32 r7 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 8
@@ -109,7 +109,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<float, 8, 3, 8, 16, 1>, FWD_FINE>("f32 r8 3d tile 32x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<float, 8, 2, 64, 1, 1>, FWD_AUTO>("f32 r8 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<float, 8, 2, 64, 1, 1>, FWD_AUTO>("f32 r8 2d tile 256x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 

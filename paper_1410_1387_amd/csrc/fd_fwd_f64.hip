@@ -12,7 +12,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 1, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r1 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 1, 2, 64, 1, 1>, FWD_AUTO>("f64 r1 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 1, 2, 64, 1, 1>, FWD_AUTO>("f64 r1 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 2
@@ -22,7 +22,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 2, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r2 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 2, 2, 64, 1, 1>, FWD_AUTO>("f64 r2 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 2, 2, 64, 1, 1>, FWD_AUTO>("f64 r2 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 3
@@ -32,7 +32,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 3, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r3 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 3, 2, 64, 1, 1>, FWD_AUTO>("f64 r3 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 3, 2, 64, 1, 1>, FWD_AUTO>("f64 r3 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 4
@@ -45,7 +45,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 4, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r4 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 1.0f, 4),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 4, 2, 64, 1, 1>, FWD_AUTO>("f64 r4 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 4, 2, 64, 1, 1>, FWD_AUTO>("f64 r4 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 5
@@ -55,7 +55,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 5, 3, 8, 16, 1>, FWD_FINE>("f64 r5 3d tile 16x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 5, 2, 64, 1, 1>, FWD_AUTO>("f64 r5 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 5, 2, 64, 1, 1>, FWD_AUTO>("f64 r5 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 6
@@ -65,7 +65,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 6, 3, 8, 16, 1>, FWD_FINE>("f64 r6 3d tile 16x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 6, 2, 64, 1, 1>, FWD_AUTO>("f64 r6 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 6, 2, 64, 1, 1>, FWD_AUTO>("f64 r6 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 7
@@ -75,7 +75,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 7, 3, 8, 16, 1>, FWD_FINE>("f64 r7 3d tile 16x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 7, 2, 64, 1, 1>, FWD_AUTO>("f64 r7 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 7, 2, 64, 1, 1>, FWD_AUTO>("f64 r7 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 #if FD_RADIUS == 8
@@ -86,7 +86,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 8, 3, 8, 16, 1>, FWD_FINE>("f64 r8 3d tile 16x16 (128 thr, 1 row/thr)", 1.17f),
 };
 static const FwdEntry k2[] = {
-    fwd_entry<TileCfg<double, 8, 2, 64, 1, 1>, FWD_AUTO>("f64 r8 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f),
+    fwd_entry<TileCfg<double, 8, 2, 64, 1, 1>, FWD_AUTO>("f64 r8 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),
 };
 #endif
 

@@ -54,14 +54,16 @@ double cached_tile_cost(const Entry &e, int64_t nwg, int64_t zch, int r, int cus
 constexpr double kCacheBytes = 208.0 * (1 << 20);
 inline bool cache_keeps(double bytes) { return bytes <= kCacheBytes; }
 
-// Planes per chunk of a FINE tile on fields that stay in the last-level cache; count(Z) is
+// Planes per chunk of a FINE tile, or rows of a 2-D one, on fields that stay in the last-level cache; count(Z) is
 // the number of workgroups with chunks of at most Z of nz planes.  Where there are plenty,
 // short chunks in many rounds are best: a chunk's first planes come from the L2 that the
 // chunk below has just filled, and the CUs stay balanced.  Otherwise one round, but of at
 // most eight waves per CU: more of them push each other's planes out.  Best measured length
 // against one round of all places, us per step: 201x119x333 r = 2 2 planes 22.1 (9: 25.1),
 // r = 4 4 planes 25.5 (12: 29.9); 160^3 r = 4 8 planes 15.2 (6: 15.8), 93x118x141 4 planes
-// 8.2 (3: 8.4); a batch of seven 78..152-cubes 6 planes 50.9 (23: 55).
+// 8.2 (3: 8.4); a batch of seven 78..152-cubes 6 planes 50.9 (23: 55);
+// 2-D 4096^2 r = 8 4 rows 39.7 (22: 51), 2500^2 FP64 4 rows 30.6 (17: 39), 1203x801 r = 5 2
+// rows 6.2 (1: 6.6).
 template <class Count>
 int fine_zch(const Count &count, int64_t nz, int nt, int short_zch, int cus)
 {

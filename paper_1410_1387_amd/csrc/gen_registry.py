@@ -48,7 +48,7 @@ F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
 FINE_CACHED = {"f32": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.25f", 4)},
                "f64": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.0f", 4)}}
 SWEEP_RADII = {4, 8}      # radii that get the OPTION tiles
-F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads
+F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads; chunks as FINE tiles'
 # 3-D adjoint tiles: (shape, role, relative cost per point); half of a tile's threads own mu,
 # half u, so a workgroup has twice the threads of the shape.  FP32, radii <= 4: the library
 # takes the 128-wide tile or one of the 64-wide ones by how rows fill them, then the cheaper
@@ -133,7 +133,7 @@ def fwd_file(T, auto, options, auto_big_r, options_big_r):
         out += "};\n"
         txn = F2D[0]
         out += f"static const FwdEntry k2[] = {{\n"
-        out += f'    fwd_entry<TileCfg<{T}, {R}, 2, {txn}, 1, 1>, FWD_AUTO>("{cfgname(T, R, 2, txn, 1, 1)}", 1.0f),\n'
+        out += f'    fwd_entry<TileCfg<{T}, {R}, 2, {txn}, 1, 1>, FWD_AUTO>("{cfgname(T, R, 2, txn, 1, 1)}", 1.0f, 1.0f, 4),\n'
         out += "};\n#endif\n"
     out += ("\n#define FD_CAT_(a, b) a##b\n#define FD_CAT(a, b) FD_CAT_(a, b)\n"
             f"const FwdEntry *FD_CAT(fwd_configs_{tag}_r, FD_RADIUS)(int ndim, int *count)\n{{\n"

@@ -110,3 +110,34 @@ def test_shared_launches_under_capture(oracle_mod):
             g.replay()
             assert torch.equal(p.state()[0], want)
             assert torch.equal(traces, want_tr)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_own_chunks_bitwise(oracle_mod, dtype):
+    # the library's own rows per chunk (few, many short ones, and those of a grid past the
+    # last-level cache) give the bits of one chunk of all rows
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    for shape, r in [((3, 2000), 8), ((1203, 801), 5), ((1600, 1601), 8), ((4500, 4300), 6)]:
+        say(f"2-D chunks shape={shape} r={r} dtype={dtype}")
+        v = torch.full(shape, 2000.0, dtype=tdt, device="cuda")
+        gen = torch.Generator(device="cuda").manual_seed(r)
+        u0 = torch.randn(shape, generator=gen, dtype=tdt, device="cuda")
+        got = []
+        for tuning in (None, (0, shape[0])):
+            if tuning:
+                F.fd_set_tuning(dtype, r, 2, *tuning)
+            try:
+                p = Propagator(v, r, 10.0, 0.4 * oracle_mod.dt_max(2, r, 10.0, 2000.0), dtype)
+            finally:
+                F.fd_set_tuning(dtype, r, 2, -1, 0)
+            p.set_state(u0, 0.5 * u0, 0)
+            for _ in range(3):
+                p.step(1)
+            got.append(p.state()[0])
+            p.sync()
+        assert torch.equal(*got)
