@@ -230,6 +230,14 @@ int fd_step_explicit(fd_ctx *ctx, const void *cur, const void *prev, void *out, 
  * Same arguments and errors as fd_step_explicit. */
 int fd_step_record(fd_ctx *ctx, const void *cur, const void *prev, void *out, int64_t step);
 
+/* fd_step_record for the steps 0 .. nsteps-1 of a run whose states are all kept, with the
+ * same results: 2-D grids take several steps per launch as in fd_step.
+ *   states    device, nsteps + 1 consecutive padded fields (field i at byte offset
+ *             i * fd_field_bytes): u^0 in field 0 and u^{-1} in field nsteps on entry;
+ *             u^1 .. u^nsteps in fields 1 .. nsteps on return
+ * Errors: FD_E_INVAL (null states, nsteps < 0), FD_E_STATE (periodic context). */
+int fd_steps_record(fd_ctx *ctx, void *states, int64_t nsteps);
+
 /* ----------------------------------------------------------------- adjoint (gradient) */
 
 /* Discrete adjoint of the forward scheme for J = 1/2 sum_n sum_j resid[n][j]^2 with

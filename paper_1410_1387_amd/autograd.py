@@ -122,11 +122,7 @@ class WaveProp(torch.autograd.Function):
             F.fd_clear_ghosts(prop.ctx, fields, T + 1)  # on the context's stream, the current one
             fields[0].zero_()
             fields[T].zero_()
-            prev, cur = fields[T], fields[0]
-            for k in range(T):
-                out = fields[k + 1] if k + 1 < T else fields[T]
-                F.fd_step_record(prop.ctx, cur, prev, out, k)
-                prev, cur = cur, out
+            F.fd_steps_record(prop.ctx, fields, T)
         else:
             for k0 in range(0, T, K):
                 cur, prv = prop.new_field(), prop.new_field()

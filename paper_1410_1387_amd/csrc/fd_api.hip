@@ -1090,6 +1090,31 @@ extern "C" int fd_step_record(fd_ctx *ctx, const void *cur, const void *prev, vo
     return step_explicit(ctx, cur, prev, out, step, 1, "fd_step_record");
 }
 
+extern "C" int fd_steps_record(fd_ctx *ctx, void *states, int64_t nsteps)
+{
+    int st = check_ctx(ctx);
+    if (st) return st;
+    if (!states || nsteps < 0) return fail(FD_E_INVAL, "fd_steps_record: bad arguments");
+    if (ctx->bc != FD_BC_ZERO) return fail(FD_E_STATE, "fd_steps_record: zero boundary only");
+    auto field = [&](int64_t i) -> void * { return (char *)states + (size_t)i * ctx->L.field_bytes; };
+    for (int64_t k = 0; k < nsteps;) {
+        void *const prev = field(k ? k - 1 : nsteps);
+        // the first launch reads the field that takes the last state
+        const int64_t left = k ? nsteps - k : nsteps - 1;
+        if (multi2d_ok(ctx) && left >= 2) {
+            const int64_t n = std::min<int64_t>(left, ctx->km->kmax);
+            launch_multi2d(ctx, field(k), prev, nullptr, nullptr, field(k + 1), k, n, 1);
+            HIP_TRY(ctx, hipGetLastError());
+            k += n;
+        } else {
+            st = step_explicit(ctx, field(k), prev, field(k + 1), k, 1, "fd_steps_record");
+            if (st) return st;
+            ++k;
+        }
+    }
+    return FD_OK;
+}
+
 // ------------------------------------------------------------------ adjoint
 
 template <class Slot>
@@ -1113,10 +1138,18 @@ extern "C" int fd_adjoint_segment(fd_ctx *ctx, const void *u_ckpt_cur, const voi
         return i == 0 ? const_cast<void *>(u_ckpt_cur) : (char *)ring + (size_t)(i - 1) * fb;
     };
     // recompute u^{k_lo+1} .. u^{k_hi-1} from the checkpoint into the ring
-    for (int64_t i = 1; i < nk; ++i) {
+    for (int64_t i = 1; i < nk;) {
         const void *prev = (i == 1) ? u_ckpt_prev : slot(i - 2);
+        if (multi2d_ok(ctx) && nk - i >= 2) {
+            const int64_t n = std::min<int64_t>(nk - i, ctx->km->kmax);
+            launch_multi2d(ctx, slot(i - 1), prev, nullptr, nullptr, slot(i), k_lo + i - 1, n, 0);
+            HIP_TRY(ctx, hipGetLastError());
+            i += n;
+            continue;
+        }
         int s2 = fd_step_explicit(ctx, slot(i - 1), prev, slot(i), k_lo + i - 1);
         if (s2) return s2;
+        ++i;
     }
     return adjoint_steps(ctx, slot, k_lo, k_hi, mu, resid, resid_amp, grad, grad_seg);
 }

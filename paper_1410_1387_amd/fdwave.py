@@ -32,6 +32,7 @@ EXPORTS = [
     "fd_weights", "fd_dt_max", "fd_field_bytes", "fd_workspace_bytes", "fd_create", "fd_destroy",
     "fd_set_stream", "fd_inject", "fd_clear_sources", "fd_set_damping", "fd_record", "fd_ricker", "fd_step", "fd_sync",
     "fd_get_step", "fd_get_state", "fd_set_time_blocking", "fd_set_state", "fd_step_explicit", "fd_step_record",
+    "fd_steps_record",
     "fd_adjoint_segment", "fd_adjoint_stored", "fd_clear_ghosts", "fd_gradient_finish", "fd_batch_workspace_bytes", "fd_batch_create",
     "fd_batch_create_noalloc", "fd_batch_destroy", "fd_batch_set", "fd_batch_step", "fd_copy_probe", "fd_stream_probe",
     "fd_check_finite", "fd_kernel_config", "fd_adjoint_config", "fd_set_tuning", "fd_set_adj_tuning",
@@ -92,6 +93,7 @@ def lib():
             "fd_set_state": (ctypes.c_int, [P, P, P, I64, ctypes.c_int]),
             "fd_step_explicit": (ctypes.c_int, [P, P, P, P, I64]),
             "fd_step_record": (ctypes.c_int, [P, P, P, P, I64]),
+            "fd_steps_record": (ctypes.c_int, [P, P, I64]),
             "fd_adjoint_segment": (ctypes.c_int, [P, P, P, I64, I64, P, P, P, D, P, P]),
             "fd_adjoint_stored": (ctypes.c_int, [P, P, I64, I64, P, P, D, P, P]),
             "fd_clear_ghosts": (ctypes.c_int, [P, P, I64]),
@@ -290,6 +292,10 @@ def fd_step_explicit(ctx: int, cur, prev, out, step: int):
 
 def fd_step_record(ctx: int, cur, prev, out, step: int):
     _check(lib().fd_step_record(ctx, ptr(cur), ptr(prev), ptr(out), int(step)), "fd_step_record")
+
+
+def fd_steps_record(ctx: int, states, nsteps: int):
+    _check(lib().fd_steps_record(ctx, ptr(states), int(nsteps)), "fd_steps_record")
 
 
 def fd_adjoint_segment(ctx: int, ckpt_cur, ckpt_prev, k_lo: int, k_hi: int, ring, mu, resid, resid_amp: float, grad,

@@ -141,3 +141,61 @@ def test_own_chunks_bitwise(oracle_mod, dtype):
             got.append(p.state()[0])
             p.sync()
         assert torch.equal(*got)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("shape,r", [((45, 130), 1), ((300, 420), 4), ((700, 900), 4), ((61, 77), 8), ((801, 900), 8),
+                                     ((20, 24, 30), 2)])
+def test_kept_states_bitwise(oracle_mod, shape, r, dtype):
+    # every state kept, in one call and step by step; the adjoint of the kept states and of
+    # states recomputed from a checkpoint, all with the bits of single steps
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    nd = len(shape)
+    v = torch.tensor(workloads.layered_velocity(shape, seed=r), dtype=tdt, device="cuda")
+    dt = 0.4 * oracle_mod.dt_max(nd, r, 10.0, float(v.max()))
+    nx, nz = shape[-1], shape[0]
+    mid = (shape[1] // 2,) if nd == 3 else ()
+    rec = np.array([(x, *mid, nz // 2) for x in range(0, nx, 3)] + [(1, *mid, z) for z in range(nz)])
+    for T in (1, 2, 3, 9, 20):
+        say(f"kept states shape={shape} r={r} dtype={dtype} T={T}")
+        kept = []
+        for whole in (True, False):
+            p = Propagator(v, r, 10.0, dt, dtype, max_receivers=len(rec))
+            p.inject(p.ricker(T, 30.0, 0.0), (nx // 2, *mid, nz // 3))
+            traces = p.record(rec, T)
+            n = p.new_field().numel()
+            fields = torch.zeros((T + 1, n), dtype=tdt, device="cuda")
+            gen = torch.Generator(device="cuda").manual_seed(7)
+            u0 = torch.randn(shape, generator=gen, dtype=tdt, device="cuda")
+            p.set_state(u0, 0.5 * u0, 0)
+            p.save_padded(fields[0], fields[T])
+            start = [fields[0].clone(), fields[T].clone()]
+            if whole:
+                F.fd_steps_record(p.ctx, fields, T)
+            else:
+                prev, cur = fields[T], fields[0]
+                for k in range(T):
+                    F.fd_step_record(p.ctx, cur, prev, fields[k + 1], k)
+                    prev, cur = cur, fields[k + 1]
+            resid = traces.clone()
+            grads = []
+            for stored in (True, False):
+                mu = torch.zeros(2 * n, dtype=tdt, device="cuda")
+                g = p.new_field()
+                if stored:
+                    F.fd_adjoint_stored(p.ctx, fields, 0, T, mu, resid, 1.0, g, None)
+                else:
+                    ring = torch.zeros((T, n), dtype=tdt, device="cuda")
+                    F.fd_adjoint_segment(p.ctx, start[0], start[1], 0, T, ring, mu, resid, 1.0, g, None)
+                grads.append(g)
+            p.sync()
+            assert torch.equal(*grads)
+            kept.append((fields, traces, grads[0]))
+        for a, b in zip(*kept):
+            assert torch.equal(a, b)
+        assert float(kept[0][1].abs().max()) > 0 and float(kept[0][2].abs().max()) > 0
