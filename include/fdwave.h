@@ -263,6 +263,8 @@ int fd_steps_record(fd_ctx *ctx, void *states, int64_t nsteps);
  *   grad      device padded field of dtype, accumulated (zero it before the first segment)
  *   grad_seg  device padded field of dtype used as the segment partial sum, or NULL for
  *             plain accumulation into grad (its contents need no initialisation)
+ * On 2-D grids of up to 64 MiB per field with no tile set by fd_set_adj_tuning a launch
+ * takes several steps, through two more fields in the workspace, with the same results.
  * Receivers must have been registered with fd_record (the traces buffer is not touched).
  * resid must hold at least k_hi rows. */
 int fd_adjoint_segment(fd_ctx *ctx, const void *u_ckpt_cur, const void *u_ckpt_prev, int64_t k_lo,

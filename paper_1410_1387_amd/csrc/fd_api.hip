@@ -324,18 +324,16 @@ TileChoice<AdjEntry> choose_adj_tile(const AdjEntry *tab, int count, const Layou
     return best;
 }
 
-// The several-steps kernel of a 2-D grid.  While one round of workgroups covers the grid the
-// time is the chain load, k steps, store, so many steps on small tiles win; beyond that it is
-// the work on the widened tiles, which wants large tiles and few steps (k r around 8), and
-// for r > 4 a tile of any size that fits LDS costs more than the launches it saves
-// (1203 x 800 points, r = 8, FP32: 7.4 us against 6.3 for a single step), so those stay with
-// the single-step kernel.  The tables hold both sides of each line.
-const Multi2dEntry *choose_multi2d(fd_dtype dt, const Layout &L)
+// The several-steps kernel of a 2-D grid, forward or adjoint, or none.  While one round of
+// workgroups covers the grid the time is the chain load, k steps, store, so many steps on
+// small tiles win; beyond that it is the work on the widened tiles, which wants large tiles
+// and few steps (k r around 8), and for r > 4 a tile of any size that fits LDS costs more than
+// the launches it saves (1203 x 800 points, r = 8, FP32: 7.4 us against 6.3 for a single
+// step), so those stay with the single-step kernel.  The tables hold both sides of each line.
+template <class Entry>
+const Entry *choose_multi2d(const Entry *tab, int count, const Layout &L)
 {
-    if (!L.pair) return nullptr;
-    int count = 0;
-    const Multi2dEntry *tab = dt == FD_F32 ? multi2d_configs_f32(L.r, &count) : multi2d_configs_f64(L.r, &count);
-    for (int i = 0; i < count; ++i) {
+    for (int i = 0; L.pair && i < count; ++i) {
         const int64_t tiles = ((L.knx + tab[i].tx - 1) / tab[i].tx) * ((L.knz + tab[i].tz - 1) / tab[i].tz);
         if (!tab[i].per_cu || tiles <= (int64_t)tab[i].per_cu * device_cus()) return &tab[i];
     }
@@ -387,6 +385,7 @@ struct fd_ctx {
     int xcd_remap;
     // several steps per launch (2-D)
     const Multi2dEntry *km;
+    const Adj2dEntry *kam;
     // two-step forward (temporal blocking): two caller-provided padded fields
     void *aux[2];
     const Fwd2Entry *k2;
@@ -645,7 +644,12 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->adj_tiles_y = adj.ty;
     c->adj_zch = adj.zch;
     c->adj_chunks_z = (L.knz + c->adj_zch - 1) / c->adj_zch;
-    c->km = tuned ? nullptr : choose_multi2d(dtype, L);  // a caller's tile is used for every step
+    // a caller's tile is used for every step
+    int mcount = 0, macount = 0;
+    const Multi2dEntry *mtab = dtype == FD_F32 ? multi2d_configs_f32(r, &mcount) : multi2d_configs_f64(r, &mcount);
+    const Adj2dEntry *matab = dtype == FD_F32 ? adj2d_configs_f32(r, &macount) : adj2d_configs_f64(r, &macount);
+    c->km = tuned ? nullptr : choose_multi2d(mtab, mcount, L);
+    c->kam = acfg >= 0 ? nullptr : choose_multi2d(matab, macount, L);
     c->nrec = 0;
     c->traces = nullptr;
     c->rec_cap = 0;
@@ -1185,7 +1189,40 @@ static int adjoint_steps(fd_ctx *ctx, const Slot &slot, int64_t k_lo, int64_t k_
     // (28 MB per field) 45.0 -> 44.4, r = 8 64.1 -> 61.2, 192^3 FP64 (57 MB) 82.4 -> 83.4,
     // 256^3 (67 MB) 89 -> 98.
     const int cached = cache_keeps(6.5 * interior_bytes(ctx->L));
-    for (int64_t k = k_hi; k > k_lo; --k) {
+    int64_t k = k_hi;
+    const bool blocked = grad_seg && nk > 1;
+    while (ctx->kam && k - k_lo >= 2) {  // pairs of launches through the second pair of fields, as in fd_step
+        void *const pair[2] = {ctx->ws + ctx->L.o_pair, ctx->ws + ctx->L.o_pair + fb};
+        const int64_t two = std::min<int64_t>(k - k_lo, 2 * ctx->kam->kmax), k1 = (two + 1) / 2;
+        for (int half = 0; half < 2; ++half) {
+            const int64_t top = half ? k - k1 : k, n = half ? two - k1 : k1, end = top - n;
+            Adj2dArgs a;
+            std::memset(&a, 0, sizeof(a));
+            a.one = ctx->desc;
+            a.cur = half ? pair[0] : m[(top + 1) & 1];
+            a.prev = half ? pair[1] : m[top & 1];
+            a.out = half ? m[(end + 1) & 1] : pair[0];
+            a.out_prev = half ? m[end & 1] : pair[1];
+            a.states0 = slot(0);
+            a.states1 = nk > 1 ? slot(1) : nullptr;
+            a.slot = top - 1 - k_lo;
+            a.g_in = !blocked ? grad : top == k_hi ? nullptr : grad_seg;
+            a.g_add = blocked && end == k_lo ? grad : nullptr;
+            a.g_out = !blocked || end == k_lo ? grad : grad_seg;
+            a.resid = resid;
+            a.resid_amp = resid_amp;
+            a.field = (int64_t)fb;
+            a.k0 = top;
+            a.k = (int32_t)n;
+            a.tiles_x = (int32_t)((ctx->L.knx + ctx->kam->tx - 1) / ctx->kam->tx);
+            a.tiles_z = (int32_t)((ctx->L.knz + ctx->kam->tz - 1) / ctx->kam->tz);
+            a.xcd_remap = ctx->xcd_remap;
+            ctx->kam->launch(a, ctx->stream);
+            HIP_TRY(ctx, hipGetLastError());
+        }
+        k -= two;
+    }
+    for (; k > k_lo; --k) {
         AdjArgs a;
         std::memset(&a, 0, sizeof(a));
         a.one = ctx->desc;

@@ -58,4 +58,37 @@ const Multi2dEntry *multi2d_configs_f32(int r, int *count)
     }
 }
 
+// The adjoint.  Microseconds per step, single-step kernel -> these:
+//          150 x 128     420 x 300     512^2         1203 x 801    1600^2
+//   r = 1  3.13 -> 2.24  3.55 -> 2.24  3.79 -> 2.29   5.62 -> 2.74  13.8 ->  6.6
+//   r = 2  3.31 -> 2.54  3.70 -> 2.57  3.93 -> 2.57   6.10 -> 5.25  14.6 -> 11.5
+//   r = 3  3.39 -> 3.01  3.83 -> 3.00  4.08 -> 3.01   6.56 (6 steps: 9.03)
+//   r = 4  3.52 -> 3.15  4.00 -> 3.15  4.25 -> 3.19   7.00 -> 6.05  15.1 -> 14.1
+// and for larger radii, where a strip and its neighbours spill, the single step is as good.
+static const Adj2dEntry a_r1[] = {
+    adj2d_entry<Multi2dCfg<float, 1, 8, 32, 32>>(0),
+};
+static const Adj2dEntry a_r2[] = {
+    adj2d_entry<Multi2dCfg<float, 2, 8, 32, 32>>(1),
+    adj2d_entry<Multi2dCfg<float, 2, 4, 32, 16>>(0),
+};
+static const Adj2dEntry a_r3[] = {
+    adj2d_entry<Multi2dCfg<float, 3, 6, 32, 32>>(1),
+};
+static const Adj2dEntry a_r4[] = {
+    adj2d_entry<Multi2dCfg<float, 4, 6, 32, 32>>(1),
+    adj2d_entry<Multi2dCfg<float, 4, 4, 64, 32>>(0),
+};
+
+const Adj2dEntry *adj2d_configs_f32(int r, int *count)
+{
+    switch (r) {
+    case 1: *count = (int)(sizeof(a_r1) / sizeof(Adj2dEntry)); return a_r1;
+    case 2: *count = (int)(sizeof(a_r2) / sizeof(Adj2dEntry)); return a_r2;
+    case 3: *count = (int)(sizeof(a_r3) / sizeof(Adj2dEntry)); return a_r3;
+    case 4: *count = (int)(sizeof(a_r4) / sizeof(Adj2dEntry)); return a_r4;
+    default: *count = 0; return nullptr;
+    }
+}
+
 }  // namespace fdw

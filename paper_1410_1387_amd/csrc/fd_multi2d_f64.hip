@@ -62,4 +62,43 @@ const Multi2dEntry *multi2d_configs_f64(int r, int *count)
     }
 }
 
+// The adjoint.  Microseconds per step, single-step kernel -> these:
+//          150 x 128     420 x 300     512^2         1203 x 801    1600^2
+//   r = 1  2.96 -> 1.55  3.87 -> 1.59  4.61 -> 1.70  10.9 ->  5.5  24.3 -> 12.9
+//   r = 2  3.07 -> 1.72  4.14 -> 2.28  4.96 -> 2.38  10.9 ->  8.0  26.1 -> 18.3
+//   r = 3  3.17 -> 2.25  4.38 -> 2.91  5.37 -> 3.08  11.4 -> 10.3  27.2 -> 23.6
+//   r = 4  3.28 -> 2.16  4.56 -> 3.13  5.65 -> 3.28  11.9 -> 11.5  28.6 -> 26.1
+//   r = 5  3.35 -> 2.70  4.77 (2 steps, 32x32: 5.40)
+// and for larger radii, where a strip and its neighbours spill, the single step is as good.
+static const Adj2dEntry a_r1[] = {
+    adj2d_entry<Multi2dCfg<double, 1, 8, 32, 32>>(0),
+};
+static const Adj2dEntry a_r2[] = {
+    adj2d_entry<Multi2dCfg<double, 2, 6, 16, 16>>(1),
+    adj2d_entry<Multi2dCfg<double, 2, 4, 32, 32>>(0),
+};
+static const Adj2dEntry a_r3[] = {
+    adj2d_entry<Multi2dCfg<double, 3, 4, 16, 16>>(1),
+    adj2d_entry<Multi2dCfg<double, 3, 3, 32, 32>>(0),
+};
+static const Adj2dEntry a_r4[] = {
+    adj2d_entry<Multi2dCfg<double, 4, 6, 16, 16>>(1),
+    adj2d_entry<Multi2dCfg<double, 4, 3, 32, 32>>(0),
+};
+static const Adj2dEntry a_r5[] = {
+    adj2d_entry<Multi2dCfg<double, 5, 4, 16, 16>>(1),
+};
+
+const Adj2dEntry *adj2d_configs_f64(int r, int *count)
+{
+    switch (r) {
+    case 1: *count = (int)(sizeof(a_r1) / sizeof(Adj2dEntry)); return a_r1;
+    case 2: *count = (int)(sizeof(a_r2) / sizeof(Adj2dEntry)); return a_r2;
+    case 3: *count = (int)(sizeof(a_r3) / sizeof(Adj2dEntry)); return a_r3;
+    case 4: *count = (int)(sizeof(a_r4) / sizeof(Adj2dEntry)); return a_r4;
+    case 5: *count = (int)(sizeof(a_r5) / sizeof(Adj2dEntry)); return a_r5;
+    default: *count = 0; return nullptr;
+    }
+}
+
 }  // namespace fdw

@@ -199,3 +199,53 @@ def test_kept_states_bitwise(oracle_mod, shape, r, dtype):
         for a, b in zip(*kept):
             assert torch.equal(a, b)
         assert float(kept[0][1].abs().max()) > 0 and float(kept[0][2].abs().max()) > 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("r", [1, 2, 3, 4, 5])
+def test_adjoint_launches_bitwise(oracle_mod, r, dtype):
+    # adjoint steps that share launches against the tile set by hand, which steps alone: one tile and less, remainders, the larger grids' tiles; receivers
+    # in corners, on lines and several at one point; segments of every length, their images
+    # summed directly and by segment
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    steps = 21
+    for shape in [(1, 1), (6, 3), (33, 133), (70, 38), (801, 1203), (270, 265)]:
+        nz, nx = shape
+        say(f"2-D adjoint launches shape={shape} r={r} dtype={dtype}")
+        v = torch.tensor(workloads.layered_velocity(shape, seed=r), dtype=tdt, device="cuda")
+        rec = np.array([(x, nz // 2) for x in range(nx)] + [(nx // 3, z) for z in range(nz)] +
+                       [(0, 0), (nx - 1, nz - 1), (0, 0)])
+        out = []
+        for one in (True, False):
+            if one:
+                F.fd_set_adj_tuning(dtype, r, 2, 0)
+            try:
+                p = Propagator(v, r, 10.0, 0.4 * oracle_mod.dt_max(2, r, 10.0, float(v.max())), dtype,
+                               max_receivers=len(rec))
+            finally:
+                F.fd_set_adj_tuning(dtype, r, 2, -1)
+            p.record(rec, steps)
+            n = p.new_field().numel()
+            gen = torch.Generator(device="cuda").manual_seed(5)
+            states = torch.zeros((steps, n), dtype=tdt, device="cuda")
+            for k in range(steps):
+                u = torch.randn(shape, generator=gen, dtype=tdt, device="cuda")
+                p.set_state(u, u, 0)
+                p.save_padded(states[k], p.new_field())
+            resid = torch.randn((steps, len(rec)), generator=gen, dtype=tdt, device="cuda")
+            for seg in (False, True):
+                for cuts in ([0, steps], [0, 1, 3, 6, 20, steps]):
+                    mu, g, gs = torch.zeros(2 * n, dtype=tdt, device="cuda"), p.new_field(), p.new_field()
+                    for lo, hi in reversed(list(zip(cuts, cuts[1:]))):
+                        F.fd_adjoint_stored(p.ctx, states[lo:], lo, hi, mu, resid, 0.5, g, gs if seg else None)
+                    p.sync()
+                    out.append((mu, g))
+        half = len(out) // 2
+        for a, b in zip(out[:half], out[half:]):
+            assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+        assert float(out[0][1].abs().max()) > 0 or max(shape) == 1
