@@ -493,9 +493,10 @@ __device__ __forceinline__ T *plane_at(T *base, int64_t pxy, int zp, uint32_t ob
 // list and sponge factors read through memory one after another, and as it is here:
 // 512^3 r = 4 383 -> 352 us (5.60 -> 6.10 TB/s of 16 B/pt; the three-workgroup tile would
 // take 414: loads no longer waited for keep more places in memory open at once, so the
-// one-workgroup 128x16 tile is the one to use), 256^3 56 -> 46, 384^3 r = 8 202 -> 171,
-// 256^3 FP64 93 -> 85, 64^3 6.6 -> 5.5, 97x161x203 r = 2 with sponge 25.5 -> 15.0, 2-D
-// 801x1203 r = 8 with sponge 12.5 -> 7.0.  A launch that returns at once takes 2.3 us.
+// one-workgroup 128x16 tile is the one to use), 256^3 56 -> 44, 384^3 r = 8 202 -> 171,
+// 256^3 FP64 93 -> 85, 64^3 6.6 -> 5.3, 97x161x203 r = 2 with sponge 25.5 -> 13.0, 2-D
+// 1203x801 r = 8 with sponge 12.5 -> 6.8 (of 256^3 1.5, of 64^3 0.2 and of the ragged grid
+// 2.0 us are the cached loads and short chunks).  A launch that returns at once takes 2.3 us.
 //
 // DAMP: the sponge's per-axis factors are in s.damp (a null s.damp counts as all ones, for
 // batches that mix damped and undamped shots); G = gx gy gz scales both time levels.
@@ -889,7 +890,7 @@ enum { GM_ACC = 0, GM_FIRST = 1, GM_FOLD = 2, GM_DIRECT = 3 };
 //
 // What bounds it: HBM for large grids (28 B per point; 256^3 r = 4: 96 -> 87 us per step,
 // 5.4 TB/s), and before the split, for r = 8, the registers of two queues (more than 256,
-// so one wave per SIMD): 192^3 89 -> 56 us, 93x118x141 36 -> 20 us.
+// so one wave per SIMD): 192^3 89 -> 56 us, 93x118x141 36 -> 18 us.
 template <class C, int ROLE, int LD>
 __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::type *__restrict__ field,
                                          typename C::type *mout, const typename C::type *g1,

@@ -23,7 +23,7 @@
 //    z-RZ .. z+RZ in a register queue that shifts by one plane per step.
 //  - Global traffic is x-contiguous 16-byte vectors: p^n and q^n once per point
 //    (plus the p halo and the q chunk prologue), p^{n-1}, q^{n-1} and the three
-//    coefficient fields streamed with nontemporal loads, p^{n+1} and q^{n+1}
+//    coefficient fields with nontemporal loads (see kPointLoads), p^{n+1} and q^{n+1}
 //    written with nontemporal stores over p^{n-1} and q^{n-1}.  Every load of the
 //    next plane is issued one plane ahead of its use.
 //  - The z weights of plane z are uniform across the workgroup (scalar loads).
@@ -31,7 +31,8 @@
 //
 // What bounds it: HBM for large grids (36 B per point in FP32: 512^3 R_xy = 12, R_z = 8
 // 862 -> 831 us per step, 5.81 TB/s, when the loads lost their branches and the tile
-// became 128x16), the latency of a plane for small ones (93x118x141 22.6 -> 18.5 us).
+// became 128x16), the latency of a plane for small ones (93x118x141 22.6 -> 15.1 us, of which
+// 3 since the point-wise loads keep their lines where the fields fit the last-level cache).
 #pragma once
 
 #include "fd_stencil.h"
