@@ -41,7 +41,7 @@ static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 4, 3, 32, 16, 1>, FWD_OPTION>("f64 r4 3d tile 64x16 (512 thr, 1 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 4, 3, 32, 8, 2>, FWD_OPTION>("f64 r4 3d tile 64x16 (256 thr, 2 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 4, 3, 16, 16, 1>, FWD_OPTION>("f64 r4 3d tile 32x16 (256 thr, 1 row/thr)", 1.0f),
-    fwd_entry<TileCfg<double, 4, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r4 3d tile 32x32 (512 thr, 1 row/thr)", 0.95f),
+    fwd_entry<TileCfg<double, 4, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r4 3d tile 32x32 (512 thr, 1 row/thr)", 0.85f),
     fwd_entry<TileCfg<double, 4, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r4 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 1.0f, 4),
 };
 static const FwdEntry k2[] = {

@@ -47,6 +47,9 @@ F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
 # 333 r = 8: 34.5 us with 4 planes, 31.7 with 128x16).
 FINE_CACHED = {"f32": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.25f", 4)},
                "f64": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.0f", 4)}}
+# FP64 r = 4: 512 threads and half the workgroups stream better the longer the chunks (512^3 724
+# us against 790, 480^3 624 against 685, 352^3 245 against 261, 256^3 84.4 against 84.7)
+COSTS = {("f64", 4, (16, 32, 1)): 0.85}
 SWEEP_RADII = {4, 8}      # radii that get the OPTION tiles
 F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads; chunks as FINE tiles'
 # 3-D adjoint tiles: (shape, role, relative cost per point); half of a tile's threads own mu,
@@ -127,6 +130,7 @@ def fwd_file(T, auto, options, auto_big_r, options_big_r):
             rows += au[1:]
         out += f"#if FD_RADIUS == {R}\nstatic const FwdEntry k3[] = {{\n"
         for cfg, role, cost in rows:
+            cost = COSTS.get((tag, R, cfg[:3]), cost) if role == "AUTO" else cost
             name = cfgname(T, R, 3, *cfg[:5])
             cached = "".join(f", {v}" for v in FINE_CACHED[tag].get(R, ())) if role == "FINE" else ""
             out += f'    fwd_entry<{tilecfg(T, R, 3, *cfg)}, FWD_{role}>("{name}", {cost}f{cached}),\n'
