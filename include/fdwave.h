@@ -306,15 +306,16 @@ size_t fd_batch_workspace_bytes(int max_shots);
  * in one stencil launch per step: each workgroup looks up its (shot, tile) from a prefix
  * table, and each shot keeps its step counter in device memory, so a captured graph of
  * an even number of steps can be replayed while shots come and go.  Members whose fields
- * fit the last-level cache together only in groups take one launch per step and group.
+ * fit the last-level cache together only in groups take one launch per step and group, and
+ * so do larger members apart from them.
  *   workspace  device, fd_batch_workspace_bytes(max_shots), borrowed until destroy */
 int fd_batch_create(fd_batch **out, int max_shots, void *workspace, size_t ws_bytes, void *stream);
 int fd_batch_destroy(fd_batch *b);
 
 /* Replace the member set.  Each context advances until its step reaches target[i] (host
  * array); members keep their state and step.  Members must share r, dtype and ndim
- * (FD_E_INVAL); the batch steps all of them with one stencil tile, the library's choice
- * for the member set as a whole, whatever tiles the members' contexts use (bitwise the same
+ * (FD_E_INVAL); the batch steps the members of a group with one stencil tile, the library's
+ * choice for the group as a whole, whatever tiles the members' contexts use (bitwise the same
  * results).  Invalidates the captured graph.  Work still queued on a member's own stream is completed before any batched launch touches it (the
  * batch stream waits for each member stream); the call also waits on the host for earlier
  * batched work, whose shot table it rewrites. */

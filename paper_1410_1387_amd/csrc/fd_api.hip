@@ -1287,7 +1287,10 @@ extern "C" int fd_gradient_finish(fd_ctx *ctx, const void *grad_padded, const vo
 // Members that share launches: [m0, m1) of the batch.
 struct BatchGroup {
     int m0, m1;
-    bool cached;  // their fields stay in the last-level cache
+    bool split;   // a group of members that fit the last-level cache
+    bool cached;  // all its fields stay there
+    const FwdEntry *kf;
+    int64_t zch;
 };
 
 struct fd_batch {
@@ -1302,7 +1305,6 @@ struct fd_batch {
     std::vector<BatchGroup> groups;
     std::vector<int32_t> h_prefix;
     int slot;
-    const FwdEntry *kf;
     hipGraphExec_t exec;
     int64_t exec_len;
     bool has_exec;
@@ -1336,7 +1338,6 @@ extern "C" int fd_batch_create(fd_batch **out, int max_shots, void *workspace, s
     b->ws = (char *)workspace;
     b->stream = (hipStream_t)stream;
     b->slot = 0;
-    b->kf = nullptr;
     b->has_exec = false;
     b->exec_len = 0;
     b->noalloc = false;
@@ -1409,7 +1410,6 @@ extern "C" int fd_batch_create_noalloc(fd_batch **out, int max_shots, void *stre
     b->h_prefix.clear();
     b->groups.clear();
     b->slot = 0;
-    b->kf = nullptr;
     b->has_exec = false;
     b->exec_len = 0;
     b->noalloc = true;
@@ -1455,43 +1455,117 @@ static double group_bytes(fd_ctx *const *ctxs, int m0, int m1)
 // Members whose fields fit the last-level cache are stepped in groups that fit it together,
 // each group all the steps of a call before the next one, so that a step finds the fields of
 // the step before in the cache; a run of such members is split evenly.  Members that do not
-// fit share their launches, which fill the chip without gaps.  Measured, one launch for all
+// fit share their launches, which fill the chip without gaps, and take along runs of small
+// ones, which cost less there than in launches of their own.  Measured, one launch for all
 // -> groups, us per step: eleven cubes of 64..152 points (201 MB) 69 -> 62, sixteen of 100
-// 78 -> 72, twelve of 64..152 71.6 -> 65.2, 24 of 128 186 -> 165, four of 256 216 -> 188,
-// eight of 128 (201 MB, whole lines in every row) 55.5 -> 56.9.  A limit of 100 MB costs the
-// groups more in idle places (six cubes of 192: 189 against 126 us).
-constexpr double kGroupBytes = 165.0 * (1 << 20);
+// 78 -> 72, 24 of 128 186 -> 165, four of 256 216 -> 188, eight of 128 (201 MB, whole lines
+// in every row) 55.5 -> 56.9 (since the descriptor's pointers are known to be global, now
+// 58, 61, 148, 159 and 53.6).  A limit of 100 MB costs the groups more in idle places (six
+// cubes of 192: 189 against 126 us).
+constexpr double kGroupBytes = 165.0 * (1 << 20), kTakenAlongBytes = 48.0 * (1 << 20);
 
 static std::vector<BatchGroup> batch_groups(fd_ctx *const *ctxs, int nctx)
 {
     auto fits = [&](int m) { return cache_keeps(group_bytes(ctxs, m, m + 1)); };
+    bool large = false;
+    for (int m = 0; m < nctx; ++m) large = large || !fits(m);
     std::vector<BatchGroup> groups;
     for (int m = 0, end = 0; m < nctx; m = end) {
         while (end < nctx && fits(end) == fits(m)) ++end;  // a run of members of one kind
-        if (!fits(m)) {
-            groups.push_back(BatchGroup{m, end, false});
+        const double total = group_bytes(ctxs, m, end), parts = std::ceil(total / kGroupBytes);
+        if (!fits(m) || (large && total <= kTakenAlongBytes)) {
+            if (!groups.empty() && !groups.back().split)
+                groups.back().m1 = end;
+            else
+                groups.push_back(BatchGroup{m, end, false, false, nullptr, 1});
             continue;
         }
-        const double total = group_bytes(ctxs, m, end), parts = std::ceil(total / kGroupBytes);
         int first = m;
         for (int k = 1; first < end; ++k) {
-            BatchGroup g{first, first + 1, false};
+            BatchGroup g{first, first + 1, true, false, nullptr, 1};
             while (g.m1 < end && group_bytes(ctxs, m, g.m1) + 0.5 * group_bytes(ctxs, g.m1, g.m1 + 1) < total * k / parts)
                 ++g.m1;
-            g.cached = cache_keeps(group_bytes(ctxs, g.m0, g.m1));
             groups.push_back(g);
             first = g.m1;
         }
     }
+    for (BatchGroup &g : groups) g.cached = cache_keeps(group_bytes(ctxs, g.m0, g.m1));
     return groups;
+}
+
+// The tile of a group's launches and its members' planes per chunk: the candidate that is
+// cheapest for all members together, whatever tiles their contexts chose for themselves (the
+// arithmetic, and so every result, is the same whatever the tile).
+//
+// The members are re-chunked for the group as a whole, too: the other shots supply
+// parallelism, so each shot can march longer z chunks (fewer prologue re-reads) than it
+// would alone.  For a target length Z every member takes c = ceil(nz / Z) chunks of
+// equal length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
+// ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
+// targets that are some member's exact chunk length.  A FINE tile's chunks in the last-level
+// cache are short instead (fine_zch).
+static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g)
+{
+    const int r = ctxs[g.m0]->r, cus = device_cus();
+    int count = 0;
+    const FwdEntry *tab = fwd_table(ctxs[g.m0]->dtype, r, (int)ctxs[g.m0]->g.ndim, &count);
+    std::vector<int64_t> cand;
+    for (int i = g.m0; i < g.m1; ++i) {
+        const int64_t nz = ctxs[i]->L.knz;
+        for (int64_t c = 1; c <= std::max<int64_t>(1, nz); ++c) cand.push_back((nz + c - 1) / c);
+    }
+    std::sort(cand.begin(), cand.end());
+    cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+    double kbest = 0;
+    for (int k = 0; k < count; ++k) {
+        if (tab[k].role != FWD_AUTO && tab[k].role != FWD_FINE) continue;
+        const int slots = resident_slots(tab[k].kernel, tab[k].nt);
+        double best = 1e300;
+        int64_t z = cand.back(), bwg = 0, bplanes = 0;
+        auto lay = [&](int64_t Z, int64_t *planes) {
+            int64_t nwg = 0;
+            for (int i = g.m0; i < g.m1; ++i) {
+                const Layout &L = ctxs[i]->L;
+                const int64_t cm = (L.knz + Z - 1) / Z, zm = (L.knz + cm - 1) / cm;
+                nwg += ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by) * cm;
+                *planes = std::max<int64_t>(*planes, zm);
+            }
+            return nwg;
+        };
+        const bool cached = tab[k].cached_zch && g.cached;
+        if (cached) {
+            int64_t any = 0;
+            z = fine_zch([&](int64_t Z) { return lay(Z, &any); }, cand.back(), tab[k].nt, tab[k].cached_zch, cus);
+            bwg = lay(z, &bplanes);
+        }
+        for (int64_t Z : cand) {
+            if (cached) break;
+            int64_t planes = 0;
+            const int64_t nwg = lay(Z, &planes);
+            const double cost = (double)((nwg + slots - 1) / slots) * (double)(planes + 2 * r);
+            if (cost < best - 1e-9) {
+                best = cost;
+                z = Z;
+                bwg = nwg;
+                bplanes = planes;
+            }
+        }
+        if (g.kf && tab[k].role == FWD_FINE && bplanes >= kFineZch) continue;
+        const double c = cached ? cached_tile_cost(tab[k], bwg, bplanes, r, cus)
+                                : tile_cost(tab[k], bwg, bplanes, r, cus);
+        if (!g.kf || c < kbest) {
+            g.kf = &tab[k];
+            kbest = c;
+            g.zch = z;
+        }
+    }
 }
 
 // Validate a member set and build its shot table: descriptors with both step-counter
 // slots at the member's step, the member's target and the batch's z chunking, plus the
 // workgroup prefix.
 static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, const char *who,
-                       std::vector<ShotDesc> &desc, std::vector<int32_t> &prefix, std::vector<BatchGroup> &groups,
-                       const FwdEntry **kf_out)
+                       std::vector<ShotDesc> &desc, std::vector<int32_t> &prefix, std::vector<BatchGroup> &groups)
 {
     for (int i = 0; i < nctx; ++i) {
         fd_ctx *c = ctxs[i];
@@ -1506,104 +1580,28 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
         for (int j = 0; j < i; ++j)
             if (ctxs[j] == c) return fail(FD_E_INVAL, "%s: member %d appears twice", who, i);
     }
-    // One launch runs one kernel, whatever tiles the members' contexts chose for themselves:
-    // the candidate that is cheapest for all members together (the arithmetic, and so every
-    // result, is the same whatever the tile).
-    //
-    // The members are re-chunked for the batch as a whole, too: the other shots supply
-    // parallelism, so each shot can march longer z chunks (fewer prologue re-reads) than it
-    // would alone.  For a target length Z every member takes c = ceil(nz / Z) chunks of
-    // equal length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
-    // ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
-    // targets that are some member's exact chunk length.  The largest group of members decides
-    // for all.  A FINE tile's chunks in the
-    // last-level cache are short instead (fine_zch).
-    const FwdEntry *kf = nullptr;
-    int64_t zt = 1;
     groups = batch_groups(ctxs, nctx);
-    if (nctx > 0) {
-        const int r = ctxs[0]->r, cus = device_cus();
-        BatchGroup top = groups[0];  // the largest group decides
-        for (const BatchGroup &g : groups)
-            if (group_bytes(ctxs, g.m0, g.m1) > group_bytes(ctxs, top.m0, top.m1)) top = g;
-        int count = 0;
-        const FwdEntry *tab = fwd_table(ctxs[0]->dtype, r, (int)ctxs[0]->g.ndim, &count);
-        std::vector<int64_t> cand;
-        for (int i = top.m0; i < top.m1; ++i) {
-            const int64_t nz = ctxs[i]->L.knz;
-            for (int64_t c = 1; c <= std::max<int64_t>(1, nz); ++c) cand.push_back((nz + c - 1) / c);
-        }
-        std::sort(cand.begin(), cand.end());
-        cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
-        double kbest = 0;
-        for (int k = 0; k < count; ++k) {
-            if (tab[k].role != FWD_AUTO && tab[k].role != FWD_FINE) continue;
-            const int slots = resident_slots(tab[k].kernel, tab[k].nt);
-            double best = 1e300;
-            int64_t z = cand.back(), bwg = 0, bplanes = 0;
-            auto lay = [&](int64_t Z, int64_t *planes) {
-                int64_t nwg = 0;
-                for (int i = top.m0; i < top.m1; ++i) {
-                    const Layout &L = ctxs[i]->L;
-                    const int64_t cm = (L.knz + Z - 1) / Z, zm = (L.knz + cm - 1) / cm;
-                    nwg += ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by) * cm;
-                    *planes = std::max<int64_t>(*planes, zm);
-                }
-                return nwg;
-            };
-            const bool cached = tab[k].cached_zch && top.cached;
-            if (cached) {
-                int64_t any = 0;
-                z = fine_zch([&](int64_t Z) { return lay(Z, &any); }, cand.back(), tab[k].nt, tab[k].cached_zch, cus);
-                bwg = lay(z, &bplanes);
-            }
-            for (int64_t Z : cand) {
-                if (cached) break;
-                int64_t planes = 0;
-                const int64_t nwg = lay(Z, &planes);
-                const double cost = (double)((nwg + slots - 1) / slots) * (double)(planes + 2 * r);
-                if (cost < best - 1e-9) {
-                    best = cost;
-                    z = Z;
-                    bwg = nwg;
-                    bplanes = planes;
-                }
-            }
-            if (kf && tab[k].role == FWD_FINE && bplanes >= kFineZch) continue;
-            const double c = cached ? cached_tile_cost(tab[k], bwg, bplanes, r, cus)
-                                    : tile_cost(tab[k], bwg, bplanes, r, cus);
-            if (!kf || c < kbest) {
-                kf = &tab[k];
-                kbest = c;
-                zt = z;
-            }
-        }
-    }
-    std::vector<int64_t> btx((size_t)nctx), bty((size_t)nctx), zchm((size_t)nctx, 1);
-    for (int i = 0; i < nctx; ++i) {
-        const int64_t nz = ctxs[i]->L.knz, cm = (nz + zt - 1) / zt;
-        btx[(size_t)i] = (ctxs[i]->L.knx + kf->bx - 1) / kf->bx;
-        bty[(size_t)i] = (ctxs[i]->L.kny + kf->by - 1) / kf->by;
-        zchm[(size_t)i] = (nz + cm - 1) / cm;
-    }
     desc.resize((size_t)nctx);
     prefix.assign((size_t)nctx + 1, 0);
-    for (int i = 0; i < nctx; ++i) {
-        fd_ctx *c = ctxs[i];
-        ShotDesc d = c->desc;
-        d.ctr[0] = c->step;
-        d.ctr[1] = c->step;
-        d.target = target[i];
-        d.tiles_x = (int32_t)btx[(size_t)i];
-        d.tiles_y = (int32_t)bty[(size_t)i];
-        d.zch = (int32_t)zchm[(size_t)i];
-        d.chunks_z = (int32_t)((c->L.knz + d.zch - 1) / d.zch);
-        desc[(size_t)i] = d;
-        const int64_t next = (int64_t)prefix[(size_t)i] + btx[(size_t)i] * bty[(size_t)i] * d.chunks_z;
-        if (next > INT32_MAX) return fail(FD_E_RANGE, "%s: too many workgroups in one launch", who);
-        prefix[(size_t)i + 1] = (int32_t)next;
+    for (BatchGroup &g : groups) {
+        choose_group_tile(ctxs, g);
+        for (int i = g.m0; i < g.m1; ++i) {
+            fd_ctx *c = ctxs[i];
+            const int64_t nz = c->L.knz, cm = (nz + g.zch - 1) / g.zch;
+            ShotDesc d = c->desc;
+            d.ctr[0] = c->step;
+            d.ctr[1] = c->step;
+            d.target = target[i];
+            d.tiles_x = (int32_t)((c->L.knx + g.kf->bx - 1) / g.kf->bx);
+            d.tiles_y = (int32_t)((c->L.kny + g.kf->by - 1) / g.kf->by);
+            d.zch = (int32_t)((nz + cm - 1) / cm);
+            d.chunks_z = (int32_t)((nz + d.zch - 1) / d.zch);
+            desc[(size_t)i] = d;
+            const int64_t next = (int64_t)prefix[(size_t)i] + (int64_t)d.tiles_x * d.tiles_y * d.chunks_z;
+            if (next > INT32_MAX) return fail(FD_E_RANGE, "%s: too many workgroups in one launch", who);
+            prefix[(size_t)i + 1] = (int32_t)next;
+        }
     }
-    *kf_out = kf;
     return FD_OK;
 }
 
@@ -1614,8 +1612,7 @@ extern "C" int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *tar
     std::vector<ShotDesc> desc;
     std::vector<int32_t> prefix;
     std::vector<BatchGroup> groups;
-    const FwdEntry *kf = nullptr;
-    int st = batch_table(ctxs, target, nctx, "fd_batch_set", desc, prefix, groups, &kf);
+    int st = batch_table(ctxs, target, nctx, "fd_batch_set", desc, prefix, groups);
     if (st) return st;
     if (b->noalloc)
         for (int i = 0; i < nctx; ++i)
@@ -1640,7 +1637,6 @@ extern "C" int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *tar
     b->h_desc.swap(desc);
     b->groups.swap(groups);
     b->h_prefix.swap(prefix);
-    b->kf = kf;
     b->slot = 0;
     if (nctx > 0) {
         e = hipMemcpyAsync(b->d_desc(), b->h_desc.data(), (size_t)nctx * sizeof(ShotDesc), hipMemcpyHostToDevice, b->stream);
@@ -1671,7 +1667,7 @@ static void batch_launch(const fd_batch *b, int64_t n, hipStream_t st)
         a.cached = g.cached;
         for (int64_t i = 0; i < n; ++i) {
             a.slot = (int32_t)((b->slot + i) & 1);
-            b->kf->launch(a, b->h_prefix[(size_t)g.m1] - a.wg0, st);
+            g.kf->launch(a, b->h_prefix[(size_t)g.m1] - a.wg0, st);
         }
     }
 }

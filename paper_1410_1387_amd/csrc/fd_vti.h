@@ -236,7 +236,7 @@ __device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx,
                     } else if (code != kNoEvent) {
                         const VtiSource si = s.src[~code];
                         if (step < si.nsamp) {
-                            const T sv = static_cast<const T *>(si.wav)[step];
+                            const T sv = as_global(static_cast<const T *>(si.wav))[step];
                             p += T(si.scale_p) * sv;
                             qv += T(si.scale_q) * sv;
                         }
