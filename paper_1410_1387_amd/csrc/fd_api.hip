@@ -251,11 +251,12 @@ constexpr int64_t kFineZch = 32;
 // 200 with 86; 6000^2 FP64 r = 8 194 against 217 with 93).
 constexpr int kLongZch2d = 10;
 
-// A chosen tile whose chunks are this many planes takes its build for 4 waves per SIMD,
-// where it has one: at these sizes it is as fast (256^3 r = 4, 32 planes: 45.7 against
-// 45.4 us) and leaves a second workgroup room on each CU; on longer chunks it is slower
-// (512^3: 394 against 353 us, since both places are then used).
-constexpr int64_t kTwinZchMin = 16, kTwinZchMax = 64;
+// A chosen tile whose chunks are this many planes, in one round of workgroups, takes its
+// build for 4 waves per SIMD, where it has one: at these sizes it is nearly as fast (256^3
+// r = 4, 32 planes: 44.4 against 43.0 us, 320^3, 64 planes: 87 against 85) and leaves a second
+// workgroup room on each CU.  In two rounds or on other chunks it is slower (384^3: 165
+// against 156 us; 512^3: 394 against 353, since both places are then used).
+constexpr int64_t kTwinZchMin = 32, kTwinZchMax = 64;
 
 double interior_bytes(const Layout &L) { return (double)L.knx * (double)L.kny * (double)L.knz * (double)L.esize; }
 
@@ -293,7 +294,7 @@ TileChoice<FwdEntry> choose_tile(const FwdEntry *tab, int count, const Layout &L
             cost = c;
         }
     }
-    if (best.e && best.zch >= kTwinZchMin && best.zch <= kTwinZchMax)
+    if (best.e && best.zch >= kTwinZchMin && best.zch <= kTwinZchMax && best.nwg <= cus)
         for (int i = 0; i < count; ++i)
             if (tab[i].role == FWD_TWIN && tab[i].bx == best.e->bx && tab[i].by == best.e->by) best.e = &tab[i];
     return best;
