@@ -9,8 +9,8 @@
   context is created on a separate setup stream, so admission overlaps with the
   batched work already on the GPU;
 * the admitted shots -- different grid sizes, same radius and dtype -- that make up
-  the stepping window advance together in one stencil launch per time step
-  (``fd_batch_step``): every workgroup finds its (shot, tile) in a prefix table and
+  the stepping window advance together in one stencil launch per time step, or one per
+  group of shots whose fields fit the last-level cache (``fd_batch_step``): every workgroup finds its (shot, tile) in a prefix table and
   every shot keeps its step counter in device memory, so a chunk of an even number
   of steps is a captured HIP graph that is replayed while shots come and go;
 * the window is the oldest admitted shots, taken in admission order until their grid

@@ -102,11 +102,12 @@ def test_sources_and_receivers_vs_oracle(oracle_mod, shape, r, nsrc):
 
 
 @pytest.mark.parametrize("sides", [(64, 64, 64, 64), (40, 96, 20, 130), (33,), (130, 160, 64, 40, 170, 120),
-                                   (50, 272, 60, 280, 281, 30)])
+                                   (50, 272, 60, 280, 281, 30), (170, 160, 130, 280, 40, 150, 165, 30)])
 def test_batch_tile_choice_bitwise(oracle_mod, sides):
     # a batch picks one tile for its members, whatever they step with alone: damped and
     # undamped members, with few and many sources, end with the bits they have alone; in one
-    # launch per step, in groups, and in groups with members too large for the cache between
+    # launch per step, in groups, with members too large for the cache that take small ones
+    # along, and with such members between groups
     import torch
 
     from paper_1410_1387_amd import Propagator
