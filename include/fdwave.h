@@ -33,6 +33,10 @@
  *    the null stream).  Every device operation is enqueued on it
  *    asynchronously.  A context is not thread-safe; different contexts are
  *    independent.  Argument errors are detected before anything is enqueued.
+ *  - Calls that only enqueue (steps, adjoint, state copies) may be captured into a graph.
+ *    A replay repeats them with the step indices and buffers of the captured call, and with
+ *    the sources, receivers and sponge registered when it is replayed.  Captured steps take
+ *    one launch each.
  *  - Asynchronous device faults are reported as FD_E_DEVICE by fd_sync (or the
  *    next call that synchronises); the context is then poisoned and only
  *    fd_destroy remains valid on it.

@@ -364,6 +364,7 @@ struct fd_ctx {
     int64_t max_src, max_rec;
     // kernels
     const FwdEntry *kf;
+    const FwdEntry *kt;  // the same tile with the descriptor in device memory
     const AdjEntry *ka;
     int zch;
     int64_t tiles_x, tiles_y, chunks_z;
@@ -381,6 +382,7 @@ struct fd_ctx {
     std::vector<int32_t> h_evptr;
     std::vector<Event> h_ev;
     std::vector<SourceInfo> h_src;
+    bool listed;  // the event list in device memory holds events
     int64_t step;
     bool poisoned;
     int xcd_remap;
@@ -489,12 +491,14 @@ static int upload_tables(fd_ctx *c)
     d.nrec = c->nrec;
     d.rec_base = c->rec_base;
     d.rec_cap = c->rec_cap;
-    if (any) {
+    if (any || c->listed) {  // an emptied list too: captured launches read it
+        c->listed = any;
         HIP_TRY(c, hipMemcpyAsync(c->ws + L.o_evptr, c->h_evptr.data(), c->h_evptr.size() * sizeof(int32_t),
                                   hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->ws + L.o_ev, c->h_ev.data(), c->h_ev.size() * sizeof(Event),
-                                  hipMemcpyHostToDevice, c->stream));
-        if (!c->h_src.empty())
+        if (any)
+            HIP_TRY(c, hipMemcpyAsync(c->ws + L.o_ev, c->h_ev.data(), c->h_ev.size() * sizeof(Event),
+                                      hipMemcpyHostToDevice, c->stream));
+        if (any && !c->h_src.empty())
             HIP_TRY(c, hipMemcpyAsync(c->ws + L.o_src, c->h_src.data(), c->h_src.size() * sizeof(SourceInfo),
                                       hipMemcpyHostToDevice, c->stream));
     }
@@ -635,7 +639,9 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->ws = (char *)workspace;
     c->max_src = max_sources;
     c->max_rec = max_receivers;
-    c->kf = tile.e;
+    c->kf = c->kt = tile.e;
+    for (int i = 0; i < count && tile.e->role == FWD_TWIN; ++i)
+        if (tab[i].role == FWD_AUTO && tab[i].bx == tile.e->bx && tab[i].by == tile.e->by) c->kt = &tab[i];
     c->ka = adj.e;
     c->tiles_x = tile.tx;
     c->tiles_y = tile.ty;
@@ -655,6 +661,7 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->traces = nullptr;
     c->rec_cap = 0;
     c->rec_base = 0;
+    c->listed = false;
     c->step = 0;
     c->poisoned = false;
     c->xcd_remap = 1;
@@ -850,21 +857,42 @@ extern "C" int fd_ricker(void *out, int64_t nsamp, double dt, double f0, double 
 
 // ------------------------------------------------------------------ stepping
 
-static LaunchArgs direct_args(const fd_ctx *c, int64_t step)
+// Whether calls on this stream are being captured into a graph (the null stream cannot be).
+static bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!stream) return false;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
+// One step of a context.  Captured launches read the shot's descriptor from the workspace:
+// sources, receivers and sponge may be registered anew between replays, and the event list,
+// which is at the same place whatever it holds, has to go with the descriptor it was made for.
+static LaunchArgs single_args(const fd_ctx *c, int64_t step, bool captured)
 {
     LaunchArgs a;
     std::memset(&a, 0, sizeof(a));
     a.one = c->desc;
+    if (captured) a.shots = c->d_desc();
     a.nshots = 1;
     a.step = step;
     a.record = 1;
     a.xcd_remap = c->xcd_remap;
-    a.damped = c->desc.damp != nullptr;
+    a.damped = captured || c->desc.damp != nullptr;
     a.cached = cache_keeps(3.0 * interior_bytes(c->L));
     return a;
 }
 
 static int64_t nwg_of(const fd_ctx *c) { return c->tiles_x * c->tiles_y * c->chunks_z; }
+
+static void launch_single(const fd_ctx *c, const LaunchArgs &a)
+{
+    (a.shots ? c->kt : c->kf)->launch(a, (int)nwg_of(c), c->stream);
+}
 
 static void launch_two_step(fd_ctx *c, const void *cur, const void *prev, void *out1, void *out2, int64_t step)
 {
@@ -938,10 +966,10 @@ static void launch_multi2d(fd_ctx *c, const void *cur, const void *prev, void *o
 }
 
 // Whether this context's steps can share launches: its sources have to travel in the
-// descriptor.
-static bool multi2d_ok(const fd_ctx *c)
+// descriptor, so captured ones, which a replay may find in the event list, step alone.
+static bool multi2d_ok(const fd_ctx *c, bool captured)
 {
-    return c->km && c->bc == FD_BC_ZERO && c->desc.nisrc == (int32_t)c->sources.size();
+    return c->km && !captured && c->bc == FD_BC_ZERO && c->desc.nisrc == (int32_t)c->sources.size();
 }
 
 extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
@@ -953,7 +981,7 @@ extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
     if (ctx->nrec > 0 && ctx->step + nsteps - ctx->rec_base > ctx->rec_cap)
         return fail(FD_E_RANGE, "fd_step: trace capacity %lld exceeded (step %lld + %lld, recording from %lld)",
                     (long long)ctx->rec_cap, (long long)ctx->step, (long long)nsteps, (long long)ctx->rec_base);
-    const int64_t nwg = nwg_of(ctx);
+    const bool captured = capturing(ctx->stream);
     const Geom gm = geom_of(ctx->L);
     int64_t i = 0;
     if (ctx->k2 && ctx->bc == FD_BC_ZERO && !ctx->desc.damp) {
@@ -968,7 +996,7 @@ extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
             ctx->step += 4;
         }
     }
-    if (multi2d_ok(ctx)) {
+    if (multi2d_ok(ctx, captured)) {
         // pairs of launches, into the second pair of fields and back into the first, which
         // then has its usual roles; the last pair shares out what is left
         void *const pair[2] = {ctx->ws + ctx->L.o_pair, ctx->ws + ctx->L.o_pair + ctx->L.field_bytes};
@@ -988,8 +1016,7 @@ extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
         if (ctx->bc == FD_BC_PERIODIC)
             HIP_TRY(ctx, launch_halo_periodic((int)ctx->dtype, gm, ctx->r, ctx->L.ndim == 3 ? ctx->r : 0, ctx->r,
                                               ctx->buf((int)(ctx->step & 1)), ctx->stream));
-        LaunchArgs a = direct_args(ctx, ctx->step);
-        ctx->kf->launch(a, (int)nwg, ctx->stream);
+        launch_single(ctx, single_args(ctx, ctx->step, captured));
         HIP_TRY(ctx, hipGetLastError());
         ctx->step++;
     }
@@ -1074,13 +1101,13 @@ static int step_explicit(fd_ctx *ctx, const void *cur, const void *prev, void *o
     if (!cur || !prev || !out || step < 0) return fail(FD_E_INVAL, "%s: bad arguments", who);
     if (out == cur) return fail(FD_E_INVAL, "%s: out must not alias cur", who);
     if (ctx->bc != FD_BC_ZERO) return fail(FD_E_STATE, "%s: zero boundary only", who);
-    LaunchArgs a = direct_args(ctx, step);
+    LaunchArgs a = single_args(ctx, step, capturing(ctx->stream));
     a.cur = cur;
     a.prev = prev;
     a.out = out;
     a.record = record;
     a.cached = cache_keeps(4.0 * interior_bytes(ctx->L));  // out is a field of its own
-    ctx->kf->launch(a, (int)nwg_of(ctx), ctx->stream);
+    launch_single(ctx, a);
     HIP_TRY(ctx, hipGetLastError());
     return FD_OK;
 }
@@ -1101,12 +1128,13 @@ extern "C" int fd_steps_record(fd_ctx *ctx, void *states, int64_t nsteps)
     if (st) return st;
     if (!states || nsteps < 0) return fail(FD_E_INVAL, "fd_steps_record: bad arguments");
     if (ctx->bc != FD_BC_ZERO) return fail(FD_E_STATE, "fd_steps_record: zero boundary only");
+    const bool captured = capturing(ctx->stream);
     auto field = [&](int64_t i) -> void * { return (char *)states + (size_t)i * ctx->L.field_bytes; };
     for (int64_t k = 0; k < nsteps;) {
         void *const prev = field(k ? k - 1 : nsteps);
         // the first launch reads the field that takes the last state
         const int64_t left = k ? nsteps - k : nsteps - 1;
-        if (multi2d_ok(ctx) && left >= 2) {
+        if (multi2d_ok(ctx, captured) && left >= 2) {
             const int64_t n = std::min<int64_t>(left, ctx->km->kmax);
             launch_multi2d(ctx, field(k), prev, nullptr, nullptr, field(k + 1), k, n, 1);
             HIP_TRY(ctx, hipGetLastError());
@@ -1142,10 +1170,11 @@ extern "C" int fd_adjoint_segment(fd_ctx *ctx, const void *u_ckpt_cur, const voi
     auto slot = [&](int64_t i) -> void * {  // u^{k_lo + i}
         return i == 0 ? const_cast<void *>(u_ckpt_cur) : (char *)ring + (size_t)(i - 1) * fb;
     };
+    const bool captured = capturing(ctx->stream);
     // recompute u^{k_lo+1} .. u^{k_hi-1} from the checkpoint into the ring
     for (int64_t i = 1; i < nk;) {
         const void *prev = (i == 1) ? u_ckpt_prev : slot(i - 2);
-        if (multi2d_ok(ctx) && nk - i >= 2) {
+        if (multi2d_ok(ctx, captured) && nk - i >= 2) {
             const int64_t n = std::min<int64_t>(nk - i, ctx->km->kmax);
             launch_multi2d(ctx, slot(i - 1), prev, nullptr, nullptr, slot(i), k_lo + i - 1, n, 0);
             HIP_TRY(ctx, hipGetLastError());
@@ -1192,7 +1221,8 @@ static int adjoint_steps(fd_ctx *ctx, const Slot &slot, int64_t k_lo, int64_t k_
     const int cached = cache_keeps(6.5 * interior_bytes(ctx->L));
     int64_t k = k_hi;
     const bool blocked = grad_seg && nk > 1;
-    while (ctx->kam && k - k_lo >= 2) {  // pairs of launches through the second pair of fields, as in fd_step
+    const bool captured = capturing(ctx->stream);
+    while (ctx->kam && !captured && k - k_lo >= 2) {  // pairs of launches through the second pair of fields, as in fd_step
         void *const pair[2] = {ctx->ws + ctx->L.o_pair, ctx->ws + ctx->L.o_pair + fb};
         const int64_t two = std::min<int64_t>(k - k_lo, 2 * ctx->kam->kmax), k1 = (two + 1) / 2;
         for (int half = 0; half < 2; ++half) {
@@ -1227,6 +1257,12 @@ static int adjoint_steps(fd_ctx *ctx, const Slot &slot, int64_t k_lo, int64_t k_
         AdjArgs a;
         std::memset(&a, 0, sizeof(a));
         a.one = ctx->desc;
+        if (captured) {  // the receivers of a replay's time, wherever they are: see single_args
+            a.one.ev_ptr = reinterpret_cast<const int32_t *>(ctx->ws + ctx->L.o_evptr);
+            a.one.ev_zlo = 0;
+            a.one.ev_zhi = INT32_MAX;
+            a.nrec = &ctx->d_desc()->nrec;
+        }
         a.mu_cur = m[(k + 1) & 1];
         a.mu_out = m[k & 1];
         a.u_km1 = slot(k - 1 - k_lo);

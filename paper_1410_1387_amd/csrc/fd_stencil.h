@@ -791,17 +791,19 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
     }
 }
 
-// BATCH: the shot of a workgroup is looked up in the batch's table in device memory.
-// Otherwise the one shot's descriptor comes with the launch arguments, where it is read
-// with scalar loads that wait for nothing but the launch itself.
-template <class C, bool BATCH, bool DAMP, int LD>
+// TABLE: the descriptor of a workgroup's shot is read from device memory: a batch's table, or
+// the one a context keeps in its workspace, which a captured launch reads so that a replay
+// finds the sources, receivers and sponge of its own time.  Otherwise the one shot's
+// descriptor comes with the launch arguments, where it is read with scalar loads that wait
+// for nothing but the launch itself.
+template <class C, bool TABLE, bool DAMP, int LD>
 __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
 {
     typedef typename C::type T;
     __shared__ __attribute__((aligned(16))) T lds[C::NB * C::LDS];
     int wg = blockIdx.x;
     if (a.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
-    if constexpr (!BATCH) {
+    if constexpr (!TABLE) {
         const ShotDesc &s = a.one;
         const int64_t step = a.step;
         const T *cur;
@@ -838,11 +840,14 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
             local = wg - a.wg_prefix[lo];
         }
         ShotDesc *sp = a.shots + shot;
-        const int64_t step = sp->ctr[a.slot];
-        const bool active = step < sp->target;
-        if (local == 0 && threadIdx.x == 0) sp->ctr[a.slot ^ 1] = active ? step + 1 : step;
-        if (!active) return;
-        // the descriptor but for its counters is constant while batched steps run
+        int64_t step = a.step;
+        if (step < 0) {  // a batch: the shot counts its own steps
+            step = sp->ctr[a.slot];
+            const bool active = step < sp->target;
+            if (local == 0 && threadIdx.x == 0) sp->ctr[a.slot ^ 1] = active ? step + 1 : step;
+            if (!active) return;
+        }
+        // the descriptor but for its counters is constant while the steps run
         const __attribute__((address_space(4))) int *cp = (const __attribute__((address_space(4))) int *)(uintptr_t)sp;
         int words[sizeof(ShotDesc) / sizeof(int)];
 #pragma unroll
@@ -860,27 +865,33 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         for (int i = 0; i < kInlineSources; ++i) s.isrc[i].wav = as_global(s.isrc[i].wav);
         const T *cur = static_cast<const T *>(step & 1 ? s.buf[1] : s.buf[0]);
         T *out = static_cast<T *>(step & 1 ? s.buf[0] : s.buf[1]);
+        const T *prev = out;
+        if (a.cur) {
+            cur = static_cast<const T *>(as_global(a.cur));
+            prev = static_cast<const T *>(as_global(a.prev));
+            out = static_cast<T *>(as_global(a.out));
+        }
         const int tx = local % s.tiles_x;
         const int t2 = local / s.tiles_x;
         const int ty = t2 % s.tiles_y;
         const int cz = t2 / s.tiles_y;
         if (cz >= s.chunks_z) return;
-        fwd_tile<C, DAMP, LD>(s, cur, out, out, step, a.record != 0, tx, ty, cz, lds);
+        fwd_tile<C, DAMP, LD>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
     }
 }
 
-template <class C, bool BATCH, bool DAMP, int LD>
+template <class C, bool TABLE, bool DAMP, int LD>
 __global__ __launch_bounds__(C::NT) void fwd_kernel(LaunchArgs a)
 {
-    fwd_body<C, BATCH, DAMP, LD>(a);
+    fwd_body<C, TABLE, DAMP, LD>(a);
 }
 
 // the same step built for C::OCC waves per SIMD
-template <class C, bool BATCH, bool DAMP, int LD>
+template <class C, bool TABLE, bool DAMP, int LD>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC > 0 ? C::OCC : 1)))
 void fwd_kernel_occ(LaunchArgs a)
 {
-    fwd_body<C, BATCH, DAMP, LD>(a);
+    fwd_body<C, TABLE, DAMP, LD>(a);
 }
 
 // ------------------------------------------------------------------ adjoint step
@@ -1165,7 +1176,8 @@ __global__ __launch_bounds__(2 * C::NT) void adj_kernel(AdjArgs a)
                        lds + C::NB * C::LDS, mx);
     else
         adj_half<C, 0, LD>(s, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out), nullptr, nullptr, nullptr,
-                       static_cast<const T *>(a.resid) + (a.k - 1) * s.nrec, T(a.resid_amp), g, lds, mx);
+                       static_cast<const T *>(a.resid) + (a.k - 1) * (a.nrec ? *a.nrec : s.nrec), T(a.resid_amp), g,
+                       lds, mx);
 }
 
 // ------------------------------------------------------------------ registry
@@ -1200,31 +1212,31 @@ struct AdjEntry {
     float cost;  // as in FwdEntry
 };
 
-template <class C, bool BATCH, bool DAMP, int LD>
+template <class C, bool TABLE, bool DAMP, int LD>
 constexpr auto fwd_kernel_of()
 {
     if constexpr (C::OCC > 0)
-        return &fwd_kernel_occ<C, BATCH, DAMP, LD>;
+        return &fwd_kernel_occ<C, TABLE, DAMP, LD>;
     else
-        return &fwd_kernel<C, BATCH, DAMP, LD>;
+        return &fwd_kernel<C, TABLE, DAMP, LD>;
 }
 
-// a.step >= 0: one shot, described by a.one; else a batch's table (the tiles the library
-// chooses from, which are the ones a batch can take; the others have no build for it, nor
-// one for fields that stay in the cache).
+// OPTION and TWIN tiles have no build for fields that stay in the cache in theirs; with the
+// descriptor in device memory OPTION ones have the damped build alone (right for undamped
+// shots too) and TWIN ones none, since the tile they stand in for takes the same launch.
 template <class C, int ROLE, bool DAMP>
 void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
 {
     const dim3 grid(nwg), block(C::NT);
     constexpr int KEEP = kPointLoads<ROLE != FWD_OPTION>, ONCE = kPointLoads<false>;
-    if (a.step >= 0) {
+    if (!a.shots) {
         if (a.cached)
             hipLaunchKernelGGL((fwd_kernel_of<C, false, DAMP, KEEP>()), grid, block, 0, st, a);
         else
             hipLaunchKernelGGL((fwd_kernel_of<C, false, DAMP, ONCE>()), grid, block, 0, st, a);
         return;
     }
-    if constexpr (ROLE == FWD_AUTO || ROLE == FWD_FINE) {
+    if constexpr (ROLE != FWD_TWIN && (DAMP || ROLE != FWD_OPTION)) {
         if (a.cached)
             hipLaunchKernelGGL((fwd_kernel_of<C, true, DAMP, KEEP>()), grid, block, 0, st, a);
         else
@@ -1235,7 +1247,7 @@ void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
 template <class C, int ROLE>
 void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
 {
-    if (a.damped)
+    if (a.damped || (ROLE == FWD_OPTION && a.shots))
         launch_fwd_as<C, ROLE, true>(a, nwg, st);
     else
         launch_fwd_as<C, ROLE, false>(a, nwg, st);

@@ -32,8 +32,9 @@ struct InlineSource {
     double scale;
 };
 
-// Everything a stencil launch needs to know about one shot.  Lives in device memory
-// (inside the context workspace); `ctr` is written by the kernels.
+// Everything a stencil launch needs to know about one shot.  A single shot's launch carries
+// it as an argument; batched and captured launches read it from device memory (the batch's
+// table, the context's workspace), where batched ones write `ctr`.
 struct ShotDesc {
     void *buf[2];          // padded wavefields; u^n is buf[n & 1], u^{n+1} overwrites buf[(n+1) & 1]
     const void *c;         // padded coefficient field c = (v dt / h)^2
@@ -55,12 +56,12 @@ struct ShotDesc {
 
 // Per-launch arguments (passed by value).
 struct LaunchArgs {
-    ShotDesc *shots;           // device array of shot descriptors
+    ShotDesc *shots;           // device array of shot descriptors; NULL: one shot, described by `one`
     const int32_t *wg_prefix;  // device, nshots + 1 workgroup offsets (NULL when nshots == 1)
     int32_t nshots, shot0;     // shots of this launch: [shot0, shot0 + nshots)
     int32_t wg0;               // and the workgroup offset of the first one
     int32_t slot;              // counter mode: this launch reads ctr[slot], writes ctr[slot ^ 1]
-    int64_t step;              // >= 0: step index for the single shot; < 0: counter mode
+    int64_t step;              // >= 0: step index for a single shot; < 0: counter mode
     const void *cur;           // explicit-pointer mode (single shot): u^n, u^{n-1}, u^{n+1}
     const void *prev;
     void *out;
@@ -68,7 +69,7 @@ struct LaunchArgs {
     int32_t xcd_remap;         // map consecutive tiles onto one XCD
     int32_t damped;            // some shot of the launch has a sponge
     int32_t cached;            // the fields stay in the last-level cache from step to step
-    ShotDesc one;              // single shot: its descriptor
+    ShotDesc one;
 };
 
 // Adjoint launch arguments (single shot, explicit pointers).
@@ -82,6 +83,7 @@ struct AdjArgs {
     int32_t gmode;         // imaging accumulation, see adj_tile
     int32_t pad1;
     const void *resid;     // [T][nrec]
+    const int64_t *nrec;   // captured launches: where nrec is in device memory; else null
     int64_t k;             // adjoint step index (residual row k - 1)
     double resid_amp;
     int32_t xcd_remap;
