@@ -216,6 +216,17 @@ int resident_slots(const void *kernel, int nt)
     return cus * per_cu;
 }
 
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!stream) return false;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
+}
+
 // Planes per z chunk.  More chunks mean more workgroups but each chunk re-reads 2r planes
 // of u^n (its prologue).  Workgroups run in waves of `slots`; with equal-length
 // workgroups a launch costs about ceil(nwg / slots) x (zch + 2r) plane-times, which is
@@ -857,18 +868,6 @@ extern "C" int fd_ricker(void *out, int64_t nsamp, double dt, double f0, double 
 
 // ------------------------------------------------------------------ stepping
 
-// Whether calls on this stream are being captured into a graph (the null stream cannot be).
-static bool capturing(hipStream_t stream)
-{
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (!stream) return false;
-    if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return status != hipStreamCaptureStatusNone;
-}
-
 // One step of a context.  Captured launches read the shot's descriptor from the workspace:
 // sources, receivers and sponge may be registered anew between replays, and the event list,
 // which is at the same place whatever it holds, has to go with the descriptor it was made for.
@@ -1261,7 +1260,8 @@ static int adjoint_steps(fd_ctx *ctx, const Slot &slot, int64_t k_lo, int64_t k_
             a.one.ev_ptr = reinterpret_cast<const int32_t *>(ctx->ws + ctx->L.o_evptr);
             a.one.ev_zlo = 0;
             a.one.ev_zhi = INT32_MAX;
-            a.nrec = &ctx->d_desc()->nrec;
+            a.one.traces = &ctx->d_desc()->nrec;
+            a.live = 1;
         }
         a.mu_cur = m[(k + 1) & 1];
         a.mu_out = m[k & 1];

@@ -18,6 +18,9 @@ __attribute__((visibility("hidden"))) int device_cus();
 // Workgroups of `kernel` (nt threads) the whole device runs at once.
 __attribute__((visibility("hidden"))) int resident_slots(const void *kernel, int nt);
 
+// Whether calls on `stream` are being captured into a graph (the null stream cannot be).
+__attribute__((visibility("hidden"))) bool capturing(hipStream_t stream);
+
 // Planes per z chunk for tiles_xy tiles over nz planes with a z halo of r planes.
 __attribute__((visibility("hidden"))) int choose_zch(int64_t tiles_xy, int64_t nz, int r, int slots);
 

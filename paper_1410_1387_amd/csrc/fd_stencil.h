@@ -791,19 +791,22 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
     }
 }
 
-// TABLE: the descriptor of a workgroup's shot is read from device memory: a batch's table, or
-// the one a context keeps in its workspace, which a captured launch reads so that a replay
-// finds the sources, receivers and sponge of its own time.  Otherwise the one shot's
-// descriptor comes with the launch arguments, where it is read with scalar loads that wait
-// for nothing but the launch itself.
-template <class C, bool TABLE, bool DAMP, int LD>
+// Where a workgroup finds its shot's descriptor.  FROM_ARGS: in the launch arguments, where it
+// is read with scalar loads that wait for nothing but the launch itself.  FROM_TABLE: in a
+// batch's table in device memory, where each shot also counts its own steps.  FROM_CONTEXT: in
+// the context's workspace, for captured launches, so that a replay finds the sources,
+// receivers and sponge of its own time.  (One build for the last two costs small batches the
+// choice of step and fields, 1-2 %: eight 256^2 FP32 r = 4 4.70 -> 4.80 us per step.)
+enum { FROM_ARGS = 0, FROM_TABLE = 1, FROM_CONTEXT = 2 };
+
+template <class C, int FROM, bool DAMP, int LD>
 __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
 {
     typedef typename C::type T;
     __shared__ __attribute__((aligned(16))) T lds[C::NB * C::LDS];
     int wg = blockIdx.x;
     if (a.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
-    if constexpr (!TABLE) {
+    if constexpr (FROM == FROM_ARGS) {
         const ShotDesc &s = a.one;
         const int64_t step = a.step;
         const T *cur;
@@ -826,7 +829,7 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         fwd_tile<C, DAMP, LD>(s, cur, prev, out, step, a.record != 0, tx, ty, cz, lds);
     } else {
         int shot = a.shot0, local = wg;
-        if (a.nshots > 1) {
+        if (FROM == FROM_TABLE && a.nshots > 1) {
             wg += a.wg0;
             int lo = a.shot0, hi = a.shot0 + a.nshots;
             while (hi - lo > 1) {
@@ -841,7 +844,7 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         }
         ShotDesc *sp = a.shots + shot;
         int64_t step = a.step;
-        if (step < 0) {  // a batch: the shot counts its own steps
+        if constexpr (FROM == FROM_TABLE) {
             step = sp->ctr[a.slot];
             const bool active = step < sp->target;
             if (local == 0 && threadIdx.x == 0) sp->ctr[a.slot ^ 1] = active ? step + 1 : step;
@@ -866,7 +869,7 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
         const T *cur = static_cast<const T *>(step & 1 ? s.buf[1] : s.buf[0]);
         T *out = static_cast<T *>(step & 1 ? s.buf[0] : s.buf[1]);
         const T *prev = out;
-        if (a.cur) {
+        if (FROM == FROM_CONTEXT && a.cur) {
             cur = static_cast<const T *>(as_global(a.cur));
             prev = static_cast<const T *>(as_global(a.prev));
             out = static_cast<T *>(as_global(a.out));
@@ -880,18 +883,18 @@ __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
     }
 }
 
-template <class C, bool TABLE, bool DAMP, int LD>
+template <class C, int FROM, bool DAMP, int LD>
 __global__ __launch_bounds__(C::NT) void fwd_kernel(LaunchArgs a)
 {
-    fwd_body<C, TABLE, DAMP, LD>(a);
+    fwd_body<C, FROM, DAMP, LD>(a);
 }
 
 // the same step built for C::OCC waves per SIMD
-template <class C, bool TABLE, bool DAMP, int LD>
+template <class C, int FROM, bool DAMP, int LD>
 __global__ __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(C::OCC > 0 ? C::OCC : 1)))
 void fwd_kernel_occ(LaunchArgs a)
 {
-    fwd_body<C, TABLE, DAMP, LD>(a);
+    fwd_body<C, FROM, DAMP, LD>(a);
 }
 
 // ------------------------------------------------------------------ adjoint step
@@ -1171,13 +1174,13 @@ __global__ __launch_bounds__(2 * C::NT) void adj_kernel(AdjArgs a)
     const T *g2 = a.gmode == GM_FOLD ? grad : nullptr;
     T *gout = (a.gmode == GM_ACC || a.gmode == GM_FIRST) ? gseg : grad;
     T *const mx = lds + 2 * C::NB * C::LDS;
+    const int64_t nrec = a.live ? *as_global(static_cast<const int64_t *>(s.traces)) : s.nrec;
     if (image)
         adj_half<C, 1, LD>(s, static_cast<const T *>(a.u_km1), nullptr, g1, g2, gout, nullptr, T(0), g,
                        lds + C::NB * C::LDS, mx);
     else
         adj_half<C, 0, LD>(s, static_cast<const T *>(a.mu_cur), static_cast<T *>(a.mu_out), nullptr, nullptr, nullptr,
-                       static_cast<const T *>(a.resid) + (a.k - 1) * (a.nrec ? *a.nrec : s.nrec), T(a.resid_amp), g,
-                       lds, mx);
+                       static_cast<const T *>(a.resid) + (a.k - 1) * nrec, T(a.resid_amp), g, lds, mx);
 }
 
 // ------------------------------------------------------------------ registry
@@ -1212,18 +1215,18 @@ struct AdjEntry {
     float cost;  // as in FwdEntry
 };
 
-template <class C, bool TABLE, bool DAMP, int LD>
+template <class C, int FROM, bool DAMP, int LD>
 constexpr auto fwd_kernel_of()
 {
     if constexpr (C::OCC > 0)
-        return &fwd_kernel_occ<C, TABLE, DAMP, LD>;
+        return &fwd_kernel_occ<C, FROM, DAMP, LD>;
     else
-        return &fwd_kernel<C, TABLE, DAMP, LD>;
+        return &fwd_kernel<C, FROM, DAMP, LD>;
 }
 
-// OPTION and TWIN tiles have no build for fields that stay in the cache in theirs; with the
-// descriptor in device memory OPTION ones have the damped build alone (right for undamped
-// shots too) and TWIN ones none, since the tile they stand in for takes the same launch.
+// A batch takes the tiles the library chooses from.  OPTION tiles have no build for fields that
+// stay in the cache; captured launches have the damped, nontemporal one alone, which is right
+// for every shot, and none of a TWIN tile, since the one it stands in for takes the same launch.
 template <class C, int ROLE, bool DAMP>
 void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
 {
@@ -1231,23 +1234,28 @@ void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
     constexpr int KEEP = kPointLoads<ROLE != FWD_OPTION>, ONCE = kPointLoads<false>;
     if (!a.shots) {
         if (a.cached)
-            hipLaunchKernelGGL((fwd_kernel_of<C, false, DAMP, KEEP>()), grid, block, 0, st, a);
+            hipLaunchKernelGGL((fwd_kernel_of<C, FROM_ARGS, DAMP, KEEP>()), grid, block, 0, st, a);
         else
-            hipLaunchKernelGGL((fwd_kernel_of<C, false, DAMP, ONCE>()), grid, block, 0, st, a);
+            hipLaunchKernelGGL((fwd_kernel_of<C, FROM_ARGS, DAMP, ONCE>()), grid, block, 0, st, a);
         return;
     }
-    if constexpr (ROLE != FWD_TWIN && (DAMP || ROLE != FWD_OPTION)) {
+    if (a.step >= 0) {
+        if constexpr (DAMP && ROLE != FWD_TWIN)
+            hipLaunchKernelGGL((fwd_kernel_of<C, FROM_CONTEXT, DAMP, ONCE>()), grid, block, 0, st, a);
+        return;
+    }
+    if constexpr (ROLE == FWD_AUTO || ROLE == FWD_FINE) {
         if (a.cached)
-            hipLaunchKernelGGL((fwd_kernel_of<C, true, DAMP, KEEP>()), grid, block, 0, st, a);
+            hipLaunchKernelGGL((fwd_kernel_of<C, FROM_TABLE, DAMP, KEEP>()), grid, block, 0, st, a);
         else
-            hipLaunchKernelGGL((fwd_kernel_of<C, true, DAMP, ONCE>()), grid, block, 0, st, a);
+            hipLaunchKernelGGL((fwd_kernel_of<C, FROM_TABLE, DAMP, ONCE>()), grid, block, 0, st, a);
     }
 }
 
 template <class C, int ROLE>
 void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
 {
-    if (a.damped || (ROLE == FWD_OPTION && a.shots))
+    if (a.damped)
         launch_fwd_as<C, ROLE, true>(a, nwg, st);
     else
         launch_fwd_as<C, ROLE, false>(a, nwg, st);
@@ -1267,7 +1275,7 @@ template <class C, int ROLE>
 FwdEntry fwd_entry(const char *name, float cost, float cached_cost = 0, int cached_zch = 0)
 {
     return FwdEntry{name, C::BX, C::BY, C::NT, &launch_fwd<C, ROLE>,
-                    reinterpret_cast<const void *>(fwd_kernel_of<C, false, false, kNontemporal>()), ROLE, cost, cached_cost,
+                    reinterpret_cast<const void *>(fwd_kernel_of<C, FROM_ARGS, false, kNontemporal>()), ROLE, cost, cached_cost,
                     cached_zch};
 }
 

@@ -81,9 +81,8 @@ struct AdjArgs {
     void *grad;            // accumulator g (padded)
     void *gseg;            // segment partial sum of the imaging term (padded), or null
     int32_t gmode;         // imaging accumulation, see adj_tile
-    int32_t pad1;
+    int32_t live;          // captured launches: one.traces, which the adjoint leaves alone, is where nrec is
     const void *resid;     // [T][nrec]
-    const int64_t *nrec;   // captured launches: where nrec is in device memory; else null
     int64_t k;             // adjoint step index (residual row k - 1)
     double resid_amp;
     int32_t xcd_remap;
