@@ -105,7 +105,8 @@ struct VtiInlineSource {  // as InlineSource
     VtiSource src;
 };
 
-// Everything one VTI launch reads (passed by value as the kernel argument).
+// Everything one VTI launch reads (passed by value as the kernel argument; captured launches
+// read the copy in the context's workspace).
 struct VtiDesc {
     void *pbuf[2];         // padded p fields: p^n is pbuf[n & 1], p^{n+1} overwrites pbuf[(n+1) & 1]
     void *qbuf[2];         // the same for q

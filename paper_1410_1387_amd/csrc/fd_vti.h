@@ -65,15 +65,16 @@ struct VtiCfg {
     static_assert(256 % BX == 0 && 64 % BY == 0, "tile must divide the layout alignment");
 };
 
+// cb: which of the two buffers of each field holds level n
 template <class C, int LD>
-__device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int tx, int ty, int cz,
+__device__ __forceinline__ void vti_tile(const VtiDesc &s, int64_t step, int cb, int tx, int ty, int cz,
                                          typename C::type *lds)
 {
     typedef typename C::type T;
     constexpr int RXY = C::RXY, RZ = C::RZ, VEC = C::VEC, HPT = C::HPT, NWZ = C::NWZ;
     constexpr int P = 2 * RZ + 2;  // q planes z-RZ .. z+RZ and the slot receiving z+RZ+1
     constexpr StencilWeights<RXY> W{};
-    const int cb = (int)(step & 1), nb = cb ^ 1;
+    const int nb = cb ^ 1;
     const T *__restrict__ pcur = static_cast<const T *>(s.pbuf[cb]);
     const T *__restrict__ qcur = static_cast<const T *>(s.qbuf[cb]);
     const T *pprev = static_cast<const T *>(s.pbuf[nb]);  // read point-wise, then overwritten
@@ -279,7 +280,45 @@ __global__ __launch_bounds__(C::NT) void vti_kernel(VtiDesc s, int64_t step)
     const int ty = t2 % s.tiles_y;
     const int cz = t2 / s.tiles_y;
     if (cz >= s.chunks_z) return;
-    vti_tile<C, LD>(s, step, tx, ty, cz, lds);
+    vti_tile<C, LD>(s, step, (int)(step & 1), tx, ty, cz, lds);
+}
+
+// The same for captured launches: the descriptor is read from the context's workspace, so that
+// a replay finds the sources and receivers of its own time (a build of its own, because
+// choosing in the launch, or a longer argument, costs small grids 2-9 %).
+template <class C>
+__global__ __launch_bounds__(C::NT) void vti_kernel_live(const VtiDesc *live, int64_t step)
+{
+    typedef typename C::type T;
+    __shared__ __attribute__((aligned(16))) T lds[2 * C::LDS];
+    const auto *words = (const __attribute__((address_space(4))) int *)(uintptr_t)live;
+    int copy[sizeof(VtiDesc) / sizeof(int)];
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(VtiDesc) / sizeof(int)); ++i) copy[i] = words[i];
+    VtiDesc s = __builtin_bit_cast(VtiDesc, copy);
+    s.wz = as_global(s.wz);
+    s.ev_ptr = as_global(s.ev_ptr);
+    s.ev = as_global(s.ev);
+    s.src = as_global(s.src);
+    s.traces_p = as_global(s.traces_p);
+    s.traces_q = as_global(s.traces_q);
+#pragma unroll
+    for (int i = 0; i < kInlineSources; ++i) s.isrc[i].src.wav = as_global(s.isrc[i].src.wav);
+    // level n first: an index by parity would keep the copy in scratch memory
+    void *const p0 = s.pbuf[0], *const q0 = s.qbuf[0];
+    const bool odd = step & 1;
+    s.pbuf[0] = odd ? s.pbuf[1] : p0;
+    s.pbuf[1] = odd ? p0 : s.pbuf[1];
+    s.qbuf[0] = odd ? s.qbuf[1] : q0;
+    s.qbuf[1] = odd ? q0 : s.qbuf[1];
+    int wg = blockIdx.x;
+    if (s.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
+    const int tx = wg % s.tiles_x;
+    const int t2 = wg / s.tiles_x;
+    const int ty = t2 % s.tiles_y;
+    const int cz = t2 / s.tiles_y;
+    if (cz >= s.chunks_z) return;
+    vti_tile<C, kNontemporal>(s, step, 0, tx, ty, cz, lds);
 }
 
 // Roles: reached with fd_vti_set_tuning alone, or one the library chooses from by itself.
@@ -288,17 +327,20 @@ enum { VTI_OPTION = 0, VTI_AUTO = 1 };
 struct VtiEntry {
     const char *name;
     int rxy, rz, bx, by, nt;
-    void (*launch)(const VtiDesc &, int64_t step, int nwg, hipStream_t);
+    // live: null, or the descriptor in device memory (captured launches)
+    void (*launch)(const VtiDesc &, const VtiDesc *live, int64_t step, int nwg, hipStream_t);
     const void *kernel;
     int role;
     float cost;  // as in FwdEntry
 };
 
 template <class C, int ROLE>
-void launch_vti(const VtiDesc &d, int64_t step, int nwg, hipStream_t st)
+void launch_vti(const VtiDesc &d, const VtiDesc *live, int64_t step, int nwg, hipStream_t st)
 {
     constexpr int KEEP = kPointLoads<ROLE != VTI_OPTION>, ONCE = kPointLoads<false>;
-    if (d.cached)
+    if (live)
+        hipLaunchKernelGGL((vti_kernel_live<C>), dim3(nwg), dim3(C::NT), 0, st, live, step);
+    else if (d.cached)
         hipLaunchKernelGGL((vti_kernel<C, KEEP>), dim3(nwg), dim3(C::NT), 0, st, d, step);
     else
         hipLaunchKernelGGL((vti_kernel<C, ONCE>), dim3(nwg), dim3(C::NT), 0, st, d, step);

@@ -36,6 +36,8 @@ namespace {
 
 constexpr int64_t kRowAlignBytes = 128;  // byte offset of each row's interior
 constexpr int kMaxRz = 8;
+constexpr size_t kPartialBytes = 3 * kPrepBlocks * sizeof(double);
+static_assert(sizeof(VtiDesc) <= kPartialBytes, "they share the place");
 
 inline int64_t align_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
@@ -90,7 +92,7 @@ bool make_vti_layout(const fd_grid *g, int rxy, int rz, fd_dtype dt, int64_t max
     L->o_wz = o;
     o += align_up(L->nz * (2 * rz + 1) * (int64_t)L->esize, 256);
     L->o_partial = o;
-    o += align_up(3 * kPrepBlocks * sizeof(double), 256);
+    o += align_up(kPartialBytes, 256);
     L->o_out = o;
     o += 256;
     L->o_evptr = o;
@@ -225,6 +227,8 @@ struct fd_vti_ctx {
     bool poisoned;
 
     void *field(int f) const { return ws + L.o_field[f]; }
+    // the descriptor in device memory, where fd_vti_create's reductions were
+    VtiDesc *live() const { return reinterpret_cast<VtiDesc *>(ws + L.o_partial); }
     Geom geom() const
     {
         Geom gm;
@@ -312,6 +316,7 @@ static int upload_vti_tables(fd_vti_ctx *c)
             HIP_TRY(c, hipMemcpyAsync(c->ws + L.o_src, c->h_src.data(), c->h_src.size() * sizeof(VtiSource),
                                       hipMemcpyHostToDevice, c->stream));
     }
+    HIP_TRY(c, hipMemcpyAsync(c->live(), &d, sizeof(d), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return FD_OK;
 }
@@ -597,8 +602,9 @@ extern "C" int fd_vti_step(fd_vti_ctx *ctx, int64_t nsteps)
     if (ctx->nrec > 0 && ctx->step + nsteps - ctx->rec_base > ctx->rec_cap)
         return fail(FD_E_RANGE, "fd_vti_step: trace capacity %lld exceeded", (long long)ctx->rec_cap);
     const int nwg = (int)(ctx->tiles_x * ctx->tiles_y * ctx->chunks_z);
+    const VtiDesc *live = capturing(ctx->stream) ? ctx->live() : nullptr;
     for (int64_t i = 0; i < nsteps; ++i) {
-        ctx->kv->launch(ctx->desc, ctx->step, nwg, ctx->stream);
+        ctx->kv->launch(ctx->desc, live, ctx->step, nwg, ctx->stream);
         HIP_TRY(ctx, hipGetLastError());
         ctx->step++;
     }
