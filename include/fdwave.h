@@ -259,7 +259,7 @@ int fd_steps_record(fd_ctx *ctx, void *states, int64_t nsteps);
  *   u_ckpt_cur, u_ckpt_prev  device padded u^{k_lo}, u^{k_lo - 1} (a forward checkpoint)
  *   ring      device, (k_hi - k_lo - 1) padded fields; filled with u^{k_lo+1} ..
  *             u^{k_hi-1} by recomputation from the checkpoint (may be NULL if
- *             k_hi - k_lo == 1)
+ *             k_hi - k_lo == 1); u_ckpt_prev may lie in it
  *   mu        device, 2 padded fields; mu^k lives in mu[k & 1]; both zero before the
  *             first (highest) segment
  *   resid     device [T][nrec] of dtype, rows indexed by step n (receivers as given to

@@ -1170,10 +1170,17 @@ extern "C" int fd_adjoint_segment(fd_ctx *ctx, const void *u_ckpt_cur, const voi
         return i == 0 ? const_cast<void *>(u_ckpt_cur) : (char *)ring + (size_t)(i - 1) * fb;
     };
     const bool captured = capturing(ctx->stream);
+    // A single step may write over u^{k_lo-1}, which it reads point by point; a launch of several
+    // reads the checkpoint's fields around each point while it fills the ring.
+    auto in_ring = [&](const void *f) {
+        const char *const p = static_cast<const char *>(f), *const r0 = static_cast<const char *>(ring);
+        return p + fb > r0 && p < r0 + (size_t)(nk - 1) * fb;
+    };
+    const bool shared = multi2d_ok(ctx, captured) && !in_ring(u_ckpt_cur) && !in_ring(u_ckpt_prev);
     // recompute u^{k_lo+1} .. u^{k_hi-1} from the checkpoint into the ring
     for (int64_t i = 1; i < nk;) {
         const void *prev = (i == 1) ? u_ckpt_prev : slot(i - 2);
-        if (multi2d_ok(ctx, captured) && nk - i >= 2) {
+        if (shared && nk - i >= 2) {
             const int64_t n = std::min<int64_t>(nk - i, ctx->km->kmax);
             launch_multi2d(ctx, slot(i - 1), prev, nullptr, nullptr, slot(i), k_lo + i - 1, n, 0);
             HIP_TRY(ctx, hipGetLastError());

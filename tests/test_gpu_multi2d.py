@@ -249,3 +249,38 @@ def test_adjoint_launches_bitwise(oracle_mod, r, dtype):
         for a, b in zip(out[:half], out[half:]):
             assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
         assert float(out[0][1].abs().max()) > 0 or max(shape) == 1
+
+
+@pytest.mark.parametrize("shape,r,dtype", [((300, 420), 4, "f32"), ((90, 130), 2, "f64"), ((20, 24, 30), 2, "f32")])
+def test_ring_over_checkpoint(oracle_mod, shape, r, dtype):
+    # u^{k_lo-1} of the checkpoint may lie in the ring, whose first step then writes over it (or
+    # a later one); u^{k_lo} may not be the ring's first field
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    tdt, steps = torch.float32 if dtype == "f32" else torch.float64, 9
+    v = torch.tensor(workloads.layered_velocity(shape, seed=r), dtype=tdt, device="cuda")
+    p = Propagator(v, r, 10.0, 0.4 * oracle_mod.dt_max(len(shape), r, 10.0, float(v.max())), dtype, max_receivers=1)
+    p.record([tuple(n // 2 for n in shape[::-1])], steps)
+    n = p.new_field().numel()
+    u0 = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(5), dtype=tdt, device="cuda")
+    resid = torch.ones((steps, 1), dtype=tdt, device="cuda")
+    got = []
+    for place in (None, 0, 2, steps - 2):
+        say(f"ring over checkpoint shape={shape} dtype={dtype} place={place}")
+        ring = torch.zeros((steps - 1, n), dtype=tdt, device="cuda")
+        cur, prev = p.new_field(), p.new_field() if place is None else ring[place]
+        p.set_state(u0, 0.5 * u0, 0)
+        p.save_padded(cur, prev)
+        mu, g = torch.zeros(2 * n, dtype=tdt, device="cuda"), p.new_field()
+        F.fd_adjoint_segment(p.ctx, cur, prev, 0, steps, ring, mu, resid, 1.0, g, None)
+        p.sync()
+        got.append((ring, mu, g))
+    for other in got[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(got[0], other))
+    assert float(got[0][2].abs().max()) > 0
+    with pytest.raises(F.FdError) as e:
+        F.fd_adjoint_segment(p.ctx, ring[0], cur, 0, steps, ring, mu, resid, 1.0, g, None)
+    assert e.value.status == F.FD_E_INVAL
