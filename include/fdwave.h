@@ -127,7 +127,9 @@ int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double dt, const 
 
 int fd_destroy(fd_ctx *ctx);
 
-/* Rebind the context to another stream (e.g. after a caller switches streams). */
+/* Rebind the context to another stream (e.g. after a caller switches streams).  Work still
+ * queued on the former stream is not waited for; until fd_sync (or another call that waits)
+ * has run there, 2-D steps on the new one take a launch each (see fd_step). */
 int fd_set_stream(fd_ctx *ctx, void *stream);
 
 /* ----------------------------------------------------------------- source and receivers */

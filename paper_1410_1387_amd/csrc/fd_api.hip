@@ -400,6 +400,8 @@ struct fd_ctx {
     // several steps per launch (2-D)
     const Multi2dEntry *km;
     const Adj2dEntry *kam;
+    hipStream_t pair_stream;  // the stream whose work may still use the second pair of fields
+    bool pair_busy;
     // two-step forward (temporal blocking): two caller-provided padded fields
     void *aux[2];
     const Fwd2Entry *k2;
@@ -410,6 +412,24 @@ struct fd_ctx {
     void *cfield() const { return ws + L.o_c; }
     ShotDesc *d_desc() const { return reinterpret_cast<ShotDesc *>(ws + L.o_desc); }
 };
+
+// The second pair of fields serves one stream at a time: nothing orders the work a context has
+// queued on a stream before fd_set_stream against what follows on the next one, which may use
+// other fields of the caller's.  Until the host has waited for the former stream, steps on
+// another take a launch each.
+static bool take_pair(fd_ctx *c)
+{
+    if (c->pair_busy && c->pair_stream != c->stream) return false;
+    c->pair_busy = true;
+    c->pair_stream = c->stream;
+    return true;
+}
+
+// The host has waited for the context's stream.
+static void stream_idle(fd_ctx *c)
+{
+    if (c->pair_stream == c->stream) c->pair_busy = false;
+}
 
 static int check_ctx(const fd_ctx *c)
 {
@@ -515,6 +535,7 @@ static int upload_tables(fd_ctx *c)
     }
     HIP_TRY(c, hipMemcpyAsync(c->d_desc(), &c->desc, sizeof(ShotDesc), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    stream_idle(c);
     return FD_OK;
 }
 
@@ -672,6 +693,8 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->traces = nullptr;
     c->rec_cap = 0;
     c->rec_base = 0;
+    c->pair_stream = nullptr;
+    c->pair_busy = false;
     c->listed = false;
     c->step = 0;
     c->poisoned = false;
@@ -995,7 +1018,7 @@ extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)
             ctx->step += 4;
         }
     }
-    if (multi2d_ok(ctx, captured)) {
+    if (nsteps - i >= 2 && multi2d_ok(ctx, captured) && take_pair(ctx)) {
         // pairs of launches, into the second pair of fields and back into the first, which
         // then has its usual roles; the last pair shares out what is left
         void *const pair[2] = {ctx->ws + ctx->L.o_pair, ctx->ws + ctx->L.o_pair + ctx->L.field_bytes};
@@ -1028,6 +1051,7 @@ extern "C" int fd_sync(fd_ctx *ctx)
     if (ctx->poisoned) return fail(FD_E_STATE, "context is poisoned");
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     HIP_TRY(ctx, hipGetLastError());
+    stream_idle(ctx);
     return FD_OK;
 }
 
@@ -1043,6 +1067,7 @@ extern "C" int fd_check_finite(fd_ctx *ctx, int *finite)
     double flag[2] = {0.0, 0.0};
     HIP_TRY(ctx, hipMemcpyAsync(flag, out, sizeof(flag), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    stream_idle(ctx);
     *finite = flag[1] == 0.0 ? 1 : 0;
     return FD_OK;
 }
@@ -1228,7 +1253,8 @@ static int adjoint_steps(fd_ctx *ctx, const Slot &slot, int64_t k_lo, int64_t k_
     int64_t k = k_hi;
     const bool blocked = grad_seg && nk > 1;
     const bool captured = capturing(ctx->stream);
-    while (ctx->kam && !captured && k - k_lo >= 2) {  // pairs of launches through the second pair of fields, as in fd_step
+    const bool shared = ctx->kam && !captured && nk >= 2 && take_pair(ctx);
+    while (shared && k - k_lo >= 2) {  // pairs of launches through the second pair of fields, as in fd_step
         void *const pair[2] = {ctx->ws + ctx->L.o_pair, ctx->ws + ctx->L.o_pair + fb};
         const int64_t two = std::min<int64_t>(k - k_lo, 2 * ctx->kam->kmax), k1 = (two + 1) / 2;
         for (int half = 0; half < 2; ++half) {

@@ -284,3 +284,51 @@ def test_ring_over_checkpoint(oracle_mod, shape, r, dtype):
     with pytest.raises(F.FdError) as e:
         F.fd_adjoint_segment(p.ctx, ring[0], cur, 0, steps, ring, mu, resid, 1.0, g, None)
     assert e.value.status == F.FD_E_INVAL
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_two_streams_at_once(oracle_mod, dtype):
+    # a context moved to a second stream while a first adjoint run is queued behind other work:
+    # the two runs, in fields of their own, end as they do one after the other
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    tdt, steps, shape, r = torch.float32 if dtype == "f32" else torch.float64, 24, (300, 420), 4
+    v = torch.tensor(workloads.layered_velocity(shape, seed=r), dtype=tdt, device="cuda")
+    p = Propagator(v, r, 10.0, 0.4 * oracle_mod.dt_max(2, r, 10.0, float(v.max())), dtype, max_receivers=400)
+    rec = np.array([(x, 5) for x in range(400)])
+    p.record(rec, steps)
+    n = p.new_field().numel()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    states = torch.zeros((steps, n), dtype=tdt, device="cuda")
+    for k in range(steps):
+        u = torch.randn(shape, generator=gen, dtype=tdt, device="cuda")
+        p.set_state(u, u, 0)
+        p.save_padded(states[k], p.new_field())
+    resid = torch.randn((2, steps, 400), generator=gen, dtype=tdt, device="cuda")
+    busy = torch.randn((4096, 4096), generator=gen, dtype=torch.float32, device="cuda")
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    p.sync()
+    torch.cuda.synchronize()
+    runs = []
+    for together in (False, True):
+        say(f"two streams {dtype} together={together}")
+        out = [(torch.zeros(2 * n, dtype=tdt, device="cuda"), p.new_field()) for _ in streams]
+        torch.cuda.synchronize()
+        for k, s in enumerate(streams):
+            F.fd_set_stream(p.ctx, F.stream_ptr(s))
+            with torch.cuda.stream(s):
+                if together and k == 0:
+                    for _ in range(4):
+                        busy @ busy
+                F.fd_adjoint_stored(p.ctx, states, 0, steps, out[k][0], resid[k], 1.0, out[k][1], None)
+            if not together:
+                p.sync()
+        torch.cuda.synchronize()
+        p.sync()
+        runs.append(out)
+    for a, b in zip(*runs):
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+        assert float(a[1].abs().max()) > 0
