@@ -102,11 +102,19 @@ double fd_dt_max(int ndim, int r, double h, double vmax);
  * must stay zero.  *bytes written. */
 int fd_field_bytes(const fd_grid *g, int r, fd_dtype dtype, size_t *bytes);
 
-/* Device bytes of the workspace a context needs: two padded wavefields, the padded
- * coefficient field c = (v dt / h)^2, and the source/receiver tables for at most
- * max_sources sources and max_receivers receivers.  *bytes written. */
+/* Device bytes of the workspace a context uses: two padded wavefields, the padded
+ * coefficient field c = (v dt / h)^2, the source/receiver tables for at most
+ * max_sources sources and max_receivers receivers, and the optional part below.
+ * *bytes written. */
 int fd_workspace_bytes(const fd_grid *g, int r, fd_dtype dtype, int64_t max_sources,
                        int64_t max_receivers, size_t *bytes);
+
+/* The part of fd_workspace_bytes that a context can do without: two more padded fields, on
+ * 2-D grids of up to 64 MiB per field whose steps can share launches (fd_step,
+ * fd_adjoint_segment), else 0.  fd_create also takes a workspace smaller by this; every step
+ * is then a launch of its own, as it is anyway in batches, with the periodic boundary and
+ * with a tile set by hand.  *bytes written. */
+int fd_workspace_optional_bytes(const fd_grid *g, int r, fd_dtype dtype, size_t *bytes);
 
 /* ----------------------------------------------------------------- lifecycle */
 
@@ -114,8 +122,9 @@ int fd_workspace_bytes(const fd_grid *g, int r, fd_dtype dtype, int64_t max_sour
  * and velocity).
  *   velocity   device, dense, dtype, >0 m/s; read during the call only (converted to
  *              c = (v dt / h)^2 in the workspace by a device kernel)
- *   workspace  device, >= fd_workspace_bytes(...) bytes, 256-byte aligned; borrowed
- *              until fd_destroy; zeroed here (both wavefields start at zero, step 0)
+ *   workspace  device, >= fd_workspace_bytes(...) bytes (or that less
+ *              fd_workspace_optional_bytes(...)), 256-byte aligned; borrowed until
+ *              fd_destroy; zeroed here (both wavefields start at zero, step 0)
  *   stream     hipStream_t the context enqueues on
  * Errors: FD_E_INVAL (ndim not 2/3, r not in [1, 8], h or dt <= 0, null pointers,
  * non-positive velocity), FD_E_NOMEM (workspace too small), FD_E_UNSTABLE
@@ -176,9 +185,10 @@ int fd_ricker(void *out, int64_t nsamp, double dt, double f0, double t0, fd_dtyp
 
 /* Advance nsteps leapfrog steps (Sec. 1 time scheme), one stencil launch per step, with
  * the sources added and the receivers recorded inside the launch.  nsteps = 0 is a no-op.
- * On 2-D grids of up to 64 MiB per field with the zero boundary, no tile set by
- * fd_set_tuning and at most two sources a launch advances up to eight steps (through two
- * more fields in the workspace); the results are bitwise those of single steps.
+ * On 2-D grids with the zero boundary, the workspace's optional part, no tile set by
+ * fd_set_tuning and at most two sources a launch advances up to eight steps: up to 64 MiB per
+ * field for r <= 4, up to 512 x 512 points or so for r >= 5 (a tile of 32 x 32 points per
+ * compute unit).  The results are bitwise those of single steps.
  * Errors: FD_E_RANGE if recording is on and the trace capacity would be exceeded (checked
  * before anything is enqueued), FD_E_STATE if poisoned. */
 int fd_step(fd_ctx *ctx, int64_t nsteps);
@@ -269,8 +279,9 @@ int fd_steps_record(fd_ctx *ctx, void *states, int64_t nsteps);
  *   grad      device padded field of dtype, accumulated (zero it before the first segment)
  *   grad_seg  device padded field of dtype used as the segment partial sum, or NULL for
  *             plain accumulation into grad (its contents need no initialisation)
- * On 2-D grids of up to 64 MiB per field with no tile set by fd_set_adj_tuning a launch
- * takes several steps, through two more fields in the workspace, with the same results.
+ * On 2-D grids with the workspace's optional part and no tile set by fd_set_adj_tuning a launch
+ * takes several steps, with the same results: up to 64 MiB per field for r <= 4 (FP32 r = 3:
+ * 512 x 512 points or so), and in FP64 up to 256 x 256 points or so for r = 5.
  * Receivers must have been registered with fd_record (the traces buffer is not touched).
  * resid must hold at least k_hi rows. */
 int fd_adjoint_segment(fd_ctx *ctx, const void *u_ckpt_cur, const void *u_ckpt_prev, int64_t k_lo,

@@ -76,12 +76,45 @@ struct Layout {
     size_t field_bytes;      // one padded field, rounded to 256 bytes
     // workspace offsets
     size_t o_desc, o_partial, o_minmax, o_buf0, o_buf1, o_c, o_evptr, o_ev, o_src, o_damp, o_pair, total;
-    bool pair;  // two more fields for launches of several steps (2-D)
+    bool pair;  // two more fields, at the end, for launches of several steps (2-D)
     int64_t ncol;
 };
 
+// The several-steps kernel of a 2-D grid on cus compute units, forward or adjoint, or none.
+// While one round of workgroups covers the grid the time is the chain load, k steps, store, so
+// many steps on small tiles win; beyond that it is the work on the widened tiles, which wants
+// large tiles and few steps (k r around 8), and for r > 4 a tile of any size that fits LDS costs
+// more than the launches it saves (1203 x 800 points, r = 8, FP32: 7.4 us against 6.3 for a
+// single step), so those stay with the single-step kernel.  The tables hold both sides of each
+// line.
+template <class Entry>
+const Entry *choose_multi2d(const Entry *tab, int count, int64_t nx, int64_t nz, int cus)
+{
+    for (int i = 0; i < count; ++i) {
+        const int64_t tiles = ((nx + tab[i].tx - 1) / tab[i].tx) * ((nz + tab[i].tz - 1) / tab[i].tz);
+        if (!tab[i].per_cu || tiles <= (int64_t)tab[i].per_cu * cus) return &tab[i];
+    }
+    return nullptr;
+}
+
+const Multi2dEntry *multi2d_entry_of(fd_dtype dt, int r, int64_t nx, int64_t nz, int cus)
+{
+    int count = 0;
+    const Multi2dEntry *tab = dt == FD_F32 ? multi2d_configs_f32(r, &count) : multi2d_configs_f64(r, &count);
+    return choose_multi2d(tab, count, nx, nz, cus);
+}
+
+const Adj2dEntry *adj2d_entry_of(fd_dtype dt, int r, int64_t nx, int64_t nz, int cus)
+{
+    int count = 0;
+    const Adj2dEntry *tab = dt == FD_F32 ? adj2d_configs_f32(r, &count) : adj2d_configs_f64(r, &count);
+    return choose_multi2d(tab, count, nx, nz, cus);
+}
+
 // 2-D grids of up to this many bytes per field step several times per launch.
 constexpr size_t kMulti2dFieldBytes = (size_t)64 << 20;
+// Compute units of a whole MI355X: with fewer (a partition) there are no more kernels to choose.
+constexpr int kChipCus = 256;
 
 bool make_layout(const fd_grid *g, int r, fd_dtype dt, int64_t max_src, int64_t max_rec, Layout *L)
 {
@@ -131,7 +164,8 @@ bool make_layout(const fd_grid *g, int r, fd_dtype dt, int64_t max_src, int64_t 
     o += align_up(std::max<int64_t>(1, max_src) * (int64_t)sizeof(SourceInfo), 256);
     L->o_damp = o;
     o += align_up((L->knx + L->kny + L->knz) * (int64_t)L->esize, 256);
-    L->pair = L->ndim == 2 && L->field_bytes <= kMulti2dFieldBytes;
+    L->pair = L->ndim == 2 && L->field_bytes <= kMulti2dFieldBytes &&
+              (multi2d_entry_of(dt, r, L->knx, L->knz, kChipCus) || adj2d_entry_of(dt, r, L->knx, L->knz, kChipCus));
     L->o_pair = o;
     if (L->pair) o += 2 * L->field_bytes;
     L->total = o;
@@ -334,22 +368,6 @@ TileChoice<AdjEntry> choose_adj_tile(const AdjEntry *tab, int count, const Layou
         for (int i = 0; i < count; ++i)
             if (tab[i].role == ADJ_ONE_PLANE) best = plan_tile(tab[i], L);
     return best;
-}
-
-// The several-steps kernel of a 2-D grid, forward or adjoint, or none.  While one round of
-// workgroups covers the grid the time is the chain load, k steps, store, so many steps on
-// small tiles win; beyond that it is the work on the widened tiles, which wants large tiles
-// and few steps (k r around 8), and for r > 4 a tile of any size that fits LDS costs more than
-// the launches it saves (1203 x 800 points, r = 8, FP32: 7.4 us against 6.3 for a single
-// step), so those stay with the single-step kernel.  The tables hold both sides of each line.
-template <class Entry>
-const Entry *choose_multi2d(const Entry *tab, int count, const Layout &L)
-{
-    for (int i = 0; L.pair && i < count; ++i) {
-        const int64_t tiles = ((L.knx + tab[i].tx - 1) / tab[i].tx) * ((L.knz + tab[i].tz - 1) / tab[i].tz);
-        if (!tab[i].per_cu || tiles <= (int64_t)tab[i].per_cu * device_cus()) return &tab[i];
-    }
-    return nullptr;
 }
 
 }  // namespace
@@ -582,6 +600,15 @@ extern "C" int fd_workspace_bytes(const fd_grid *g, int r, fd_dtype dtype, int64
     return FD_OK;
 }
 
+extern "C" int fd_workspace_optional_bytes(const fd_grid *g, int r, fd_dtype dtype, size_t *bytes)
+{
+    Layout L;
+    if (!bytes || !make_layout(g, r, dtype, 0, 0, &L))
+        return fail(FD_E_INVAL, "fd_workspace_optional_bytes: bad grid/r/dtype");
+    *bytes = L.total - L.o_pair;
+    return FD_OK;
+}
+
 extern "C" int fd_set_tuning(fd_dtype dtype, int r, int ndim, int config, int zchunk)
 {
     int count = 0;
@@ -627,8 +654,8 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     if (bc != FD_BC_ZERO && bc != FD_BC_PERIODIC) return fail(FD_E_INVAL, "fd_create: bad boundary");
     if (!velocity || !workspace) return fail(FD_E_INVAL, "fd_create: null velocity or workspace");
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return fail(FD_E_INVAL, "fd_create: workspace not 256-byte aligned");
-    if (ws_bytes < L.total)
-        return fail(FD_E_NOMEM, "fd_create: workspace %zu bytes < %zu needed", ws_bytes, L.total);
+    if (ws_bytes < L.o_pair)
+        return fail(FD_E_NOMEM, "fd_create: workspace %zu bytes < %zu needed", ws_bytes, L.o_pair);
     if (bc == FD_BC_PERIODIC) {
         const int64_t ext[3] = {L.knx, L.kny, L.knz};
         for (int a = 0; a < 3; ++a)
@@ -684,11 +711,9 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->adj_zch = adj.zch;
     c->adj_chunks_z = (L.knz + c->adj_zch - 1) / c->adj_zch;
     // a caller's tile is used for every step
-    int mcount = 0, macount = 0;
-    const Multi2dEntry *mtab = dtype == FD_F32 ? multi2d_configs_f32(r, &mcount) : multi2d_configs_f64(r, &mcount);
-    const Adj2dEntry *matab = dtype == FD_F32 ? adj2d_configs_f32(r, &macount) : adj2d_configs_f64(r, &macount);
-    c->km = tuned ? nullptr : choose_multi2d(mtab, mcount, L);
-    c->kam = acfg >= 0 ? nullptr : choose_multi2d(matab, macount, L);
+    const bool pair = L.pair && ws_bytes >= L.total && bc == FD_BC_ZERO;
+    c->km = pair && !tuned ? multi2d_entry_of(dtype, r, L.knx, L.knz, device_cus()) : nullptr;
+    c->kam = pair && acfg < 0 ? adj2d_entry_of(dtype, r, L.knx, L.knz, device_cus()) : nullptr;
     c->nrec = 0;
     c->traces = nullptr;
     c->rec_cap = 0;
@@ -991,7 +1016,7 @@ static void launch_multi2d(fd_ctx *c, const void *cur, const void *prev, void *o
 // descriptor, so captured ones, which a replay may find in the event list, step alone.
 static bool multi2d_ok(const fd_ctx *c, bool captured)
 {
-    return c->km && !captured && c->bc == FD_BC_ZERO && c->desc.nisrc == (int32_t)c->sources.size();
+    return c->km && !captured && c->desc.nisrc == (int32_t)c->sources.size();
 }
 
 extern "C" int fd_step(fd_ctx *ctx, int64_t nsteps)

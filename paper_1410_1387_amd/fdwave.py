@@ -29,7 +29,7 @@ STATUS_NAMES = {
 
 # every symbol include/fdwave.h declares
 EXPORTS = [
-    "fd_weights", "fd_dt_max", "fd_field_bytes", "fd_workspace_bytes", "fd_create", "fd_destroy",
+    "fd_weights", "fd_dt_max", "fd_field_bytes", "fd_workspace_bytes", "fd_workspace_optional_bytes", "fd_create", "fd_destroy",
     "fd_set_stream", "fd_inject", "fd_clear_sources", "fd_set_damping", "fd_record", "fd_ricker", "fd_step", "fd_sync",
     "fd_get_step", "fd_get_state", "fd_set_time_blocking", "fd_set_state", "fd_step_explicit", "fd_step_record",
     "fd_steps_record",
@@ -76,6 +76,7 @@ def lib():
             "fd_dt_max": (D, [ctypes.c_int, ctypes.c_int, D, D]),
             "fd_field_bytes": (ctypes.c_int, [pgrid, ctypes.c_int, ctypes.c_int, ctypes.POINTER(SZ)]),
             "fd_workspace_bytes": (ctypes.c_int, [pgrid, ctypes.c_int, ctypes.c_int, I64, I64, ctypes.POINTER(SZ)]),
+            "fd_workspace_optional_bytes": (ctypes.c_int, [pgrid, ctypes.c_int, ctypes.c_int, ctypes.POINTER(SZ)]),
             "fd_create": (ctypes.c_int, [ctypes.POINTER(P), pgrid, ctypes.c_int, D, D, P, ctypes.c_int,
                                          ctypes.c_int, P, SZ, I64, I64, P]),
             "fd_destroy": (ctypes.c_int, [P]),
@@ -208,6 +209,13 @@ def fd_workspace_bytes(shape, r: int, dtype, max_sources: int, max_receivers: in
     out = ctypes.c_size_t()
     _check(lib().fd_workspace_bytes(ctypes.byref(make_grid(shape)), r, dtype_code(dtype), max_sources,
                                     max_receivers, ctypes.byref(out)), "fd_workspace_bytes")
+    return out.value
+
+
+def fd_workspace_optional_bytes(shape, r: int, dtype) -> int:
+    out = ctypes.c_size_t()
+    _check(lib().fd_workspace_optional_bytes(ctypes.byref(make_grid(shape)), r, dtype_code(dtype), ctypes.byref(out)),
+           "fd_workspace_optional_bytes")
     return out.value
 
 

@@ -41,6 +41,8 @@ class Propagator:
         self._stream = stream
         v = v.to(self.tdtype).contiguous()
         nbytes = F.fd_workspace_bytes(self.shape, r, dtype, max_sources, max_receivers)
+        if bc == "periodic":  # steps alone
+            nbytes -= F.fd_workspace_optional_bytes(self.shape, r, dtype)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         self.field_bytes = F.fd_field_bytes(self.shape, r, dtype)
         self._wavelets = []

@@ -110,11 +110,17 @@ def kernel_of(ctx: int) -> str:
     return F.fd_kernel_config(ctx).split(" tile")[0]
 
 
+def workspace_bytes(shape, nrec: int, r: int, dtype: str, batched: bool = True) -> int:
+    """Workspace of a one-source shot: 2 wavefields, c and tables; stepped by itself it may also
+    use the optional part, which batches do not."""
+    optional = F.fd_workspace_optional_bytes(shape, r, dtype) if batched else 0
+    return F.fd_workspace_bytes(shape, r, dtype, 1, nrec) - optional
+
+
 def shot_footprint(shape, nsteps: int, nrec: int, r: int, dtype: str) -> int:
-    """HBM bytes a shot holds while resident: context workspace (2 wavefields, c, tables),
-    traces and wavelet."""
+    """HBM bytes a shot holds while resident: context workspace, traces and wavelet."""
     es = 4 if dtype == "f32" else 8
-    return F.fd_workspace_bytes(shape, r, dtype, 1, nrec) + (nsteps * nrec + nsteps) * es
+    return workspace_bytes(shape, nrec, r, dtype) + (nsteps * nrec + nsteps) * es
 
 
 def staging_bytes(shape, dtype: str) -> int:
@@ -127,8 +133,8 @@ def staging_bytes(shape, dtype: str) -> int:
 class _ShotFactory:
     """Creates one shot's context and device buffers on a given stream."""
 
-    def __init__(self, r: int, dtype: str, device):
-        self.r, self.dtype, self.device = r, dtype, device
+    def __init__(self, r: int, dtype: str, device, batched: bool = True):
+        self.r, self.dtype, self.device, self.batched = r, dtype, device, batched
         self.tdt = torch.float32 if dtype == "f32" else torch.float64
         self.npdt = np.float32 if dtype == "f32" else np.float64
 
@@ -142,7 +148,7 @@ class _ShotFactory:
             else:
                 v = torch.from_numpy(np.ascontiguousarray(vin, dtype=self.npdt)).to(self.device)
             shape = tuple(v.shape)
-            ws = torch.empty(F.fd_workspace_bytes(shape, self.r, self.dtype, 1, nrec), dtype=torch.uint8,
+            ws = torch.empty(workspace_bytes(shape, nrec, self.r, self.dtype, self.batched), dtype=torch.uint8,
                              device=self.device)
             wav = torch.empty(req.nsteps, dtype=self.tdt, device=self.device)
             traces = torch.zeros((req.nsteps, nrec), dtype=self.tdt, device=self.device)
@@ -435,7 +441,7 @@ def run_sequential(requests: list, r: int = 4, dtype: str = "f32", realtime: boo
     """Serve the requests one at a time in arrival order (one shot on the GPU at once,
     fd_step with one launch per step): the baseline the batched server is compared with."""
     dev = torch.device(device)
-    factory = _ShotFactory(r, dtype, dev)
+    factory = _ShotFactory(r, dtype, dev, batched=False)
     stream = torch.cuda.Stream(device=dev)
     t0 = time.perf_counter()
     now = lambda: time.perf_counter() - t0  # noqa: E731

@@ -207,3 +207,22 @@ def test_c_program_links_and_runs(F, oracle_mod, tmp_path):
     assert int(vals["field_bytes"]) == F.fd_field_bytes((512, 512, 512), 4, "f32")
     assert int(vals["workspace_bytes"]) == F.fd_workspace_bytes((512, 512, 512), 4, "f32", 1, 16384)
     assert vals["bad_radius"] == f"{F.FD_E_INVAL} msg" and vals["bad_grid"] == f"{F.FD_E_INVAL} msg"
+
+
+def test_second_pair_of_fields_is_optional(F):
+    # two more fields on 2-D grids where several steps share a launch, forward or adjoint; none
+    # where no such kernel applies, and none in 3-D
+    from paper_1410_1387_amd.serving import shot_footprint
+
+    for shape, r, dt, pair in [((256, 256), 4, "f64", 1), ((300, 420), 4, "f32", 1), ((801, 1203), 8, "f32", 0),
+                               ((512, 512), 8, "f32", 1), ((800, 1203), 5, "f64", 0), ((801, 1203), 3, "f64", 1),
+                               ((4500, 4300), 4, "f32", 0), ((40, 40, 40), 4, "f32", 0), ((1, 1), 1, "f32", 1)]:
+        fb, opt = F.fd_field_bytes(shape, r, dt), F.fd_workspace_optional_bytes(shape, r, dt)
+        assert opt == 2 * pair * fb, (shape, r, dt)
+        ncol, es = int(np.prod(shape[1:])), 4 if dt == "f32" else 8
+        tables = 20000 + 8 * (ncol + 1) + 8 * 100 + es * sum(shape)  # reductions, columns, events, sponge
+        assert 3 * fb <= F.fd_workspace_bytes(shape, r, dt, 1, 99) - opt <= 3 * fb + tables, (shape, r, dt)
+        # a shot of the server steps in batches, without them
+        assert shot_footprint(shape, 10, 99, r, dt) == F.fd_workspace_bytes(shape, r, dt, 1, 99) - opt + 1000 * es
+    with pytest.raises(F.FdError):
+        F.fd_workspace_optional_bytes((8, 8), 9, "f32")
