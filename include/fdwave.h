@@ -331,11 +331,12 @@ int fd_batch_destroy(fd_batch *b);
 
 /* Replace the member set.  Each context advances until its step reaches target[i] (host
  * array); members keep their state and step.  Members must share r, dtype and ndim
- * (FD_E_INVAL); the batch steps the members of a group with one stencil tile, the library's
- * choice for the group as a whole, whatever tiles the members' contexts use (bitwise the same
- * results).  Invalidates the captured graph.  Work still queued on a member's own stream is completed before any batched launch touches it (the
- * batch stream waits for each member stream); the call also waits on the host for earlier
- * batched work, whose shot table it rewrites. */
+ * (FD_E_INVAL); the batch steps the members of a group with one stencil tile: the one set with
+ * fd_set_tuning, if it is the same for all members of the batch, else the library's choice for
+ * the group as a whole, whatever tiles the members' contexts use (bitwise the same results).
+ * Invalidates the captured graph.  Work still queued on a member's own stream is completed
+ * before any batched launch touches it (the batch stream waits for each member stream); the
+ * call also waits on the host for earlier batched work, whose shot table it rewrites. */
 int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *target, int nctx);
 
 /* Shots a no-allocation batch can hold: the size of its fixed shot table. */
@@ -398,8 +399,8 @@ const char *fd_adjoint_config(const fd_ctx *ctx);
  * planes each workgroup marches in z.  config = -1 restores the library's own choice,
  * which is also what holds before any call: the registered tile whose estimated launch
  * time is lowest for the context's grid (a wide tile on large grids, smaller ones where
- * rows are ragged or the grid is small).  Batches (fd_batch_set) always make their own
- * choice.  Results are bitwise the same whatever the tile. */
+ * rows are ragged or the grid is small).  A batch takes a tile set by hand for all its members
+ * (with chunks of its own).  Results are bitwise the same whatever the tile. */
 int fd_set_tuning(fd_dtype dtype, int r, int ndim, int config, int zchunk);
 
 /* The adjoint kernel's tile shape for contexts created afterwards with this (dtype, r,

@@ -394,6 +394,7 @@ struct fd_ctx {
     // kernels
     const FwdEntry *kf;
     const FwdEntry *kt;  // the same tile with the descriptor in device memory
+    bool tuned;          // the tile was set by hand
     const AdjEntry *ka;
     int zch;
     int64_t tiles_x, tiles_y, chunks_z;
@@ -701,6 +702,7 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     c->kf = c->kt = tile.e;
     for (int i = 0; i < count && tile.e->role == FWD_TWIN; ++i)
         if (tab[i].role == FWD_AUTO && tab[i].bx == tile.e->bx && tab[i].by == tile.e->by) c->kt = &tab[i];
+    c->tuned = tuned;
     c->ka = adj.e;
     c->tiles_x = tile.tx;
     c->tiles_y = tile.ty;
@@ -1588,9 +1590,10 @@ static std::vector<BatchGroup> batch_groups(fd_ctx *const *ctxs, int nctx)
     return groups;
 }
 
-// The tile of a group's launches and its members' planes per chunk: the candidate that is
-// cheapest for all members together, whatever tiles their contexts chose for themselves (the
-// arithmetic, and so every result, is the same whatever the tile).
+// The tile of a group's launches and its members' planes per chunk: the one set by hand for all
+// members of the batch, else the candidate that is cheapest for the group's members together,
+// whatever tiles their contexts chose for themselves (the arithmetic, and so every result, is
+// the same whatever the tile).
 //
 // The members are re-chunked for the group as a whole, too: the other shots supply
 // parallelism, so each shot can march longer z chunks (fewer prologue re-reads) than it
@@ -1599,7 +1602,7 @@ static std::vector<BatchGroup> batch_groups(fd_ctx *const *ctxs, int nctx)
 // ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
 // targets that are some member's exact chunk length.  A FINE tile's chunks in the last-level
 // cache are short instead (fine_zch).
-static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g)
+static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g, const FwdEntry *by_hand)
 {
     const int r = ctxs[g.m0]->r, cus = device_cus();
     int count = 0;
@@ -1613,7 +1616,7 @@ static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g)
     cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
     double kbest = 0;
     for (int k = 0; k < count; ++k) {
-        if (tab[k].role != FWD_AUTO && tab[k].role != FWD_FINE) continue;
+        if (by_hand ? &tab[k] != by_hand : tab[k].role != FWD_AUTO && tab[k].role != FWD_FINE) continue;
         const int slots = resident_slots(tab[k].kernel, tab[k].nt);
         double best = 1e300;
         int64_t z = cand.back(), bwg = 0, bplanes = 0;
@@ -1676,10 +1679,13 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
             if (ctxs[j] == c) return fail(FD_E_INVAL, "%s: member %d appears twice", who, i);
     }
     groups = batch_groups(ctxs, nctx);
+    const FwdEntry *by_hand = nctx > 0 ? ctxs[0]->kt : nullptr;
+    for (int i = 0; i < nctx; ++i)
+        if (!ctxs[i]->tuned || ctxs[i]->kt != by_hand) by_hand = nullptr;
     desc.resize((size_t)nctx);
     prefix.assign((size_t)nctx + 1, 0);
     for (BatchGroup &g : groups) {
-        choose_group_tile(ctxs, g);
+        choose_group_tile(ctxs, g, by_hand);
         for (int i = g.m0; i < g.m1; ++i) {
             fd_ctx *c = ctxs[i];
             const int64_t nz = c->L.knz, cm = (nz + g.zch - 1) / g.zch;

@@ -1224,9 +1224,9 @@ constexpr auto fwd_kernel_of()
         return &fwd_kernel<C, FROM, DAMP, LD>;
 }
 
-// A batch takes the tiles the library chooses from.  OPTION tiles have no build for fields that
-// stay in the cache; captured launches have the damped, nontemporal one alone, which is right
-// for every shot, and none of a TWIN tile, since the one it stands in for takes the same launch.
+// OPTION tiles have no build for fields that stay in the cache, and one for batches; captured
+// launches have one.  Such a single build is the damped, nontemporal one, which is right for
+// every shot.  TWIN tiles have neither: the tile they stand in for takes the same launch.
 template <class C, int ROLE, bool DAMP>
 void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
 {
@@ -1249,13 +1249,15 @@ void launch_fwd_as(const LaunchArgs &a, int nwg, hipStream_t st)
             hipLaunchKernelGGL((fwd_kernel_of<C, FROM_TABLE, DAMP, KEEP>()), grid, block, 0, st, a);
         else
             hipLaunchKernelGGL((fwd_kernel_of<C, FROM_TABLE, DAMP, ONCE>()), grid, block, 0, st, a);
+    } else if constexpr (DAMP && ROLE == FWD_OPTION) {
+        hipLaunchKernelGGL((fwd_kernel_of<C, FROM_TABLE, DAMP, ONCE>()), grid, block, 0, st, a);
     }
 }
 
 template <class C, int ROLE>
 void launch_fwd(const LaunchArgs &a, int nwg, hipStream_t st)
 {
-    if (a.damped)
+    if (a.damped || (ROLE == FWD_OPTION && a.shots))
         launch_fwd_as<C, ROLE, true>(a, nwg, st);
     else
         launch_fwd_as<C, ROLE, false>(a, nwg, st);

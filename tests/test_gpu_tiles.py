@@ -212,3 +212,64 @@ def test_registered_vti_tiles(oracle_mod, rxy, rz, nsrc, dtype, tol):
         cfg += 1
     F.fd_vti_set_tuning(dtype, rxy, rz, 0, 0)
     assert cfg >= 3
+
+
+@pytest.mark.parametrize("dtype,r,shape", [("f32", 4, (1, 250, 300)), ("f64", 4, (1, 250, 300)), ("f32", 8, (1, 250, 300)),
+                                           ("f32", 2, (1, 250, 300))])
+def test_batch_takes_the_tile_set_by_hand(oracle_mod, dtype, r, shape):
+    # a batch whose members were all created with one tile steps with that tile: the prefix at
+    # the end of its table counts the workgroups of that tile (one plane: one chunk), and the
+    # bits are those of a member alone; with two tiles among them, too
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    T, tdt = 6, torch.float32 if dtype == "f32" else torch.float64
+    v, u0, um1 = (torch.tensor(a, dtype=tdt, device="cuda") for a in _case(shape, r))
+    dt = 0.5 * oracle_mod.dt_max(3, r, 10.0, float(v.max()))
+    base, counts = [], []
+
+    def member(cfg, damped):
+        F.fd_set_tuning(dtype, r, 3, cfg)
+        try:
+            p = Propagator(v, r, 10.0, dt, dtype)
+        finally:
+            F.fd_set_tuning(dtype, r, 3, -1)
+        if damped:
+            p.set_damping(5, 0.03)
+        p.set_state(u0, um1, 0)
+        return p
+
+    def batch(ps):
+        ws = torch.empty(F.fd_batch_workspace_bytes(2), dtype=torch.uint8, device="cuda")
+        b = F.fd_batch_create(2, ws, F.stream_ptr(None))
+        F.fd_batch_set(b, [p.ctx for p in ps], [T, T])
+        prefix = ws[-256:][:12].view(torch.int32).tolist()
+        F.fd_batch_step(b, T)
+        got = [p.state()[:2] for p in ps]
+        torch.cuda.synchronize()
+        F.fd_batch_destroy(b)
+        assert all(torch.equal(x, y) for one, other in zip(got, base) for x, y in zip(one, other))
+        assert prefix[0] == 0 and prefix[2] == 2 * prefix[1]
+        return prefix[1]
+
+    for damped in (False, True):
+        p = member(-1, damped)
+        p.step(T)
+        base.append(p.state()[:2])
+    own = batch([member(-1, False), member(-1, True)])
+    cfg = 0
+    while True:
+        try:
+            ps = [member(cfg, False), member(cfg, True)]
+        except F.FdError as e:
+            assert e.status == F.FD_E_RANGE
+            break
+        say(f"batch by hand {ps[0].kernel_config}")
+        counts.append(batch(ps))
+        assert counts[-1] == int(ps[0].kernel_config.split("grid ")[1].split()[0])
+        cfg += 1
+    assert len(set(counts)) >= 3
+    batch([member(0, False), member(cfg - 1, True)])
+    assert own in counts
