@@ -386,12 +386,12 @@ int fd_copy_probe(void *dst, const void *src, size_t bytes, void *stream);
 int fd_stream_probe(const void *a, const void *b, void *c, size_t bytes, int blocks, void *stream);
 
 /* Name of the stencil kernel configuration used for (dtype, r, ndim): tile shape,
- * z-chunk and launch size. */
+ * z-chunk and launch size, and in 2-D the steps per launch with the tile and size of such a
+ * launch (which more than two sources keep from being used), or "single steps". */
 const char *fd_kernel_config(const fd_ctx *ctx);
 
-/* The same for the context's adjoint kernel (fd_adjoint_segment): tile shape, z-chunk
- * and launch size.  The string is owned by the context (valid until fd_destroy); a null
- * context gives "". */
+/* The same for the context's adjoint kernel (fd_adjoint_segment).  The string is owned by
+ * the context (valid until fd_destroy); a null context gives "". */
 const char *fd_adjoint_config(const fd_ctx *ctx);
 
 /* Select a stencil tile configuration by index for contexts created afterwards with this

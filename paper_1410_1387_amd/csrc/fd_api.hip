@@ -733,6 +733,16 @@ extern "C" int fd_create(fd_ctx **out, const fd_grid *g, int r, double h, double
     snprintf(nm, sizeof(nm), "%s, zchunk %d, grid %lld wg", c->ka->name, c->adj_zch,
              (long long)(c->adj_tiles_x * c->adj_tiles_y * c->adj_chunks_z));
     c->adj_cfg_name = nm;
+    if (L.ndim == 2) {  // the kernels that most steps take, where steps share launches
+        auto shared = [&](const auto *e) -> std::string {
+            if (!e) return "; single steps";
+            snprintf(nm, sizeof(nm), "; up to %d steps per launch, tile %dx%d, %lld wg", e->kmax, e->tx, e->tz,
+                     (long long)((L.knx + e->tx - 1) / e->tx * ((L.knz + e->tz - 1) / e->tz)));
+            return nm;
+        };
+        c->cfg_name += shared(c->km);
+        c->adj_cfg_name += shared(c->kam);
+    }
 
     // zero the workspace: both wavefields (u^0 = u^-1 = 0), c ghosts, tables
     hipError_t e = hipMemsetAsync(workspace, 0, L.o_pair, c->stream);

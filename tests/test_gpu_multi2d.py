@@ -377,3 +377,44 @@ def test_workspace_without_second_pair(oracle_mod, shape, r, dtype):
     res, ref = server.serve_trace([req], realtime=False), run_sequential([req], r, dtype, realtime=False)
     assert res[0].status == ref[0].status == "ok", (res[0].error, ref[0].error)
     assert torch.equal(res[0].traces, ref[0].traces)
+
+
+@pytest.mark.parametrize("shape,r,dtype,fwd,adj", [
+    ((256, 256), 1, "f32", (8, 64, 32), (8, 32, 32)), ((90, 210), 4, "f32", (8, 32, 32), (6, 32, 32)),
+    ((550, 1601), 4, "f32", (3, 64, 32), (4, 64, 32)), ((1101, 1599), 4, "f32", (2, 64, 32), (4, 64, 32)),
+    ((801, 1203), 3, "f32", (4, 64, 32), None), ((521, 545), 2, "f32", (4, 64, 32), (4, 32, 16)),
+    ((300, 420), 8, "f32", (3, 32, 32), None), ((801, 1203), 8, "f32", None, None),
+    ((256, 256), 4, "f64", (6, 16, 16), (6, 16, 16)), ((270, 265), 4, "f64", (4, 32, 32), (3, 32, 32)),
+    ((270, 265), 3, "f64", (6, 32, 32), (3, 32, 32)), ((521, 545), 3, "f64", (4, 32, 32), (3, 32, 32)),
+    ((70, 38), 5, "f64", (4, 16, 16), (4, 16, 16)), ((270, 265), 5, "f64", (3, 32, 32), None),
+    ((801, 1203), 5, "f64", None, None), ((4500, 4300), 1, "f32", None, None)])
+def test_config_names_the_shared_launch(shape, r, dtype, fwd, adj):
+    # the configuration strings name the kernel that most steps take: the deep, the shallow or no
+    # shared launch by grid and radius; a tile set by hand and the periodic boundary step alone
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    def name(entry):
+        if entry is None:
+            return "; single steps"
+        k, tx, tz = entry
+        return f"; up to {k} steps per launch, tile {tx}x{tz}, {-(-shape[1] // tx) * -(-shape[0] // tz)} wg"
+
+    v = torch.full(shape, 2000.0, dtype=torch.float32 if dtype == "f32" else torch.float64, device="cuda")
+
+    def configs(bc="zero"):
+        p = Propagator(v, r, 10.0, 1e-4, dtype, bc=bc)
+        say(f"{p.kernel_config} | {p.adjoint_config}")
+        return [c[c.index(";"):] for c in (p.kernel_config, p.adjoint_config)]
+
+    assert configs() == [name(fwd), name(adj)]
+    assert configs("periodic") == [name(None)] * 2
+    F.fd_set_tuning(dtype, r, 2, 0)
+    F.fd_set_adj_tuning(dtype, r, 2, 0)
+    try:
+        assert configs() == [name(None)] * 2
+    finally:
+        F.fd_set_tuning(dtype, r, 2, -1)
+        F.fd_set_adj_tuning(dtype, r, 2, -1)
