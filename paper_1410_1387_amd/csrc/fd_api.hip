@@ -1611,32 +1611,44 @@ static std::vector<BatchGroup> batch_groups(fd_ctx *const *ctxs, int nctx)
 // equal length ceil(nz / c) <= Z (no short tail chunk); the launch costs about
 // ceil(workgroups / slots) x (longest chunk + 2r) plane-times, minimised over the
 // targets that are some member's exact chunk length.  A FINE tile's chunks in the last-level
-// cache are short instead (fine_zch).
-static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g, const FwdEntry *by_hand)
+// cache are short instead (fine_zch).  slots: of each tile, or 0 before it is asked for.
+static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g, const FwdEntry *by_hand, int cus,
+                              std::vector<int> &slots)
 {
-    const int r = ctxs[g.m0]->r, cus = device_cus();
+    const int r = ctxs[g.m0]->r;
     int count = 0;
     const FwdEntry *tab = fwd_table(ctxs[g.m0]->dtype, r, (int)ctxs[g.m0]->g.ndim, &count);
-    std::vector<int64_t> cand;
-    for (int i = g.m0; i < g.m1; ++i) {
-        const int64_t nz = ctxs[i]->L.knz;
-        for (int64_t c = 1; c <= std::max<int64_t>(1, nz); ++c) cand.push_back((nz + c - 1) / c);
-    }
+    // members of one depth count together, and of its chunks the exact lengths alone
+    std::vector<int64_t> depth, cand;
+    for (int i = g.m0; i < g.m1; ++i) depth.push_back(ctxs[i]->L.knz);
+    std::sort(depth.begin(), depth.end());
+    depth.erase(std::unique(depth.begin(), depth.end()), depth.end());
+    for (int64_t nz : depth)
+        for (int64_t c = 1, z = nz;; z = (nz + c - 1) / c) {
+            cand.push_back(z);
+            if (z == 1) break;
+            c = (nz + z - 2) / (z - 1);  // the first count of chunks shorter than z
+        }
     std::sort(cand.begin(), cand.end());
     cand.erase(std::unique(cand.begin(), cand.end()), cand.end());
+    std::vector<int64_t> tiles(depth.size());
     double kbest = 0;
     for (int k = 0; k < count; ++k) {
         if (by_hand ? &tab[k] != by_hand : tab[k].role != FWD_AUTO && tab[k].role != FWD_FINE) continue;
-        const int slots = resident_slots(tab[k].kernel, tab[k].nt);
         double best = 1e300;
         int64_t z = cand.back(), bwg = 0, bplanes = 0;
+        std::fill(tiles.begin(), tiles.end(), 0);
+        for (int i = g.m0; i < g.m1; ++i) {
+            const Layout &L = ctxs[i]->L;
+            tiles[(size_t)(std::lower_bound(depth.begin(), depth.end(), L.knz) - depth.begin())] +=
+                ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by);
+        }
         auto lay = [&](int64_t Z, int64_t *planes) {
             int64_t nwg = 0;
-            for (int i = g.m0; i < g.m1; ++i) {
-                const Layout &L = ctxs[i]->L;
-                const int64_t cm = (L.knz + Z - 1) / Z, zm = (L.knz + cm - 1) / cm;
-                nwg += ((L.knx + tab[k].bx - 1) / tab[k].bx) * ((L.kny + tab[k].by - 1) / tab[k].by) * cm;
-                *planes = std::max<int64_t>(*planes, zm);
+            for (size_t d = 0; d < depth.size(); ++d) {
+                const int64_t cm = (depth[d] + Z - 1) / Z;
+                nwg += tiles[d] * cm;
+                *planes = std::max<int64_t>(*planes, (depth[d] + cm - 1) / cm);
             }
             return nwg;
         };
@@ -1645,12 +1657,14 @@ static void choose_group_tile(fd_ctx *const *ctxs, BatchGroup &g, const FwdEntry
             int64_t any = 0;
             z = fine_zch([&](int64_t Z) { return lay(Z, &any); }, cand.back(), tab[k].nt, tab[k].cached_zch, cus);
             bwg = lay(z, &bplanes);
+        } else if (!slots[(size_t)k]) {
+            slots[(size_t)k] = resident_slots(tab[k].kernel, tab[k].nt);
         }
         for (int64_t Z : cand) {
             if (cached) break;
             int64_t planes = 0;
             const int64_t nwg = lay(Z, &planes);
-            const double cost = (double)((nwg + slots - 1) / slots) * (double)(planes + 2 * r);
+            const double cost = (double)((nwg + slots[(size_t)k] - 1) / slots[(size_t)k]) * (double)(planes + 2 * r);
             if (cost < best - 1e-9) {
                 best = cost;
                 z = Z;
@@ -1694,8 +1708,12 @@ static int batch_table(fd_ctx *const *ctxs, const int64_t *target, int nctx, con
         if (!ctxs[i]->tuned || ctxs[i]->kt != by_hand) by_hand = nullptr;
     desc.resize((size_t)nctx);
     prefix.assign((size_t)nctx + 1, 0);
+    int count = 0;
+    if (nctx > 0) fwd_table(ctxs[0]->dtype, ctxs[0]->r, (int)ctxs[0]->g.ndim, &count);
+    std::vector<int> slots((size_t)count, 0);
+    const int cus = device_cus();
     for (BatchGroup &g : groups) {
-        choose_group_tile(ctxs, g, by_hand);
+        choose_group_tile(ctxs, g, by_hand, cus, slots);
         for (int i = g.m0; i < g.m1; ++i) {
             fd_ctx *c = ctxs[i];
             const int64_t nz = c->L.knz, cm = (nz + g.zch - 1) / g.zch;
