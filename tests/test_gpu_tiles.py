@@ -273,3 +273,73 @@ def test_batch_takes_the_tile_set_by_hand(oracle_mod, dtype, r, shape):
     assert len(set(counts)) >= 3
     batch([member(0, False), member(cfg - 1, True)])
     assert own in counts
+
+
+@pytest.mark.parametrize("dtype,r,shapes", [
+    ("f64", 4, [(40, 43, 41), (64, 67, 65), (212, 215, 213), (96, 99, 97)]), ("f32", 2, [(50, 53, 51), (130, 133, 131), (268, 271, 269)]),
+    ("f32", 8, [(50, 53, 51), (130, 133, 131), (268, 271, 269)]), ("f64", 1, [(33, 36, 34), (100, 103, 101), (90, 93, 300)]),
+    ("f64", 7, [(33, 36, 34), (100, 103, 101)]), ("f32", 4, [(300, 420), (801, 1203), (33, 70), (4300, 4301)]),
+    ("f64", 8, [(300, 420), (801, 1203), (3100, 3000), (1, 9)]), ("f32", 2, [(256, 256)] * 5 + [(90, 700)])])
+def test_batch_tile_choice_types(oracle_mod, dtype, r, shapes):
+    # the tiles, chunks and loads that batches choose in either type, at other radii and in 2-D:
+    # members that stay in the last-level cache and ones that do not, damped and undamped, with
+    # few and many sources, end with the bits they have alone
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    T, tdt = 7, torch.float32 if dtype == "f32" else torch.float64
+    dt = 0.4 * oracle_mod.dt_max(len(shapes[0]), r, 10.0, 4500.0)
+    stream = torch.cuda.Stream()
+
+    def make(i, shape):
+        v = torch.full(shape, 2000.0, dtype=tdt, device="cuda")
+        v[shape[0] // 2:] = 2500.0 + 100 * i
+        u0 = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(i), dtype=tdt, device="cuda")
+        torch.cuda.synchronize()
+        mid = tuple(n // 2 for n in shape[::-1])
+        rec = [(x,) + mid[1:] for x in range(0, shape[-1], 3)] + [mid[:-1] + (z,) for z in range(shape[0])]
+        p = Propagator(v, r, 10.0, dt, dtype, max_sources=4, max_receivers=len(rec), stream=stream)
+        with torch.cuda.stream(stream):
+            if i % 2:
+                p.set_damping(3, 0.03)
+            for k in range(1 + i % 4):
+                p.inject(p.ricker(T, 30.0, 0.0), (mid[0], *mid[1:-1], min(k, shape[0] - 1)), 1e6)
+            tr = p.record(rec, T)
+            p.set_state(u0, 0.5 * u0, 0)
+        stream.synchronize()
+        return p, tr
+
+    say(f"batch {dtype} r={r} {shapes}")
+    alone = [make(i, s) for i, s in enumerate(shapes)]
+    for p, _ in alone:
+        p.step(T)
+    both = [make(i, s) for i, s in enumerate(shapes)]
+    ws = torch.empty(F.fd_batch_workspace_bytes(len(shapes)), dtype=torch.uint8, device="cuda")
+    b = F.fd_batch_create(len(shapes), ws, F.stream_ptr(stream))
+    F.fd_batch_set(b, [p.ctx for p, _ in both], [T] * len(shapes))
+    F.fd_batch_step(b, 4)
+    F.fd_batch_step(b, 3)
+    for (pa, ta), (pb, tb) in zip(alone, both):
+        with torch.cuda.stream(stream):
+            ua, ub = pa.state(), pb.state()
+        stream.synchronize()
+        assert torch.equal(ua[0], ub[0]) and torch.equal(ua[1], ub[1]) and torch.equal(ta, tb), pa.shape
+        assert float(ta.abs().max()) > 0
+    F.fd_batch_destroy(b)
+
+
+@pytest.mark.parametrize("leave", [True, False])
+def test_tiles_set_by_hand_end_with_their_test(leave):
+    # the second run of this test does not find what the first one left set
+    import torch
+
+    from paper_1410_1387_amd import Propagator
+    from paper_1410_1387_amd import fdwave as F
+
+    v = torch.full((50, 30, 60), 2000.0, dtype=torch.float32, device="cuda")
+    assert "zchunk 17," not in Propagator(v, 3, 10.0, 1e-4).kernel_config
+    if leave:
+        F.fd_set_tuning("f32", 3, 3, 0, 17)
+        assert "zchunk 17," in Propagator(v, 3, 10.0, 1e-4).kernel_config
