@@ -1559,38 +1559,67 @@ static double group_bytes(fd_ctx *const *ctxs, int m0, int m1)
     return bytes;
 }
 
+// The same with every row rounded up to whole 256-byte granules: by it eight cubes of 128
+// points (192 MiB, whole granules) want one group, and ten of 144 (171 MiB per five, 228 in
+// granules) three, which plain bytes cannot tell apart.
+constexpr int64_t kGranule = 256;
+
+static double granule_bytes(fd_ctx *const *ctxs, int m0, int m1)
+{
+    double bytes = 0;
+    for (int i = m0; i < m1; ++i) {
+        const Layout &L = ctxs[i]->L;
+        bytes += 3.0 * (double)align_up(L.knx * (int64_t)L.esize, kGranule) * (double)L.kny * (double)L.knz;
+    }
+    return bytes;
+}
+
 // Members whose fields fit the last-level cache are stepped in groups that fit it together,
 // each group all the steps of a call before the next one, so that a step finds the fields of
 // the step before in the cache; a run of such members is split evenly.  Members that do not
 // fit share their launches, which fill the chip without gaps, and take along runs of small
 // ones, which cost less there than in launches of their own.  Measured, one launch for all
-// -> groups, us per step: eleven cubes of 64..152 points (201 MB) 69 -> 62, sixteen of 100
-// 78 -> 72, 24 of 128 186 -> 165, four of 256 216 -> 188, eight of 128 (201 MB, whole lines
-// in every row) 55.5 -> 56.9 (since the descriptor's pointers are known to be global, now
-// 58, 61, 148, 159 and 53.6).  A limit of 100 MB costs the groups more in idle places (six
-// cubes of 192: 189 against 126 us).
-constexpr double kGroupBytes = 165.0 * (1 << 20), kTakenAlongBytes = 48.0 * (1 << 20);
+// -> groups, us per step: eleven cubes of 64..152 points r = 4 68 -> 58 (r = 2 61 -> 50), ten of
+// 144 114 -> 94, 24 of 128 168 -> 142, sixteen of 128 r = 2 100 -> 90; a group more than needed
+// costs as much (24 of 128 r = 4 in four groups 146, eight of 128 r = 8 in two 67 against 57 in
+// one).  Radii up to 2 want smaller groups (64 cubes of 64 points r = 2: 53 in two, 59 in one;
+// FP64, 60 of 64 r = 2 93 in three, 103 in two; 8 of 128 r = 1 83 in three, 93 in two).
+// FP64 members with whole granules in every row run at HBM's rate in one launch, and no faster
+// from the cache, where their arithmetic is the limit: eight cubes of 128 points r = 3 90 in one
+// launch, 104 in groups, r = 8 102 against 114; three of 160 r = 4 72 against 76.
+constexpr double kGroupBytes = 208.0 * (1 << 20), kShallowGroupBytes = 165.0 * (1 << 20);
+constexpr double kTakenAlongBytes = 48.0 * (1 << 20);
 
 static std::vector<BatchGroup> batch_groups(fd_ctx *const *ctxs, int nctx)
 {
     auto fits = [&](int m) { return cache_keeps(group_bytes(ctxs, m, m + 1)); };
-    bool large = false;
-    for (int m = 0; m < nctx; ++m) large = large || !fits(m);
+    bool large = false, streams = nctx > 0;
+    for (int m = 0; m < nctx; ++m) {
+        const Layout &L = ctxs[m]->L;
+        large = large || !fits(m);
+        streams = streams && L.ndim == 3 && L.r > 2 && L.esize == 8 && L.knx * (int64_t)L.esize % kGranule == 0;
+    }
+    streams = streams && !large;
     std::vector<BatchGroup> groups;
-    for (int m = 0, end = 0; m < nctx; m = end) {
+    if (streams) groups.push_back(BatchGroup{0, nctx, false, false, nullptr, 1});
+    for (int m = streams ? nctx : 0, end = m; m < nctx; m = end) {
         while (end < nctx && fits(end) == fits(m)) ++end;  // a run of members of one kind
-        const double total = group_bytes(ctxs, m, end), parts = std::ceil(total / kGroupBytes);
-        if (!fits(m) || (large && total <= kTakenAlongBytes)) {
+        if (!fits(m) || (large && group_bytes(ctxs, m, end) <= kTakenAlongBytes)) {
             if (!groups.empty() && !groups.back().split)
                 groups.back().m1 = end;
             else
                 groups.push_back(BatchGroup{m, end, false, false, nullptr, 1});
             continue;
         }
+        auto share = [&](int m0, int m1) {  // of the cache
+            return ctxs[m0]->r <= 2 ? group_bytes(ctxs, m0, m1) / kShallowGroupBytes : granule_bytes(ctxs, m0, m1) / kGroupBytes;
+        };
+        const double parts = std::ceil(share(m, end)), total = group_bytes(ctxs, m, end);
         int first = m;
         for (int k = 1; first < end; ++k) {
             BatchGroup g{first, first + 1, true, false, nullptr, 1};
-            while (g.m1 < end && group_bytes(ctxs, m, g.m1) + 0.5 * group_bytes(ctxs, g.m1, g.m1 + 1) < total * k / parts)
+            while (g.m1 < end && share(first, g.m1 + 1) <= 1.0 &&
+                   group_bytes(ctxs, m, g.m1) + 0.5 * group_bytes(ctxs, g.m1, g.m1 + 1) < total * k / parts)
                 ++g.m1;
             groups.push_back(g);
             first = g.m1;

@@ -279,11 +279,14 @@ def test_batch_takes_the_tile_set_by_hand(oracle_mod, dtype, r, shape):
     ("f64", 4, [(40, 43, 41), (64, 67, 65), (212, 215, 213), (96, 99, 97)]), ("f32", 2, [(50, 53, 51), (130, 133, 131), (268, 271, 269)]),
     ("f32", 8, [(50, 53, 51), (130, 133, 131), (268, 271, 269)]), ("f64", 1, [(33, 36, 34), (100, 103, 101), (90, 93, 300)]),
     ("f64", 7, [(33, 36, 34), (100, 103, 101)]), ("f32", 4, [(300, 420), (801, 1203), (33, 70), (4300, 4301)]),
-    ("f64", 8, [(300, 420), (801, 1203), (3100, 3000), (1, 9)]), ("f32", 2, [(256, 256)] * 5 + [(90, 700)])])
+    ("f64", 8, [(300, 420), (801, 1203), (3100, 3000), (1, 9)]), ("f32", 2, [(256, 256)] * 5 + [(90, 700)]),
+    ("f64", 5, [(40, 40, 32), (64, 64, 64), (33, 30, 96)]), ("f32", 4, [(128, 128, 128)] * 9),
+    ("f64", 4, [(2500, 2500)] * 4), ("f64", 3, [(96, 95, 97)] * 5)])
 def test_batch_tile_choice_types(oracle_mod, dtype, r, shapes):
     # the tiles, chunks and loads that batches choose in either type, at other radii and in 2-D:
-    # members that stay in the last-level cache and ones that do not, damped and undamped, with
-    # few and many sources, end with the bits they have alone
+    # members that stay in the last-level cache and ones that do not, whole rows that stream,
+    # groups that a member more would overfill; damped and undamped, with few and many sources,
+    # all end with the bits they have alone
     import torch
 
     from paper_1410_1387_amd import Propagator
