@@ -29,7 +29,7 @@ static const FwdEntry k2[] = {
 static const FwdEntry k3[] = {
     fwd_entry<TileCfg<double, 3, 3, 16, 16, 2>, FWD_AUTO>("f64 r3 3d tile 32x32 (256 thr, 2 row/thr)", 1.0f),
     fwd_entry<TileCfg<double, 3, 3, 16, 32, 1, 2, 0, false, 0>, FWD_AUTO>("f64 r3 3d tile 32x32 (512 thr, 1 row/thr)", 0.95f),
-    fwd_entry<TileCfg<double, 3, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r3 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 2),
+    fwd_entry<TileCfg<double, 3, 3, 8, 16, 1, 2, 0, false, 0>, FWD_FINE>("f64 r3 3d tile 16x16 (128 thr, 1 row/thr)", 1.15f, 0.9f, 3),
 };
 static const FwdEntry k2[] = {
     fwd_entry<TileCfg<double, 3, 2, 64, 1, 1>, FWD_AUTO>("f64 r3 2d tile 128x1 (64 thr, 1 row/thr)", 1.0f, 1.0f, 4),

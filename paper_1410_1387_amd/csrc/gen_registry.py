@@ -43,10 +43,11 @@ F64_3D_BIG_R_AUTO = [((16, 16, 1), "AUTO", 1.1), ((32, 16, 1), "AUTO", 1.0), ((8
 F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
 # FINE tiles of grids that stay in the last-level cache: relative cost per point and planes per
 # chunk (224^3 r = 2 FP32: 29.1 us with chunks of 2 planes, 30.0 of 4, 33.9 with 128x16; 192^3
-# FP64 35.1 against 39.9).  At larger radii a short chunk's first planes cost too much (201x119x
+# FP64 35.1 against 39.9; r = 3 FP64 40.2 with 3 planes against 43.8 with 2, twelve cubes of 96
+# 64 against 72, but in FP32 192^3 22.4 with 3 against 21.5 with 2).  At larger radii a short chunk's first planes cost too much (201x119x
 # 333 r = 8: 34.5 us with 4 planes, 31.7 with 128x16).
 FINE_CACHED = {"f32": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.25f", 4)},
-               "f64": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.0f", 4)}}
+               "f64": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 3), 4: ("1.0f", 4)}}
 # FP64 r = 4: 512 threads and half the workgroups stream better the longer the chunks (512^3 724
 # us against 790, 480^3 624 against 685, 352^3 245 against 261, 256^3 84.4 against 84.7)
 COSTS = {("f64", 4, (16, 32, 1)): 0.85}
