@@ -145,6 +145,18 @@ __device__ __forceinline__ void vzero(T (&d)[N])
     for (int i = 0; i < N; ++i) d[i] = T(0);
 }
 
+// A whole number kept in the register of a floating one.
+template <typename T>
+__device__ __forceinline__ T bits_of(int i)
+{
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, (int64_t)i);
+    else
+        return __builtin_bit_cast(T, i);
+}
+__device__ __forceinline__ int bits_to_int(float x) { return __builtin_bit_cast(int, x); }
+__device__ __forceinline__ int bits_to_int(double x) { return (int)__builtin_bit_cast(int64_t, x); }
+
 __device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -185,6 +197,16 @@ __device__ __forceinline__ int lower_bound_z(const Event *ev, int lo, int hi, in
 
 // ------------------------------------------------------------------ tile configuration
 
+// Elements of LDS to declare for a kernel that uses `used`, so that no more than `waves` waves
+// per SIMD (0: no limit) fit on a compute unit, in workgroups of nt threads.  A compute unit
+// hands out its 160 KB in 128 units of 1280 bytes.
+template <typename T>
+constexpr int lds_limited(int used, int waves, int nt)
+{
+    const int least = waves ? (128 / (waves * 256 / nt + 1) + 1) * 1280 / (int)sizeof(T) : 0;
+    return used > least ? used : least;
+}
+
 template <typename T, int R_, int NDIM_, int TXN_, int TYN_, int EY_, int VEC_ = V16<T>::N, int OCC_ = 0,
           bool LEAN_ = (OCC_ > 0), int HOFF_ = -1>
 struct TileCfg {
@@ -220,6 +242,20 @@ struct TileCfg {
     static constexpr bool LEAN = LEAN_;
     static constexpr int HOFF = HOFF_ >= 0 ? HOFF_ : (R <= 4) ? (OCC_ >= 4 ? R - 1 : R) : 0;
     static constexpr int NB = HOFF + 2;
+    // Waves per SIMD that the forward kernel may hold (0: what its registers allow).  With one
+    // more the chunks of the larger grids get shorter or the compute unit streams more rows at
+    // once: 512^3 r = 4 388 us against 352, 320^3 r = 6 109 against 94, 201x119x333 r = 5 31.2
+    // against 27.5, 512^3 r = 3 damped 378 against 369 (where no limit stands, both measure
+    // the same or the registers allow no more).
+    static constexpr int max_waves(bool damp)
+    {
+        if (NDIM < 3 || OCC > 0 || VEC * (int)sizeof(T) < 16) return 0;
+        if (NT == 512 && R == 3 && damp) return 2;
+        if (NT == 512 && sizeof(T) == 4) return R == 4 ? 2 : R == 1 ? 4 : 0;
+        if (NT == 256 && R == 5 && sizeof(T) == 8 && damp) return 2;
+        return (NT == 128 && R == 5) || (NT == 256 && R == 6) ? 2 : 0;
+    }
+    static constexpr int lds_fwd(bool damp) { return lds_limited<T>(NB * LDS, max_waves(damp), NT); }
     static_assert(256 % BX == 0 && 64 % BY == 0, "tile must divide the layout alignment");
 };
 
@@ -352,23 +388,6 @@ struct TileGeom {
 
 // ------------------------------------------------------------------ sources and receivers
 
-// Next plane >= z at which one of this thread's columns has an event (INT_MAX if none).
-template <class C, class Desc>
-__device__ __forceinline__ int next_event(const Desc &s, const TileGeom<C> &g, int z)
-{
-    int nxt = 0x7fffffff;
-#pragma unroll 1
-    for (int slot = 0; slot < C::EY * C::VEC; ++slot) {
-        const int y = g.gy + slot / C::VEC, x = g.gx + slot % C::VEC;
-        if (x < s.nx && y < s.ny) {
-            const int cidx = y * s.nx + x;
-            const int hi = s.ev_ptr[cidx + 1], p = lower_bound_z(s.ev, s.ev_ptr[cidx], hi, z);
-            if (p < hi) nxt = min(nxt, s.ev[p].z);
-        }
-    }
-    return nxt;
-}
-
 // Column bounds of this thread's events, loaded before the fields so that the look-ups that
 // depend on them overlap with those loads.
 template <class C>
@@ -392,9 +411,18 @@ struct EventBounds {
 
 // The next plane z at which this thread's columns have an event.  While no column has more
 // than one event left, the usual case of receivers, `code` holds the event of each column
-// at that plane (kNoEvent: none) and the plane needs no look-up when it comes; otherwise
-// (`look`) its events are looked up then.
+// at that plane (kNoEvent: none) and the plane needs no look-up when it comes.  Otherwise
+// (`look`) it holds the place in the list of each column's next event (kNoEvent: none left),
+// which is read when its plane comes.  That waits for all loads of the next plane, but once a
+// plane: a search from the column's bounds, as many times as the list is deep, had a column of
+// receivers cost 64^3 r = 4 8.2 us per step instead of 6.3, 256^3 103 instead of 67.
 constexpr int kNoEvent = -0x7fffffff - 1;
+
+// Waits for this wave's loads (vmcnt 0).  At the end of a branch that has waited for all but
+// some lanes' loads, it keeps the compiler from waiting for those in the plane loop, and so
+// for the fields' loads with them.
+__device__ __forceinline__ void loads_done() { __builtin_amdgcn_s_waitcnt(0x0f70); }
+
 template <class C>
 struct EventNext {
     int z, code[C::EY][C::VEC];
@@ -405,19 +433,24 @@ struct EventNext {
     {
         z = 0x7fffffff;
         look = false;
-        int ez[C::EY][C::VEC];
+        int ez[C::EY][C::VEC], first_z[C::EY][C::VEC];
 #pragma unroll
         for (int e = 0; e < C::EY; ++e)
 #pragma unroll
             for (int v = 0; v < C::VEC; ++v) code[e][v] = kNoEvent;
-        if (!b.any) return;
+        bool mine = false;
+#pragma unroll
+        for (int e = 0; e < C::EY; ++e)
+#pragma unroll
+            for (int v = 0; v < C::VEC; ++v) mine = mine || (g.rin[e] && b.p[e][v] < b.p[e][v + 1]);
+        if (!b.any || !mine) return;
         // the first event of each column (of the list, where it has none)
 #pragma unroll
         for (int e = 0; e < C::EY; ++e)
 #pragma unroll
             for (int v = 0; v < C::VEC; ++v) {
                 const Event *ev = s.ev + (b.p[e][v] < b.p[e][v + 1] ? b.p[e][v] : 0);
-                ez[e][v] = ev->z;
+                ez[e][v] = first_z[e][v] = ev->z;
                 code[e][v] = ev->code;
             }
 #pragma unroll
@@ -436,31 +469,62 @@ struct EventNext {
         for (int e = 0; e < C::EY; ++e)
 #pragma unroll
             for (int v = 0; v < C::VEC; ++v) look = look || (code[e][v] != kNoEvent && ez[e][v] != z);
-        if (look) z = next_event<C>(s, g, g.z0);
+        if (look) seek(s, g, b, first_z);
+        loads_done();
+    }
+
+    // the first event of each column from plane z0 on
+    template <class Desc>
+    __device__ __forceinline__ void seek(const Desc &s, const TileGeom<C> &g, const EventBounds<C> &b,
+                                         const int (&first_z)[C::EY][C::VEC])
+    {
+        z = 0x7fffffff;
+        static_for<C::EY * C::VEC>([&](auto slot) __attribute__((always_inline)) {
+            constexpr int e = decltype(slot)::value / C::VEC, v = decltype(slot)::value % C::VEC;
+            const int lo = b.p[e][v], hi = g.rin[e] ? b.p[e][v + 1] : lo;
+            int at = lo, at_z = lo < hi ? first_z[e][v] : 0x7fffffff;
+            // receivers of a column are mostly on consecutive planes, a few planes with more
+            // events than one among them: two steps of that length, then a search
+            for (int i = 0; i < 2 && at_z < g.z0; ++i) {
+                const int to = min(at + (g.z0 - at_z), hi);
+                const int before = s.ev[to - 1].z, to_z = s.ev[min(to, hi - 1)].z;
+                if (before >= g.z0) break;
+                at = to;
+                at_z = to < hi ? to_z : 0x7fffffff;
+            }
+            if (at_z < g.z0) {
+                at = lower_bound_z(s.ev, at + 1, hi, g.z0);
+                at_z = at < hi ? s.ev[at].z : 0x7fffffff;
+            }
+            code[e][v] = at < hi ? at : kNoEvent;
+            z = min(z, at_z);
+        });
     }
 };
 
-// Looks up the events of this thread's columns at plane z and runs f(code, row, lane) over
-// them in list order (row and lane are compile-time constants); returns the next plane with
-// one.
+// Runs f(code, row, lane) over the events of this thread's columns at plane z in list order
+// (row and lane are compile-time constants) and moves the columns' places in `at` past them;
+// returns the next plane with an event.  (The entry behind the list's last is workspace, too.)
 template <class C, class Desc, class F>
-__device__ __forceinline__ int look_events(const Desc &s, const TileGeom<C> &g, int z, F &&f)
+__device__ __forceinline__ int look_events(const Desc &s, const TileGeom<C> &g, int (&at)[C::EY][C::VEC], int z, F &&f)
 {
     int nxt = 0x7fffffff;
     static_for<C::EY * C::VEC>([&](auto slot) __attribute__((always_inline)) {
-        constexpr int i = decltype(slot)::value;
-        const int y = g.gy + i / C::VEC, x = g.gx + i % C::VEC;
-        if (x < s.nx && y < s.ny) {
-            const int cidx = y * s.nx + x;
-            const int lo = s.ev_ptr[cidx], hi = s.ev_ptr[cidx + 1];
-            if (lo < hi) {
-                int p = lower_bound_z(s.ev, lo, hi, z);
-                for (; p < hi && s.ev[p].z == z; ++p)
-                    f(s.ev[p].code, std::integral_constant<int, i / C::VEC>{}, std::integral_constant<int, i % C::VEC>{});
-                if (p < hi) nxt = min(nxt, s.ev[p].z);
-            }
+        constexpr int e = decltype(slot)::value / C::VEC, v = decltype(slot)::value % C::VEC;
+        int p = at[e][v];
+        if (p == kNoEvent) return;
+        const int hi = s.ev_ptr[(g.gy + e) * s.nx + g.gx + v + 1];
+        Event ev = s.ev[p], next = s.ev[p + 1];
+        while (ev.z == z) {
+            f(ev.code, std::integral_constant<int, e>{}, std::integral_constant<int, v>{});
+            if (++p == hi) break;
+            ev = next;
+            if (ev.z == z) next = s.ev[p + 1];
         }
+        at[e][v] = p < hi ? p : kNoEvent;
+        if (p < hi) nxt = min(nxt, ev.z);
     });
+    loads_done();
     return nxt;
 }
 
@@ -761,7 +825,7 @@ __device__ __forceinline__ void fwd_tile(const ShotDesc &s, const typename C::ty
                         }
                     nev.z = 0x7fffffff;
                 } else {
-                    nev.z = look_events<C>(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                    nev.z = look_events<C>(s, g, nev.code, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
                         if (code >= 0) {
                             if (trow) trow[code] = un[e][v];
                         } else {
@@ -803,7 +867,7 @@ template <class C, int FROM, bool DAMP, int LD>
 __device__ __forceinline__ void fwd_body(const LaunchArgs &a)
 {
     typedef typename C::type T;
-    __shared__ __attribute__((aligned(16))) T lds[C::NB * C::LDS];
+    __shared__ __attribute__((aligned(16))) T lds[C::lds_fwd(DAMP)];
     int wg = blockIdx.x;
     if (a.xcd_remap) wg = xcd_remap(wg, (int)gridDim.x);
     if constexpr (FROM == FROM_ARGS) {
@@ -971,16 +1035,26 @@ __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::ty
 #pragma unroll
         for (int k = 0; k < HPT; ++k) bld<0>(hv[0][k], bh, g.hob[k]);
     }
-    EventNext<C> nev;
-    T rnext[EY][VEC];  // the residuals of the events in nev
+    // the next plane with events, and of its columns the residual, where `has` says so, or the
+    // bits of the place in the list (with registers for both the kernel holds fewer waves)
+    int nev_z = 0x7fffffff, has = 0;
+    bool look = false;
+    T next[EY][VEC];
     if constexpr (ROLE == 0) {
+        EventNext<C> nev;
         nev.first(s, g, evb);
+        nev_z = nev.z;
+        look = nev.look;
 #pragma unroll
         for (int e = 0; e < EY; ++e)
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
-                rnext[e][v] = T(0);
-                if (evb.any && nev.code[e][v] >= 0) rnext[e][v] = rrow[nev.code[e][v]];
+                const int code = nev.code[e][v];
+                next[e][v] = look ? bits_of<T>(code) : T(0);
+                if (evb.any && !look && code >= 0) {
+                    next[e][v] = rrow[code];
+                    has |= 1 << (e * VEC + v);
+                }
             }
     }
     int bz = g.z0 % NB, bh = (g.z0 + HOFF) % NB;
@@ -1105,19 +1179,28 @@ __device__ __forceinline__ void adj_half(const ShotDesc &s, const typename C::ty
 
             if constexpr (ROLE == 0) {
                 // adjoint sources: the residual enters at the receivers, scaled by c there
-                if (z == nev.z) {
-                    if (!nev.look) {
+                if (z == nev_z) {
+                    if (!look) {
 #pragma unroll
                         for (int e = 0; e < EY; ++e)
 #pragma unroll
                             for (int v = 0; v < VEC; ++v)
-                                if (nev.code[e][v] >= 0)
-                                    mnew[e][v] = fma_t(ramp * cv[cs][e][v], rnext[e][v], mnew[e][v]);
-                        nev.z = 0x7fffffff;
+                                if (has >> (e * VEC + v) & 1)
+                                    mnew[e][v] = fma_t(ramp * cv[cs][e][v], next[e][v], mnew[e][v]);
+                        nev_z = 0x7fffffff;
                     } else {
-                        nev.z = look_events<C>(s, g, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
+                        int at[EY][VEC];
+#pragma unroll
+                        for (int e = 0; e < EY; ++e)
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) at[e][v] = bits_to_int(next[e][v]);
+                        nev_z = look_events<C>(s, g, at, z, [&](int code, auto e, auto v) __attribute__((always_inline)) {
                             if (code >= 0) mnew[e][v] = fma_t(ramp * cv[cs][e][v], rrow[code], mnew[e][v]);
                         });
+#pragma unroll
+                        for (int e = 0; e < EY; ++e)
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) next[e][v] = bits_of<T>(at[e][v]);
                     }
                 }
                 const auto bpm = plane_buf(mout, pxy, z + R);
