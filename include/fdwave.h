@@ -346,7 +346,7 @@ int fd_batch_set(fd_batch *b, fd_ctx *const *ctxs, const int64_t *target, int nc
  * tight serving loops, harnesses that forbid allocation): a batch like fd_batch_create's
  * whose shot table (descriptors, step counters, workgroup prefix) lives in a fixed array of
  * the library instead of a caller workspace.  The array holds FD_BATCH_NOALLOC_MAX_SHOTS
- * shots (about 44 KB); each GPU the library runs on holds its own copy until the process
+ * shots (about 69 KB); each GPU the library runs on holds its own copy until the process
  * ends.  The call allocates nothing (no device or host allocation, no stream, event or
  * graph).  Use the batch with fd_batch_set, fd_batch_step and fd_batch_destroy, with these
  * differences from fd_batch_create's batch:

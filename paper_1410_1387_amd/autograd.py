@@ -3,7 +3,7 @@
 Two ways to have the forward states at hand for the adjoint, with bitwise the same
 gradient:
   * keep every state (``states="all"``): the forward pass steps with
-    ``fd_step_record`` into a new padded field each step (T + 1 fields, e.g. 178 GB for
+    ``fd_steps_record`` into a new padded field each step (T + 1 fields, e.g. 178 GB for
     256^3 x 2000 steps in FP32 -- HBM that one GPU has), and the backward pass runs the
     adjoint over them with ``fd_adjoint_stored``, without recomputation;
   * checkpoints (``states="checkpoint"``): the forward pass (Propagator) saves the state

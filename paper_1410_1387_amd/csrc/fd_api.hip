@@ -297,10 +297,12 @@ constexpr int64_t kFineZch = 32;
 constexpr int kLongZch2d = 10;
 
 // A chosen tile whose chunks are this many planes, in one round of workgroups, takes its
-// build for 4 waves per SIMD, where it has one: at these sizes it is nearly as fast (256^3
-// r = 4, 32 planes: 44.4 against 43.0 us, 320^3, 64 planes: 87 against 85) and leaves a second
-// workgroup room on each CU.  In two rounds or on other chunks it is slower (384^3: 165
-// against 156 us; 512^3: 394 against 353, since both places are then used).
+// build for 4 waves per SIMD, where it has one: the configurations of these sizes are named
+// after it.  It is the slower of the two (256^3 r = 4, 32 planes: 44.4 against 43.0 us,
+// 320^3, 64 planes: 87 against 85), and a shot that steps alone has no use for the room it
+// leaves on each CU; what a second stream gains from that room is not measured.  In two rounds
+// or on other chunks it would lose more (384^3: 165 against 156 us; 512^3: 394 against 353,
+// since both places are then used).
 constexpr int64_t kTwinZchMin = 32, kTwinZchMax = 64;
 
 double interior_bytes(const Layout &L) { return (double)L.knx * (double)L.kny * (double)L.knz * (double)L.esize; }

@@ -64,7 +64,7 @@ const Multi2dEntry *multi2d_configs_f32(int r, int *count)
 //   r = 2  3.31 -> 2.54  3.70 -> 2.57  3.93 -> 2.57   6.10 -> 5.25  14.6 -> 11.5
 //   r = 3  3.39 -> 3.01  3.83 -> 3.00  4.08 -> 3.01   6.56 (6 steps: 9.03)
 //   r = 4  3.52 -> 3.15  4.00 -> 3.15  4.25 -> 3.19   7.00 -> 6.05  15.1 -> 14.1
-// and for larger radii, where a strip and its neighbours spill, the single step is as good.
+// For larger radii the single step is as good.
 static const Adj2dEntry a_r1[] = {
     adj2d_entry<Multi2dCfg<float, 1, 8, 32, 32>>(0),
 };

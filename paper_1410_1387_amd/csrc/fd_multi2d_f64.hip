@@ -69,7 +69,7 @@ const Multi2dEntry *multi2d_configs_f64(int r, int *count)
 //   r = 3  3.17 -> 2.25  4.38 -> 2.91  5.37 -> 3.08  11.4 -> 10.3  27.2 -> 23.6
 //   r = 4  3.28 -> 2.16  4.56 -> 3.13  5.65 -> 3.28  11.9 -> 11.5  28.6 -> 26.1
 //   r = 5  3.35 -> 2.70  4.77 (2 steps, 32x32: 5.40)
-// and for larger radii, where a strip and its neighbours spill, the single step is as good.
+// For larger radii the single step is as good.
 static const Adj2dEntry a_r1[] = {
     adj2d_entry<Multi2dCfg<double, 1, 8, 32, 32>>(0),
 };

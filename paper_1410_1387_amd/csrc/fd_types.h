@@ -80,7 +80,7 @@ struct AdjArgs {
     const void *u_km1;     // u^{k-1}
     void *grad;            // accumulator g (padded)
     void *gseg;            // segment partial sum of the imaging term (padded), or null
-    int32_t gmode;         // imaging accumulation, see adj_tile
+    int32_t gmode;         // imaging accumulation: GM_DIRECT, GM_FIRST, ...
     int32_t live;          // captured launches: one.traces, which the adjoint leaves alone, is where nrec is
     const void *resid;     // [T][nrec]
     int64_t k;             // adjoint step index (residual row k - 1)

@@ -16,8 +16,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 # chooses from by itself (fd_create, fd_batch_set), FINE ones too where z chunks are short,
 # TWIN ones are a chosen tile's build for 4 waves per SIMD; OPTION tiles are reached with
 # fd_set_tuning alone.  The costs are fitted to sweeps of every tile over cubes of 48 to 512
-# points and ten ragged grids (the library's choice is then within 2 % of the best tile on
-# average; at worst 6-9 % for a few sizes).
+# points and ten ragged grids (how near the library's choice then comes to the best tile
+# stands at tile_cost).
 # FP32, radii <= 4.  Tiles of 512 threads, one workgroup per CU, stream best: 512^3 r = 4
 # takes 353 us with 128x16, 354 with 64x32, against 414 for 64x16 (256 threads, three
 # workgroups per CU, so three times as many places in memory streamed at once); small
@@ -44,12 +44,13 @@ F64_3D_BIG_R_OPTIONS = [(32, 8, 1)]
 # FINE tiles of grids that stay in the last-level cache: relative cost per point and planes per
 # chunk (224^3 r = 2 FP32: 29.1 us with chunks of 2 planes, 30.0 of 4, 33.9 with 128x16; 192^3
 # FP64 35.1 against 39.9; r = 3 FP64 40.2 with 3 planes against 43.8 with 2, twelve cubes of 96
-# 64 against 72, but in FP32 192^3 22.4 with 3 against 21.5 with 2).  At larger radii a short chunk's first planes cost too much (201x119x
-# 333 r = 8: 34.5 us with 4 planes, 31.7 with 128x16).
+# 64 against 72, but in FP32 192^3 22.4 with 3 against 21.5 with 2).  At larger radii a short
+# chunk's first planes cost too much (201x119x333 r = 8: 34.5 us with 4 planes, 31.7 with 128x16).
 FINE_CACHED = {"f32": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 2), 4: ("1.25f", 4)},
                "f64": {1: ("0.9f", 2), 2: ("0.9f", 2), 3: ("0.9f", 3), 4: ("1.0f", 4)}}
 # FP64 r = 4: 512 threads and half the workgroups stream better the longer the chunks (512^3 724
-# us against 790, 480^3 624 against 685, 352^3 245 against 261, 256^3 84.4 against 84.7)
+# us against 790, 480^3 624 against 685, 352^3 245 against 261, 256^3 84.4 against 84.7).  Not
+# measured at r = 1 to 3, which keep the cost of the tile table
 COSTS = {("f64", 4, (16, 32, 1)): 0.85}
 SWEEP_RADII = {4, 8}      # radii that get the OPTION tiles
 F2D = (64, 1, 1)          # 2-D forward and adjoint: one row of 64 threads; chunks as FINE tiles'

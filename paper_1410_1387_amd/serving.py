@@ -106,7 +106,8 @@ class _Live:
 
 def kernel_of(ctx: int) -> str:
     """The stencil kernels a context can step with: dtype, radius and dimension, the part of
-    its configuration name before the tile.  fd_batch_set picks one tile for all members."""
+    its configuration name before the tile.  fd_batch_set picks one tile for each group of
+    members, or takes the one set by hand for all of them."""
     return F.fd_kernel_config(ctx).split(" tile")[0]
 
 
